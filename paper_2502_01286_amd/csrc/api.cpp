@@ -14,6 +14,7 @@
 #include <limits>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <sstream>
 #include <string>
 #include <thread>
@@ -164,16 +165,32 @@ struct sncc_ctx {
   }
 };
 
+// A template's operands of one matrix-core form (FP32 or FP64;
+// dense_kernel.hip), built at the first call that uses them and kept with the
+// template set.
+struct DenseTmpl {
+  bool built = false;
+  DevBuf frag;       // operands, then the fixed-point image they come from
+  int digits = 0;
+  double scale = 0;  // 2^e: c in units of the last digit
+  double csum = 0;   // sum of the fixed-point image
+};
+
 struct sncc_tmpl {
   sncc_ctx *ctx = nullptr;
   uint64_t serial = 0;  // unique per uploaded set (plan cache key)
   int T = 0;
   std::vector<int> W, H, K, seg_off;
+  std::vector<int> digits32;  // fixed-point digits of the FP32 matrix-core form
   std::vector<std::vector<Seg>> segs;
   std::vector<std::vector<double>> c64;
   std::vector<double> q_k, r64;
   std::vector<DevTmpl> dev;  // generic (plain / refine) descriptors
   DevBuf d_geom, d_c64, d_area, d_dev, d_c32;
+  // built on demand by calls that take the set as const, from any thread
+  mutable std::mutex dense_mu;
+  mutable std::unique_ptr<DenseTmpl[]> dense;  // FP32 and FP64 form of each template
+  mutable size_t dense_bytes = 0;
 };
 
 namespace {
@@ -1043,6 +1060,168 @@ int fill_templates(sncc_tmpl *tm, int T, const sncc_segment *const *segs, const 
   return SNCC_OK;
 }
 
+// ------------------------------------------------------- matrix-core form
+// Operands a template set may hold in all; templates beyond it keep the other
+// forms.
+constexpr size_t kDenseSetBytes = (size_t)2 << 30;
+
+// -1: by rule; with SNCC_TEST_DENSE=0 or 1 in the environment never, or
+// wherever it is possible (read at each call), so that a test can compare the
+// forms on the same call.
+int dense_forced() {
+  const char *v = std::getenv("SNCC_TEST_DENSE");
+  return v && (v[0] == '0' || v[0] == '1') ? v[0] - '0' : -1;
+}
+
+// Fixed point for template t's c with `digits` balanced base-256 digits: the
+// largest scale 2^e they hold (127 in every digit: 0.498 256^digits), and the
+// sum of the image dense_paint makes.  Returns the rounding's bound on |rho|,
+// sqrt(sum of squared rounding errors / q_k) (Cauchy-Schwarz; a pixel of
+// segment i is off by f or 1 - f units, f the fraction of 2^e c_i, in shares
+// that make the sum right: f (1 - f) on average).
+double dense_fixed_point(const sncc_tmpl *tm, int t, int digits, DenseTmpl &dt) {
+  const std::vector<double> &c = tm->c64[t];
+  double top = 0;
+  for (double x : c) top = std::max(top, std::fabs(x));
+  int e = 0;
+  (void)std::frexp(top, &e);  // top in [2^(e-1), 2^e)
+  dt.digits = digits;
+  dt.scale = std::ldexp(1.0, 8 * digits - (top <= std::ldexp(0.995, e) ? 1 : 2) - e);
+  __int128 sum = 0;
+  double err = 0;
+  for (size_t i = 0; i < c.size(); ++i) {
+    const double q = c[i] * dt.scale, whole = std::rint(q), part = q - whole;
+    const double area = (double)tm->segs[t][i].area;
+    sum += (__int128)(long long)whole * tm->segs[t][i].area + std::llrint(part * area);
+    err += area * std::fabs(part) * (1.0 - std::fabs(part));
+  }
+  dt.csum = (double)sum;
+  return std::sqrt(err / tm->q_k[t]) / dt.scale;
+}
+
+// Digits of the FP32 form: three where the rounding's bound is at most 2^-22
+// (as for four uncompensated FP32 products in the segment form; smooth frames
+// stay far below it), else four.
+int dense_digits32(const sncc_tmpl *tm, int t) {
+  DenseTmpl d;
+  return dense_fixed_point(tm, t, 3, d) <= std::ldexp(1.0, -22) ? 3 : 4;
+}
+
+// Template t's operands, built on first use (small launches, then a wait, so
+// that any stream may read them afterwards); nullptr where they cannot be
+// had: no memory, or the stream is being captured.
+const DenseTmpl *dense_tmpl(sncc_ctx *ctx, const sncc_tmpl *tm, int t, int digits) {
+  std::lock_guard<std::mutex> lk(tm->dense_mu);
+  if (!tm->dense) tm->dense.reset(new (std::nothrow) DenseTmpl[2 * (size_t)tm->T]);
+  if (!tm->dense) return nullptr;
+  DenseTmpl &dt = tm->dense[2 * (size_t)t + (digits == kDenseDigits)];
+  if (dt.built) return &dt;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
+    return nullptr;
+  const int W = tm->W[t], H = tm->H[t];
+  const size_t fb = dense_frag_bytes(W, H, digits), bytes = fb + (size_t)W * H * 8;
+  if (tm->dense_bytes + bytes > kDenseSetBytes || dt.frag.reserve(bytes) != SNCC_OK) {
+    g_err.clear();
+    return nullptr;
+  }
+  (void)dense_fixed_point(tm, t, digits, dt);
+  if (launch_dense_pack(tm->d_geom.as<int4>() + tm->seg_off[t],
+                        tm->d_c64.as<double>() + tm->seg_off[t], tm->K[t], dt.scale, W, H, digits,
+                        reinterpret_cast<long long *>(dt.frag.as<char>() + fb), dt.frag.p,
+                        ctx->stream) != 0 ||
+      hipStreamSynchronize(ctx->stream) != hipSuccess)
+    return nullptr;
+  tm->dense_bytes += bytes;
+  dt.built = true;
+  return &dt;
+}
+
+// Launch shape of the matrix-core form for a map of nu x nv offsets: false
+// where it does not apply.  Rows per wave half: eight where the tiles then
+// still fill the CUs twice (FP32; 3840 x 2160, 128 x 128: 309 us against 343
+// with four and 493 with two), else four while they fill them once (1920 x
+// 1080, 64 x 64: 37.7 us, 45.6 with eight, 45.7 with two; FP64, at most four
+// for its 28 accumulators a row: while they fill 5/8), else two (640 x 480, 32
+// x 32: 10.6 us, 15.7 with four).  LDS for two workgroups per CU, three where
+// one pass over the template fits that.
+bool dense_shape(const sncc_tmpl *tm, int t, int digits, int nu, int nv, int num_cu,
+                 DenseArgs &a) {
+  const int W = tm->W[t], H = tm->H[t], rows_all = 4 * dense_rows4(H);
+  if ((long long)W * H > kDenseMaxArea) return false;
+  a.W = W;
+  a.H = H;
+  a.n = W * H;
+  a.nu = nu;
+  a.nv = nv;
+  a.sq_rows = tm->dev[t].sq_rows;
+  a.G = dense_groups(W);
+  // an odd number of 16-byte pieces: the two row halves of a B operand, rv
+  // rows apart, then start 32 LDS banks apart for rv = 8
+  a.pitch = 16 * ((7 + a.G) | 1);
+  a.digits = digits;
+  a.ntu = (nu + kDenseBU - 1) / kDenseBU;
+  auto tiles = [&](int rv) {
+    const int bv = 2 * kDenseNW * rv;
+    return (long long)a.ntu * ((nv + bv - 1) / bv);
+  };
+  a.rv = digits == 3 && tiles(8) >= 2LL * num_cu                       ? 8
+         : 8 * tiles(4) >= (digits == kDenseDigits ? 5LL : 8LL) * num_cu ? 4
+                                                                       : 2;
+  const int bv = 2 * kDenseNW * a.rv;
+  a.ntv = (nv + bv - 1) / bv;
+  auto rows = [&](int lds) { return std::min(rows_all, (lds / a.pitch - (bv - 1)) & ~7); };
+  a.hb = rows(kTileMaxLds / 3 - 256);
+  if (a.hb < rows_all) a.hb = rows(kTileMaxLds / 2 - 256);
+  return a.hb >= 8;
+}
+
+// Whether the matrix-core form is the faster one: estimates in ps per offset
+// from maps measured both ways (one MI355X, us a map, other form / this one).
+// FP32: the segment form's evaluations and staged rows against the matrix
+// steps: 1920 x 1080 with 64 x 64 at K 110 62.7 / 40.2, K 1005 457 / 37.7;
+// 61 x 47, K 118 63.4 / 33.9; 128 x 96, K 73 70.1 / 82.6; 3840 x 2160 with
+// 256 x 256, K 287 774 / 1006.  FP64: the plain form's evaluations: 64 x 64,
+// K 110 144 / 62, K 1005 1017 / 62; 128 x 96, K 73 103 / 138; 192 x 180,
+// K 579 530 / 339; 256 x 256, K 287 1153 / 2004.  Two rows per wave half cost
+// 1.6 times the steps.
+bool dense_wins(const sncc_tmpl *tm, int t, const DenseArgs &a) {
+  const int forced = dense_forced();
+  if (forced >= 0) return forced == 1;
+  const double W = a.W, H = a.H, K = tm->K[t], mac = H * a.G * 16 * (a.rv == 2 ? 1.6 : 1.0);
+  if (a.digits == kDenseDigits) return 0.52 * K + 16.0 > 10.0 + 4.9e-3 * mac;
+  return 0.22 * K + 6e-4 * (W + 128.0) * (H + 32.0) > 6.0 + 0.8e-3 * a.digits * mac;
+}
+
+// Scores a map with the matrix-core form; returns 1 when it ran, 0 when the
+// call belongs to another form, or an error.
+int dense_map(sncc_ctx *ctx, const sncc_tmpl *tm, int t, const uint32_t *s, const uint32_t *s2,
+              int N, int P, int nu, int nv, bool fp64, void *rho, int rho_pitch,
+              uint8_t *degen) {
+  DenseArgs a{};
+  if ((long long)tm->W[t] * tm->H[t] > kDenseMaxArea) return 0;
+  const int digits = fp64 ? kDenseDigits : tm->digits32[t];
+  if (!dense_shape(tm, t, digits, nu, nv, ctx->num_cu, a) || !dense_wins(tm, t, a)) return 0;
+  const DenseTmpl *dt = dense_tmpl(ctx, tm, t, digits);
+  if (!dt) return 0;
+  a.s = s;
+  a.s2 = s2;
+  a.frag = dt->frag.p;
+  a.P = P;
+  a.N = N;
+  a.csum = dt->csum;
+  a.inv_scale = 1.0 / dt->scale;
+  a.q_k = tm->q_k[t];
+  a.qnd = a.q_k / (double)a.n;
+  a.inv_n = 1.0 / (double)a.n;
+  a.rho = rho;
+  a.rho_pitch = rho_pitch;
+  a.degen = degen;
+  if (launch_dense(a, ctx->stream) != 0)
+    SNCC_FAIL(SNCC_EDEVICE, "matrix-core launch: %s", hipGetErrorString(hipGetLastError()));
+  return 1;
+}
+
 }  // namespace
 
 // ================================================================ C-ABI
@@ -1290,6 +1469,7 @@ int sncc_upload_templates(sncc_ctx *ctx, int T, const sncc_segment *const *segs,
   std::vector<double> c64all;
   std::vector<int> areas;
   CHK(fill_templates(tm.get(), T, segs, K, W, H, geom, c64all, areas));
+  for (int t = 0; t < T; ++t) tm->digits32.push_back(dense_digits32(tm.get(), t));
   std::vector<float> c32all(c64all.begin(), c64all.end());
   CHK(tm->d_geom.upload(geom, ctx->stream));
   CHK(tm->d_c64.upload(c64all, ctx->stream));
@@ -1340,6 +1520,11 @@ int sncc_score(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint32_t *d_
   const int nu = M - tm->W[index] + 1, nv = N - tm->H[index] + 1;
   if (nu < 1 || nv < 1) SNCC_FAIL(SNCC_EINVAL, "template larger than image");
   if (rho_pitch < nu) SNCC_FAIL(SNCC_EINVAL, "rho_pitch %d < %d", rho_pitch, nu);
+  if (precision != SNCC_FP64 && precision != SNCC_FP32_KAHAN)
+    SNCC_FAIL(SNCC_EINVAL, "unknown precision %d", precision);
+  const int dense = dense_map(ctx, tm, index, d_s, d_s2, N, sat_pitch, nu, nv,
+                              precision == SNCC_FP64, d_rho, rho_pitch, d_degenerate);
+  if (dense != 0) return dense < 0 ? dense : SNCC_OK;
   if (precision == SNCC_FP64) {
     PlainArgs a;
     a.s = d_s;
@@ -1363,7 +1548,6 @@ int sncc_score(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint32_t *d_
       SNCC_FAIL(SNCC_EDEVICE, "plain launch: %s", hipGetErrorString(hipGetLastError()));
     return SNCC_OK;
   }
-  if (precision != SNCC_FP32_KAHAN) SNCC_FAIL(SNCC_EINVAL, "unknown precision %d", precision);
   // the plan of the last map call is kept and reused when the call repeats
   // (same template set and index, sizes and pitch)
   const int32_t pair[2] = {0, index};

@@ -1,0 +1,340 @@
+// Matrix-core scoring of a rho map (Eqs. (11)-(18)) for approximations with
+// many segments.
+//
+// The numerator sum_i c_i F_i of Eq. (12) equals the correlation of the frame
+// with the approximation's zero-mean image c(x, y) (c_i on segment i).  Its
+// cost does not grow with the number of segments, so above some K per template
+// pixel it beats the segment sums.  It is formed in integers: c is held as
+// fixed-point digits, c ~ 2^-e sum_d q_d 256^d with q_d in [-128, 127], the
+// frame as f - 128 in [-128, 127], and each digit's correlation is an exact
+// 32-bit integer sum on the i8 matrix instructions.  Seven digits serve FP64,
+// three or four FP32 (dense_digits32 in api.cpp).  The only roundings are those
+// of c and of the result: rms error of an FP32 map against 64 bits 2.5e-8
+// relative (the result's own rounding; 4.5e-8 to 6e-8 in the segment form), of
+// an FP64 map 0 to 1e-14 (0 to 1e-13 in the plain form).
+//
+// What bounds it: large templates the matrix rate (3840 x 2160, 128 x 128,
+// K 4465: 309 us, 2.7e15 operations/s, where a loop of these instructions alone
+// reaches 3.4e15 on random data; the segment form took 6678 us; FP64 645 us,
+// 3.0e15/s, against 16.0 ms in the plain form), small ones the launch, the
+// staging and the epilogue's table reads (1920 x 1080, 64 x 64: 37.7 us, about
+// half of it matrix work).
+//
+// Contraction: one instruction multiplies A (16 x 64) by B (64 x 16).  Column
+// j of B is a block of 16 offset columns, u = u0 + 16 (j mod 8) + i, of one of
+// two offset rows (j / 8); row i of A is the offset within the block.  The 64 products are four template rows y .. y + 3
+// of 16 template columns 16 x - i .. + 15 (x = 0 .. G - 1, G = ceil((W + 15) /
+// 16)), so that B's entries are aligned 16-byte pieces of frame rows, the same
+// for every i, and A holds the template rows shifted by i (banded Toeplitz
+// blocks, zero outside the template), prepared once per template in the
+// instruction's register layout (dense_pack).  W / (16 G) of the products are
+// not zero: 0.80 at W = 64, 0.89 at 128.  B of offset row v + 4 is B of offset
+// row v one step (four template rows) later, so a wave with eight offset rows
+// reads each B once for two uses.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdint>
+
+#include "device_util.hpp"
+
+namespace sncc {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef uint32_t v4u_a4 __attribute__((ext_vector_type(4), aligned(4)));  // any word address
+
+// ------------------------------------------------------------- preparation
+// c in fixed point, painted over the template: one workgroup per segment.
+// Pixel i of a segment gets rint(c scale (i + 1)) - rint(c scale i), so that
+// the rounding of a segment's pixels adds up to less than one unit instead of
+// A_i times the rounding of c_i.
+__global__ __launch_bounds__(64) void dense_paint(const int4 *__restrict__ geom,
+                                                  const double *__restrict__ c64, double scale,
+                                                  int W, long long *__restrict__ img) {
+  const int4 g = geom[blockIdx.x];
+  const double c = c64[blockIdx.x] * scale;
+  const int n = g.z * g.w;
+  const double whole = rint(c), part = c - whole;  // the part's multiples stay exact enough
+  for (int i = threadIdx.x; i < n; i += 64) {
+    const int y = i / g.z, x = i - y * g.z;
+    img[(long long)(g.y + y) * W + g.x + x] =
+        (long long)whole + (long long)(rint(part * (i + 1)) - rint(part * i));
+  }
+}
+
+// A operands: one thread per (step, lane) writes its 16 bytes of every digit,
+// leading digit first: frag[(step * D + d) * 64 + lane], steps ordered by
+// column group x, then by rows.
+template <int D>
+__global__ __launch_bounds__(64) void dense_pack(const long long *__restrict__ img, int W, int H,
+                                                 v4i *__restrict__ frag) {
+  const int n4 = dense_rows4(H), step = blockIdx.x, xg = step / n4;
+  const int lane = threadIdx.x, y = 4 * (step - xg * n4) + (lane >> 4);
+  const int x0 = 16 * xg - (lane & 15);
+  uint32_t w[D][4] = {};
+#pragma unroll
+  for (int b = 0; b < 16; ++b) {
+    const int x = x0 + b;
+    long long c = x >= 0 && x < W && y < H ? img[(long long)y * W + x] : 0;
+#pragma unroll
+    for (int d = D - 1; d >= 0; --d) {  // balanced digits, last one first
+      const int lo = (int)(int8_t)(c & 0xff);
+      w[d][b >> 2] |= (uint32_t)(lo & 0xff) << (8 * (b & 3));
+      c = (c - lo) >> 8;
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    v4i o;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] = (int)w[d][k];
+    frag[((long long)step * D + d) * 64 + lane] = o;
+  }
+}
+
+int launch_dense_pack(const int4 *geom, const double *c64, int K, double scale, int W, int H,
+                      int digits, long long *img, void *frag, hipStream_t st) {
+  hipLaunchKernelGGL(dense_paint, dim3(K), dim3(64), 0, st, geom, c64, scale, W, img);
+  const dim3 grid(dense_steps(W, H));
+  v4i *o = static_cast<v4i *>(frag);
+  switch (digits) {
+    case 3: hipLaunchKernelGGL(dense_pack<3>, grid, dim3(64), 0, st, img, W, H, o); break;
+    case 4: hipLaunchKernelGGL(dense_pack<4>, grid, dim3(64), 0, st, img, W, H, o); break;
+    default: hipLaunchKernelGGL(dense_pack<7>, grid, dim3(64), 0, st, img, W, H, o); break;
+  }
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// ------------------------------------------------------------------ scoring
+// Rows [y0, y0 + rows) x columns [x0, x0 + 4 n4) of the frame to LDS, each
+// pixel as f - 128 in a byte, `pitch` bytes per row.  Pixels come from the sum
+// table: f(x, y) is the one-pixel box sum of Eq. (11).  A thread walks down a
+// stripe of rows with four columns, eight rows of table entries requested at a
+// time.  Table rows past N and entries past the pitch are clamped: only
+// offsets outside the valid range and zero rows of A use such pixels.
+template <int NT>
+__device__ __forceinline__ void dense_region(const uint32_t *__restrict__ S, int P, int N, int x0,
+                                             int y0, int rows, int n4, int pitch,
+                                             uint8_t *__restrict__ lds, int t) {
+  const int ns = max(1, NT / n4), per = (rows + ns - 1) / ns;
+  for (int unit = t; unit < n4 * ns; unit += NT) {
+    const int stripe = unit / n4, c4 = unit - stripe * n4;
+    const int ra = stripe * per, rb = min(rows, ra + per);
+    const int c = min(x0 + 4 * c4, P - 4), e = min(x0 + 4 * c4 + 4, P - 1);
+    auto row = [&](int r, uint32_t (&d)[4]) {  // horizontal differences of table row r
+      const uint32_t *p = S + (long long)min(r, N) * P;
+      const uint4 a = *reinterpret_cast<const uint4 *>(p + c);
+      const uint32_t z = p[e];
+      d[0] = a.y - a.x;
+      d[1] = a.z - a.y;
+      d[2] = a.w - a.z;
+      d[3] = z - a.w;
+    };
+    uint32_t up[4];
+    row(y0 + ra, up);
+    for (int r = ra; r < rb; r += 8) {
+      uint32_t d[8][4];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) row(y0 + min(r + k, rb - 1) + 1, d[k]);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if (r + k < rb) {
+          const uint32_t px = (d[k][0] - up[0]) | (d[k][1] - up[1]) << 8 |
+                              (d[k][2] - up[2]) << 16 | (d[k][3] - up[3]) << 24;
+          *reinterpret_cast<uint32_t *>(lds + (r + k) * pitch + 4 * c4) = px ^ 0x80808080u;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) up[q] = d[k][q];
+      }
+    }
+  }
+}
+
+// Four consecutive entries of a table row from entry x on, all when x + 3 is
+// inside the pitch, else each from the nearest entry inside it.
+__device__ __forceinline__ v4u_a4 dense_row4(const uint32_t *__restrict__ p, int x, int P) {
+  if (x + 3 < P) return *reinterpret_cast<const v4u_a4 *>(p + x);
+  v4u_a4 o;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) o[k] = p[min(x + k, P - 1)];
+  return o;
+}
+
+// One tile of 128 x (2 NW RV) offsets per workgroup; wave w takes offset rows
+// 2 w RV .. 2 w RV + 2 RV - 1, and lane (j = lane mod 16, g = lane / 16) ends
+// with the offsets u0 + 16 (j mod 8) + 4 g + 0..3 of rows RV (2 w + j / 8) + r.
+// (Against 256 x (NW RV): fewer staged bytes per offset and less waste at the
+// right edge.)  Template rows are taken in
+// passes of a.hb, whose frame rows are staged in LDS.  Per step a wave loads D
+// operands A (from the caches: every wave of the launch reads the same ones)
+// and min(RV, 4) operands B (LDS) for D RV instructions.
+template <int D, int RV, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dense_kernel(
+    const uint32_t *__restrict__ S, const uint32_t *__restrict__ S2,
+    const v4i *__restrict__ frag, DenseArgs a) {
+  extern __shared__ __align__(16) uint8_t lds8[];
+  constexpr int BV = 2 * NW * RV;
+  constexpr bool F64 = D == kDenseDigits;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // tiles row by row, a contiguous range of them per XCD (workgroups go round
+  // the XCDs), so that neighbouring tiles share the table rows in its L2
+  const int per = (int)gridDim.x >> 3;
+  const int tile = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+  if (tile >= a.ntu * a.ntv) return;
+  const int tv = tile / a.ntu, tu = tile - tv * a.ntu;
+  const int u0 = tu * kDenseBU, v0 = tv * BV;
+  const int j = lane & 7, g = lane >> 4;
+  const int row0 = RV * (2 * wave + ((lane >> 3) & 1));  // the lane's first offset row
+
+  v4i acc[RV][D];
+#pragma unroll
+  for (int r = 0; r < RV; ++r)
+#pragma unroll
+    for (int d = 0; d < D; ++d) acc[r][d] = v4i{0, 0, 0, 0};
+
+  // B of offset rows row0 + t .. t + NB - 1 (t = 4 y for the step of template
+  // rows 4 y .. 4 y + 3), two register sets: with eight rows per wave a step
+  // uses both (rows 0-3, 4-7) and the first is the next step's second; with
+  // fewer the second holds the next step's.  A set is reloaded as soon as its
+  // last use is issued, A's two sets likewise one step ahead.
+  constexpr int NB = RV < 4 ? RV : 4;
+  const int G = a.G, pitch = a.pitch, n4all = dense_rows4(a.H), hb4 = a.hb >> 2;
+  for (int yp4 = 0; yp4 < n4all; yp4 += hb4) {
+    const int n4 = min(hb4, n4all - yp4);
+    if (yp4) __syncthreads();
+    dense_region<64 * NW>(S, a.P, a.N, u0, v0 + 4 * yp4, BV + 4 * n4 - 1, 28 + 4 * G, pitch, lds8,
+                          threadIdx.x);
+    __syncthreads();
+    // A of the pass's steps in order, the last one's again after it
+    const v4i *fa = frag + (long long)yp4 * (D * 64) + lane;
+    int ax = 0, ay = 0;
+    auto load_A = [&](v4i(&A)[D]) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) A[d] = fa[d * 64];
+      const bool wrap = ++ay == n4;
+      ax += wrap;
+      ay = wrap ? 0 : ay;
+      fa += ax >= G ? 0 : (wrap ? n4all - n4 + 1 : 1) * (D * 64);
+    };
+    v4i A0[D], A1[D], b0[NB], b1[NB];
+    load_A(A0);
+    load_A(A1);
+    const uint8_t *base = lds8 + (row0 + g) * pitch + 16 * j;
+    for (int x = 0; x < G; ++x, base += 16) {
+      auto load_B = [&](int y, v4i(&b)[NB]) {
+#pragma unroll
+        for (int r = 0; r < NB; ++r)
+          b[r] = *reinterpret_cast<const v4i *>(base + (4 * y + r) * pitch);
+      };
+      auto mul = [&](const v4i(&A)[D], const v4i(&b)[NB], int r0) {
+#pragma unroll
+        for (int r = 0; r < NB; ++r)
+#pragma unroll
+          for (int d = 0; d < D; ++d)
+            acc[r0 + r][d] =
+                __builtin_amdgcn_mfma_i32_16x16x64_i8(A[d], b[r], acc[r0 + r][d], 0, 0, 0);
+      };
+      load_B(0, b0);
+      load_B(1, b1);
+      for (int y = 0; y < n4; y += 2) {
+        const bool more = y + 2 < n4;
+        mul(A0, b0, 0);
+        if (RV > 4 || more) load_B(y + 2, b0);
+        if constexpr (RV > 4) mul(A0, b1, 4);
+        load_A(A0);
+        mul(A1, b1, 0);
+        if (more) load_B(y + 3, b1);
+        if constexpr (RV > 4) mul(A1, b0, 4);
+        load_A(A1);
+      }
+    }
+  }
+
+  // epilogue: window sums (Eqs. (13), (15)) and the exact window energy as in
+  // the other forms; the numerator is the digits' sum less the digits' own
+  // mean term (the rounded c need not sum to zero), in FP64
+  const int u = u0 + 16 * j + 4 * g;
+  const int uc = min(u, a.nu - 1);
+#pragma unroll
+  for (int r = 0; r < RV; ++r) {
+    const int v = v0 + row0 + r, vc = min(v, a.nv - 1);
+    const uint32_t *t0 = S + (long long)vc * a.P, *t1 = t0 + (long long)a.H * a.P;
+    const v4u_a4 sf = (dense_row4(t1, uc + a.W, a.P) - dense_row4(t1, uc, a.P)) -
+                      (dense_row4(t0, uc + a.W, a.P) - dense_row4(t0, uc, a.P));
+    u64 sf2[4] = {0, 0, 0, 0};
+    for (int y = 0; y < a.H; y += a.sq_rows) {
+      const uint32_t *q0 = S2 + (long long)(vc + y) * a.P;
+      const uint32_t *q1 = q0 + (long long)min(a.sq_rows, a.H - y) * a.P;
+      const v4u_a4 b = (dense_row4(q1, uc + a.W, a.P) - dense_row4(q1, uc, a.P)) -
+                       (dense_row4(q0, uc + a.W, a.P) - dense_row4(q0, uc, a.P));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) sf2[k] += b[k];
+    }
+    const bool row_ok = v < a.nv;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const long long V = (long long)((u64)(uint32_t)a.n * sf2[k] - (u64)sf[k] * sf[k]);
+      const double fbar = (double)sf[k] * a.inv_n;
+      double T;
+      if constexpr (F64) {
+        const long long hi = ((long long)acc[r][0][k] << 16) + ((long long)acc[r][1][k] << 8) +
+                             acc[r][2][k];
+        const long long lo = ((long long)acc[r][3][k] << 24) + ((long long)acc[r][4][k] << 16) +
+                             ((long long)acc[r][5][k] << 8) + acc[r][6][k];
+        T = __builtin_fma((double)hi, 4294967296.0, (double)lo);
+      } else {
+        long long t = acc[r][0][k];
+#pragma unroll
+        for (int d = 1; d < D; ++d) t = (t << 8) + acc[r][d][k];
+        T = (double)t;
+      }
+      const double num = (T - a.csum * (fbar - 128.0)) * a.inv_scale;
+      const long long o = (long long)v * a.rho_pitch + u + k;
+      if (row_ok && u + k < a.nu) {
+        if constexpr (F64) {
+          const double rho = V == 0 ? 0.0 : num / sqrt((double)V / (double)a.n * a.q_k);
+          static_cast<double *>(a.rho)[o] = rho;
+        } else {
+          // 1 / sqrt of the energy in FP64: the FP32 estimate and one Newton step
+          const double e = (double)V * a.qnd;
+          const double y0 = (double)__builtin_amdgcn_rsqf((float)e);
+          const double y1 = y0 * __builtin_fma(-0.5 * e * y0, y0, 1.5);
+          static_cast<float *>(a.rho)[o] = V == 0 ? 0.f : (float)(num * y1);
+        }
+        if (a.degen) a.degen[o] = V == 0 ? 1 : 0;
+      }
+    }
+  }
+}
+
+template <int D, int RV, int NW>
+static int dense_go(const DenseArgs &a, hipStream_t st) {
+  static bool attr = false;
+  const void *fn = (const void *)dense_kernel<D, RV, NW>;
+  if (!attr) {
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kTileMaxLds) !=
+        hipSuccess)
+      return -1;
+    attr = true;
+  }
+  const int lds = (2 * NW * RV + a.hb - 1) * a.pitch;
+  const int grid = (a.ntu * a.ntv + 7) / 8 * 8;
+  hipLaunchKernelGGL((dense_kernel<D, RV, NW>), dim3(grid), dim3(64 * NW), lds, st, a.s, a.s2,
+                     static_cast<const v4i *>(a.frag), a);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_dense(const DenseArgs &a, hipStream_t st) {
+  switch (a.digits * 100 + a.rv) {
+    case 308: return dense_go<3, 8, kDenseNW>(a, st);
+    case 304: return dense_go<3, 4, kDenseNW>(a, st);
+    case 302: return dense_go<3, 2, kDenseNW>(a, st);
+    case 404: return dense_go<4, 4, kDenseNW>(a, st);
+    case 402: return dense_go<4, 2, kDenseNW>(a, st);
+    case 704: return dense_go<7, 4, kDenseNW>(a, st);
+    case 702: return dense_go<7, 2, kDenseNW>(a, st);
+    default: return -1;
+  }
+}
+
+}  // namespace sncc

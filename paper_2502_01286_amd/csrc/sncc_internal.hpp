@@ -278,6 +278,45 @@ constexpr int kFusedNW = 4;                    // waves per workgroup
 constexpr int kFusedBU = 64;                   // offset columns per tile
 constexpr int kFusedBV = kFusedRV * kFusedNW;  // offset rows per tile
 
+// Matrix-core form (dense_kernel.hip): the numerator as a correlation with the
+// approximation's image in fixed-point digits.
+constexpr int kDenseDigits = 7;        // digits of the FP64 form (FP32: 3 or 4)
+constexpr int kDenseNW = 4;            // waves per workgroup
+constexpr int kDenseBU = 128;          // offset columns per tile
+constexpr int kDenseMaxArea = 131071;  // n 2^14 < 2^31: a digit's sum fits 32 bits
+// 16-pixel groups of a template row: 16 shifts of W columns.
+inline int dense_groups(int W) { return (W + 30) / 16; }
+// Steps of four template rows (rows padded with zeros to a multiple of 8: the
+// kernel takes two steps at a time), and matrix steps in all.
+__host__ __device__ inline int dense_rows4(int H) { return (H + 7) / 8 * 2; }
+inline int dense_steps(int W, int H) { return dense_rows4(H) * dense_groups(W); }
+inline size_t dense_frag_bytes(int W, int H, int digits) {
+  return (size_t)dense_steps(W, H) * digits * 1024;
+}
+struct DenseArgs {
+  const uint32_t *s, *s2;
+  const void *frag;        // dense_pack's operands
+  int P, N;
+  int nu, nv, W, H, n;
+  int sq_rows;             // rows per band of the f^2 window sum
+  int G;                   // dense_groups(W)
+  int hb;                  // template rows per pass (a multiple of 8)
+  int pitch;               // LDS bytes per staged row, at least 112 + 16 G
+  int ntu, ntv;
+  int digits;              // 3 or 4 (FP32 map), 7 (FP64 map)
+  int rv;                  // offset rows per wave half: tiles of 8 rv rows
+  double csum;             // sum over the template of the digits' values
+  double inv_scale;        // value of one unit of the last digit
+  double q_k, qnd, inv_n;  // Eq. (17); q_k / n; 1 / n
+  void *rho;
+  int rho_pitch;
+  uint8_t *degen;
+};
+// Weak: the planner also links into host-only programs without the kernels.
+int launch_dense_pack(const int4 *geom, const double *c64, int K, double scale, int W, int H,
+                      int digits, long long *img, void *frag, hipStream_t st) __attribute__((weak));
+int launch_dense(const DenseArgs &a, hipStream_t st) __attribute__((weak));
+
 // Tile kernel configuration: offsets per lane RU (u, stride 64) x RV (v),
 // NW waves per workgroup, each wave owning RV offset rows; `wgs` is the
 // number of workgroups per CU the LDS budget is sized for; with
