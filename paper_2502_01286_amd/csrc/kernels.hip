@@ -56,11 +56,12 @@ size_t sat_scratch_words(int B, int M, int N) {
 }
 
 // Pixels x0 .. x0 + 3 of a row packed into one word (byte q = pixel x0 + q,
-// 0 beyond M): one 32-bit load when all four are inside the row and the
-// address is 4-byte aligned, else byte loads.
+// 0 beyond M): one 32-bit load, at any address, when all four are inside the
+// row, else byte loads.  (Byte loads for every row of a frame whose pitch is
+// no multiple of 4 took a 1917 x 1079 build from 20.5 to 26.8 us.)
+typedef uint32_t u32_a1 __attribute__((aligned(1)));
 __device__ __forceinline__ uint32_t load_pk4(const uint8_t *row, int x0, int M) {
-  if (x0 + 3 < M && ((reinterpret_cast<uintptr_t>(row + x0) & 3) == 0))
-    return *reinterpret_cast<const uint32_t *>(row + x0);
+  if (x0 + 3 < M) return *reinterpret_cast<const u32_a1 *>(row + x0);
   uint32_t w = 0;
 #pragma unroll
   for (int q = 0; q < 4; ++q)
@@ -92,14 +93,40 @@ __device__ __forceinline__ void store_cols4(uint32_t *o, int x0, int M, int P,
 constexpr int SAT_WAVES = 4;
 constexpr int SAT_WR = SAT_TY / SAT_WAVES;  // rows per wave
 
-// A lane's four columns over one wave's rows, requested before any is used.
-__device__ __forceinline__ void load_wave_rows(const uint8_t *fb, int y0, int r0, int rows,
-                                               int f_pitch, int x0, int M,
-                                               uint32_t (&pk)[SAT_WR]) {
+// A lane's four columns over RW rows of a tile from row r0 on, requested
+// before any is used (0 past the tile's rows and the frame's columns).
+template <int RW>
+__device__ __forceinline__ void load_rows(const uint8_t *fb, int y0, int r0, int rows,
+                                          int f_pitch, int x0, int M, uint32_t (&pk)[RW]) {
 #pragma unroll
-  for (int r = 0; r < SAT_WR; ++r)
+  for (int r = 0; r < RW; ++r)
     pk[r] = (r0 + r < rows && x0 < M) ? load_pk4(fb + (size_t)(y0 + r0 + r) * f_pitch, x0, M)
                                       : 0u;
+}
+
+// Column totals of RW rows (at most 16) of a lane's four columns, added to
+// cs, cs2: f as two 16-bit halves of a word (16 rows of bytes stay below
+// 2^16), f^2 as byte dot products of one byte each.
+template <int RW>
+__device__ __forceinline__ void add_columns(const uint32_t (&pk)[RW], uint32_t (&cs)[4],
+                                            uint32_t (&cs2)[4]) {
+  static_assert(RW <= 16, "16-bit halves");
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int r = 0; r < RW; ++r) {
+    const uint32_t x = pk[r];
+    lo += x & 0x00ff00ffu;         // columns 0 and 2
+    hi += (x >> 8) & 0x00ff00ffu;  // columns 1 and 3
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t m = x & (0xffu << (8 * q));
+      cs2[q] = __builtin_amdgcn_udot4(m, m, cs2[q], false);
+    }
+  }
+  cs[0] += lo & 0xffffu;
+  cs[1] += hi & 0xffffu;
+  cs[2] += lo >> 16;
+  cs[3] += hi >> 16;
 }
 
 // DPP add within quads of lanes: lanes 0-1 and 2-3 exchanged (quad_perm
@@ -130,31 +157,17 @@ __global__ __launch_bounds__(256) void sat_totals(const uint8_t *__restrict__ f,
   const int r0 = w * SAT_WR;
   const uint8_t *fb = f + (size_t)b * N * f_pitch;
   uint32_t pk[SAT_WR];
-  load_wave_rows(fb, y0, r0, rows, f_pitch, x0, M, pk);  // 0 past the frame
-  // column sums: f as two 16-bit halves of a word (16 rows of bytes stay
-  // below 2^16), f^2 as byte dot products of one byte each
-  uint32_t lo = 0, hi = 0, t2[4] = {0, 0, 0, 0};
-#pragma unroll
-  for (int r = 0; r < SAT_WR; ++r) {
-    const uint32_t x = pk[r];
-    lo += x & 0x00ff00ffu;         // columns 0 and 2
-    hi += (x >> 8) & 0x00ff00ffu;  // columns 1 and 3
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t m = x & (0xffu << (8 * q));
-      t2[q] = __builtin_amdgcn_udot4(m, m, t2[q], false);
-    }
-  }
+  load_rows<SAT_WR>(fb, y0, r0, rows, f_pitch, x0, M, pk);  // 0 past the frame
+  uint32_t cs[4] = {0, 0, 0, 0}, cs2[4] = {0, 0, 0, 0};
+  add_columns<SAT_WR>(pk, cs, cs2);
 #pragma unroll
   for (int r = 0; r < SAT_WR; ++r) {
     const uint32_t a = quad_sum(__builtin_amdgcn_udot4(pk[r], 0x01010101u, 0u, false));
     const uint32_t a2 = quad_sum(__builtin_amdgcn_udot4(pk[r], pk[r], 0u, false));
     if ((lane & 3) == 0) rq[w][r][lane >> 2] = make_uint2(a, a2);
   }
-  uint32_t cs[4] = {lo & 0xffffu, hi & 0xffffu, lo >> 16, hi >> 16}, cs2[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    cs2[q] = t2[q];
     wcol[w][q][lane] = cs[q];
     wcol[w][4 + q][lane] = cs2[q];
   }
@@ -203,6 +216,12 @@ __global__ __launch_bounds__(256) void sat_totals(const uint8_t *__restrict__ f,
   }
 }
 
+// RW rows per wave, 4 RW per workgroup: whole tiles (RW = 16), or quarters of
+// them (RW = 4), whose waves also sum the tile's rows above their quarter from
+// the frame (at most 48, from L2).  Quarters cost a batch more reads, but a
+// frame of a few dozen tiles leaves most CUs idle and waits for each wave's
+// chain of 16 rows (two wavefront scans each) after its carries.
+template <int RW>
 __global__ __launch_bounds__(256) void sat_scan(const uint8_t *__restrict__ f,
                                                 int B, int M, int N, int f_pitch,
                                                 const uint32_t *__restrict__ scratch,
@@ -213,49 +232,49 @@ __global__ __launch_bounds__(256) void sat_scan(const uint8_t *__restrict__ f,
   __shared__ uint32_t wcar[SAT_WAVES][8][64];  // per wave: its part of the column carries
   SatScratch sc = sat_layout(const_cast<uint32_t *>(scratch), B, M, N);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int J = blockIdx.x, I = blockIdx.y, b = blockIdx.z;
+  const int J = blockIdx.x, b = blockIdx.z;
+  constexpr int WGR = SAT_WAVES * RW;  // rows per workgroup
+  const int I = blockIdx.y * WGR / SAT_TY;
   const int x0 = J * SAT_TX + 4 * lane;
   const int y0 = I * SAT_TY;
+  const int above = (int)blockIdx.y * WGR - y0;  // the tile's rows above this workgroup's
   const int rows = min(SAT_TY, N - y0);
-  const int r0 = w * SAT_WR;
+  const int r0 = above + w * RW;
   const uint8_t *fb = f + (size_t)b * N * f_pitch;
   uint32_t *sb = s + (size_t)b * (N + 1) * P;
   uint32_t *s2b = s2 + (size_t)b * (N + 1) * P;
 
-  uint32_t pk[SAT_WR];
-  load_wave_rows(fb, y0, r0, rows, f_pitch, x0, M, pk);
-  // this wave's column totals, for the waves below it (rows past the frame
-  // are 0).  Sums of f as two 16-bit halves of a word (16 rows of bytes stay
-  // below 2^16), squares as byte dot products: other instructions than the
-  // row loop's, so the compiler does not keep the products of all 16 rows
-  // live for the loop to reuse.
-  {
-    uint32_t lo = 0, hi = 0, t2[4] = {0, 0, 0, 0};
+  uint32_t pk[RW];
+  load_rows<RW>(fb, y0, r0, rows, f_pitch, x0, M, pk);
+  uint32_t cs[4] = {0, 0, 0, 0}, cs2[4] = {0, 0, 0, 0};
+  if constexpr (RW < SAT_WR) {
+    // this wave's share of the rows above: a quarter of every 4 RW of them
 #pragma unroll
-    for (int r = 0; r < SAT_WR; ++r) {
-      const uint32_t x = pk[r];
-      lo += x & 0x00ff00ffu;           // columns 0 and 2
-      hi += (x >> 8) & 0x00ff00ffu;    // columns 1 and 3
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t m = x & (0xffu << (8 * q));
-        t2[q] = __builtin_amdgcn_udot4(m, m, t2[q], false);
-      }
+    for (int q = 0; q < SAT_TY / WGR - 1; ++q) {
+      uint32_t up[RW];
+      load_rows<RW>(fb, y0, q * WGR + w * RW, above, f_pitch, x0, M, up);
+      add_columns<RW>(up, cs, cs2);
     }
-    wcol[w][0][lane] = lo & 0xffffu;
-    wcol[w][1][lane] = hi & 0xffffu;
-    wcol[w][2][lane] = lo >> 16;
-    wcol[w][3][lane] = hi >> 16;
+  }
+  // this wave's column totals, for the waves below it (rows past the frame
+  // are 0), by other instructions than the row loop's, so that the compiler
+  // does not keep the products of all its rows live for the loop to reuse
+  {
+    uint32_t t[4] = {0, 0, 0, 0}, t2[4] = {0, 0, 0, 0};
+    add_columns<RW>(pk, t, t2);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) wcol[w][4 + q][lane] = t2[q];
+    for (int q = 0; q < 4; ++q) {
+      wcol[w][q][lane] = t[q];
+      wcol[w][4 + q][lane] = t2[q];
+    }
   }
   // The carries, summed here from sat_totals' totals (modulo 2^32, so in any
   // order): the column totals of the tile rows above (the waves take every
   // fourth tile row and add their parts through LDS), each row's totals of
   // the tile columns to its left (lane r: row y0 + r), and the tile totals
   // above-left (spread over the lanes, then a wave sum).
-  uint32_t cs[4] = {0, 0, 0, 0}, cs2[4] = {0, 0, 0, 0};
   const size_t plane_col = (size_t)B * sc.nTY * M;
+#pragma unroll 4
   for (int Ip = w; Ip < I; Ip += SAT_WAVES) {
     const size_t o = ((size_t)b * sc.nTY + Ip) * M + x0;
 #pragma unroll
@@ -273,6 +292,7 @@ __global__ __launch_bounds__(256) void sat_scan(const uint8_t *__restrict__ f,
   const size_t plane_row = (size_t)B * N * sc.nTX;
   uint32_t rl = 0, rl2 = 0;
   if (lane < rows)
+#pragma unroll 4
     for (int Jp = 0; Jp < J; ++Jp) {
       const size_t o = ((size_t)b * sc.nTX + Jp) * N + y0 + lane;
       rl += sc.rowT[o];
@@ -303,7 +323,7 @@ __global__ __launch_bounds__(256) void sat_scan(const uint8_t *__restrict__ f,
     }
 
 #pragma unroll
-  for (int r = 0; r < SAT_WR; ++r) {
+  for (int r = 0; r < RW; ++r) {
     if (r0 + r >= rows) continue;  // uniform; every pk index stays a constant
     const int y = y0 + r0 + r;
     uint32_t p[4], p2[4];
@@ -349,7 +369,7 @@ __global__ __launch_bounds__(256) void sat_scan(const uint8_t *__restrict__ f,
     // wave's rows (which held every row's partial sums live at once)
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (I == 0 && w == 0) {  // padded row 0
+  if (blockIdx.y == 0 && w == 0) {  // padded row 0
     for (int c = J * SAT_TX + lane; c < (J + 1) * SAT_TX + (J == sc.nTX - 1 ? P : 0) && c < P;
          c += 64) {
       sb[c] = 0;
@@ -358,14 +378,26 @@ __global__ __launch_bounds__(256) void sat_scan(const uint8_t *__restrict__ f,
   }
 }
 
+// Batches of at most this many tiles are scanned in quarters of tiles.  Whole /
+// quarter, us a build: 640 x 480 (24 tiles) 16.3 / 11.7, 1920 x 1080 (136)
+// 19.0 / 16.1, two of them (272) 22.6 / 20.5, eight 1280 x 720 (480)
+// 23.1 / 26.5, 3840 x 2160 (510) 30.1 / 39.5, 32 x 1280 x 720 61.2 / 69.9.
+constexpr long long kSatQuarterTiles = 320;
+
 int launch_sat(const uint8_t *f, int B, int M, int N, int f_pitch, uint32_t *s,
                uint32_t *s2, int sat_pitch, uint32_t *scratch, hipStream_t st) {
   const int nTX = (M + SAT_TX - 1) / SAT_TX, nTY = (N + SAT_TY - 1) / SAT_TY;
   dim3 grid(nTX, nTY, B);
   hipLaunchKernelGGL(sat_totals, grid, dim3(64 * SAT_WAVES), 0, st, f, B, M, N, f_pitch,
                      scratch);
-  hipLaunchKernelGGL(sat_scan, grid, dim3(64 * SAT_WAVES), 0, st, f, B, M, N, f_pitch, scratch,
-                     s, s2, sat_pitch);
+  if ((long long)nTX * nTY * B <= kSatQuarterTiles) {
+    grid.y = (N + SAT_TY / 4 - 1) / (SAT_TY / 4);
+    hipLaunchKernelGGL(sat_scan<SAT_WR / 4>, grid, dim3(64 * SAT_WAVES), 0, st, f, B, M, N,
+                       f_pitch, scratch, s, s2, sat_pitch);
+  } else {
+    hipLaunchKernelGGL(sat_scan<SAT_WR>, grid, dim3(64 * SAT_WAVES), 0, st, f, B, M, N, f_pitch,
+                       scratch, s, s2, sat_pitch);
+  }
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
