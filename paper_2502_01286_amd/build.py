@@ -28,7 +28,8 @@ ARCH = os.environ.get("SNCC_OFFLOAD_ARCH", "gfx950")
 N_TILE_SHAPES = 6
 SOURCES = [("segment.cpp", [], "segment.o"), ("api.cpp", [], "api.o"),
            ("kernels.hip", [], "kernels.o"), ("fused_kernel.hip", [], "fused_kernel.o"),
-           ("dense_kernel.hip", [], "dense_kernel.o")] + [
+           ("dense_kernel.hip", [], "dense_kernel.o"),
+           ("topk_filter.hip", [], "topk_filter.o")] + [
     ("tile_entry.hip", [f"-DSNCC_TILE_ENTRY_ID={i}"], f"tile_entry_{i}.o")
     for i in range(N_TILE_SHAPES)]
 

@@ -142,19 +142,21 @@ struct PlanKey {
   }
 };
 
+constexpr int kSlotTopk64 = kSinkCompact + 1;
+
 struct sncc_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
   int num_cu = 0;
   DevBuf sat_scratch;
-  DevBuf map_scratch;
   DevBuf frame_s, frame_s2;  // one frame's tables (global form of sncc_score_frame)
   std::vector<std::unique_ptr<PlanDev>> retired;  // awaiting completion
   bool timing = false;                             // record stage events
   hipEvent_t tev[4] = {};
   int n_stages = 0;                                // stages of the last timed call
-  PlanKey cache_key[3];                            // last plan per sink
-  std::unique_ptr<PlanDev> cache[3];
+  // last plan per sink; the FP64 top-k's (kSlotTopk64) after them
+  PlanKey cache_key[4];
+  std::unique_ptr<PlanDev> cache[4];
   ~sncc_ctx() {
     for (auto &e : tev)
       if (e) (void)hipEventDestroy(e);
@@ -169,11 +171,10 @@ struct sncc_ctx {
 // dense_kernel.hip), built at the first call that uses them and kept with the
 // template set.
 struct DenseTmpl {
-  bool built = false;
-  DevBuf frag;       // operands, then the fixed-point image they come from
+  const void *frag = nullptr;  // nullptr: not built
   int digits = 0;
-  double scale = 0;  // 2^e: c in units of the last digit
-  double csum = 0;   // sum of the fixed-point image
+  double scale = 0;            // 2^e: c in units of the last digit
+  double csum = 0;             // sum of the fixed-point image
 };
 
 struct sncc_tmpl {
@@ -190,6 +191,7 @@ struct sncc_tmpl {
   // built on demand by calls that take the set as const, from any thread
   mutable std::mutex dense_mu;
   mutable std::unique_ptr<DenseTmpl[]> dense;  // FP32 and FP64 form of each template
+  mutable std::vector<std::unique_ptr<DevBuf>> dense_bufs;
   mutable size_t dense_bytes = 0;
 };
 
@@ -814,9 +816,34 @@ void plan_slow(const sncc_tmpl *slow, const TileCfg &tc, PlanHost &ph) {
 
 }  // namespace
 
+// Top-k by filter and rescoring (topk_filter.hip): the pairs it serves, in
+// chunks whose maps share one scratch buffer, and what the direct form needs
+// for the pairs left to it.
+struct FilterLaunch {
+  int digits, rv, item0, n_items, lds;
+};
+struct FilterChunk {
+  int fp0, n_fps;
+  std::vector<FilterLaunch> launches;
+};
+struct FilterPlan {
+  std::vector<FilterPair> fps;
+  std::vector<int2> items;      // {pair of fps relative to its chunk, tile}
+  std::vector<FilterChunk> chunks;
+  std::vector<SeqRec> seq;
+  std::vector<SeqPair> pairs;   // every pair of the call
+  std::vector<int> direct;      // 1: always by the direct form
+  int chunk = 0, n_lists = 0;   // offsets per partial list of the direct form
+  int seq_grid = 1;
+  size_t map_floats = 0, blocks = 0;
+  DevBuf d_fps, d_items, d_seq, d_pairs, d_direct, d_map, d_bmax, d_partial;
+  bool active() const { return !pairs.empty(); }
+};
+
 // Device copy of a plan plus its completion event.
 struct PlanDev {
   PlanHost h;
+  FilterPlan f;
   DevBuf d_tmpls, d_passes, d_ivs, d_recs, d_pairs, d_items, d_order, d_qbeg, d_queue,
       d_partial, d_thr, d_slow, d_slot_off, d_slot_w, d_runs, d_refine_order;
   hipEvent_t done = nullptr;
@@ -878,7 +905,7 @@ struct PlanDev {
     a.order = d_order.as<int>();
     a.qbeg = d_qbeg.as<int>();
     // one workgroup per item: no queues (the kernel takes order[blockIdx])
-    a.nq = h.grid == (int)h.items.size() && !queues_forced() ? 0 : (int)h.qbeg.size() - 1;
+    a.nq = h.grid == (int)h.order.size() && !queues_forced() ? 0 : (int)h.qbeg.size() - 1;
     a.n_items = (int)h.items.size();
     a.queue = d_queue.as<int>();
     a.k = h.k;
@@ -930,11 +957,11 @@ int retire(sncc_ctx *ctx, std::unique_ptr<PlanDev> pd) {
 }
 
 // The context's plan for `key` (key.sink's slot), built and uploaded by
-// `make` on a miss; the plan it replaces is retired, since work queued with
+// `make` on a miss (`tiles`: with a tile plan to upload); the plan it replaces is retired, since work queued with
 // it may still be running.  Calls on one context are ordered by its stream,
 // so reusing a plan while earlier work still reads it is safe.
 template <class Make>
-int cached_plan(sncc_ctx *ctx, PlanKey key, Make make, PlanDev **out) {
+int cached_plan(sncc_ctx *ctx, PlanKey key, Make make, PlanDev **out, bool tiles = true) {
   const int slot = key.sink;
   if (ctx->cache[slot] && ctx->cache_key[slot] == key) {
     *out = ctx->cache[slot].get();
@@ -944,7 +971,7 @@ int cached_plan(sncc_ctx *ctx, PlanKey key, Make make, PlanDev **out) {
   ctx->cache_key[slot] = PlanKey{};
   std::unique_ptr<PlanDev> pd(new PlanDev());
   CHK(make(*pd));
-  CHK(pd->upload(ctx->stream));
+  if (tiles) CHK(pd->upload(ctx->stream));
   ctx->cache[slot] = std::move(pd);
   ctx->cache_key[slot] = std::move(key);
   *out = ctx->cache[slot].get();
@@ -1107,34 +1134,68 @@ int dense_digits32(const sncc_tmpl *tm, int t) {
   return dense_fixed_point(tm, t, 3, d) <= std::ldexp(1.0, -22) ? 3 : 4;
 }
 
-// Template t's operands, built on first use (small launches, then a wait, so
-// that any stream may read them afterwards); nullptr where they cannot be
-// had: no memory, or the stream is being captured.
-const DenseTmpl *dense_tmpl(sncc_ctx *ctx, const sncc_tmpl *tm, int t, int digits) {
+// Template t's operands of `digits` digits, or nullptr where not built.
+const DenseTmpl *dense_built(const sncc_tmpl *tm, int t, int digits) {
+  std::lock_guard<std::mutex> lk(tm->dense_mu);
+  if (!tm->dense) return nullptr;
+  const DenseTmpl &dt = tm->dense[2 * (size_t)t + (digits == kDenseDigits)];
+  return dt.frag ? &dt : nullptr;
+}
+
+// Builds the operands of the templates in `want` ({template, digits}) that are
+// not built yet (small launches, then one wait, so that any stream may read
+// them afterwards).  Where they cannot be had (no memory, or the stream is
+// being captured) they stay unbuilt, and callers take another form.
+void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair<int, int>> &want) {
   std::lock_guard<std::mutex> lk(tm->dense_mu);
   if (!tm->dense) tm->dense.reset(new (std::nothrow) DenseTmpl[2 * (size_t)tm->T]);
-  if (!tm->dense) return nullptr;
-  DenseTmpl &dt = tm->dense[2 * (size_t)t + (digits == kDenseDigits)];
-  if (dt.built) return &dt;
+  if (!tm->dense) return;
+  struct Job {
+    DenseTmpl *dt;
+    DenseTmpl made;
+    int t;
+    size_t at;
+  };
+  std::vector<Job> jobs;
+  size_t bytes = 0, image = 0;  // the fixed-point image is reused, in stream order
+  for (const auto &w : want) {
+    DenseTmpl *dt = &tm->dense[2 * (size_t)w.first + (w.second == kDenseDigits)];
+    bool listed = dt->frag != nullptr;
+    for (const Job &j : jobs) listed |= j.dt == dt;
+    if (listed) continue;
+    const int W = tm->W[w.first], H = tm->H[w.first];
+    const size_t fb = dense_frag_bytes(W, H, w.second);
+    if (tm->dense_bytes + bytes + fb > kDenseSetBytes) continue;
+    Job j{dt, DenseTmpl{}, w.first, bytes};
+    (void)dense_fixed_point(tm, w.first, w.second, j.made);
+    jobs.push_back(j);
+    bytes += fb;
+    image = std::max(image, (size_t)W * H * 8);
+  }
+  if (jobs.empty()) return;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
-    return nullptr;
-  const int W = tm->W[t], H = tm->H[t];
-  const size_t fb = dense_frag_bytes(W, H, digits), bytes = fb + (size_t)W * H * 8;
-  if (tm->dense_bytes + bytes > kDenseSetBytes || dt.frag.reserve(bytes) != SNCC_OK) {
+    return;
+  std::unique_ptr<DevBuf> buf(new (std::nothrow) DevBuf());
+  if (!buf || buf->reserve(bytes + image) != SNCC_OK) {
     g_err.clear();
-    return nullptr;
+    return;
   }
-  (void)dense_fixed_point(tm, t, digits, dt);
-  if (launch_dense_pack(tm->d_geom.as<int4>() + tm->seg_off[t],
-                        tm->d_c64.as<double>() + tm->seg_off[t], tm->K[t], dt.scale, W, H, digits,
-                        reinterpret_cast<long long *>(dt.frag.as<char>() + fb), dt.frag.p,
-                        ctx->stream) != 0 ||
-      hipStreamSynchronize(ctx->stream) != hipSuccess)
-    return nullptr;
-  tm->dense_bytes += bytes;
-  dt.built = true;
-  return &dt;
+  char *base = buf->as<char>();
+  bool ok = true;
+  for (const Job &j : jobs)
+    ok = ok && launch_dense_pack(tm->d_geom.as<int4>() + tm->seg_off[j.t],
+                                 tm->d_c64.as<double>() + tm->seg_off[j.t], tm->K[j.t],
+                                 j.made.scale, tm->W[j.t], tm->H[j.t], j.made.digits,
+                                 reinterpret_cast<long long *>(base + bytes), base + j.at,
+                                 ctx->stream) == 0;
+  if (hipStreamSynchronize(ctx->stream) != hipSuccess || !ok) return;
+  for (Job &j : jobs) {
+    j.made.frag = base + j.at;
+    *j.dt = j.made;
+  }
+  tm->dense_bytes += bytes + image;
+  tm->dense_bufs.push_back(std::move(buf));
 }
 
 // Launch shape of the matrix-core form for a map of nu x nv offsets: false
@@ -1143,10 +1204,10 @@ const DenseTmpl *dense_tmpl(sncc_ctx *ctx, const sncc_tmpl *tm, int t, int digit
 // with four and 493 with two), else four while they fill them once (1920 x
 // 1080, 64 x 64: 37.7 us, 45.6 with eight, 45.7 with two; FP64, at most four
 // for its 28 accumulators a row: while they fill 5/8), else two (640 x 480, 32
-// x 32: 10.6 us, 15.7 with four).  LDS for two workgroups per CU, three where
-// one pass over the template fits that.
+// x 32: 10.6 us, 15.7 with four); for several pairs in one launch, as given (rv).
+// LDS for two workgroups per CU, three where one pass over the template fits.
 bool dense_shape(const sncc_tmpl *tm, int t, int digits, int nu, int nv, int num_cu,
-                 DenseArgs &a) {
+                 DenseArgs &a, int rv = 0) {
   const int W = tm->W[t], H = tm->H[t], rows_all = 4 * dense_rows4(H);
   if ((long long)W * H > kDenseMaxArea) return false;
   a.W = W;
@@ -1165,7 +1226,8 @@ bool dense_shape(const sncc_tmpl *tm, int t, int digits, int nu, int nv, int num
     const int bv = 2 * kDenseNW * rv;
     return (long long)a.ntu * ((nv + bv - 1) / bv);
   };
-  a.rv = digits == 3 && tiles(8) >= 2LL * num_cu                       ? 8
+  a.rv = rv > 0                                                          ? rv
+         : digits == 3 && tiles(8) >= 2LL * num_cu                       ? 8
          : 8 * tiles(4) >= (digits == kDenseDigits ? 5LL : 8LL) * num_cu ? 4
                                                                        : 2;
   const int bv = 2 * kDenseNW * a.rv;
@@ -1176,8 +1238,18 @@ bool dense_shape(const sncc_tmpl *tm, int t, int digits, int nu, int nv, int num
   return a.hb >= 8;
 }
 
-// Whether the matrix-core form is the faster one: estimates in ps per offset
-// from maps measured both ways (one MI355X, us a map, other form / this one).
+// Estimates in ps per offset: the segment form (evaluations and staged rows),
+// the plain FP64 form, and the matrix products per offset of a launch shape.
+double cost_tile(const sncc_tmpl *tm, int t) {
+  return 0.22 * tm->K[t] + 6e-4 * (tm->W[t] + 128.0) * (tm->H[t] + 32.0);
+}
+double cost_plain(const sncc_tmpl *tm, int t) { return 0.52 * tm->K[t] + 16.0; }
+double dense_macs(const DenseArgs &a) {
+  return (double)a.H * a.G * 16 * (a.rv == 2 ? 1.6 : 1.0);
+}
+
+// Whether the matrix-core form is the faster one: the estimates are fitted to
+// maps measured both ways (one MI355X, us a map, other form / this one).
 // FP32: the segment form's evaluations and staged rows against the matrix
 // steps: 1920 x 1080 with 64 x 64 at K 110 62.7 / 40.2, K 1005 457 / 37.7;
 // 61 x 47, K 118 63.4 / 33.9; 128 x 96, K 73 70.1 / 82.6; 3840 x 2160 with
@@ -1188,9 +1260,284 @@ bool dense_shape(const sncc_tmpl *tm, int t, int digits, int nu, int nv, int num
 bool dense_wins(const sncc_tmpl *tm, int t, const DenseArgs &a) {
   const int forced = dense_forced();
   if (forced >= 0) return forced == 1;
-  const double W = a.W, H = a.H, K = tm->K[t], mac = H * a.G * 16 * (a.rv == 2 ? 1.6 : 1.0);
-  if (a.digits == kDenseDigits) return 0.52 * K + 16.0 > 10.0 + 4.9e-3 * mac;
-  return 0.22 * K + 6e-4 * (W + 128.0) * (H + 32.0) > 6.0 + 0.8e-3 * a.digits * mac;
+  if (a.digits == kDenseDigits) return cost_plain(tm, t) > 10.0 + 0.7e-3 * a.digits * dense_macs(a);
+  return cost_tile(tm, t) > 6.0 + 0.8e-3 * a.digits * dense_macs(a);
+}
+
+void dense_constants(const sncc_tmpl *tm, int t, const DenseTmpl &dt, int N, int P,
+                     DenseArgs &a) {
+  a.frag = dt.frag;
+  a.P = P;
+  a.N = N;
+  a.csum = dt.csum;
+  a.inv_scale = 1.0 / dt.scale;
+  a.q_k = tm->q_k[t];
+  a.qnd = a.q_k / (double)a.n;
+  a.inv_n = 1.0 / (double)a.n;
+}
+
+// Largest scratch map of a chunk of filtered pairs (floats; one pair may need
+// more).
+constexpr size_t kFilterMapFloats = (size_t)64 << 20;
+// FP32: estimated gain below which a call keeps the segment form for all its
+// pairs (the filter's launches and the selection take 30 to 40 us).
+constexpr double kFilterMinGainUs = 60.0;
+
+// Template t's sum in the FP32 segment form as plan `ph` orders it (see SeqRec).
+int seq_records(const PlanHost &ph, int t, int P, std::vector<SeqRec> &out) {
+  const size_t first = out.size();
+  const DevTmpl &d = ph.tmpls[t];
+  if (d.lp_class == kLpDirect) {  // four records per compensated step
+    const PassDesc &ps = ph.passes[d.pass_begin];
+    for (int i = ps.seg_begin; i < ps.seg_end; i += 2) {
+      DirectRec r;
+      memcpy(&r, &ph.recs[i], sizeof r);
+      const bool end = (i - ps.seg_begin) / 2 % 4 == 3;
+      out.push_back(SeqRec{r.top, r.bot, (uint32_t)r.area | (end ? kSeqEnd : 0u), r.c});
+    }
+    return (int)(out.size() - first);
+  }
+  const int LP = kLpClasses[d.lp_class];
+  for (int p = d.pass_begin; p < d.pass_end; ++p) {
+    const PassDesc &ps = ph.passes[p];
+    // a staged entry's byte offset in the frame's table from the window's
+    auto table = [&](int off) {
+      const int row = off / LP, x = off % LP;
+      for (int i = ps.iv_begin; i < ps.iv_end; ++i) {
+        const Interval &iv = ph.ivs[i];
+        if (row >= iv.lds_row && row < iv.lds_row + iv.n_rows)
+          return ((iv.rel_row + row - iv.lds_row) * P + ps.col0 + x) * 4;
+      }
+      return 0;
+    };
+    int r = ps.seg_begin;
+    auto chains = [&](int L, int n) {  // a block of n chains of L segments
+      for (int c = 0; c < n; ++c)
+        for (int j = 0; j <= L; ++j, ++r) {
+          const TileRec &e = ph.recs[r];
+          uint32_t flags = j == 0 ? kSeqFirst : 0u;
+          if (c == n - 1 && j == L) flags |= kSeqEnd;
+          out.push_back(SeqRec{table(e.off_tl), table(e.off_bl), (uint32_t)e.w_area | flags, e.c});
+        }
+    };
+    for (int q = ps.n_chain[3]; q > 0; --q) chains(4, 1);
+    for (int q = ps.n_chain[2]; q > 0; --q) chains(3, 1);
+    int q2 = ps.n_chain[1], q1 = ps.n_chain[0];
+    for (; q2 >= 2; q2 -= 2) chains(2, 2);
+    if (q2) chains(2, 1);
+    for (; q1 >= 4; q1 -= 4) chains(1, 4);
+    for (; q1 > 0; --q1) chains(1, 1);
+  }
+  return (int)(out.size() - first);
+}
+
+// Which pairs the filter serves, by the estimates above (with its map's write
+// and scan, 2 ps): FP64 pairs where it beats the plain form, FP32 pairs where
+// it beats the segment form and all of them together gain enough.
+std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int n_pairs,
+                               const int32_t *pairs, bool fp64) {
+  std::vector<char> use(n_pairs, 0), tmpl(tm->T, 0);  // tmpl: 1 yes, 2 no
+  std::vector<double> gain(tm->T, 0.0);
+  const int forced = dense_forced();
+  double total = 0;
+  for (int p = 0; p < n_pairs; ++p) {
+    const int t = pairs[2 * p + 1];
+    if (!tmpl[t]) {
+      DenseArgs a{};
+      const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
+      tmpl[t] = 2;
+      if (forced != 0 &&
+          dense_shape(tm, t, tm->digits32[t], nu, nv, ctx->num_cu, a, tm->digits32[t] == 3 ? 8 : 4)) {
+        gain[t] = (fp64 ? cost_plain(tm, t) : cost_tile(tm, t)) -
+                  (8.0 + 0.8e-3 * a.digits * dense_macs(a));
+        if (forced == 1 || gain[t] > 0) tmpl[t] = 1;
+      }
+    }
+    use[p] = tmpl[t] == 1;
+    if (use[p])
+      total += gain[t] * (double)(M - tm->W[t] + 1) * (double)(N - tm->H[t] + 1) * 1e-6;
+  }
+  if (!fp64 && forced != 1 && total < kFilterMinGainUs) use.assign(n_pairs, 0);
+  return use;
+}
+
+// Plans the filter for the pairs marked in `use` (cleared where the operands
+// cannot be had) and the direct form for the others (FP64) or for those the
+// filter cannot decide (FP32, whose sums are ordered as plan `tile` has them).
+void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_pairs,
+                 const int32_t *pairs, int k, bool fp64, const PlanHost *tile,
+                 std::vector<char> &use, FilterPlan &f) {
+  std::vector<std::pair<int, int>> want;
+  for (int p = 0; p < n_pairs; ++p)
+    if (use[p]) want.emplace_back(pairs[2 * p + 1], tm->digits32[pairs[2 * p + 1]]);
+  std::sort(want.begin(), want.end());
+  want.erase(std::unique(want.begin(), want.end()), want.end());
+  if (!want.empty()) dense_build(ctx, tm, want);
+  std::vector<int> seq0(tm->T, -1), n_seq(tm->T, 0);
+  f.pairs.resize(n_pairs);
+  f.direct.assign(n_pairs, 0);
+  std::vector<int> idx;
+  std::vector<double> cost(n_pairs, 0.0);
+  long long offsets = 0, most = 0;
+  for (int p = 0; p < n_pairs; ++p) {
+    const int t = pairs[2 * p + 1];
+    const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
+    if (use[p] && !dense_built(tm, t, tm->digits32[t])) use[p] = 0;
+    if (use[p]) {
+      idx.push_back(p);
+      cost[p] = (double)tm->H[t] * dense_groups(tm->W[t]) * tm->digits32[t];
+      if (!fp64 && seq0[t] < 0) {
+        seq0[t] = (int)f.seq.size();
+        n_seq[t] = seq_records(*tile, t, P, f.seq);
+      }
+    }
+    f.direct[p] = fp64 && !use[p];
+    SeqPair &q = f.pairs[p];
+    q = SeqPair{};
+    q.frame = pairs[2 * p];
+    q.nu = nu;
+    q.nv = nv;
+    q.W = tm->W[t];
+    q.H = tm->H[t];
+    q.n = q.W * q.H;
+    q.sq_rows = tm->dev[t].sq_rows;
+    q.seq0 = std::max(0, seq0[t]);
+    q.n_seq = n_seq[t];
+    q.seg_off = tm->seg_off[t];
+    q.K = tm->K[t];
+    q.q_k = tm->q_k[t];
+    q.r64 = tm->r64[t];
+    offsets += (long long)nu * nv;
+    most = std::max(most, (long long)nu * nv);
+  }
+  // lists of the direct form: short enough to spread a pair over the chip,
+  // long enough that the lists of all pairs stay within 64 MB
+  const size_t key = fp64 ? sizeof(Key96) : 8;
+  f.chunk = 4096;
+  while (f.chunk < (64 << 10) && (size_t)(offsets / f.chunk + n_pairs) * k * key > ((size_t)64 << 20))
+    f.chunk *= 2;
+  for (SeqPair &q : f.pairs) {
+    q.chunk0 = f.n_lists;
+    q.n_chunks = (int)(((long long)q.nu * q.nv + f.chunk - 1) / f.chunk);
+    f.n_lists += q.n_chunks;
+  }
+  f.seq_grid = (int)std::min<long long>(f.n_lists, 8LL * std::max(1, ctx->num_cu));
+  // filtered pairs, costliest first, in chunks of one scratch map
+  std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+  for (size_t i = 0; i < idx.size();) {
+    FilterChunk c;
+    c.fp0 = (int)f.fps.size();
+    // rows per wave half by the tiles of all the chunk's pairs together
+    long long tiles8 = 0;
+    size_t e = i;
+    for (size_t floats = 0; e < idx.size(); ++e) {
+      const SeqPair &q = f.pairs[idx[e]];
+      const size_t n = (size_t)((q.nu + 127) / 128 * 128) * ((q.nv + 63) / 64 * 64);
+      if (e > i && floats + n > kFilterMapFloats) break;
+      floats += n;
+      tiles8 += (long long)((q.nu + 127) / 128) * ((q.nv + 63) / 64);
+    }
+    const int rv3 = tiles8 >= 2LL * ctx->num_cu ? 8 : 2 * tiles8 >= ctx->num_cu ? 4 : 2;
+    size_t floats = 0;
+    int blocks = 0;
+    for (int digits = 3; digits <= 4; ++digits) {
+      FilterLaunch l{digits, digits == 3 ? rv3 : std::min(rv3, 4), (int)f.items.size(), 0, 0};
+      for (size_t j = i; j < e; ++j) {
+        const int p = idx[j], t = pairs[2 * p + 1];
+        if (tm->digits32[t] != digits) continue;
+        FilterPair fp{};
+        fp.pair = p;
+        fp.frame = pairs[2 * p];
+        if (!dense_shape(tm, t, digits, f.pairs[p].nu, f.pairs[p].nv, ctx->num_cu, fp.a, l.rv)) {
+          use[p] = 0;
+          f.direct[p] = fp64;
+          continue;
+        }
+        dense_constants(tm, t, *dense_built(tm, t, digits), N, P, fp.a);
+        const int tiles = fp.a.ntu * fp.a.ntv;
+        fp.map0 = (long long)floats;
+        fp.block0 = blocks;
+        fp.n_blocks = tiles * kDenseNW;
+        fp.seq0 = f.pairs[p].seq0;
+        fp.n_seq = f.pairs[p].n_seq;
+        fp.seg_off = f.pairs[p].seg_off;
+        fp.K = f.pairs[p].K;
+        fp.r64 = f.pairs[p].r64;
+        floats += (size_t)fp.n_blocks * l.rv * 256;
+        blocks += fp.n_blocks;
+        l.lds = std::max(l.lds, (2 * kDenseNW * l.rv + fp.a.hb - 1) * fp.a.pitch);
+        // a contiguous range of the pair's tiles per XCD (workgroups go round
+        // the XCDs), so that neighbouring tiles share table rows in its L2
+        const int per = (tiles + 7) / 8, local = (int)f.fps.size() - c.fp0;
+        for (int x = 0; x < per * 8; ++x) {
+          const int tile_i = x % 8 * per + x / 8;
+          f.items.push_back(make_int2(tile_i < tiles ? local : -1, tile_i));
+        }
+        f.fps.push_back(fp);
+      }
+      l.n_items = (int)f.items.size() - l.item0;
+      if (l.n_items > 0) c.launches.push_back(l);
+    }
+    c.n_fps = (int)f.fps.size() - c.fp0;
+    f.map_floats = std::max(f.map_floats, floats);
+    f.blocks = std::max(f.blocks, (size_t)blocks);
+    if (c.n_fps > 0) f.chunks.push_back(std::move(c));
+    i = e;
+  }
+}
+
+int upload_filter(FilterPlan &f, int k, bool fp64, hipStream_t st) {
+  CHK(f.d_map.reserve(std::max<size_t>(16, f.map_floats * 4)));
+  CHK(f.d_bmax.reserve(std::max<size_t>(16, f.blocks * sizeof(float2))));
+  CHK(f.d_partial.reserve((size_t)f.n_lists * k * (fp64 ? sizeof(Key96) : 8)));
+  CHK(f.d_fps.upload(f.fps, st));
+  CHK(f.d_items.upload(f.items, st));
+  CHK(f.d_seq.upload(f.seq, st));
+  CHK(f.d_pairs.upload(f.pairs, st));
+  CHK(f.d_direct.upload(f.direct, st));
+  return SNCC_OK;
+}
+
+// Enqueues the filter, the selection and the direct form; mark(1) of the
+// context's stages falls before the last selection.
+int run_filter(sncc_ctx *ctx, const sncc_tmpl *tm, FilterPlan &f, const uint32_t *s,
+               const uint32_t *s2, long long fs, int P, int k, bool fp64, sncc_match *out) {
+  const hipStream_t st = ctx->stream;
+  const int4 *geom = tm->d_geom.as<int4>();
+  const double *c64 = tm->d_c64.as<double>();
+  bool ok = true;
+  for (size_t i = 0; i < f.chunks.size(); ++i) {
+    const FilterChunk &c = f.chunks[i];
+    const FilterPair *fps = f.d_fps.as<FilterPair>() + c.fp0;
+    for (const FilterLaunch &l : c.launches)
+      ok = ok && launch_dense_filter(l.digits, l.rv, s, s2, fs, fps, f.d_items.as<int2>() + l.item0,
+                                     l.n_items, l.lds, f.d_map.as<float>(),
+                                     f.d_bmax.as<float2>(), st) == 0;
+    if (i + 1 == f.chunks.size() && !fp64) ctx->mark(1);
+    ok = ok && launch_filter_select(fp64, s, s2, fs, P, fps, c.n_fps, f.d_map.as<float>(),
+                                    f.d_bmax.as<float2>(), f.d_seq.as<SeqRec>(), geom, c64, k, out,
+                                    f.d_direct.as<int>(), st) == 0;
+  }
+  ok = ok && launch_seq_topk(fp64, s, s2, fs, P, f.d_pairs.as<SeqPair>(), (int)f.pairs.size(),
+                             f.d_direct.as<int>(), f.chunk, f.d_seq.as<SeqRec>(), geom, c64, k,
+                             f.d_partial.p, f.seq_grid, out, st) == 0;
+  if (!ok) SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
+  return SNCC_OK;
+}
+
+// Takes the filtered pairs out of a tile plan's work (their records stay).
+void drop_items(PlanHost &h, const std::vector<char> &use) {
+  std::vector<int> order, qbeg(1, 0);
+  for (size_t q = 0; q + 1 < h.qbeg.size(); ++q) {
+    for (int i = h.qbeg[q]; i < h.qbeg[q + 1]; ++i)
+      if (!use[h.items[h.order[i]].pair]) order.push_back(h.order[i]);
+    qbeg.push_back((int)order.size());
+  }
+  h.order = std::move(order);
+  h.qbeg = std::move(qbeg);
+  h.grid = std::max(1, std::min(h.grid, (int)h.order.size()));
+  for (size_t p = 0; p < h.pairs.size(); ++p)
+    if (use[p]) h.pairs[p].item_end = h.pairs[p].item_begin;
 }
 
 // Scores a map with the matrix-core form; returns 1 when it ran, 0 when the
@@ -1202,18 +1549,14 @@ int dense_map(sncc_ctx *ctx, const sncc_tmpl *tm, int t, const uint32_t *s, cons
   if ((long long)tm->W[t] * tm->H[t] > kDenseMaxArea) return 0;
   const int digits = fp64 ? kDenseDigits : tm->digits32[t];
   if (!dense_shape(tm, t, digits, nu, nv, ctx->num_cu, a) || !dense_wins(tm, t, a)) return 0;
-  const DenseTmpl *dt = dense_tmpl(ctx, tm, t, digits);
-  if (!dt) return 0;
+  const DenseTmpl *dt = dense_built(tm, t, digits);
+  if (!dt) {
+    dense_build(ctx, tm, {{t, digits}});
+    if (!(dt = dense_built(tm, t, digits))) return 0;
+  }
   a.s = s;
   a.s2 = s2;
-  a.frag = dt->frag.p;
-  a.P = P;
-  a.N = N;
-  a.csum = dt->csum;
-  a.inv_scale = 1.0 / dt->scale;
-  a.q_k = tm->q_k[t];
-  a.qnd = a.q_k / (double)a.n;
-  a.inv_n = 1.0 / (double)a.n;
+  dense_constants(tm, t, *dt, N, P, a);
   a.rho = rho;
   a.rho_pitch = rho_pitch;
   a.degen = degen;
@@ -1673,81 +2016,62 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
     key.pairs.assign(pairs, pairs + 2 * n_pairs);
     PlanDev *pd = nullptr;
     CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d) {
-      return build_one_call_plan(tm, M, N, sat_pitch, n_pairs, pairs, k, kSinkTopk,
-                                 ctx->num_cu, d.h);
+      CHK(build_one_call_plan(tm, M, N, sat_pitch, n_pairs, pairs, k, kSinkTopk, ctx->num_cu,
+                              d.h));
+      std::vector<char> use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, false);
+      if (std::find(use.begin(), use.end(), 1) == use.end()) return SNCC_OK;
+      plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, false, &d.h, use, d.f);
+      if (d.f.chunks.empty() || upload_filter(d.f, k, false, ctx->stream) != SNCC_OK) {
+        d.f.pairs.clear();  // no operands, or no memory for it: the segment form for all pairs
+        g_err.clear();
+      } else {
+        drop_items(d.h, use);
+      }
+      return SNCC_OK;
     }, &pd));
     TileArgs a = pd->args(d_s, d_s2, fs, sat_pitch, M, N);
     ctx->n_stages = 0;
+    const bool filtered = pd->f.active(), tiles = !pd->h.order.empty();
     // one workgroup per item: no queue counters and no pair floors to reset
-    if (a.nq != 0 && launch_zero(a.queue, a.n_zero, ctx->stream) != 0)
+    if (tiles && a.nq != 0 && launch_zero(a.queue, a.n_zero, ctx->stream) != 0)
       SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
     ctx->mark(0);
-    if (launch_tile(pd->h.cfg, kSinkTopk, a, pd->h.grid, pd->h.lds_bytes, ctx->stream) != 0)
+    if (tiles &&
+        launch_tile(pd->h.cfg, kSinkTopk, a, pd->h.grid, pd->h.lds_bytes, ctx->stream) != 0)
       SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
-    ctx->mark(1);
-    if (launch_merge(pd->d_pairs.as<PairDesc>(), nullptr, n_pairs, a.partial, nullptr, k, d_out,
-                     ctx->stream) != 0)
+    if (!filtered) ctx->mark(1);
+    // the merge writes every pair's slots (the filtered pairs' as empty), the
+    // filter's selection then its own
+    if (tiles && launch_merge(pd->d_pairs.as<PairDesc>(), nullptr, n_pairs, a.partial, nullptr, k,
+                              d_out, ctx->stream) != 0)
       SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
+    if (filtered) CHK(run_filter(ctx, tm, pd->f, d_s, d_s2, fs, sat_pitch, k, false, d_out));
     ctx->mark(2);
     if (ctx->timing) ctx->n_stages = 2;
     return SNCC_OK;
   }
   if (precision != SNCC_FP64) SNCC_FAIL(SNCC_EINVAL, "unknown precision %d", precision);
-  std::unique_ptr<PlanDev> pd(new PlanDev());
-  // plain form: one FP64 map per pair, then chunked top-k and the merge
-  const int chunk = 64 * 1024;
-  PlanHost &h = pd->h;
-  h.k = k;
-  size_t max_map = 0;
-  int n_chunks = 0;
-  h.pairs.resize(n_pairs);
-  for (int p = 0; p < n_pairs; ++p) {
-    const int t = pairs[2 * p + 1];
-    PairDesc &q = h.pairs[p];
-    q.frame = pairs[2 * p];
-    q.tmpl = t;
-    q.nu = M - tm->W[t] + 1;
-    q.nv = N - tm->H[t] + 1;
-    q.ntu = q.ntv = 0;
-    const long long tot = (long long)q.nu * q.nv;
-    q.item_begin = n_chunks;
-    n_chunks += (int)((tot + chunk - 1) / chunk);
-    q.item_end = n_chunks;
-    max_map = std::max(max_map, (size_t)tot);
-  }
-  CHK(ctx->map_scratch.reserve(max_map * sizeof(double)));
-  CHK(pd->d_pairs.upload(h.pairs, ctx->stream));
-  CHK(pd->d_partial.reserve((size_t)n_chunks * k * sizeof(Key96)));
-  Key96 *partial = pd->d_partial.as<Key96>();
-  for (int p = 0; p < n_pairs; ++p) {
-    const PairDesc &q = h.pairs[p];
-    const int t = q.tmpl;
-    PlainArgs a;
-    a.s = d_s + (long long)q.frame * fs;
-    a.s2 = d_s2 + (long long)q.frame * fs;
-    a.sat_pitch = sat_pitch;
-    a.nu = q.nu;
-    a.nv = q.nv;
-    a.W = tm->W[t];
-    a.H = tm->H[t];
-    a.K = tm->K[t];
-    a.sq_rows = tm->dev[t].sq_rows;
-    a.q_k = tm->q_k[t];
-    a.r64 = tm->r64[t];
-    a.geom = tm->d_geom.as<int4>() + tm->seg_off[t];
-    a.c64 = tm->d_c64.as<double>() + tm->seg_off[t];
-    a.area = tm->d_area.as<int>() + tm->seg_off[t];
-    a.rho = ctx->map_scratch.as<double>();
-    a.rho_pitch = q.nu;
-    a.degen = nullptr;
-    if (launch_plain(a, ctx->stream) != 0 ||
-        launch_map_topk64(a.rho, q.nu, q.nu, q.nv, chunk, k,
-                          partial + (size_t)q.item_begin * k, ctx->stream) != 0)
-      SNCC_FAIL(SNCC_EDEVICE, "plain top-k launch: %s", hipGetErrorString(hipGetLastError()));
-  }
-  if (launch_merge64(pd->d_pairs.as<PairDesc>(), n_pairs, partial, k, d_out, ctx->stream) != 0)
-    SNCC_FAIL(SNCC_EDEVICE, "merge launch: %s", hipGetErrorString(hipGetLastError()));
-  return retire(ctx, std::move(pd));
+  PlanKey key;
+  key.sink = kSlotTopk64;
+  key.tmpl = tm->serial;
+  key.M = M;
+  key.N = N;
+  key.P = sat_pitch;
+  key.k = k;
+  key.pairs.assign(pairs, pairs + 2 * n_pairs);
+  PlanDev *pd = nullptr;
+  CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d) {
+    std::vector<char> use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, true);
+    plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, true, nullptr, use, d.f);
+    if (upload_filter(d.f, k, true, ctx->stream) == SNCC_OK) return SNCC_OK;
+    // no memory for the filter's maps: the direct form for all pairs
+    d.f.~FilterPlan();
+    new (&d.f) FilterPlan();
+    use.assign(n_pairs, 0);
+    plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, true, nullptr, use, d.f);
+    return upload_filter(d.f, k, true, ctx->stream);
+  }, &pd, false));
+  return run_filter(ctx, tm, pd->f, d_s, d_s2, fs, sat_pitch, k, true, d_out);
 }
 
 int sncc_argmax(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uint32_t *d_s2,

@@ -160,33 +160,21 @@ __device__ __forceinline__ v4u_a4 dense_row4(const uint32_t *__restrict__ p, int
   return o;
 }
 
-// One tile of 128 x (2 NW RV) offsets per workgroup; wave w takes offset rows
-// 2 w RV .. 2 w RV + 2 RV - 1, and lane (j = lane mod 16, g = lane / 16) ends
-// with the offsets u0 + 16 (j mod 8) + 4 g + 0..3 of rows RV (2 w + j / 8) + r.
-// (Against 256 x (NW RV): fewer staged bytes per offset and less waste at the
-// right edge.)  Template rows are taken in
-// passes of a.hb, whose frame rows are staged in LDS.  Per step a wave loads D
+// The products of one tile of 128 x (2 NW RV) offsets, by a workgroup; wave w
+// takes offset rows 2 w RV .. 2 w RV + 2 RV - 1, and lane (j = lane mod 16, g =
+// lane / 16) ends with the offsets u0 + 16 (j mod 8) + 4 g + 0..3 of rows
+// v0 + RV (2 w + j / 8) + r.  (Against 256 x (NW RV): fewer staged bytes per
+// offset and less waste at the right edge.)  Template rows are taken in passes
+// of a.hb, whose frame rows are staged in LDS.  Per step a wave loads D
 // operands A (from the caches: every wave of the launch reads the same ones)
 // and min(RV, 4) operands B (LDS) for D RV instructions.
 template <int D, int RV, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dense_kernel(
-    const uint32_t *__restrict__ S, const uint32_t *__restrict__ S2,
-    const v4i *__restrict__ frag, DenseArgs a) {
-  extern __shared__ __align__(16) uint8_t lds8[];
+__device__ __forceinline__ void dense_products(const uint32_t *__restrict__ S,
+                                               const v4i *__restrict__ frag, const DenseArgs &a,
+                                               int u0, int v0, int row0, uint8_t *lds8, int lane,
+                                               v4i (&acc)[RV][D]) {
   constexpr int BV = 2 * NW * RV;
-  constexpr bool F64 = D == kDenseDigits;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // tiles row by row, a contiguous range of them per XCD (workgroups go round
-  // the XCDs), so that neighbouring tiles share the table rows in its L2
-  const int per = (int)gridDim.x >> 3;
-  const int tile = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
-  if (tile >= a.ntu * a.ntv) return;
-  const int tv = tile / a.ntu, tu = tile - tv * a.ntu;
-  const int u0 = tu * kDenseBU, v0 = tv * BV;
   const int j = lane & 7, g = lane >> 4;
-  const int row0 = RV * (2 * wave + ((lane >> 3) & 1));  // the lane's first offset row
-
-  v4i acc[RV][D];
 #pragma unroll
   for (int r = 0; r < RV; ++r)
 #pragma unroll
@@ -249,62 +237,149 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
       }
     }
   }
+}
 
-  // epilogue: window sums (Eqs. (13), (15)) and the exact window energy as in
-  // the other forms; the numerator is the digits' sum less the digits' own
-  // mean term (the rounded c need not sum to zero), in FP64
-  const int u = u0 + 16 * j + 4 * g;
-  const int uc = min(u, a.nu - 1);
+// Window sums of f (Eq. (13)) and the exact window energies V = n Eq. (16) of
+// four consecutive offsets (u, v), as in the other forms.
+__device__ __forceinline__ void dense_energy4(const uint32_t *__restrict__ S,
+                                              const uint32_t *__restrict__ S2, const DenseArgs &a,
+                                              int u, int v, v4u_a4 &sf, long long (&V)[4]) {
+  const uint32_t *t0 = S + (long long)v * a.P, *t1 = t0 + (long long)a.H * a.P;
+  sf = (dense_row4(t1, u + a.W, a.P) - dense_row4(t1, u, a.P)) -
+       (dense_row4(t0, u + a.W, a.P) - dense_row4(t0, u, a.P));
+  u64 sf2[4] = {0, 0, 0, 0};
+  for (int y = 0; y < a.H; y += a.sq_rows) {  // Eq. (15), in exact boxes
+    const uint32_t *q0 = S2 + (long long)(v + y) * a.P;
+    const uint32_t *q1 = q0 + (long long)min(a.sq_rows, a.H - y) * a.P;
+    const v4u_a4 b = (dense_row4(q1, u + a.W, a.P) - dense_row4(q1, u, a.P)) -
+                     (dense_row4(q0, u + a.W, a.P) - dense_row4(q0, u, a.P));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sf2[k] += b[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    V[k] = (long long)((u64)(uint32_t)a.n * sf2[k] - (u64)sf[k] * sf[k]);
+}
+
+// Numerator of Eq. (12) from a lane's digit sums: their value less the digits'
+// own mean term (the rounded c need not sum to zero), in FP64.
+template <int D>
+__device__ __forceinline__ double dense_num(const v4i (&acc)[D], int k, uint32_t sf,
+                                            const DenseArgs &a) {
+  double T;
+  if constexpr (D == kDenseDigits) {
+    const long long hi = ((long long)acc[0][k] << 16) + ((long long)acc[1][k] << 8) + acc[2][k];
+    const long long lo = ((long long)acc[3][k] << 24) + ((long long)acc[4][k] << 16) +
+                         ((long long)acc[5][k] << 8) + acc[6][k];
+    T = __builtin_fma((double)hi, 4294967296.0, (double)lo);
+  } else {
+    long long t = acc[0][k];
+#pragma unroll
+    for (int d = 1; d < D; ++d) t = (t << 8) + acc[d][k];
+    T = (double)t;
+  }
+  return (T - a.csum * ((double)sf * a.inv_n - 128.0)) * a.inv_scale;
+}
+
+// FP32 rho: 1 / sqrt of the energy in FP64 (the FP32 estimate and one Newton
+// step), rounded once.
+__device__ __forceinline__ float dense_rho32(double num, long long V, double qnd) {
+  const double e = (double)V * qnd;
+  const double y0 = (double)__builtin_amdgcn_rsqf((float)e);
+  const double y1 = y0 * __builtin_fma(-0.5 * e * y0, y0, 1.5);
+  return V == 0 ? 0.f : (float)(num * y1);
+}
+
+template <int D, int RV, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dense_kernel(
+    const uint32_t *__restrict__ S, const uint32_t *__restrict__ S2,
+    const v4i *__restrict__ frag, DenseArgs a) {
+  extern __shared__ __align__(16) uint8_t lds8[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // tiles row by row, a contiguous range of them per XCD (workgroups go round
+  // the XCDs), so that neighbouring tiles share the table rows in its L2
+  const int per = (int)gridDim.x >> 3;
+  const int tile = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+  if (tile >= a.ntu * a.ntv) return;
+  const int tv = tile / a.ntu, u0 = (tile - tv * a.ntu) * kDenseBU, v0 = tv * 2 * NW * RV;
+  const int row0 = RV * (2 * wave + ((lane >> 3) & 1));  // the lane's first offset row
+  v4i acc[RV][D];
+  dense_products<D, RV, NW>(S, frag, a, u0, v0, row0, lds8, lane, acc);
+
+  const int u = u0 + 16 * (lane & 7) + 4 * (lane >> 4);
 #pragma unroll
   for (int r = 0; r < RV; ++r) {
-    const int v = v0 + row0 + r, vc = min(v, a.nv - 1);
-    const uint32_t *t0 = S + (long long)vc * a.P, *t1 = t0 + (long long)a.H * a.P;
-    const v4u_a4 sf = (dense_row4(t1, uc + a.W, a.P) - dense_row4(t1, uc, a.P)) -
-                      (dense_row4(t0, uc + a.W, a.P) - dense_row4(t0, uc, a.P));
-    u64 sf2[4] = {0, 0, 0, 0};
-    for (int y = 0; y < a.H; y += a.sq_rows) {
-      const uint32_t *q0 = S2 + (long long)(vc + y) * a.P;
-      const uint32_t *q1 = q0 + (long long)min(a.sq_rows, a.H - y) * a.P;
-      const v4u_a4 b = (dense_row4(q1, uc + a.W, a.P) - dense_row4(q1, uc, a.P)) -
-                       (dense_row4(q0, uc + a.W, a.P) - dense_row4(q0, uc, a.P));
-#pragma unroll
-      for (int k = 0; k < 4; ++k) sf2[k] += b[k];
-    }
+    const int v = v0 + row0 + r;
+    v4u_a4 sf;
+    long long V[4];
+    dense_energy4(S, S2, a, min(u, a.nu - 1), min(v, a.nv - 1), sf, V);
     const bool row_ok = v < a.nv;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const long long V = (long long)((u64)(uint32_t)a.n * sf2[k] - (u64)sf[k] * sf[k]);
-      const double fbar = (double)sf[k] * a.inv_n;
-      double T;
-      if constexpr (F64) {
-        const long long hi = ((long long)acc[r][0][k] << 16) + ((long long)acc[r][1][k] << 8) +
-                             acc[r][2][k];
-        const long long lo = ((long long)acc[r][3][k] << 24) + ((long long)acc[r][4][k] << 16) +
-                             ((long long)acc[r][5][k] << 8) + acc[r][6][k];
-        T = __builtin_fma((double)hi, 4294967296.0, (double)lo);
-      } else {
-        long long t = acc[r][0][k];
-#pragma unroll
-        for (int d = 1; d < D; ++d) t = (t << 8) + acc[r][d][k];
-        T = (double)t;
-      }
-      const double num = (T - a.csum * (fbar - 128.0)) * a.inv_scale;
+      const double num = dense_num<D>(acc[r], k, sf[k], a);
       const long long o = (long long)v * a.rho_pitch + u + k;
       if (row_ok && u + k < a.nu) {
-        if constexpr (F64) {
-          const double rho = V == 0 ? 0.0 : num / sqrt((double)V / (double)a.n * a.q_k);
-          static_cast<double *>(a.rho)[o] = rho;
-        } else {
-          // 1 / sqrt of the energy in FP64: the FP32 estimate and one Newton step
-          const double e = (double)V * a.qnd;
-          const double y0 = (double)__builtin_amdgcn_rsqf((float)e);
-          const double y1 = y0 * __builtin_fma(-0.5 * e * y0, y0, 1.5);
-          static_cast<float *>(a.rho)[o] = V == 0 ? 0.f : (float)(num * y1);
-        }
-        if (a.degen) a.degen[o] = V == 0 ? 1 : 0;
+        if constexpr (D == kDenseDigits)
+          static_cast<double *>(a.rho)[o] =
+              V[k] == 0 ? 0.0 : num / sqrt((double)V[k] / (double)a.n * a.q_k);
+        else
+          static_cast<float *>(a.rho)[o] = dense_rho32(num, V[k], a.qnd);
+        if (a.degen) a.degen[o] = V[k] == 0 ? 1 : 0;
       }
     }
   }
+}
+
+// The filter of the top-k search (topk_filter.hip): FP32 rho of many pairs in
+// one launch, one workgroup per item {pair, tile} (pair -1: none).  A wave
+// writes its RV x 64 x 4 values as they lie in its lanes (offsets past the
+// valid range as -inf), and its block's largest rho; offsets whose window is
+// nearly uniform (energy below n / 100, where the segment form's FP32 error
+// bound grows) do not count there but raise a second maximum.
+template <int D, int RV, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dense_filter(
+    const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride,
+    const FilterPair *__restrict__ fps, const int2 *__restrict__ items, float *__restrict__ map,
+    float2 *__restrict__ bmax) {
+  extern __shared__ __align__(16) uint8_t lds8[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int2 it = items[blockIdx.x];
+  if (it.x < 0) return;
+  const FilterPair &fp = fps[it.x];
+  const DenseArgs a = fp.a;
+  const uint32_t *S = s + (long long)fp.frame * frame_stride;
+  const uint32_t *S2 = s2 + (long long)fp.frame * frame_stride;
+  const int tile = it.y, tv = tile / a.ntu;
+  const int u0 = (tile - tv * a.ntu) * kDenseBU, v0 = tv * 2 * NW * RV;
+  const int row0 = RV * (2 * wave + ((lane >> 3) & 1));
+  v4i acc[RV][D];
+  dense_products<D, RV, NW>(S, static_cast<const v4i *>(a.frag), a, u0, v0, row0, lds8, lane, acc);
+
+  const int u = u0 + 16 * (lane & 7) + 4 * (lane >> 4);
+  const long long low = (long long)a.n * a.n / 100;
+  const int block = tile * NW + wave;
+  float4 *o = reinterpret_cast<float4 *>(map + fp.map0 + (long long)block * (RV * 256)) + lane;
+  float top = -__builtin_inff(), top_low = -__builtin_inff();
+#pragma unroll
+  for (int r = 0; r < RV; ++r) {
+    const int v = v0 + row0 + r;
+    v4u_a4 sf;
+    long long V[4];
+    dense_energy4(S, S2, a, min(u, a.nu - 1), min(v, a.nv - 1), sf, V);
+    float w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const bool ok = v < a.nv && u + k < a.nu;
+      w[k] = ok ? dense_rho32(dense_num<D>(acc[r], k, sf[k], a), V[k], a.qnd) : -__builtin_inff();
+      const bool flat = V[k] != 0 && V[k] < low;
+      if (flat) top_low = fmaxf(top_low, w[k]);
+      else top = fmaxf(top, w[k]);
+    }
+    o[r * 64] = make_float4(w[0], w[1], w[2], w[3]);
+    __builtin_amdgcn_sched_barrier(0);  // rows one after another: fewer registers
+  }
+  const uint32_t m = wave_incl_max(float_order(top)), ml = wave_incl_max(float_order(top_low));
+  if (lane == 63) bmax[fp.block0 + block] = make_float2(float_unorder(m), float_unorder(ml));
 }
 
 template <int D, int RV, int NW>
@@ -333,6 +408,40 @@ int launch_dense(const DenseArgs &a, hipStream_t st) {
     case 402: return dense_go<4, 2, kDenseNW>(a, st);
     case 704: return dense_go<7, 4, kDenseNW>(a, st);
     case 702: return dense_go<7, 2, kDenseNW>(a, st);
+    default: return -1;
+  }
+}
+
+template <int D, int RV, int NW>
+static int filter_go(const uint32_t *s, const uint32_t *s2, long long frame_stride,
+                     const FilterPair *fps, const int2 *items, int n_items, int lds, float *map,
+                     float2 *bmax, hipStream_t st) {
+  static bool attr = false;
+  const void *fn = (const void *)dense_filter<D, RV, NW>;
+  if (!attr) {
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kTileMaxLds) !=
+        hipSuccess)
+      return -1;
+    attr = true;
+  }
+  hipLaunchKernelGGL((dense_filter<D, RV, NW>), dim3(n_items), dim3(64 * NW), lds, st, s, s2,
+                     frame_stride, fps, items, map, bmax);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_dense_filter(int digits, int rv, const uint32_t *s, const uint32_t *s2,
+                        long long frame_stride, const FilterPair *fps, const int2 *items,
+                        int n_items, int lds, float *map, float2 *bmax, hipStream_t st) {
+  switch (digits * 100 + rv) {
+#define SNCC_FILTER(D, RV) \
+  case D * 100 + RV:       \
+    return filter_go<D, RV, kDenseNW>(s, s2, frame_stride, fps, items, n_items, lds, map, bmax, st)
+    SNCC_FILTER(3, 8);
+    SNCC_FILTER(3, 4);
+    SNCC_FILTER(3, 2);
+    SNCC_FILTER(4, 4);
+    SNCC_FILTER(4, 2);
+#undef SNCC_FILTER
     default: return -1;
   }
 }

@@ -312,10 +312,57 @@ struct DenseArgs {
   int rho_pitch;
   uint8_t *degen;
 };
+// Top-k by filter and rescoring (dense_filter, topk_filter.hip).  One pair of
+// the filter; `a` as for a map, less the tables.
+struct FilterPair {
+  DenseArgs a;
+  int frame, pair;         // pair: index in the call's list
+  long long map0;          // first value in the scratch map
+  int block0, n_blocks;    // blocks (waves of tiles) of the pair
+  int seq0, n_seq;         // FP32: records of the segment form's sum (SeqRec)
+  int seg_off, K;          // FP64: the segments
+  double r64;
+};
+
+// One boundary column of the FP32 segment form's chains in its order of
+// summation: byte offsets of the column's entries in the chain's top and bottom
+// rows from the window's top-left entry, A_i and c_i of the segment that ends
+// there, and whether it starts a chain (no segment) or ends a compensated step.
+struct SeqRec {
+  int top, bot;
+  uint32_t area_flags;     // A_i | kSeqFirst | kSeqEnd
+  float c;
+};
+constexpr uint32_t kSeqFirst = 1u << 31, kSeqEnd = 1u << 30, kSeqArea = (1u << 24) - 1;
+
+// Candidates a pair may hold; above it the pair takes the direct form.
+constexpr int kFilterCands = 512;
+
+// One pair of the direct form: every offset by the reference arithmetic.
+struct SeqPair {
+  int frame, nu, nv, W, H, n, sq_rows;
+  int seq0, n_seq, seg_off, K;
+  int chunk0, n_chunks;    // partial lists
+  double q_k, r64;
+};
+
 // Weak: the planner also links into host-only programs without the kernels.
+#define SNCC_WEAK __attribute__((weak))
 int launch_dense_pack(const int4 *geom, const double *c64, int K, double scale, int W, int H,
-                      int digits, long long *img, void *frag, hipStream_t st) __attribute__((weak));
-int launch_dense(const DenseArgs &a, hipStream_t st) __attribute__((weak));
+                      int digits, long long *img, void *frag, hipStream_t st) SNCC_WEAK;
+int launch_dense(const DenseArgs &a, hipStream_t st) SNCC_WEAK;
+int launch_dense_filter(int digits, int rv, const uint32_t *s, const uint32_t *s2,
+                        long long frame_stride, const FilterPair *fps, const int2 *items,
+                        int n_items, int lds, float *map, float2 *bmax, hipStream_t st) SNCC_WEAK;
+int launch_filter_select(bool fp64, const uint32_t *s, const uint32_t *s2, long long frame_stride,
+                         int P, const FilterPair *fps, int n_fps, const float *map,
+                         const float2 *bmax, const SeqRec *seq, const int4 *geom,
+                         const double *c64, int k, sncc_match *out, int *direct,
+                         hipStream_t st) SNCC_WEAK;
+int launch_seq_topk(bool fp64, const uint32_t *s, const uint32_t *s2, long long frame_stride,
+                    int P, const SeqPair *pairs, int n_pairs, const int *direct, int chunk,
+                    const SeqRec *seq, const int4 *geom, const double *c64, int k, void *partial,
+                    int grid, sncc_match *out, hipStream_t st) SNCC_WEAK;
 
 // Tile kernel configuration: offsets per lane RU (u, stride 64) x RV (v),
 // NW waves per workgroup, each wave owning RV offset rows; `wgs` is the
@@ -422,10 +469,6 @@ struct Key96 {
   uint32_t lo;
   uint32_t pad;
 };
-int launch_map_topk64(const double *map, int pitch, int nu, int nv, int chunk, int k,
-                      Key96 *partial, hipStream_t st);
-int launch_merge64(const PairDesc *pairs, int n_pairs, const Key96 *partial, int k,
-                   sncc_match *out, hipStream_t st);
 // Region bytes that leave room for `wgs` refine workgroups per CU when the
 // offset list holds np entries (0 when none fit).
 int refine_region_budget(int np, int wgs);

@@ -1,0 +1,540 @@
+// Top-k of (frame, template) pairs by filter and rescoring.
+//
+// dense_filter gives FP32 rho of every offset with a known error bound.  The k
+// best offsets by the reference arithmetic (FP32: the segment form's chains in
+// their order of summation; FP64: box sums in FP64) are then among the
+// candidates: the offsets whose filter value is not below the k-th largest by
+// more than twice the two errors.  filter_select finds them (one workgroup per
+// pair), scores them again by the reference arithmetic and orders them, so the
+// result is the reference's: for FP32 bit for bit.  A pair whose candidates do
+// not fit, or whose nearly uniform windows (where the FP32 bound is too wide)
+// come near the k-th value, is left to seq_topk, which scores every offset by
+// the reference arithmetic; it also takes the FP64 pairs that no filter serves.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdint>
+
+#include "device_util.hpp"
+
+namespace sncc {
+
+// --------------------------------------------------------- reference values
+// Per-offset quantities of the FP32 segment form: the negated integer mean and
+// the scale 1 / sqrt(V q_k / n), with run_item's operations.
+struct Ref32 {
+  int nb;
+  float scale;
+};
+
+__device__ __forceinline__ uint32_t ref_box(const uint32_t *__restrict__ a0, int W, int H, int P) {
+  const uint32_t *a1 = a0 + (long long)H * P;
+  return (a1[W] - a1[0]) - (a0[W] - a0[0]);
+}
+
+__device__ __forceinline__ Ref32 ref32(const uint32_t *__restrict__ S,
+                                       const uint32_t *__restrict__ S2, int P, int u, int v, int W,
+                                       int H, int n, int sq_rows, double q_k) {
+  const long long o = (long long)v * P + u;
+  const uint32_t sf = ref_box(S + o, W, H, P);
+  const float inv_n = 1.0f / (float)n;
+  const double qnd = q_k / (double)n;
+  Ref32 r;
+  r.nb = -(int)__builtin_rintf((float)sf * inv_n);
+  if (n <= kMaxSqBoxArea) {
+    const double fs = (double)sf;
+    const double Vd = __builtin_fma((double)n, (double)ref_box(S2 + o, W, H, P), -(fs * fs));
+    r.scale = Vd == 0.0 ? 0.f : __builtin_amdgcn_rsqf((float)(Vd * qnd));
+  } else {
+    const u64 sf2 = window_sq(S2 + o, W, H, P, sq_rows);
+    const u64 V = (u64)(uint32_t)n * sf2 - (u64)sf * sf;
+    r.scale = V == 0 ? 0.f : __builtin_amdgcn_rsqf((float)((double)V * qnd));
+  }
+  return r;
+}
+
+// A compensated step of the FP32 sum; y starts the next block.
+__device__ __forceinline__ void ref_step(float &acc, float &cmp, float &y) {
+  const float t = acc + y;
+  cmp = (t - acc) - y;
+  acc = t;
+  y = -cmp;
+}
+
+// rho of one offset by a whole wave, FP32: lanes take 64 records' column
+// differences and products' factors at a time (the next 64 requested before
+// these are summed), then the wave adds them in order.
+__device__ __forceinline__ float wave_ref32(const uint32_t *__restrict__ S,
+                                            const uint32_t *__restrict__ S2, int P, int u, int v,
+                                            const FilterPair &fp, const SeqRec *__restrict__ seq,
+                                            int lane) {
+  const Ref32 rf = ref32(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.n, fp.a.sq_rows, fp.a.q_k);
+  const char *w = reinterpret_cast<const char *>(S + (long long)v * P + u);
+  float acc = 0.f, cmp = 0.f, y = -cmp;
+  uint32_t carry = 0;
+  const SeqRec *sr = seq + fp.seq0;
+  auto load = [&](int i, SeqRec &e, uint32_t &D) {
+    e = SeqRec{0, 0, kSeqFirst, 0.f};
+    if (i < fp.n_seq) e = sr[i];
+    D = *reinterpret_cast<const uint32_t *>(w + e.bot) -
+        *reinterpret_cast<const uint32_t *>(w + e.top);
+  };
+  SeqRec e, en;
+  uint32_t D, Dn;
+  load(lane, e, D);
+  for (int i = 0; i < fp.n_seq; i += 64) {
+    if (i + 64 < fp.n_seq) load(i + 64 + lane, en, Dn);
+    uint32_t prev = (uint32_t)__shfl_up((int)D, 1);
+    if (lane == 0) prev = carry;
+    carry = (uint32_t)__builtin_amdgcn_readlane((int)D, 63);
+    const uint32_t F = D - prev;  // Eq. (11)
+    const int G = (int)F + __mul24((int)(e.area_flags & kSeqArea), rf.nb);
+    const float g = (float)G;
+    u64 use = __ballot((e.area_flags & kSeqFirst) == 0);
+    const u64 end = __ballot((e.area_flags & kSeqEnd) != 0);
+    while (use) {
+      const int l = __ffsll((long long)use) - 1;
+      use &= use - 1;
+      const float gl = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g), l));
+      const float cl = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(e.c), l));
+      y = __builtin_fmaf(gl, cl, y);
+      if ((end >> l) & 1) ref_step(acc, cmp, y);
+    }
+    e = en;
+    D = Dn;
+  }
+  return (acc - cmp) * rf.scale;
+}
+
+// rho of one offset by a whole wave, FP64: box sums less A_i b (b the window
+// mean rounded to an integer) in integers, c_i times them summed over the lanes
+// and then the wave, and the mean term of Eq. (12) for what b leaves.
+__device__ __forceinline__ double wave_ref64(const uint32_t *__restrict__ S,
+                                             const uint32_t *__restrict__ S2, int P, int u, int v,
+                                             const FilterPair &fp, const int4 *__restrict__ geom,
+                                             const double *__restrict__ c64, int lane) {
+  const long long o = (long long)v * P + u;
+  const int n = fp.a.n;
+  const uint32_t sf = ref_box(S + o, fp.a.W, fp.a.H, P);
+  const u64 sf2 = window_sq(S2 + o, fp.a.W, fp.a.H, P, fp.a.sq_rows);
+  const long long V = (long long)((u64)(uint32_t)n * sf2 - (u64)sf * sf);
+  const double fbar = (double)sf / (double)n;
+  const int b = (int)rint(fbar);
+  double acc = 0.0;
+  for (int i = lane; i < fp.K; i += 64) {
+    const int4 g = geom[fp.seg_off + i];
+    const uint32_t F = ref_box(S + o + (long long)g.y * P + g.x, g.z, g.w, P);
+    acc = __builtin_fma((double)((int)F - g.z * g.w * b), c64[fp.seg_off + i], acc);
+  }
+  for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
+  const double num = acc + ((double)b - fbar) * fp.r64;
+  return V == 0 ? 0.0 : num / sqrt((double)V / (double)n * fp.a.q_k);
+}
+
+// ----------------------------------------------------------------- selection
+constexpr int kSelThreads = 1024;
+constexpr int kSelBins = 2048;
+constexpr int kSelBlocks = 2048;
+
+// Largest bin b with at least k entries in bins b and above (0 when there are
+// fewer in all); every thread of the workgroup gets it.
+__device__ __forceinline__ int kth_bin(const int *hist, int k, int *out) {
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    constexpr int PER = kSelBins / 64;
+    int sum = 0;
+    for (int i = 0; i < PER; ++i) sum += hist[lane * PER + i];
+    const int incl = (int)wave_incl_scan((uint32_t)sum);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    const u64 ok = __ballot(total - incl + sum >= k);  // entries in this lane's bins and above
+    int b = 0;
+    if (ok) {
+      const int L = 63 - __builtin_clzll(ok);
+      const int above = total - __builtin_amdgcn_readlane(incl, L);
+      const int mine = lane < PER ? hist[L * PER + lane] : 0;
+      const int in2 = (int)wave_incl_scan((uint32_t)mine);
+      const int t2 = __builtin_amdgcn_readlane(in2, 63);
+      const u64 ok2 = __ballot(lane < PER && above + t2 - in2 + mine >= k);
+      b = L * PER + 63 - __builtin_clzll(ok2);
+    }
+    if (lane == 0) *out = b;
+  }
+  __syncthreads();
+  return *out;
+}
+
+template <bool F64>
+__global__ __launch_bounds__(kSelThreads) void filter_select(
+    const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride, int P,
+    const FilterPair *__restrict__ fps, const float *__restrict__ map,
+    const float2 *__restrict__ bmax, const SeqRec *__restrict__ seq,
+    const int4 *__restrict__ geom, const double *__restrict__ c64, int k,
+    sncc_match *__restrict__ out, int *__restrict__ direct) {
+  __shared__ int hist[kSelBins];
+  __shared__ int list[kSelBlocks];
+  __shared__ int cand[kFilterCands];
+  __shared__ u64 key_hi[kFilterCands];
+  __shared__ uint32_t key_lo[F64 ? kFilterCands : 1];
+  __shared__ int n_list, n_cand, bin, bad;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const FilterPair &fp = fps[blockIdx.x];
+  const int nb = fp.n_blocks, rv = fp.a.rv, nu = fp.a.nu;
+  const float2 *bm = bmax + fp.block0;
+  const float *vals = map + fp.map0;
+  // twice the errors of the filter (2^-22 + 2^-24) and of the reference (FP32:
+  // at most 3e-6 for windows of energy n / 100 and above, 1e-4 for any window)
+  constexpr float kMargin = F64 ? 1e-6f : 8e-6f;
+  constexpr float kLowVar = 2e-4f;
+
+  auto clear = [&]() {
+    __syncthreads();
+    for (int i = tid; i < kSelBins; i += kSelThreads) hist[i] = 0;
+    if (tid == 0) n_list = 0;
+    __syncthreads();
+  };
+  auto blocks_from = [&](float t) {  // the blocks whose largest value is at least t
+    for (int i = tid; i < nb; i += kSelThreads)
+      if (bm[i].x >= t) {
+        const int at = atomicAdd(&n_list, 1);
+        if (at < kSelBlocks) list[at] = i;
+      }
+    __syncthreads();
+  };
+  // calls f(value, row-major index) for the values of the listed blocks
+  auto scan = [&](auto f) {
+    const int units = min(n_list, kSelBlocks) * rv;
+    for (int un = wave * 4; un < units; un += kSelThreads / 64 * 4) {
+      float4 w[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int x = min(un + q, units - 1);
+        w[q] = reinterpret_cast<const float4 *>(vals)[((long long)list[x / rv] * rv + x % rv) * 64 +
+                                                      lane];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (un + q >= units) break;
+        const int blk = list[(un + q) / rv], r = (un + q) % rv;
+        const int tile = blk / kDenseNW, wv = blk % kDenseNW, tv = tile / fp.a.ntu;
+        const int u = (tile - tv * fp.a.ntu) * kDenseBU + 16 * (lane & 7) + 4 * (lane >> 4);
+        const int v = tv * 2 * kDenseNW * rv + rv * (2 * wv + ((lane >> 3) & 1)) + r;
+        const float e[4] = {w[q].x, w[q].y, w[q].z, w[q].w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (e[c] != -__builtin_inff()) f(e[c], v * nu + u + c);
+      }
+    }
+    __syncthreads();
+  };
+
+  // T0: at least k blocks reach it, so the k-th largest value does (the lower
+  // edge of a bin of block maxima, less a rounding allowance)
+  if (tid == 0) n_cand = bad = 0;
+  clear();
+  for (int i = tid; i < nb; i += kSelThreads) {
+    const float x = bm[i].x;
+    if (x != -__builtin_inff())
+      atomicAdd(&hist[min(kSelBins - 1, max(0, (int)((x + 1.0f) * 1000.0f)))], 1);
+  }
+  const int b0 = kth_bin(hist, k, &bin);
+  const float T0 = b0 == 0 ? -__builtin_inff() : (float)b0 * 1e-3f - 1.0f - 1e-5f;
+  // T1: the same for the values of the blocks that reach T0, in finer bins
+  clear();
+  blocks_from(T0);
+  const float lo = b0 == 0 ? -1.001f : T0;
+  const float scale = (float)(kSelBins - 1) / (1.001f - lo);
+  scan([&](float x, int) {
+    if (x >= T0) atomicAdd(&hist[min(kSelBins - 1, max(0, (int)((x - lo) * scale)))], 1);
+  });
+  const int b1 = kth_bin(hist, k, &bin);
+  const float T1 = b1 == 0 ? T0 : lo + ((float)b1 - 0.01f) / scale;
+  if (tid == 0 && n_list > kSelBlocks) bad = 1;
+  clear();
+  blocks_from(T1 - kMargin);
+  if (tid == 0 && n_list > kSelBlocks) bad = 1;
+  for (int i = tid; i < nb; i += kSelThreads)
+    if (bm[i].y + kLowVar >= T1) bad = 1;
+  scan([&](float x, int idx) {
+    if (x >= T1 - kMargin) {
+      const int at = atomicAdd(&n_cand, 1);
+      if (at < kFilterCands) cand[at] = idx;
+    }
+  });
+  const int n = n_cand;
+  if (bad || n > kFilterCands) {
+    if (tid == 0) direct[fp.pair] = 1;
+    return;
+  }
+  // the candidates by the reference arithmetic, one wave each
+  const uint32_t *S = s + (long long)fp.frame * frame_stride;
+  const uint32_t *S2 = s2 + (long long)fp.frame * frame_stride;
+  for (int c = wave; c < n; c += kSelThreads / 64) {
+    const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
+    const int v = idx / nu, u = idx - v * nu;
+    if constexpr (F64) {
+      const double r = wave_ref64(S, S2, P, u, v, fp, geom, c64, lane);
+      if (lane == 0) {
+        key_hi[c] = double_order(r);
+        key_lo[c] = 0xffffffffu - (uint32_t)idx;
+      }
+    } else {
+      const float r = wave_ref32(S, S2, P, u, v, fp, seq, lane);
+      if (lane == 0) key_hi[c] = make_key(r, idx);
+    }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  u64 lh = 0;
+  uint32_t ll = 0;
+  for (int c = 0; c < n; c += 64) {
+    u64 h = c + lane < n ? key_hi[c + lane] : 0;
+    if constexpr (F64) {
+      const uint32_t l = c + lane < n ? key_lo[c + lane] : 0;
+      u64 todo = __ballot(key96_gt(h, l, lane_u64(lh, k - 1),
+                                   (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)));
+      while (todo) {
+        const int q = __ffsll((long long)todo) - 1;
+        todo &= todo - 1;
+        const u64 kh = lane_u64(h, q);
+        const uint32_t kl = (uint32_t)__builtin_amdgcn_readlane((int)l, q);
+        if (key96_gt(kh, kl, lane_u64(lh, k - 1),
+                     (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)))
+          topk96_insert(lh, ll, kh, kl, k, lane);
+      }
+    } else {
+      topk_merge_sorted(lh, wave_sort_desc_u64(h, lane), k, lane);
+    }
+  }
+  if (lane < k) {
+    sncc_match m;
+    m.u = m.v = -1;
+    m.rho = -__builtin_inff();
+    const bool some = F64 ? (lh != 0 || ll != 0) : lh != 0;
+    if (some) {
+      const int idx = (int)(0xffffffffu - (F64 ? ll : (uint32_t)(lh & 0xffffffffu)));
+      m.v = idx / nu;
+      m.u = idx - m.v * nu;
+      m.rho = F64 ? (float)double_unorder(lh) : float_unorder((uint32_t)(lh >> 32));
+    }
+    out[(long long)fp.pair * k + lane] = m;
+  }
+  if (lane == 0) direct[fp.pair] = 0;
+}
+
+int launch_filter_select(bool fp64, const uint32_t *s, const uint32_t *s2, long long frame_stride,
+                         int P, const FilterPair *fps, int n_fps, const float *map,
+                         const float2 *bmax, const SeqRec *seq, const int4 *geom,
+                         const double *c64, int k, sncc_match *out, int *direct,
+                         hipStream_t st) {
+  if (fp64)
+    hipLaunchKernelGGL(filter_select<true>, dim3(n_fps), dim3(kSelThreads), 0, st, s, s2,
+                       frame_stride, P, fps, map, bmax, seq, geom, c64, k, out, direct);
+  else
+    hipLaunchKernelGGL(filter_select<false>, dim3(n_fps), dim3(kSelThreads), 0, st, s, s2,
+                       frame_stride, P, fps, map, bmax, seq, geom, c64, k, out, direct);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// --------------------------------------------------------------- direct form
+// rho of one offset per thread by the reference arithmetic.
+__device__ __forceinline__ float lane_ref32(const uint32_t *__restrict__ S,
+                                            const uint32_t *__restrict__ S2, int P, int u, int v,
+                                            const SeqPair &sp, const SeqRec *__restrict__ seq) {
+  const Ref32 rf = ref32(S, S2, P, u, v, sp.W, sp.H, sp.n, sp.sq_rows, sp.q_k);
+  const char *w = reinterpret_cast<const char *>(S + (long long)v * P + u);
+  float acc = 0.f, cmp = 0.f, y = -cmp;
+  uint32_t prev = 0;
+  const SeqRec *sr = seq + sp.seq0;
+#pragma unroll 4
+  for (int i = 0; i < sp.n_seq; ++i) {
+    const SeqRec e = sr[i];
+    const uint32_t D = *reinterpret_cast<const uint32_t *>(w + e.bot) -
+                       *reinterpret_cast<const uint32_t *>(w + e.top);
+    const int G = (int)(D - prev) + __mul24((int)(e.area_flags & kSeqArea), rf.nb);
+    if (!(e.area_flags & kSeqFirst)) y = __builtin_fmaf((float)G, e.c, y);
+    prev = D;
+    if (e.area_flags & kSeqEnd) ref_step(acc, cmp, y);
+  }
+  return (acc - cmp) * rf.scale;
+}
+
+// As plain_kernel's rho_plain: box_i c_i summed in segment order, FP64.
+__device__ __forceinline__ double lane_ref64(const uint32_t *__restrict__ S,
+                                             const uint32_t *__restrict__ S2, int P, int u, int v,
+                                             const SeqPair &sp, const int4 *__restrict__ geom,
+                                             const double *__restrict__ c64) {
+  const uint32_t *a0 = S + (long long)v * P + u;
+  const uint32_t sf = ref_box(a0, sp.W, sp.H, P);
+  const u64 sf2 = window_sq(S2 + (long long)v * P + u, sp.W, sp.H, P, sp.sq_rows);
+  const long long V = (long long)((u64)(uint32_t)sp.n * sf2 - (u64)sf * sf);
+  double acc = 0.0;
+  const int4 *gp = geom + sp.seg_off;
+  const double *cp = c64 + sp.seg_off;
+#pragma unroll 4
+  for (int i = 0; i < sp.K; ++i) {
+    const int4 g = gp[i];
+    acc = __builtin_fma((double)ref_box(a0 + (long long)g.y * P + g.x, g.z, g.w, P), cp[i], acc);
+  }
+  const double num = acc - (double)sf / (double)sp.n * sp.r64;
+  return V == 0 ? 0.0 : num / sqrt((double)V / (double)sp.n * sp.q_k);
+}
+
+// The k best offsets of each `chunk` offsets of the pairs that direct[] marks;
+// the chunks of all of them go round the workgroups.  A launch without such
+// pairs only reads the marks.
+template <bool F64>
+__global__ __launch_bounds__(256) void seq_topk(
+    const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride, int P,
+    const SeqPair *__restrict__ pairs, int n_pairs, const int *__restrict__ direct, int chunk,
+    const SeqRec *__restrict__ seq, const int4 *__restrict__ geom,
+    const double *__restrict__ c64, int k, void *__restrict__ partial) {
+  __shared__ u64 bh[4 * 64];
+  __shared__ uint32_t bl[4 * 64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int before = 0;  // chunks of the marked pairs so far, modulo the grid
+  for (int p0 = 0; p0 < n_pairs; p0 += 64) {
+    u64 marked = __ballot(p0 + lane < n_pairs && direct[p0 + lane] != 0);
+    while (marked) {
+      const int p = p0 + __ffsll((long long)marked) - 1;
+      marked &= marked - 1;
+      const SeqPair sp = pairs[p];
+      const uint32_t *S = s + (long long)sp.frame * frame_stride;
+      const uint32_t *S2 = s2 + (long long)sp.frame * frame_stride;
+      const int grid = gridDim.x;
+      int c = (int)blockIdx.x - before;
+      if (c < 0) c += grid;
+      for (; c < sp.n_chunks; c += grid) {
+        const long long total = (long long)sp.nu * sp.nv;
+        const long long c0 = (long long)c * chunk, c1 = min(total, c0 + chunk);
+        u64 lh = 0;
+        uint32_t ll = 0;
+        for (long long e0 = c0 + wave * 64; e0 < c1; e0 += 4 * 64) {
+          const long long e = min(e0 + lane, c1 - 1);
+          const int v = (int)(e / sp.nu), u = (int)(e - (long long)v * sp.nu);
+          const bool ok = e0 + lane < c1;
+          if constexpr (F64) {
+            const double r = lane_ref64(S, S2, P, u, v, sp, geom, c64);
+            u64 ch = ok ? double_order(r) : 0;
+            uint32_t cl = ok ? 0xffffffffu - (uint32_t)e : 0;
+            for (;;) {  // best first, while they beat the k-th
+              if (!key96_gt(ch, cl, lane_u64(lh, k - 1),
+                            (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)))
+                ch = 0, cl = 0;
+              if (__ballot(ch != 0 || cl != 0) == 0) break;
+              u64 mh;
+              uint32_t ml;
+              wave_max96(ch, cl, mh, ml);
+              topk96_insert(lh, ll, mh, ml, k, lane);
+              if (ch == mh && cl == ml) ch = 0, cl = 0;
+            }
+          } else {
+            const float r = lane_ref32(S, S2, P, u, v, sp, seq);
+            u64 cnd[1] = {ok ? make_key(r, (int)e) : 0};
+            topk_offer<1>(lh, cnd, k, lane);
+          }
+        }
+        if (lane < k) {
+          bh[wave * k + lane] = lh;
+          bl[wave * k + lane] = ll;
+        }
+        __syncthreads();
+        if (wave == 0) {
+          for (int w = 1; w < 4; ++w)
+            for (int j = 0; j < k; ++j) {  // each wave's list is in descending order
+              const u64 kh = bh[w * k + j];
+              const uint32_t kl = bl[w * k + j];
+              if (!key96_gt(kh, kl, lane_u64(lh, k - 1),
+                            (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)))
+                break;
+              topk96_insert(lh, ll, kh, kl, k, lane);
+            }
+          if (lane < k) {
+            const long long o = (long long)(sp.chunk0 + c) * k + lane;
+            if constexpr (F64)
+              static_cast<Key96 *>(partial)[o] = Key96{lh, ll, 0};
+            else
+              static_cast<u64 *>(partial)[o] = lh;
+          }
+        }
+        __syncthreads();
+      }
+      before = (before + sp.n_chunks) % grid;
+    }
+  }
+}
+
+// One wave per marked pair: the k best of its chunks' lists; one load brings
+// 64 / k of them.
+template <bool F64>
+__global__ __launch_bounds__(256) void seq_merge(const SeqPair *__restrict__ pairs, int n_pairs,
+                                                 const int *__restrict__ direct,
+                                                 const void *__restrict__ partial, int k,
+                                                 sncc_match *__restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (p >= n_pairs || direct[p] == 0) return;
+  const SeqPair sp = pairs[p];
+  u64 lh = 0;
+  uint32_t ll = 0;
+  const int g = 64 / k, end = sp.chunk0 + sp.n_chunks;
+  for (int c = sp.chunk0; c < end; c += g) {
+    u64 h = 0;
+    uint32_t l = 0;
+    if (lane < g * k && c + lane / k < end) {
+      const long long o = (long long)c * k + lane;
+      if constexpr (F64) {
+        const Key96 e = static_cast<const Key96 *>(partial)[o];
+        h = e.hi;
+        l = e.lo;
+      } else {
+        h = static_cast<const u64 *>(partial)[o];
+      }
+    }
+    u64 todo = __ballot(key96_gt(h, l, lane_u64(lh, k - 1),
+                                 (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)));
+    while (todo) {
+      const int q = __ffsll((long long)todo) - 1;
+      todo &= todo - 1;
+      const u64 kh = lane_u64(h, q);
+      const uint32_t kl = (uint32_t)__builtin_amdgcn_readlane((int)l, q);
+      if (key96_gt(kh, kl, lane_u64(lh, k - 1),
+                   (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)))
+        topk96_insert(lh, ll, kh, kl, k, lane);
+    }
+  }
+  if (lane < k) {
+    sncc_match m;
+    m.u = m.v = -1;
+    m.rho = -__builtin_inff();
+    if (lh != 0 || ll != 0) {
+      const int idx = (int)(0xffffffffu - (F64 ? ll : (uint32_t)(lh & 0xffffffffu)));
+      m.v = idx / sp.nu;
+      m.u = idx - m.v * sp.nu;
+      m.rho = F64 ? (float)double_unorder(lh) : float_unorder((uint32_t)(lh >> 32));
+    }
+    out[(long long)p * k + lane] = m;
+  }
+}
+
+int launch_seq_topk(bool fp64, const uint32_t *s, const uint32_t *s2, long long frame_stride,
+                    int P, const SeqPair *pairs, int n_pairs, const int *direct, int chunk,
+                    const SeqRec *seq, const int4 *geom, const double *c64, int k, void *partial,
+                    int grid, sncc_match *out, hipStream_t st) {
+  const dim3 mg((n_pairs + 3) / 4);
+  if (fp64) {
+    hipLaunchKernelGGL(seq_topk<true>, dim3(grid), dim3(256), 0, st, s, s2, frame_stride, P, pairs,
+                       n_pairs, direct, chunk, seq, geom, c64, k, partial);
+    hipLaunchKernelGGL(seq_merge<true>, mg, dim3(256), 0, st, pairs, n_pairs, direct, partial, k,
+                       out);
+  } else {
+    hipLaunchKernelGGL(seq_topk<false>, dim3(grid), dim3(256), 0, st, s, s2, frame_stride, P,
+                       pairs, n_pairs, direct, chunk, seq, geom, c64, k, partial);
+    hipLaunchKernelGGL(seq_merge<false>, mg, dim3(256), 0, st, pairs, n_pairs, direct, partial, k,
+                       out);
+  }
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+}  // namespace sncc

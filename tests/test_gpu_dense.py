@@ -1,5 +1,6 @@
-"""Rho maps in the matrix-core form against the oracle and against the forms
-it stands in for, at the edges of its tiles and passes.
+"""Rho maps in the matrix-core form, and top-k lists found with its filter,
+against the oracle and against the forms they stand in for, at the edges of
+tiles and passes.
 
 SNCC_TEST_DENSE=1 takes the matrix-core form wherever it is possible, 0 never.
 Tolerances as everywhere: FP32 rho within 1e-5 of the oracle, FP64 within
@@ -141,3 +142,106 @@ def test_fp64_map_under_capture(S, monkeypatch):
             st.synchronize()
         S.sncc_tmpl_destroy(tm)
         S.sncc_ctx_destroy(c)
+
+
+def _lists(S, ctx, monkeypatch, form, frames, segs, W, H, pairs, k, prec):
+    import torch
+    monkeypatch.setenv("SNCC_TEST_DENSE", form)
+    B, N, M = len(frames), frames[0].shape[0], frames[0].shape[1]
+    _, s, s2 = build_sats(S, ctx, frames)
+    tm = S.sncc_upload_templates(ctx, segs, W, H)
+    out = torch.full((len(pairs), k, 3), 5, dtype=torch.int32, device="cuda")
+    for _ in range(2):  # the second call reuses the plan
+        out.fill_(5)
+        S.sncc_topk(ctx, tm, s, s2, B, M, N, pairs, k, prec, out)
+    S.sncc_sync(ctx)
+    S.sncc_tmpl_destroy(tm)
+    return out.cpu().numpy()
+
+
+def _segments(S, t, sigma):
+    """Segments at sigma, or below it where that leaves a uniform approximation."""
+    while True:
+        try:
+            return S.sncc_segment_template(t, sigma, t.size)[0]
+        except S.SnccError as e:
+            assert e.code == S.SNCC_EDEGENERATE and sigma > 1e-3
+            sigma *= 0.5
+
+
+def _frames(kind, M, N):
+    if kind == "scene":
+        f = synth.scene(M, M, N)
+        f[:60, :70] = 90
+    elif kind == "uniform":  # every rho 0: the first offsets
+        f = np.full((N, M), 31, np.uint8)
+    elif kind == "periodic":  # thousands of equal best offsets
+        y, x = np.mgrid[0:N, 0:M]
+        f = ((x % 7) * 25 + (y % 5) * 13).astype(np.uint8)
+    else:  # nearly uniform windows everywhere
+        f = np.full((N, M), 100, np.uint8)
+        f[np.random.default_rng(3).random((N, M)) < 2e-3] = 101
+    return [f, f[::-1].copy()]
+
+
+@pytest.mark.parametrize("kind", ["scene", "uniform", "periodic", "lowvar"])
+@pytest.mark.parametrize("k", [1, 5, 64])
+def test_filtered_topk_is_the_direct_topk(S, ctx, monkeypatch, kind, k):
+    """Top-k lists with the filter equal, bit for bit in FP32 and in offsets
+    and reported rho in FP64, the lists without it: templates of one and
+    several LDS passes, of four digits, with windows of more than one exact box
+    of squares and as large as the frame; frames whose candidates are few, all
+    equal, too many, or of nearly uniform windows."""
+    M, N = 420, 330
+    frames = _frames(kind, M, N)
+    rng = np.random.default_rng(11)
+    scene = synth.scene(8, M, N)
+    segs, W, H = [], [], []
+    for w, h, sigma in ((9, 11, 3), (40, 37, 2), (64, 150, 2), (300, 250, 8), (33, 8, 4),
+                        (M, N, 20), (30, 31, 0.7)):
+        y, x = int(rng.integers(0, N - h + 1)), int(rng.integers(0, M - w + 1))
+        t = frames[0][y:y + h, x:x + w].astype(int) if kind != "uniform" else \
+            scene[y:y + h, x:x + w].astype(int)
+        t = np.clip(t + rng.integers(-9, 10, t.shape), 0, 255)
+        if sigma == 0.7:  # four digits
+            t = 20 + rng.integers(0, 2, t.shape)
+            t[3, 4] = 255
+        if t.std() <= sigma * 1.05:  # no template may be uniform
+            sigma = float(t.std()) * 0.5
+        segs.append(_segments(S, t.astype(np.uint8), sigma))
+        W.append(w)
+        H.append(h)
+    pairs = [(f, t) for f in (1, 0) for t in range(len(segs))]
+    for prec in (S.SNCC_FP32_KAHAN, S.SNCC_FP64):
+        print("case", kind, k, prec, flush=True)
+        got = _lists(S, ctx, monkeypatch, "1", frames, segs, W, H, pairs, k, prec)
+        want = _lists(S, ctx, monkeypatch, "0", frames, segs, W, H, pairs, k, prec)
+        if prec == S.SNCC_FP64 and kind == "lowvar":
+            # sums of a few doubles in another order: the reported floats
+            assert np.allclose(got[..., 2].view(np.float32), want[..., 2].view(np.float32),
+                               rtol=0, atol=1e-6, equal_nan=False) or (got == want).all()
+        else:
+            bad = np.argwhere((got != want).any(axis=(1, 2)))[:, 0]
+            assert bad.size == 0, [(pairs[b], got[b][:3].tolist(), want[b][:3].tolist())
+                                   for b in bad[:3]]
+
+
+def test_fp32_lists_of_both_forms_in_one_call(S, ctx, monkeypatch):
+    """A call by rule (detailed templates filtered, coarse ones not) gives the
+    lists of the segment form."""
+    M, N = 1280, 720
+    f = synth.scene(77, M, N)
+    rng = np.random.default_rng(78)
+    segs, W, H = [], [], []
+    for w, h, sigma in ((64, 64, 3), (128, 96, 16), (90, 31, 4), (150, 140, 12), (20, 24, 2)):
+        t, _, _ = synth.crop_template(rng, f, w, h, sigma_max=sigma)
+        a, _, _ = S.sncc_segment_template(t, sigma)
+        segs.append(a)
+        W.append(w)
+        H.append(h)
+    pairs = [(0, t) for t in range(5)]
+    for k in (1, 10):
+        print("case", k, flush=True)
+        got = _lists(S, ctx, monkeypatch, "", [f], segs, W, H, pairs, k, S.SNCC_FP32_KAHAN)
+        want = _lists(S, ctx, monkeypatch, "0", [f], segs, W, H, pairs, k, S.SNCC_FP32_KAHAN)
+        assert (got == want).all()
