@@ -170,6 +170,8 @@ struct sncc_ctx {
 // A template's operands of one matrix-core form (FP32 or FP64;
 // dense_kernel.hip), built at the first call that uses them and kept with the
 // template set.
+constexpr int kDenseForms = 4;
+int dense_form(int digits) { return digits == 7 ? 3 : digits - 2; }
 struct DenseTmpl {
   const void *frag = nullptr;  // nullptr: not built
   int digits = 0;
@@ -182,7 +184,10 @@ struct sncc_tmpl {
   uint64_t serial = 0;  // unique per uploaded set (plan cache key)
   int T = 0;
   std::vector<int> W, H, K, seg_off;
-  std::vector<int> digits32;  // fixed-point digits of the FP32 matrix-core form
+  // fixed-point digits of the FP32 matrix-core form and of the filter (0: none
+  // is close enough), and the filter's error bound
+  std::vector<int> digits32, digits_f;
+  std::vector<float> error_f;
   std::vector<std::vector<Seg>> segs;
   std::vector<std::vector<double>> c64;
   std::vector<double> q_k, r64;
@@ -190,7 +195,7 @@ struct sncc_tmpl {
   DevBuf d_geom, d_c64, d_area, d_dev, d_c32;
   // built on demand by calls that take the set as const, from any thread
   mutable std::mutex dense_mu;
-  mutable std::unique_ptr<DenseTmpl[]> dense;  // FP32 and FP64 form of each template
+  mutable std::unique_ptr<DenseTmpl[]> dense;  // kDenseForms per template (dense_form)
   mutable std::vector<std::unique_ptr<DevBuf>> dense_bufs;
   mutable size_t dense_bytes = 0;
 };
@@ -1103,9 +1108,9 @@ int dense_forced() {
 // Fixed point for template t's c with `digits` balanced base-256 digits: the
 // largest scale 2^e they hold (127 in every digit: 0.498 256^digits), and the
 // sum of the image dense_paint makes.  Returns the rounding's bound on |rho|,
-// sqrt(sum of squared rounding errors / q_k) (Cauchy-Schwarz; a pixel of
-// segment i is off by f or 1 - f units, f the fraction of 2^e c_i, in shares
-// that make the sum right: f (1 - f) on average).
+// sqrt(sum of squared rounding errors / q_k) (Cauchy-Schwarz; with f the
+// fraction of 2^e c_i, rint(f A_i) pixels of segment i are off by 1 - f units
+// and the others by f).
 double dense_fixed_point(const sncc_tmpl *tm, int t, int digits, DenseTmpl &dt) {
   const std::vector<double> &c = tm->c64[t];
   double top = 0;
@@ -1119,8 +1124,9 @@ double dense_fixed_point(const sncc_tmpl *tm, int t, int digits, DenseTmpl &dt) 
   for (size_t i = 0; i < c.size(); ++i) {
     const double q = c[i] * dt.scale, whole = std::rint(q), part = q - whole;
     const double area = (double)tm->segs[t][i].area;
-    sum += (__int128)(long long)whole * tm->segs[t][i].area + std::llrint(part * area);
-    err += area * std::fabs(part) * (1.0 - std::fabs(part));
+    const double up = std::rint(part * area), f = std::fabs(part), m = std::fabs(up);
+    sum += (__int128)(long long)whole * tm->segs[t][i].area + (long long)up;
+    err += m * (1.0 - f) * (1.0 - f) + (area - m) * f * f;
   }
   dt.csum = (double)sum;
   return std::sqrt(err / tm->q_k[t]) / dt.scale;
@@ -1134,11 +1140,23 @@ int dense_digits32(const sncc_tmpl *tm, int t) {
   return dense_fixed_point(tm, t, 3, d) <= std::ldexp(1.0, -22) ? 3 : 4;
 }
 
+// Digits of the filter's form, whose values only choose the candidates: two
+// where the bound is at most 2^-12, else three where that is, else 0.
+int dense_digits_filter(const sncc_tmpl *tm, int t, float *error) {
+  DenseTmpl d;
+  for (int digits = 2; digits <= 3; ++digits) {
+    const double e = dense_fixed_point(tm, t, digits, d);
+    *error = (float)(e * 1.0001);
+    if (e <= std::ldexp(1.0, -12)) return digits;
+  }
+  return 0;
+}
+
 // Template t's operands of `digits` digits, or nullptr where not built.
 const DenseTmpl *dense_built(const sncc_tmpl *tm, int t, int digits) {
   std::lock_guard<std::mutex> lk(tm->dense_mu);
   if (!tm->dense) return nullptr;
-  const DenseTmpl &dt = tm->dense[2 * (size_t)t + (digits == kDenseDigits)];
+  const DenseTmpl &dt = tm->dense[kDenseForms * (size_t)t + dense_form(digits)];
   return dt.frag ? &dt : nullptr;
 }
 
@@ -1148,7 +1166,7 @@ const DenseTmpl *dense_built(const sncc_tmpl *tm, int t, int digits) {
 // being captured) they stay unbuilt, and callers take another form.
 void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair<int, int>> &want) {
   std::lock_guard<std::mutex> lk(tm->dense_mu);
-  if (!tm->dense) tm->dense.reset(new (std::nothrow) DenseTmpl[2 * (size_t)tm->T]);
+  if (!tm->dense) tm->dense.reset(new (std::nothrow) DenseTmpl[kDenseForms * (size_t)tm->T]);
   if (!tm->dense) return;
   struct Job {
     DenseTmpl *dt;
@@ -1159,7 +1177,7 @@ void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair
   std::vector<Job> jobs;
   size_t bytes = 0, image = 0;  // the fixed-point image is reused, in stream order
   for (const auto &w : want) {
-    DenseTmpl *dt = &tm->dense[2 * (size_t)w.first + (w.second == kDenseDigits)];
+    DenseTmpl *dt = &tm->dense[kDenseForms * (size_t)w.first + dense_form(w.second)];
     bool listed = dt->frag != nullptr;
     for (const Job &j : jobs) listed |= j.dt == dt;
     if (listed) continue;
@@ -1346,8 +1364,8 @@ std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N,
       DenseArgs a{};
       const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
       tmpl[t] = 2;
-      if (forced != 0 &&
-          dense_shape(tm, t, tm->digits32[t], nu, nv, ctx->num_cu, a, tm->digits32[t] == 3 ? 8 : 4)) {
+      if (forced != 0 && tm->digits_f[t] &&
+          dense_shape(tm, t, tm->digits_f[t], nu, nv, ctx->num_cu, a, 8)) {
         gain[t] = (fp64 ? cost_plain(tm, t) : cost_tile(tm, t)) -
                   (8.0 + 0.8e-3 * a.digits * dense_macs(a));
         if (forced == 1 || gain[t] > 0) tmpl[t] = 1;
@@ -1369,7 +1387,7 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
                  std::vector<char> &use, FilterPlan &f) {
   std::vector<std::pair<int, int>> want;
   for (int p = 0; p < n_pairs; ++p)
-    if (use[p]) want.emplace_back(pairs[2 * p + 1], tm->digits32[pairs[2 * p + 1]]);
+    if (use[p]) want.emplace_back(pairs[2 * p + 1], tm->digits_f[pairs[2 * p + 1]]);
   std::sort(want.begin(), want.end());
   want.erase(std::unique(want.begin(), want.end()), want.end());
   if (!want.empty()) dense_build(ctx, tm, want);
@@ -1382,10 +1400,10 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
   for (int p = 0; p < n_pairs; ++p) {
     const int t = pairs[2 * p + 1];
     const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
-    if (use[p] && !dense_built(tm, t, tm->digits32[t])) use[p] = 0;
+    if (use[p] && !dense_built(tm, t, tm->digits_f[t])) use[p] = 0;
     if (use[p]) {
       idx.push_back(p);
-      cost[p] = (double)tm->H[t] * dense_groups(tm->W[t]) * tm->digits32[t];
+      cost[p] = (double)tm->H[t] * dense_groups(tm->W[t]) * tm->digits_f[t];
       if (!fp64 && seq0[t] < 0) {
         seq0[t] = (int)f.seq.size();
         n_seq[t] = seq_records(*tile, t, P, f.seq);
@@ -1437,14 +1455,14 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
       floats += n;
       tiles8 += (long long)((q.nu + 127) / 128) * ((q.nv + 63) / 64);
     }
-    const int rv3 = tiles8 >= 2LL * ctx->num_cu ? 8 : 2 * tiles8 >= ctx->num_cu ? 4 : 2;
+    const int rv = tiles8 >= 2LL * ctx->num_cu ? 8 : 2 * tiles8 >= ctx->num_cu ? 4 : 2;
     size_t floats = 0;
     int blocks = 0;
-    for (int digits = 3; digits <= 4; ++digits) {
-      FilterLaunch l{digits, digits == 3 ? rv3 : std::min(rv3, 4), (int)f.items.size(), 0, 0};
+    for (int digits = 2; digits <= 3; ++digits) {
+      FilterLaunch l{digits, rv, (int)f.items.size(), 0, 0};
       for (size_t j = i; j < e; ++j) {
         const int p = idx[j], t = pairs[2 * p + 1];
-        if (tm->digits32[t] != digits) continue;
+        if (tm->digits_f[t] != digits) continue;
         FilterPair fp{};
         fp.pair = p;
         fp.frame = pairs[2 * p];
@@ -1463,6 +1481,7 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
         fp.seg_off = f.pairs[p].seg_off;
         fp.K = f.pairs[p].K;
         fp.r64 = f.pairs[p].r64;
+        fp.error = tm->error_f[t];
         floats += (size_t)fp.n_blocks * l.rv * 256;
         blocks += fp.n_blocks;
         l.lds = std::max(l.lds, (2 * kDenseNW * l.rv + fp.a.hb - 1) * fp.a.pitch);
@@ -1812,7 +1831,12 @@ int sncc_upload_templates(sncc_ctx *ctx, int T, const sncc_segment *const *segs,
   std::vector<double> c64all;
   std::vector<int> areas;
   CHK(fill_templates(tm.get(), T, segs, K, W, H, geom, c64all, areas));
-  for (int t = 0; t < T; ++t) tm->digits32.push_back(dense_digits32(tm.get(), t));
+  for (int t = 0; t < T; ++t) {
+    float error = 0.f;
+    tm->digits32.push_back(dense_digits32(tm.get(), t));
+    tm->digits_f.push_back(dense_digits_filter(tm.get(), t, &error));
+    tm->error_f.push_back(error);
+  }
   std::vector<float> c32all(c64all.begin(), c64all.end());
   CHK(tm->d_geom.upload(geom, ctx->stream));
   CHK(tm->d_c64.upload(c64all, ctx->stream));

@@ -98,6 +98,7 @@ int launch_dense_pack(const int4 *geom, const double *c64, int K, double scale, 
   const dim3 grid(dense_steps(W, H));
   v4i *o = static_cast<v4i *>(frag);
   switch (digits) {
+    case 2: hipLaunchKernelGGL(dense_pack<2>, grid, dim3(64), 0, st, img, W, H, o); break;
     case 3: hipLaunchKernelGGL(dense_pack<3>, grid, dim3(64), 0, st, img, W, H, o); break;
     case 4: hipLaunchKernelGGL(dense_pack<4>, grid, dim3(64), 0, st, img, W, H, o); break;
     default: hipLaunchKernelGGL(dense_pack<7>, grid, dim3(64), 0, st, img, W, H, o); break;
@@ -330,8 +331,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   }
 }
 
-// The filter of the top-k search (topk_filter.hip): FP32 rho of many pairs in
-// one launch, one workgroup per item {pair, tile} (pair -1: none).  A wave
+// The filter of the top-k search (topk_filter.hip): rho of many pairs in
+// one launch, from two digits of c (its values only choose which offsets are
+// scored again; three digits where two would leave a bound above 2^-12), one workgroup per item {pair, tile} (pair -1: none).  A wave
 // writes its RV x 64 x 4 values as they lie in its lanes (offsets past the
 // valid range as -inf), and its block's largest rho; offsets whose window is
 // nearly uniform (energy below n / 100, where the segment form's FP32 error
@@ -436,11 +438,12 @@ int launch_dense_filter(int digits, int rv, const uint32_t *s, const uint32_t *s
 #define SNCC_FILTER(D, RV) \
   case D * 100 + RV:       \
     return filter_go<D, RV, kDenseNW>(s, s2, frame_stride, fps, items, n_items, lds, map, bmax, st)
+    SNCC_FILTER(2, 8);
+    SNCC_FILTER(2, 4);
+    SNCC_FILTER(2, 2);
     SNCC_FILTER(3, 8);
     SNCC_FILTER(3, 4);
     SNCC_FILTER(3, 2);
-    SNCC_FILTER(4, 4);
-    SNCC_FILTER(4, 2);
 #undef SNCC_FILTER
     default: return -1;
   }

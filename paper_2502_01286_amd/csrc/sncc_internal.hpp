@@ -280,7 +280,7 @@ constexpr int kFusedBV = kFusedRV * kFusedNW;  // offset rows per tile
 
 // Matrix-core form (dense_kernel.hip): the numerator as a correlation with the
 // approximation's image in fixed-point digits.
-constexpr int kDenseDigits = 7;        // digits of the FP64 form (FP32: 3 or 4)
+constexpr int kDenseDigits = 7;        // digits of the FP64 form (FP32: 3 or 4, filter: 2)
 constexpr int kDenseNW = 4;            // waves per workgroup
 constexpr int kDenseBU = 128;          // offset columns per tile
 constexpr int kDenseMaxArea = 131071;  // n 2^14 < 2^31: a digit's sum fits 32 bits
@@ -303,7 +303,7 @@ struct DenseArgs {
   int hb;                  // template rows per pass (a multiple of 8)
   int pitch;               // LDS bytes per staged row, at least 112 + 16 G
   int ntu, ntv;
-  int digits;              // 3 or 4 (FP32 map), 7 (FP64 map)
+  int digits;              // 3 or 4 (FP32 map), 7 (FP64 map), 2 or 3 (filter)
   int rv;                  // offset rows per wave half: tiles of 8 rv rows
   double csum;             // sum over the template of the digits' values
   double inv_scale;        // value of one unit of the last digit
@@ -322,6 +322,7 @@ struct FilterPair {
   int seq0, n_seq;         // FP32: records of the segment form's sum (SeqRec)
   int seg_off, K;          // FP64: the segments
   double r64;
+  float error;             // bound on |filter - exact| from its rounded c
 };
 
 // One boundary column of the FP32 segment form's chains in its order of

@@ -61,51 +61,6 @@ __device__ __forceinline__ void ref_step(float &acc, float &cmp, float &y) {
   y = -cmp;
 }
 
-// rho of one offset by a whole wave, FP32: lanes take 64 records' column
-// differences and products' factors at a time (the next 64 requested before
-// these are summed), then the wave adds them in order.
-__device__ __forceinline__ float wave_ref32(const uint32_t *__restrict__ S,
-                                            const uint32_t *__restrict__ S2, int P, int u, int v,
-                                            const FilterPair &fp, const SeqRec *__restrict__ seq,
-                                            int lane) {
-  const Ref32 rf = ref32(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.n, fp.a.sq_rows, fp.a.q_k);
-  const char *w = reinterpret_cast<const char *>(S + (long long)v * P + u);
-  float acc = 0.f, cmp = 0.f, y = -cmp;
-  uint32_t carry = 0;
-  const SeqRec *sr = seq + fp.seq0;
-  auto load = [&](int i, SeqRec &e, uint32_t &D) {
-    e = SeqRec{0, 0, kSeqFirst, 0.f};
-    if (i < fp.n_seq) e = sr[i];
-    D = *reinterpret_cast<const uint32_t *>(w + e.bot) -
-        *reinterpret_cast<const uint32_t *>(w + e.top);
-  };
-  SeqRec e, en;
-  uint32_t D, Dn;
-  load(lane, e, D);
-  for (int i = 0; i < fp.n_seq; i += 64) {
-    if (i + 64 < fp.n_seq) load(i + 64 + lane, en, Dn);
-    uint32_t prev = (uint32_t)__shfl_up((int)D, 1);
-    if (lane == 0) prev = carry;
-    carry = (uint32_t)__builtin_amdgcn_readlane((int)D, 63);
-    const uint32_t F = D - prev;  // Eq. (11)
-    const int G = (int)F + __mul24((int)(e.area_flags & kSeqArea), rf.nb);
-    const float g = (float)G;
-    u64 use = __ballot((e.area_flags & kSeqFirst) == 0);
-    const u64 end = __ballot((e.area_flags & kSeqEnd) != 0);
-    while (use) {
-      const int l = __ffsll((long long)use) - 1;
-      use &= use - 1;
-      const float gl = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(g), l));
-      const float cl = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(e.c), l));
-      y = __builtin_fmaf(gl, cl, y);
-      if ((end >> l) & 1) ref_step(acc, cmp, y);
-    }
-    e = en;
-    D = Dn;
-  }
-  return (acc - cmp) * rf.scale;
-}
-
 // rho of one offset by a whole wave, FP64: box sums less A_i b (b the window
 // mean rounded to an integer) in integers, c_i times them summed over the lanes
 // and then the wave, and the mean term of Eq. (12) for what b leaves.
@@ -133,6 +88,8 @@ __device__ __forceinline__ double wave_ref64(const uint32_t *__restrict__ S,
 
 // ----------------------------------------------------------------- selection
 constexpr int kSelThreads = 1024;
+constexpr int kRefGroup = kSelThreads / 64 - 1;  // candidates scored at a time in FP32
+constexpr int kRefChunk = 256;                   // records per step of them
 constexpr int kSelBins = 2048;
 constexpr int kSelBlocks = 2048;
 
@@ -176,6 +133,11 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   __shared__ int cand[kFilterCands];
   __shared__ u64 key_hi[kFilterCands];
   __shared__ uint32_t key_lo[F64 ? kFilterCands : 1];
+  // FP32: terms of the candidates, their c and whether a step ends, twice
+  __shared__ float gbuf[F64 ? 1 : 2][F64 ? 1 : kRefGroup][kRefChunk + 9];
+  __shared__ float2 cbuf[F64 ? 1 : 2][kRefChunk + 8];
+  __shared__ float gscale[kRefGroup];
+  __shared__ int terms[2];
   __shared__ int n_list, n_cand, bin, bad;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -183,10 +145,11 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   const int nb = fp.n_blocks, rv = fp.a.rv, nu = fp.a.nu;
   const float2 *bm = bmax + fp.block0;
   const float *vals = map + fp.map0;
-  // twice the errors of the filter (2^-22 + 2^-24) and of the reference (FP32:
-  // at most 3e-6 for windows of energy n / 100 and above, 1e-4 for any window)
-  constexpr float kMargin = F64 ? 1e-6f : 8e-6f;
-  constexpr float kLowVar = 2e-4f;
+  // twice the errors of the filter (fp.error: its rounded c, the result's
+  // rounding, 2^-24, and the thresholds' below) and of the reference (FP32: at
+  // most 3e-6 for windows of energy n / 100 and above, 1e-4 for any window)
+  const float margin = 2.f * (fp.error + 2e-7f + (F64 ? 0.f : 3e-6f));
+  const float low_margin = 2.f * (fp.error + 1e-4f);
 
   auto clear = [&]() {
     __syncthreads();
@@ -252,17 +215,17 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   const float T1 = b1 == 0 ? T0 : lo + ((float)b1 - 0.01f) / scale;
   if (tid == 0 && n_list > kSelBlocks) bad = 1;
   clear();
-  blocks_from(T1 - kMargin);
+  blocks_from(T1 - margin);
   if (tid == 0 && n_list > kSelBlocks) bad = 1;
   for (int i = tid; i < nb; i += kSelThreads)
-    if (bm[i].y + kLowVar >= T1) bad = 1;
+    if (bm[i].y + low_margin >= T1) bad = 1;
   scan([&](float x, int idx) {
-    if (x >= T1 - kMargin) {
+    if (x >= T1 - margin) {
       const int at = atomicAdd(&n_cand, 1);
       if (at < kFilterCands) cand[at] = idx;
     }
   });
-  const int n = n_cand;
+  int n = n_cand;
   if (bad || n > kFilterCands) {
     if (tid == 0) direct[fp.pair] = 1;
     return;
@@ -270,18 +233,130 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   // the candidates by the reference arithmetic, one wave each
   const uint32_t *S = s + (long long)fp.frame * frame_stride;
   const uint32_t *S2 = s2 + (long long)fp.frame * frame_stride;
-  for (int c = wave; c < n; c += kSelThreads / 64) {
-    const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
-    const int v = idx / nu, u = idx - v * nu;
-    if constexpr (F64) {
+  if constexpr (F64) {
+    for (int c = wave; c < n; c += kSelThreads / 64) {
+      const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
+      const int v = idx / nu, u = idx - v * nu;
       const double r = wave_ref64(S, S2, P, u, v, fp, geom, c64, lane);
       if (lane == 0) {
         key_hi[c] = double_order(r);
         key_lo[c] = 0xffffffffu - (uint32_t)idx;
       }
-    } else {
-      const float r = wave_ref32(S, S2, P, u, v, fp, seq, lane);
-      if (lane == 0) key_hi[c] = make_key(r, idx);
+    }
+  } else {
+    // FP32: the accurate values first (FP64, lanes over the segments) leave
+    // few more than k candidates, those within twice the reference's error of
+    // the k-th largest
+    for (int c = wave; c < n; c += kSelThreads / 64) {
+      const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
+      const int v = idx / nu, u = idx - v * nu;
+      const double r = wave_ref64(S, S2, P, u, v, fp, geom, c64, lane);
+      if (lane == 0) key_hi[c] = make_key((float)r, idx);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      u64 lk = 0;
+      for (int c = 0; c < n; c += 64)
+        topk_merge_sorted(lk, wave_sort_desc_u64(c + lane < n ? key_hi[c + lane] : 0, lane), k,
+                          lane);
+      const u64 kth = lane_u64(lk, k - 1);
+      const float t = kth == 0 ? -__builtin_inff()
+                               : float_unorder((uint32_t)(kth >> 32)) - 2.f * (3e-6f + 1e-7f);
+      int m = 0;
+      for (int c = 0; c < n; c += 64) {
+        const u64 key = c + lane < n ? key_hi[c + lane] : 0;
+        const u64 keep = __ballot(key != 0 && float_unorder((uint32_t)(key >> 32)) >= t);
+        if ((keep >> lane) & 1)
+          cand[m + __popcll(keep & ((1ull << lane) - 1))] =
+              (int)(0xffffffffu - (uint32_t)(key & 0xffffffffu));
+        m += __popcll(keep);
+      }
+      if (lane == 0) n_cand = m;
+    }
+    __syncthreads();
+    n = n_cand;
+    // the terms are added in the segment form's order, a chain of one addition
+    // after the other.  Waves 0 .. 14 take a candidate each and form its terms
+    // G_i = F_i - A_i b, a lane per record, kRefChunk records ahead; the last
+    // wave adds them, a lane per candidate
+    const SeqRec *sr = seq + fp.seq0;
+    const int n_seq = fp.n_seq;
+    for (int c0 = 0; c0 < n; c0 += kRefGroup) {
+      const bool mine = wave < kRefGroup && c0 + wave < n;  // wave 0's always is
+      const uint32_t *w = S;
+      int nb0 = 0;
+      if (mine) {
+        const int idx = __builtin_amdgcn_readfirstlane(cand[c0 + wave]);
+        const int v = idx / nu, u = idx - v * nu;
+        const Ref32 rf = ref32(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.n, fp.a.sq_rows, fp.a.q_k);
+        nb0 = rf.nb;
+        w = S + (long long)v * P + u;
+        if (lane == 0) gscale[wave] = rf.scale;
+      }
+      uint32_t carry = 0;
+      auto produce = [&](int base, int buf) {
+        constexpr int Q = kRefChunk / 64;
+        SeqRec e[Q];
+        uint32_t D[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const int i = base + 64 * q + lane;
+          e[q] = SeqRec{0, 0, kSeqFirst, 0.f};
+          if (i < n_seq) e[q] = sr[i];
+        }
+        const char *wb = reinterpret_cast<const char *>(w);
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+          D[q] = *reinterpret_cast<const uint32_t *>(wb + e[q].bot) -
+                 *reinterpret_cast<const uint32_t *>(wb + e[q].top);
+        int at = 0;  // terms so far (records that start a chain have none)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          uint32_t prev = (uint32_t)__shfl_up((int)D[q], 1);
+          if (lane == 0) prev = carry;
+          carry = (uint32_t)__builtin_amdgcn_readlane((int)D[q], 63);
+          const int G = (int)(D[q] - prev) + __mul24((int)(e[q].area_flags & kSeqArea), nb0);
+          const bool term = (e[q].area_flags & kSeqFirst) == 0;
+          const u64 m = __ballot(term);
+          const int j = at + __popcll(m & ((1ull << lane) - 1));
+          if (term) {
+            gbuf[buf][wave][j] = (float)G;
+            if (wave == 0) cbuf[buf][j] = make_float2(e[q].c, e[q].area_flags & kSeqEnd ? 1.f : 0.f);
+          }
+          at += __popcll(m);
+        }
+        if (wave == 0 && lane == 0) terms[buf] = at;
+      };
+      if (mine) produce(0, 0);
+      float acc = 0.f, cmp = 0.f, y = -cmp;
+      __syncthreads();
+      for (int base = 0, buf = 0; base < n_seq; base += kRefChunk, buf ^= 1) {
+        if (wave == kRefGroup) {
+          const float *gl = gbuf[buf][min(lane, kRefGroup - 1)];
+          const int m = __builtin_amdgcn_readfirstlane(terms[buf]);
+          for (int l = 0; l < m; l += 8) {  // the chunk's end is padded: entries past m unused
+            float gq[8];
+            float2 cq[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              gq[q] = gl[l + q];
+              cq[q] = cbuf[buf][l + q];
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              if (l + q >= m) break;
+              y = __builtin_fmaf(gq[q], cq[q].x, y);
+              if (__builtin_amdgcn_readfirstlane(__float_as_int(cq[q].y))) ref_step(acc, cmp, y);
+            }
+          }
+        } else if (mine && base + kRefChunk < n_seq) {
+          produce(base + kRefChunk, buf ^ 1);
+        }
+        __syncthreads();
+      }
+      if (wave == kRefGroup && lane < kRefGroup && c0 + lane < n)
+        key_hi[c0 + lane] = make_key((acc - cmp) * gscale[lane], cand[c0 + lane]);
+      __syncthreads();
     }
   }
   __syncthreads();
