@@ -1219,7 +1219,7 @@ void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair
 // Launch shape of the matrix-core form for a map of nu x nv offsets: false
 // where it does not apply.  Rows per wave half: eight where the tiles then
 // still fill the CUs twice (FP32; 3840 x 2160, 128 x 128: 309 us against 343
-// with four and 493 with two), else four while they fill them once (1920 x
+// with four and 493 with two when this was chosen), else four while they fill them once (1920 x
 // 1080, 64 x 64: 37.7 us, 45.6 with eight, 45.7 with two; FP64, at most four
 // for its 28 accumulators a row: while they fill 5/8), else two (640 x 480, 32
 // x 32: 10.6 us, 15.7 with four); for several pairs in one launch, as given (rv).

@@ -14,10 +14,10 @@
 // an FP64 map 0 to 1e-14 (0 to 1e-13 in the plain form).
 //
 // What bounds it: large templates the matrix rate (3840 x 2160, 128 x 128,
-// K 4465: 309 us, 2.7e15 operations/s, where a loop of these instructions alone
-// reaches 3.4e15 on random data; the segment form took 6678 us; FP64 645 us,
-// 3.0e15/s, against 16.0 ms in the plain form), small ones the launch, the
-// staging and the epilogue's table reads (1920 x 1080, 64 x 64: 37.7 us, about
+// K 4465: 280 us, 3.0e15 operations/s, where a loop of these instructions alone
+// reaches 3.4e15 on random data; the segment form took 6678 us; FP64 620 us,
+// 3.2e15/s, against 16.0 ms in the plain form), small ones the launch, the
+// staging and the epilogue's table reads (1920 x 1080, 64 x 64: 36 us, about
 // half of it matrix work).
 //
 // Contraction: one instruction multiplies A (16 x 64) by B (64 x 16).  Column
@@ -41,6 +41,10 @@
 namespace sncc {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+// Operands in global memory, said so: through a generic pointer (one read from
+// a descriptor) they would be flat loads, which count as LDS reads too, and
+// every step would wait for all of both.
+typedef const __attribute__((address_space(1))) v4i *frag_ptr;
 typedef uint32_t v4u_a4 __attribute__((ext_vector_type(4), aligned(4)));  // any word address
 
 // ------------------------------------------------------------- preparation
@@ -110,10 +114,10 @@ int launch_dense_pack(const int4 *geom, const double *c64, int K, double scale, 
 // Rows [y0, y0 + rows) x columns [x0, x0 + 4 n4) of the frame to LDS, each
 // pixel as f - 128 in a byte, `pitch` bytes per row.  Pixels come from the sum
 // table: f(x, y) is the one-pixel box sum of Eq. (11).  A thread walks down a
-// stripe of rows with four columns, eight rows of table entries requested at a
-// time.  Table rows past N and entries past the pitch are clamped: only
+// stripe of rows with four columns, RB rows of table entries requested at a
+// time (a stripe is 20 to 40 rows: the staging is a few memory latencies).  Table rows past N and entries past the pitch are clamped: only
 // offsets outside the valid range and zero rows of A use such pixels.
-template <int NT>
+template <int NT, int RB>
 __device__ __forceinline__ void dense_region(const uint32_t *__restrict__ S, int P, int N, int x0,
                                              int y0, int rows, int n4, int pitch,
                                              uint8_t *__restrict__ lds, int t) {
@@ -133,12 +137,12 @@ __device__ __forceinline__ void dense_region(const uint32_t *__restrict__ S, int
     };
     uint32_t up[4];
     row(y0 + ra, up);
-    for (int r = ra; r < rb; r += 8) {
-      uint32_t d[8][4];
+    for (int r = ra; r < rb; r += RB) {
+      uint32_t d[RB][4];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) row(y0 + min(r + k, rb - 1) + 1, d[k]);
+      for (int k = 0; k < RB; ++k) row(y0 + min(r + k, rb - 1) + 1, d[k]);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
+      for (int k = 0; k < RB; ++k) {
         if (r + k < rb) {
           const uint32_t px = (d[k][0] - up[0]) | (d[k][1] - up[1]) << 8 |
                               (d[k][2] - up[2]) << 16 | (d[k][3] - up[3]) << 24;
@@ -171,7 +175,7 @@ __device__ __forceinline__ v4u_a4 dense_row4(const uint32_t *__restrict__ p, int
 // and min(RV, 4) operands B (LDS) for D RV instructions.
 template <int D, int RV, int NW>
 __device__ __forceinline__ void dense_products(const uint32_t *__restrict__ S,
-                                               const v4i *__restrict__ frag, const DenseArgs &a,
+                                               frag_ptr frag, const DenseArgs &a,
                                                int u0, int v0, int row0, uint8_t *lds8, int lane,
                                                v4i (&acc)[RV][D]) {
   constexpr int BV = 2 * NW * RV;
@@ -185,17 +189,18 @@ __device__ __forceinline__ void dense_products(const uint32_t *__restrict__ S,
   // rows 4 y .. 4 y + 3), two register sets: with eight rows per wave a step
   // uses both (rows 0-3, 4-7) and the first is the next step's second; with
   // fewer the second holds the next step's.  A set is reloaded as soon as its
-  // last use is issued, A's two sets likewise one step ahead.
+  // last use is issued, A's two sets one step ahead (requested before the step
+  // they are not used in, so that waiting for one leaves the other in flight).
   constexpr int NB = RV < 4 ? RV : 4;
   const int G = a.G, pitch = a.pitch, n4all = dense_rows4(a.H), hb4 = a.hb >> 2;
   for (int yp4 = 0; yp4 < n4all; yp4 += hb4) {
     const int n4 = min(hb4, n4all - yp4);
     if (yp4) __syncthreads();
-    dense_region<64 * NW>(S, a.P, a.N, u0, v0 + 4 * yp4, BV + 4 * n4 - 1, 28 + 4 * G, pitch, lds8,
+    dense_region<64 * NW, RV >= 8 ? 16 : 8>(S, a.P, a.N, u0, v0 + 4 * yp4, BV + 4 * n4 - 1, 28 + 4 * G, pitch, lds8,
                           threadIdx.x);
     __syncthreads();
     // A of the pass's steps in order, the last one's again after it
-    const v4i *fa = frag + (long long)yp4 * (D * 64) + lane;
+    frag_ptr fa = frag + (long long)yp4 * (D * 64) + lane;
     int ax = 0, ay = 0;
     auto load_A = [&](v4i(&A)[D]) {
 #pragma unroll
@@ -207,7 +212,6 @@ __device__ __forceinline__ void dense_products(const uint32_t *__restrict__ S,
     };
     v4i A0[D], A1[D], b0[NB], b1[NB];
     load_A(A0);
-    load_A(A1);
     const uint8_t *base = lds8 + (row0 + g) * pitch + 16 * j;
     for (int x = 0; x < G; ++x, base += 16) {
       auto load_B = [&](int y, v4i(&b)[NB]) {
@@ -227,6 +231,7 @@ __device__ __forceinline__ void dense_products(const uint32_t *__restrict__ S,
       load_B(1, b1);
       for (int y = 0; y < n4; y += 2) {
         const bool more = y + 2 < n4;
+        load_A(A1);
         mul(A0, b0, 0);
         if (RV > 4 || more) load_B(y + 2, b0);
         if constexpr (RV > 4) mul(A0, b1, 4);
@@ -234,32 +239,80 @@ __device__ __forceinline__ void dense_products(const uint32_t *__restrict__ S,
         mul(A1, b1, 0);
         if (more) load_B(y + 3, b1);
         if constexpr (RV > 4) mul(A1, b0, 4);
-        load_A(A1);
       }
     }
   }
 }
 
-// Window sums of f (Eq. (13)) and the exact window energies V = n Eq. (16) of
-// four consecutive offsets (u, v), as in the other forms.
-__device__ __forceinline__ void dense_energy4(const uint32_t *__restrict__ S,
+// Calls f(r, sum f (Eq. (13)), V as double) for the lane's rows v0 + r, four
+// consecutive offsets from column u each; V is the exact window energy (n
+// times Eq. (16), an integer below 2^53 where the window is one exact box of
+// squares).  Away from the table's right edge, and for such windows, all eight
+// corner loads of a row are 16 bytes at any word address; with eight rows per
+// wave half (two waves a SIMD in any case) the next row's are requested before
+// this one's are used.
+template <int RV, class F>
+__device__ __forceinline__ void dense_windows(const uint32_t *__restrict__ S,
                                               const uint32_t *__restrict__ S2, const DenseArgs &a,
-                                              int u, int v, v4u_a4 &sf, long long (&V)[4]) {
-  const uint32_t *t0 = S + (long long)v * a.P, *t1 = t0 + (long long)a.H * a.P;
-  sf = (dense_row4(t1, u + a.W, a.P) - dense_row4(t1, u, a.P)) -
-       (dense_row4(t0, u + a.W, a.P) - dense_row4(t0, u, a.P));
-  u64 sf2[4] = {0, 0, 0, 0};
-  for (int y = 0; y < a.H; y += a.sq_rows) {  // Eq. (15), in exact boxes
-    const uint32_t *q0 = S2 + (long long)(v + y) * a.P;
-    const uint32_t *q1 = q0 + (long long)min(a.sq_rows, a.H - y) * a.P;
-    const v4u_a4 b = (dense_row4(q1, u + a.W, a.P) - dense_row4(q1, u, a.P)) -
-                     (dense_row4(q0, u + a.W, a.P) - dense_row4(q0, u, a.P));
+                                              int u0, int u, int v0, F f) {
+  const int uc = min(u, a.nu - 1);
+  const double n = (double)a.n;
+  if (u0 + kDenseBU + 3 + a.W <= a.P && a.sq_rows >= a.H) {
+    constexpr bool AHEAD = RV >= 8;
+    v4u_a4 c[2][8];
+    const long long down = (long long)a.H * a.P;
+    auto load = [&](int r, v4u_a4(&q)[8]) {
+      const long long o = (long long)min(v0 + r, a.nv - 1) * a.P + uc;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) sf2[k] += b[k];
+      for (int t = 0; t < 2; ++t) {
+        const uint32_t *p = (t ? S2 : S) + o;
+        q[4 * t] = *reinterpret_cast<const v4u_a4 *>(p);
+        q[4 * t + 1] = *reinterpret_cast<const v4u_a4 *>(p + a.W);
+        q[4 * t + 2] = *reinterpret_cast<const v4u_a4 *>(p + down);
+        q[4 * t + 3] = *reinterpret_cast<const v4u_a4 *>(p + down + a.W);
+      }
+    };
+    if (AHEAD) load(0, c[0]);
+#pragma unroll
+    for (int r = 0; r < RV; ++r) {
+      if (!AHEAD) load(r, c[r & 1]);
+      if (AHEAD && r + 1 < RV) load(r + 1, c[(r + 1) & 1]);
+      if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+      const v4u_a4(&q)[8] = c[r & 1];
+      const v4u_a4 sf = (q[3] - q[2]) - (q[1] - q[0]), sf2 = (q[7] - q[6]) - (q[5] - q[4]);
+      double V[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const double fs = (double)sf[k];
+        V[k] = __builtin_fma(n, (double)sf2[k], -(fs * fs));
+      }
+      f(r, sf, V);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    return;
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k)
-    V[k] = (long long)((u64)(uint32_t)a.n * sf2[k] - (u64)sf[k] * sf[k]);
+  for (int r = 0; r < RV; ++r) {
+    const int v = min(v0 + r, a.nv - 1);
+    const uint32_t *t0 = S + (long long)v * a.P, *t1 = t0 + (long long)a.H * a.P;
+    const v4u_a4 sf = (dense_row4(t1, uc + a.W, a.P) - dense_row4(t1, uc, a.P)) -
+                      (dense_row4(t0, uc + a.W, a.P) - dense_row4(t0, uc, a.P));
+    u64 sf2[4] = {0, 0, 0, 0};
+    for (int y = 0; y < a.H; y += a.sq_rows) {  // Eq. (15), in exact boxes
+      const uint32_t *q0 = S2 + (long long)(v + y) * a.P;
+      const uint32_t *q1 = q0 + (long long)min(a.sq_rows, a.H - y) * a.P;
+      const v4u_a4 b = (dense_row4(q1, uc + a.W, a.P) - dense_row4(q1, uc, a.P)) -
+                       (dense_row4(q0, uc + a.W, a.P) - dense_row4(q0, uc, a.P));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) sf2[k] += b[k];
+    }
+    double V[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      V[k] = (double)(long long)((u64)(uint32_t)a.n * sf2[k] - (u64)sf[k] * sf[k]);
+    f(r, sf, V);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
 // Numerator of Eq. (12) from a lane's digit sums: their value less the digits'
@@ -274,27 +327,17 @@ __device__ __forceinline__ double dense_num(const v4i (&acc)[D], int k, uint32_t
                          ((long long)acc[5][k] << 8) + acc[6][k];
     T = __builtin_fma((double)hi, 4294967296.0, (double)lo);
   } else {
-    long long t = acc[0][k];
+    T = (double)acc[0][k];  // below 2^55, sums of digits exact below 2^53
 #pragma unroll
-    for (int d = 1; d < D; ++d) t = (t << 8) + acc[d][k];
-    T = (double)t;
+    for (int d = 1; d < D; ++d) T = __builtin_fma(T, 256.0, (double)acc[d][k]);
   }
   return (T - a.csum * ((double)sf * a.inv_n - 128.0)) * a.inv_scale;
-}
-
-// FP32 rho: 1 / sqrt of the energy in FP64 (the FP32 estimate and one Newton
-// step), rounded once.
-__device__ __forceinline__ float dense_rho32(double num, long long V, double qnd) {
-  const double e = (double)V * qnd;
-  const double y0 = (double)__builtin_amdgcn_rsqf((float)e);
-  const double y1 = y0 * __builtin_fma(-0.5 * e * y0, y0, 1.5);
-  return V == 0 ? 0.f : (float)(num * y1);
 }
 
 template <int D, int RV, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dense_kernel(
     const uint32_t *__restrict__ S, const uint32_t *__restrict__ S2,
-    const v4i *__restrict__ frag, DenseArgs a) {
+    DenseArgs a) {
   extern __shared__ __align__(16) uint8_t lds8[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // tiles row by row, a contiguous range of them per XCD (workgroups go round
@@ -305,39 +348,45 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int tv = tile / a.ntu, u0 = (tile - tv * a.ntu) * kDenseBU, v0 = tv * 2 * NW * RV;
   const int row0 = RV * (2 * wave + ((lane >> 3) & 1));  // the lane's first offset row
   v4i acc[RV][D];
-  dense_products<D, RV, NW>(S, frag, a, u0, v0, row0, lds8, lane, acc);
+  dense_products<D, RV, NW>(S, (frag_ptr)a.frag, a, u0, v0, row0, lds8, lane, acc);
 
   const int u = u0 + 16 * (lane & 7) + 4 * (lane >> 4);
-#pragma unroll
-  for (int r = 0; r < RV; ++r) {
+  dense_windows<RV>(S, S2, a, u0, u, v0 + row0, [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
     const int v = v0 + row0 + r;
-    v4u_a4 sf;
-    long long V[4];
-    dense_energy4(S, S2, a, min(u, a.nu - 1), min(v, a.nv - 1), sf, V);
-    const bool row_ok = v < a.nv;
+    const long long o = (long long)v * a.rho_pitch + u;
+    if (v >= a.nv) return;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const double num = dense_num<D>(acc[r], k, sf[k], a);
-      const long long o = (long long)v * a.rho_pitch + u + k;
-      if (row_ok && u + k < a.nu) {
+      double rho;
+      if constexpr (D == kDenseDigits) {
+        rho = num / sqrt(V[k] / (double)a.n * a.q_k);
+      } else {
+        // 1 / sqrt of the energy in FP64 (the FP32 estimate and one Newton
+        // step), so that the result is rounded once
+        const double e = V[k] * a.qnd, y = (double)__builtin_amdgcn_rsqf((float)e);
+        rho = num * (y * __builtin_fma(-0.5 * e * y, y, 1.5));
+      }
+      if (V[k] == 0.0) rho = 0.0;
+      if (u + k < a.nu) {
         if constexpr (D == kDenseDigits)
-          static_cast<double *>(a.rho)[o] =
-              V[k] == 0 ? 0.0 : num / sqrt((double)V[k] / (double)a.n * a.q_k);
+          static_cast<double *>(a.rho)[o + k] = rho;
         else
-          static_cast<float *>(a.rho)[o] = dense_rho32(num, V[k], a.qnd);
-        if (a.degen) a.degen[o] = V[k] == 0 ? 1 : 0;
+          static_cast<float *>(a.rho)[o + k] = (float)rho;
+        if (a.degen) a.degen[o + k] = V[k] == 0.0 ? 1 : 0;
       }
     }
-  }
+  });
 }
 
 // The filter of the top-k search (topk_filter.hip): rho of many pairs in
 // one launch, from two digits of c (its values only choose which offsets are
-// scored again; three digits where two would leave a bound above 2^-12), one workgroup per item {pair, tile} (pair -1: none).  A wave
-// writes its RV x 64 x 4 values as they lie in its lanes (offsets past the
-// valid range as -inf), and its block's largest rho; offsets whose window is
-// nearly uniform (energy below n / 100, where the segment form's FP32 error
-// bound grows) do not count there but raise a second maximum.
+// scored again; three digits where two would leave a bound above 2^-12),
+// one workgroup per item {pair, tile} (pair -1: none).  A wave writes its
+// RV x 64 x 4 values as they lie in its lanes (offsets past the valid range as
+// -inf), and its block's largest rho; offsets whose window is nearly uniform
+// (energy below n / 100, where the segment form's FP32 error bound grows) do
+// not count there but raise a second maximum.
 template <int D, int RV, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dense_filter(
     const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride,
@@ -355,31 +404,28 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int u0 = (tile - tv * a.ntu) * kDenseBU, v0 = tv * 2 * NW * RV;
   const int row0 = RV * (2 * wave + ((lane >> 3) & 1));
   v4i acc[RV][D];
-  dense_products<D, RV, NW>(S, static_cast<const v4i *>(a.frag), a, u0, v0, row0, lds8, lane, acc);
+  dense_products<D, RV, NW>(S, (frag_ptr)a.frag, a, u0, v0, row0, lds8, lane, acc);
 
   const int u = u0 + 16 * (lane & 7) + 4 * (lane >> 4);
-  const long long low = (long long)a.n * a.n / 100;
+  const double low = (double)a.n * (double)a.n * 0.01;
   const int block = tile * NW + wave;
   float4 *o = reinterpret_cast<float4 *>(map + fp.map0 + (long long)block * (RV * 256)) + lane;
   float top = -__builtin_inff(), top_low = -__builtin_inff();
-#pragma unroll
-  for (int r = 0; r < RV; ++r) {
-    const int v = v0 + row0 + r;
-    v4u_a4 sf;
-    long long V[4];
-    dense_energy4(S, S2, a, min(u, a.nu - 1), min(v, a.nv - 1), sf, V);
+  dense_windows<RV>(S, S2, a, u0, u, v0 + row0, [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
+    const bool row_ok = v0 + row0 + r < a.nv;
     float w[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const bool ok = v < a.nv && u + k < a.nu;
-      w[k] = ok ? dense_rho32(dense_num<D>(acc[r], k, sf[k], a), V[k], a.qnd) : -__builtin_inff();
-      const bool flat = V[k] != 0 && V[k] < low;
-      if (flat) top_low = fmaxf(top_low, w[k]);
-      else top = fmaxf(top, w[k]);
+      const float num = (float)dense_num<D>(acc[r], k, sf[k], a);
+      const float y = __builtin_amdgcn_rsqf((float)(V[k] * a.qnd));
+      w[k] = V[k] == 0.0 ? 0.f : num * y;
+      if (!row_ok || u + k >= a.nu) w[k] = -__builtin_inff();
+      const bool flat = V[k] != 0.0 && V[k] < low;
+      top_low = fmaxf(top_low, flat ? w[k] : -__builtin_inff());
+      top = fmaxf(top, flat ? -__builtin_inff() : w[k]);
     }
     o[r * 64] = make_float4(w[0], w[1], w[2], w[3]);
-    __builtin_amdgcn_sched_barrier(0);  // rows one after another: fewer registers
-  }
+  });
   const uint32_t m = wave_incl_max(float_order(top)), ml = wave_incl_max(float_order(top_low));
   if (lane == 63) bmax[fp.block0 + block] = make_float2(float_unorder(m), float_unorder(ml));
 }
@@ -396,8 +442,7 @@ static int dense_go(const DenseArgs &a, hipStream_t st) {
   }
   const int lds = (2 * NW * RV + a.hb - 1) * a.pitch;
   const int grid = (a.ntu * a.ntv + 7) / 8 * 8;
-  hipLaunchKernelGGL((dense_kernel<D, RV, NW>), dim3(grid), dim3(64 * NW), lds, st, a.s, a.s2,
-                     static_cast<const v4i *>(a.frag), a);
+  hipLaunchKernelGGL((dense_kernel<D, RV, NW>), dim3(grid), dim3(64 * NW), lds, st, a.s, a.s2, a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

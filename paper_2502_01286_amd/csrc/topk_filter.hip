@@ -145,10 +145,10 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   const int nb = fp.n_blocks, rv = fp.a.rv, nu = fp.a.nu;
   const float2 *bm = bmax + fp.block0;
   const float *vals = map + fp.map0;
-  // twice the errors of the filter (fp.error: its rounded c, the result's
-  // rounding, 2^-24, and the thresholds' below) and of the reference (FP32: at
+  // twice the errors of the filter (fp.error: its rounded c; the result's
+  // roundings and 1 / sqrt, 3e-7; the thresholds' below, 1e-7) and of the reference (FP32: at
   // most 3e-6 for windows of energy n / 100 and above, 1e-4 for any window)
-  const float margin = 2.f * (fp.error + 2e-7f + (F64 ? 0.f : 3e-6f));
+  const float margin = 2.f * (fp.error + 4e-7f + (F64 ? 0.f : 3e-6f));
   const float low_margin = 2.f * (fp.error + 1e-4f);
 
   auto clear = [&]() {
