@@ -829,6 +829,7 @@ struct FilterLaunch {
 };
 struct FilterChunk {
   int fp0, n_fps;
+  bool spread;  // some pair's ordered sum is long: spread over workgroups
   std::vector<FilterLaunch> launches;
 };
 struct FilterPlan {
@@ -841,7 +842,8 @@ struct FilterPlan {
   int chunk = 0, n_lists = 0;   // offsets per partial list of the direct form
   int seq_grid = 1;
   size_t map_floats = 0, blocks = 0;
-  DevBuf d_fps, d_items, d_seq, d_pairs, d_direct, d_map, d_bmax, d_partial;
+  size_t spread_fps = 0;        // most pairs of a spread chunk
+  DevBuf d_fps, d_items, d_seq, d_pairs, d_direct, d_map, d_bmax, d_partial, d_spread;
   bool active() const { return !pairs.empty(); }
 };
 
@@ -1294,24 +1296,44 @@ void dense_constants(const sncc_tmpl *tm, int t, const DenseTmpl &dt, int N, int
   a.inv_n = 1.0 / (double)a.n;
 }
 
+// Records of an FP32 sum above which a chunk's candidates are scored by many
+// workgroups in three launches instead of one per pair in the selection's.
+constexpr int kSpreadRecords = 2048;
 // Largest scratch map of a chunk of filtered pairs (floats; one pair may need
 // more).
 constexpr size_t kFilterMapFloats = (size_t)64 << 20;
-// FP32: estimated gain below which a call keeps the segment form for all its
-// pairs (the filter's launches and the selection take 30 to 40 us).
-constexpr double kFilterMinGainUs = 60.0;
-
-// Template t's sum in the FP32 segment form as plan `ph` orders it (see SeqRec).
+// Template t's sum in the FP32 segment form as plan `ph` orders it (see
+// SeqRec); returns its number of records.
 int seq_records(const PlanHost &ph, int t, int P, std::vector<SeqRec> &out) {
   const size_t first = out.size();
   const DevTmpl &d = ph.tmpls[t];
-  if (d.lp_class == kLpDirect) {  // four records per compensated step
+  std::vector<SeqRec> block;
+  int terms = 0;
+  auto left = [&](int top, int bot) { block.push_back(SeqRec{top, bot, kSeqNoTerm, 0.f}); };
+  auto term = [&](int top, int bot, int area, float c) {
+    block.push_back(SeqRec{top, bot, (uint32_t)area | (uint32_t)terms++ << kSeqSlot, c});
+  };
+  auto step = [&]() {  // the block's end: four terms and eight records
+    while (terms < 4)
+      block.push_back(SeqRec{0, 0, kSeqZero | (uint32_t)terms++ << kSeqSlot, 0.f});
+    while (block.size() < 8) left(0, 0);
+    out.insert(out.end(), block.begin(), block.end());
+    block.clear();
+    terms = 0;
+  };
+  if (d.lp_class == kLpDirect) {
+    // four records per compensated step, each less the one before it; the
+    // column before a block's first is its block's left boundary (none: 0)
     const PassDesc &ps = ph.passes[d.pass_begin];
-    for (int i = ps.seg_begin; i < ps.seg_end; i += 2) {
+    int top = 0, bot = 0;
+    for (int i = ps.seg_begin, n = 0; i < ps.seg_end; i += 2, ++n) {
       DirectRec r;
       memcpy(&r, &ph.recs[i], sizeof r);
-      const bool end = (i - ps.seg_begin) / 2 % 4 == 3;
-      out.push_back(SeqRec{r.top, r.bot, (uint32_t)r.area | (end ? kSeqEnd : 0u), r.c});
+      if (n % 4 == 0) left(top, bot);
+      term(r.top, r.bot, r.area, r.c);
+      top = r.top;
+      bot = r.bot;
+      if (n % 4 == 3) step();
     }
     return (int)(out.size() - first);
   }
@@ -1333,10 +1355,12 @@ int seq_records(const PlanHost &ph, int t, int P, std::vector<SeqRec> &out) {
       for (int c = 0; c < n; ++c)
         for (int j = 0; j <= L; ++j, ++r) {
           const TileRec &e = ph.recs[r];
-          uint32_t flags = j == 0 ? kSeqFirst : 0u;
-          if (c == n - 1 && j == L) flags |= kSeqEnd;
-          out.push_back(SeqRec{table(e.off_tl), table(e.off_bl), (uint32_t)e.w_area | flags, e.c});
+          if (j == 0)
+            left(table(e.off_tl), table(e.off_bl));
+          else
+            term(table(e.off_tl), table(e.off_bl), e.w_area, e.c);
         }
+      step();
     };
     for (int q = ps.n_chain[3]; q > 0; --q) chains(4, 1);
     for (int q = ps.n_chain[2]; q > 0; --q) chains(3, 1);
@@ -1349,33 +1373,58 @@ int seq_records(const PlanHost &ph, int t, int P, std::vector<SeqRec> &out) {
   return (int)(out.size() - first);
 }
 
-// Which pairs the filter serves, by the estimates above (with its map's write
-// and scan, 2 ps): FP64 pairs where it beats the plain form, FP32 pairs where
-// it beats the segment form and all of them together gain enough.
+// Which pairs the filter serves.  Estimates in ps per offset, fitted to calls of
+// six pairs on 1280 x 720 measured both ways (us, other form / filter).  FP64:
+// the direct form 17 + 0.6 K against 7 + 2.2e-3 matrix products per offset: 16 x
+// 16, K 11 118 / 41; 64 x 64, K 119 438 / 89; 128 x 128, K 135 435 / 194; 192 x
+// 192, K 58 225 / 318.  FP32: the segment form 0.24 K + 4e-4 staged entries
+// (and 13 for lists of more than one), with 20 us a call, against 3.5 + 2.25e-3
+// products, with 30 us and the ordered sum's 0.015 us per segment: 24 x 24,
+// K 11 122 / 52; 64 x 64, K 119 238 / 102; 128 x 128, K 135 318 / 206; 192 x
+// 192, K 58 215 / 325.  An FP32 call takes the cheapest of no filter, all
+// pairs, or those it gains on.
 std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int n_pairs,
-                               const int32_t *pairs, bool fp64) {
-  std::vector<char> use(n_pairs, 0), tmpl(tm->T, 0);  // tmpl: 1 yes, 2 no
-  std::vector<double> gain(tm->T, 0.0);
+                               const int32_t *pairs, int k, bool fp64) {
+  std::vector<char> use(n_pairs, 0), seen(tm->T, 0), can(tm->T, 0);
+  std::vector<double> other(tm->T, 0.0), mine(tm->T, 0.0);
   const int forced = dense_forced();
-  double total = 0;
+  double none = 0, some = 0, all = 0;  // us
+  int k_some = 0, k_all = 0;
+  bool rest_some = false, rest_all = false, any = false;
   for (int p = 0; p < n_pairs; ++p) {
     const int t = pairs[2 * p + 1];
-    if (!tmpl[t]) {
+    const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
+    if (!seen[t]) {
+      seen[t] = 1;
       DenseArgs a{};
-      const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
-      tmpl[t] = 2;
-      if (forced != 0 && tm->digits_f[t] &&
-          dense_shape(tm, t, tm->digits_f[t], nu, nv, ctx->num_cu, a, 8)) {
-        gain[t] = (fp64 ? cost_plain(tm, t) : cost_tile(tm, t)) -
-                  (8.0 + 0.8e-3 * a.digits * dense_macs(a));
-        if (forced == 1 || gain[t] > 0) tmpl[t] = 1;
-      }
+      can[t] = forced != 0 && tm->digits_f[t] &&
+               dense_shape(tm, t, tm->digits_f[t], nu, nv, ctx->num_cu, a, 8);
+      const double mac = 0.5 * a.digits * dense_macs(a);
+      const double staged = (tm->W[t] + 128.0) * (tm->H[t] + 32.0);
+      other[t] = fp64 ? 17.0 + 0.6 * tm->K[t] : (k > 1 ? 13.0 : 0.0) + 0.24 * tm->K[t] + 4e-4 * staged;
+      mine[t] = fp64 ? 7.0 + 2.2e-3 * mac : 3.5 + 2.25e-3 * mac;
     }
-    use[p] = tmpl[t] == 1;
-    if (use[p])
-      total += gain[t] * (double)(M - tm->W[t] + 1) * (double)(N - tm->H[t] + 1) * 1e-6;
+    const double offsets = (double)nu * nv * 1e-6;
+    const bool gains = can[t] && mine[t] < other[t];
+    none += offsets * other[t];
+    some += offsets * (gains ? mine[t] : other[t]);
+    all += offsets * (can[t] ? mine[t] : other[t]);
+    (gains ? k_some : k_all) = std::max(gains ? k_some : k_all, can[t] ? tm->K[t] : 0);
+    rest_some |= !gains;
+    rest_all |= !can[t];
+    any |= gains;
   }
-  if (!fp64 && forced != 1 && total < kFilterMinGainUs) use.assign(n_pairs, 0);
+  k_all = std::max(k_all, k_some);
+  constexpr double kTileUs = 20.0, kFilterUs = 30.0, kOrderUs = 0.015;
+  none += kTileUs;
+  some += kFilterUs + kOrderUs * k_some + (rest_some ? kTileUs : 0.0);
+  all += kFilterUs + kOrderUs * k_all + (rest_all ? kTileUs : 0.0);
+  const bool take_all = forced == 1 || (!fp64 && all < none && (!any || all < some));
+  const bool take_some = fp64 || (any && some < none);
+  for (int p = 0; p < n_pairs; ++p) {
+    const int t = pairs[2 * p + 1];
+    use[p] = can[t] && (take_all || (take_some && mine[t] < other[t]));
+  }
   return use;
 }
 
@@ -1498,6 +1547,9 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
       if (l.n_items > 0) c.launches.push_back(l);
     }
     c.n_fps = (int)f.fps.size() - c.fp0;
+    c.spread = false;
+    for (int j = c.fp0; j < c.fp0 + c.n_fps; ++j) c.spread |= f.fps[j].n_seq > kSpreadRecords;
+    if (c.spread) f.spread_fps = std::max(f.spread_fps, (size_t)c.n_fps);
     f.map_floats = std::max(f.map_floats, floats);
     f.blocks = std::max(f.blocks, (size_t)blocks);
     if (c.n_fps > 0) f.chunks.push_back(std::move(c));
@@ -1509,6 +1561,7 @@ int upload_filter(FilterPlan &f, int k, bool fp64, hipStream_t st) {
   CHK(f.d_map.reserve(std::max<size_t>(16, f.map_floats * 4)));
   CHK(f.d_bmax.reserve(std::max<size_t>(16, f.blocks * sizeof(float2))));
   CHK(f.d_partial.reserve((size_t)f.n_lists * k * (fp64 ? sizeof(Key96) : 8)));
+  if (f.spread_fps) CHK(f.d_spread.reserve(f.spread_fps * sizeof(FilterSpread)));
   CHK(f.d_fps.upload(f.fps, st));
   CHK(f.d_items.upload(f.items, st));
   CHK(f.d_seq.upload(f.seq, st));
@@ -1535,7 +1588,8 @@ int run_filter(sncc_ctx *ctx, const sncc_tmpl *tm, FilterPlan &f, const uint32_t
     if (i + 1 == f.chunks.size() && !fp64) ctx->mark(1);
     ok = ok && launch_filter_select(fp64, s, s2, fs, P, fps, c.n_fps, f.d_map.as<float>(),
                                     f.d_bmax.as<float2>(), f.d_seq.as<SeqRec>(), geom, c64, k, out,
-                                    f.d_direct.as<int>(), st) == 0;
+                                    f.d_direct.as<int>(),
+                                    c.spread ? f.d_spread.as<FilterSpread>() : nullptr, st) == 0;
   }
   ok = ok && launch_seq_topk(fp64, s, s2, fs, P, f.d_pairs.as<SeqPair>(), (int)f.pairs.size(),
                              f.d_direct.as<int>(), f.chunk, f.d_seq.as<SeqRec>(), geom, c64, k,
@@ -2042,7 +2096,7 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
     CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d) {
       CHK(build_one_call_plan(tm, M, N, sat_pitch, n_pairs, pairs, k, kSinkTopk, ctx->num_cu,
                               d.h));
-      std::vector<char> use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, false);
+      std::vector<char> use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, k, false);
       if (std::find(use.begin(), use.end(), 1) == use.end()) return SNCC_OK;
       plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, false, &d.h, use, d.f);
       if (d.f.chunks.empty() || upload_filter(d.f, k, false, ctx->stream) != SNCC_OK) {
@@ -2085,7 +2139,7 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
   key.pairs.assign(pairs, pairs + 2 * n_pairs);
   PlanDev *pd = nullptr;
   CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d) {
-    std::vector<char> use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, true);
+    std::vector<char> use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, k, true);
     plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, true, nullptr, use, d.f);
     if (upload_filter(d.f, k, true, ctx->stream) == SNCC_OK) return SNCC_OK;
     // no memory for the filter's maps: the direct form for all pairs

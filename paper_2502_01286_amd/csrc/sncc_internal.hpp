@@ -327,17 +327,30 @@ struct FilterPair {
 
 // One boundary column of the FP32 segment form's chains in its order of
 // summation: byte offsets of the column's entries in the chain's top and bottom
-// rows from the window's top-left entry, A_i and c_i of the segment that ends
-// there, and whether it starts a chain (no segment) or ends a compensated step.
+// rows from the window's top-left entry, and A_i and c_i of the segment that
+// ends there.  A compensated step adds at most four terms; its records take a
+// block of eight, the terms at slots 0 .. 3 (bits kSeqSlot), chains' first
+// columns and unused records without a term, absent terms as zeros (adding 0
+// times 0 leaves a sum as it is).
 struct SeqRec {
   int top, bot;
-  uint32_t area_flags;     // A_i | kSeqFirst | kSeqEnd
+  uint32_t area_flags;     // A_i | slot << kSeqSlot | kSeqNoTerm | kSeqZero
   float c;
 };
-constexpr uint32_t kSeqFirst = 1u << 31, kSeqEnd = 1u << 30, kSeqArea = (1u << 24) - 1;
+constexpr uint32_t kSeqNoTerm = 1u << 31, kSeqZero = 1u << 30, kSeqArea = (1u << 24) - 1;
+constexpr int kSeqSlot = 24;
 
 // Candidates a pair may hold; above it the pair takes the direct form.
 constexpr int kFilterCands = 512;
+
+// A pair's candidates where their scoring is spread over workgroups: their
+// number (-1: left to the direct form), row-major indices, keys of the accurate
+// values, and of the reference's.
+struct FilterSpread {
+  int n, m;
+  int cand[kFilterCands];
+  unsigned long long val[kFilterCands], key[kFilterCands];
+};
 
 // One pair of the direct form: every offset by the reference arithmetic.
 struct SeqPair {
@@ -359,7 +372,7 @@ int launch_filter_select(bool fp64, const uint32_t *s, const uint32_t *s2, long 
                          int P, const FilterPair *fps, int n_fps, const float *map,
                          const float2 *bmax, const SeqRec *seq, const int4 *geom,
                          const double *c64, int k, sncc_match *out, int *direct,
-                         hipStream_t st) SNCC_WEAK;
+                         FilterSpread *spread, hipStream_t st) SNCC_WEAK;
 int launch_seq_topk(bool fp64, const uint32_t *s, const uint32_t *s2, long long frame_stride,
                     int P, const SeqPair *pairs, int n_pairs, const int *direct, int chunk,
                     const SeqRec *seq, const int4 *geom, const double *c64, int k, void *partial,

@@ -93,6 +93,139 @@ constexpr int kRefChunk = 256;                   // records per step of them
 constexpr int kSelBins = 2048;
 constexpr int kSelBlocks = 2048;
 
+// Workgroup memory of ordered_group: the candidates' terms (rows of a pitch
+// that spreads 16-byte reads of one place over the banks) and their c, twice,
+// and the candidates' scales.
+template <int NP>
+struct OrderedLds {
+  alignas(16) float g[2][NP][kRefChunk / 2 + 4];
+  alignas(16) float c[2][kRefChunk / 2];
+  float scale[NP];
+};
+
+// FP32 reference values of the candidates c0 .. c0 + NP - 1 (those below n) by
+// a workgroup of NP + 1 waves, as keys.  The terms are added in the segment
+// form's order, a chain of one addition after the other: waves 0 .. NP - 1 take
+// a candidate each and form its terms G_i = F_i - A_i b, a lane per record,
+// kRefChunk records ahead, and the last wave adds them, a lane per candidate,
+// four terms and a compensated step at a time without a branch (a branch per
+// term on the step's end took 60 cycles a term: 125 us for K 5000).
+template <int NP>
+__device__ __forceinline__ void ordered_group(const uint32_t *__restrict__ S,
+                                              const uint32_t *__restrict__ S2, int P,
+                                              const FilterPair &fp,
+                                              const SeqRec *__restrict__ seq, const int *cand,
+                                              int c0, int n, OrderedLds<NP> &sh, u64 *key,
+                                              int wave, int lane) {
+  const SeqRec *sr = seq + fp.seq0;
+  const int n_seq = fp.n_seq, nu = fp.a.nu;
+  const bool mine = wave < NP && c0 + wave < n;  // wave 0's always is
+  const uint32_t *w = S;
+  int nb0 = 0;
+  if (mine) {
+    const int idx = __builtin_amdgcn_readfirstlane(cand[c0 + wave]);
+    const int v = idx / nu, u = idx - v * nu;
+    const Ref32 rf = ref32(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.n, fp.a.sq_rows, fp.a.q_k);
+    nb0 = rf.nb;
+    w = S + (long long)v * P + u;
+    if (lane == 0) sh.scale[wave] = rf.scale;
+  }
+  auto produce = [&](int base, int buf) {
+    constexpr int Q = kRefChunk / 64;
+    SeqRec e[Q];
+    uint32_t D[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i = base + 64 * q + lane;
+      e[q] = SeqRec{0, 0, kSeqNoTerm, 0.f};
+      if (i < n_seq) e[q] = sr[i];
+    }
+    const char *wb = reinterpret_cast<const char *>(w);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      D[q] = *reinterpret_cast<const uint32_t *>(wb + e[q].bot) -
+             *reinterpret_cast<const uint32_t *>(wb + e[q].top);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const uint32_t prev = (uint32_t)__shfl_up((int)D[q], 1);
+      const uint32_t af = e[q].area_flags;
+      const int G = (int)(D[q] - prev) + __mul24((int)(af & kSeqArea), nb0);
+      if (!(af & kSeqNoTerm)) {
+        const int j = (64 * q + lane) / 8 * 4 + ((af >> kSeqSlot) & 3);
+        sh.g[buf][wave][j] = af & kSeqZero ? 0.f : (float)G;
+        if (wave == 0) sh.c[buf][j] = e[q].c;
+      }
+    }
+  };
+  if (mine) produce(0, 0);
+  float acc = 0.f, cmp = 0.f, y = -cmp;
+  __syncthreads();
+  for (int base = 0, buf = 0; base < n_seq; base += kRefChunk, buf ^= 1) {
+    if (wave == NP) {
+      const float4 *gl = reinterpret_cast<const float4 *>(sh.g[buf][min(lane, NP - 1)]);
+      const float4 *cl = reinterpret_cast<const float4 *>(sh.c[buf]);
+      const int m = min(kRefChunk, n_seq - base) / 8;  // blocks
+#pragma unroll 4
+      for (int l = 0; l < m; ++l) {
+        const float4 g = gl[l], c = cl[l];
+        y = __builtin_fmaf(g.x, c.x, y);
+        y = __builtin_fmaf(g.y, c.y, y);
+        y = __builtin_fmaf(g.z, c.z, y);
+        y = __builtin_fmaf(g.w, c.w, y);
+        ref_step(acc, cmp, y);
+      }
+    } else if (mine && base + kRefChunk < n_seq) {
+      produce(base + kRefChunk, buf ^ 1);
+    }
+    __syncthreads();
+  }
+  if (wave == NP && lane < NP && c0 + lane < n)
+    key[c0 + lane] = make_key((acc - cmp) * sh.scale[lane], cand[c0 + lane]);
+  __syncthreads();
+}
+
+// From the keys of n candidates' accurate values, one wave: the candidates
+// within twice the FP32 reference's error of the k-th largest, listed in
+// `near`; returns their number.
+__device__ __forceinline__ int near_kth(const u64 *key, int n, int k, int *near, int lane) {
+  u64 lk = 0;
+  for (int c = 0; c < n; c += 64)
+    topk_merge_sorted(lk, wave_sort_desc_u64(c + lane < n ? key[c + lane] : 0, lane), k, lane);
+  const u64 kth = lane_u64(lk, k - 1);
+  const float t = kth == 0 ? -__builtin_inff()
+                           : float_unorder((uint32_t)(kth >> 32)) - 2.f * (3e-6f + 1e-7f);
+  int m = 0;
+  for (int c = 0; c < n; c += 64) {
+    const u64 x = c + lane < n ? key[c + lane] : 0;
+    const u64 keep = __ballot(x != 0 && float_unorder((uint32_t)(x >> 32)) >= t);
+    if ((keep >> lane) & 1)
+      near[m + __popcll(keep & ((1ull << lane) - 1))] =
+          (int)(0xffffffffu - (uint32_t)(x & 0xffffffffu));
+    m += __popcll(keep);
+  }
+  return m;
+}
+
+// The k best of n keys, by one wave, as a pair's matches.
+__device__ __forceinline__ void write_topk32(const u64 *key, int n, int k, int nu,
+                                             sncc_match *__restrict__ out, int lane) {
+  u64 lh = 0;
+  for (int c = 0; c < n; c += 64)
+    topk_merge_sorted(lh, wave_sort_desc_u64(c + lane < n ? key[c + lane] : 0, lane), k, lane);
+  if (lane < k) {
+    sncc_match m;
+    m.u = m.v = -1;
+    m.rho = -__builtin_inff();
+    if (lh != 0) {
+      const int idx = (int)(0xffffffffu - (uint32_t)(lh & 0xffffffffu));
+      m.v = idx / nu;
+      m.u = idx - m.v * nu;
+      m.rho = float_unorder((uint32_t)(lh >> 32));
+    }
+    out[lane] = m;
+  }
+}
+
 // Largest bin b with at least k entries in bins b and above (0 when there are
 // fewer in all); every thread of the workgroup gets it.
 __device__ __forceinline__ int kth_bin(const int *hist, int k, int *out) {
@@ -121,23 +254,20 @@ __device__ __forceinline__ int kth_bin(const int *hist, int k, int *out) {
   return *out;
 }
 
-template <bool F64>
+template <bool F64, bool SPREAD>
 __global__ __launch_bounds__(kSelThreads) void filter_select(
     const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride, int P,
     const FilterPair *__restrict__ fps, const float *__restrict__ map,
     const float2 *__restrict__ bmax, const SeqRec *__restrict__ seq,
     const int4 *__restrict__ geom, const double *__restrict__ c64, int k,
-    sncc_match *__restrict__ out, int *__restrict__ direct) {
+    sncc_match *__restrict__ out, int *__restrict__ direct,
+    FilterSpread *__restrict__ spread) {
   __shared__ int hist[kSelBins];
   __shared__ int list[kSelBlocks];
   __shared__ int cand[kFilterCands];
-  __shared__ u64 key_hi[kFilterCands];
+  __shared__ u64 key_hi[SPREAD ? 1 : kFilterCands];
   __shared__ uint32_t key_lo[F64 ? kFilterCands : 1];
-  // FP32: terms of the candidates, their c and whether a step ends, twice
-  __shared__ float gbuf[F64 ? 1 : 2][F64 ? 1 : kRefGroup][kRefChunk + 9];
-  __shared__ float2 cbuf[F64 ? 1 : 2][kRefChunk + 8];
-  __shared__ float gscale[kRefGroup];
-  __shared__ int terms[2];
+  __shared__ OrderedLds<F64 || SPREAD ? 1 : kRefGroup> group;
   __shared__ int n_list, n_cand, bin, bad;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -228,6 +358,16 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   int n = n_cand;
   if (bad || n > kFilterCands) {
     if (tid == 0) direct[fp.pair] = 1;
+    if (SPREAD && tid == 0) spread[blockIdx.x].n = -1;
+    return;
+  }
+  if constexpr (SPREAD) {
+    FilterSpread &sp = spread[blockIdx.x];
+    for (int c = tid; c < n; c += kSelThreads) sp.cand[c] = cand[c];
+    if (tid == 0) {
+      sp.n = n;
+      direct[fp.pair] = 0;
+    }
     return;
   }
   // the candidates by the reference arithmetic, one wave each
@@ -243,10 +383,8 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
         key_lo[c] = 0xffffffffu - (uint32_t)idx;
       }
     }
-  } else {
-    // FP32: the accurate values first (FP64, lanes over the segments) leave
-    // few more than k candidates, those within twice the reference's error of
-    // the k-th largest
+  } else if constexpr (!SPREAD) {
+    // FP32: the accurate values first (FP64, lanes over the segments)
     for (int c = wave; c < n; c += kSelThreads / 64) {
       const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
       const int v = idx / nu, u = idx - v * nu;
@@ -255,117 +393,22 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
     }
     __syncthreads();
     if (wave == 0) {
-      u64 lk = 0;
-      for (int c = 0; c < n; c += 64)
-        topk_merge_sorted(lk, wave_sort_desc_u64(c + lane < n ? key_hi[c + lane] : 0, lane), k,
-                          lane);
-      const u64 kth = lane_u64(lk, k - 1);
-      const float t = kth == 0 ? -__builtin_inff()
-                               : float_unorder((uint32_t)(kth >> 32)) - 2.f * (3e-6f + 1e-7f);
-      int m = 0;
-      for (int c = 0; c < n; c += 64) {
-        const u64 key = c + lane < n ? key_hi[c + lane] : 0;
-        const u64 keep = __ballot(key != 0 && float_unorder((uint32_t)(key >> 32)) >= t);
-        if ((keep >> lane) & 1)
-          cand[m + __popcll(keep & ((1ull << lane) - 1))] =
-              (int)(0xffffffffu - (uint32_t)(key & 0xffffffffu));
-        m += __popcll(keep);
-      }
+      const int m = near_kth(key_hi, n, k, cand, lane);
       if (lane == 0) n_cand = m;
     }
     __syncthreads();
     n = n_cand;
-    // the terms are added in the segment form's order, a chain of one addition
-    // after the other.  Waves 0 .. 14 take a candidate each and form its terms
-    // G_i = F_i - A_i b, a lane per record, kRefChunk records ahead; the last
-    // wave adds them, a lane per candidate
-    const SeqRec *sr = seq + fp.seq0;
-    const int n_seq = fp.n_seq;
-    for (int c0 = 0; c0 < n; c0 += kRefGroup) {
-      const bool mine = wave < kRefGroup && c0 + wave < n;  // wave 0's always is
-      const uint32_t *w = S;
-      int nb0 = 0;
-      if (mine) {
-        const int idx = __builtin_amdgcn_readfirstlane(cand[c0 + wave]);
-        const int v = idx / nu, u = idx - v * nu;
-        const Ref32 rf = ref32(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.n, fp.a.sq_rows, fp.a.q_k);
-        nb0 = rf.nb;
-        w = S + (long long)v * P + u;
-        if (lane == 0) gscale[wave] = rf.scale;
-      }
-      uint32_t carry = 0;
-      auto produce = [&](int base, int buf) {
-        constexpr int Q = kRefChunk / 64;
-        SeqRec e[Q];
-        uint32_t D[Q];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          const int i = base + 64 * q + lane;
-          e[q] = SeqRec{0, 0, kSeqFirst, 0.f};
-          if (i < n_seq) e[q] = sr[i];
-        }
-        const char *wb = reinterpret_cast<const char *>(w);
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-          D[q] = *reinterpret_cast<const uint32_t *>(wb + e[q].bot) -
-                 *reinterpret_cast<const uint32_t *>(wb + e[q].top);
-        int at = 0;  // terms so far (records that start a chain have none)
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          uint32_t prev = (uint32_t)__shfl_up((int)D[q], 1);
-          if (lane == 0) prev = carry;
-          carry = (uint32_t)__builtin_amdgcn_readlane((int)D[q], 63);
-          const int G = (int)(D[q] - prev) + __mul24((int)(e[q].area_flags & kSeqArea), nb0);
-          const bool term = (e[q].area_flags & kSeqFirst) == 0;
-          const u64 m = __ballot(term);
-          const int j = at + __popcll(m & ((1ull << lane) - 1));
-          if (term) {
-            gbuf[buf][wave][j] = (float)G;
-            if (wave == 0) cbuf[buf][j] = make_float2(e[q].c, e[q].area_flags & kSeqEnd ? 1.f : 0.f);
-          }
-          at += __popcll(m);
-        }
-        if (wave == 0 && lane == 0) terms[buf] = at;
-      };
-      if (mine) produce(0, 0);
-      float acc = 0.f, cmp = 0.f, y = -cmp;
-      __syncthreads();
-      for (int base = 0, buf = 0; base < n_seq; base += kRefChunk, buf ^= 1) {
-        if (wave == kRefGroup) {
-          const float *gl = gbuf[buf][min(lane, kRefGroup - 1)];
-          const int m = __builtin_amdgcn_readfirstlane(terms[buf]);
-          for (int l = 0; l < m; l += 8) {  // the chunk's end is padded: entries past m unused
-            float gq[8];
-            float2 cq[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              gq[q] = gl[l + q];
-              cq[q] = cbuf[buf][l + q];
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              if (l + q >= m) break;
-              y = __builtin_fmaf(gq[q], cq[q].x, y);
-              if (__builtin_amdgcn_readfirstlane(__float_as_int(cq[q].y))) ref_step(acc, cmp, y);
-            }
-          }
-        } else if (mine && base + kRefChunk < n_seq) {
-          produce(base + kRefChunk, buf ^ 1);
-        }
-        __syncthreads();
-      }
-      if (wave == kRefGroup && lane < kRefGroup && c0 + lane < n)
-        key_hi[c0 + lane] = make_key((acc - cmp) * gscale[lane], cand[c0 + lane]);
-      __syncthreads();
-    }
+    for (int c0 = 0; c0 < n; c0 += kRefGroup)
+      ordered_group<kRefGroup>(S, S2, P, fp, seq, cand, c0, n, group, key_hi, wave, lane);
   }
   __syncthreads();
   if (wave != 0) return;
-  u64 lh = 0;
-  uint32_t ll = 0;
-  for (int c = 0; c < n; c += 64) {
-    u64 h = c + lane < n ? key_hi[c + lane] : 0;
-    if constexpr (F64) {
+  sncc_match *o = out + (long long)fp.pair * k;
+  if constexpr (F64) {
+    u64 lh = 0;
+    uint32_t ll = 0;
+    for (int c = 0; c < n; c += 64) {
+      const u64 h = c + lane < n ? key_hi[c + lane] : 0;
       const uint32_t l = c + lane < n ? key_lo[c + lane] : 0;
       u64 todo = __ballot(key96_gt(h, l, lane_u64(lh, k - 1),
                                    (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)));
@@ -378,37 +421,105 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
                      (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)))
           topk96_insert(lh, ll, kh, kl, k, lane);
       }
-    } else {
-      topk_merge_sorted(lh, wave_sort_desc_u64(h, lane), k, lane);
     }
-  }
-  if (lane < k) {
-    sncc_match m;
-    m.u = m.v = -1;
-    m.rho = -__builtin_inff();
-    const bool some = F64 ? (lh != 0 || ll != 0) : lh != 0;
-    if (some) {
-      const int idx = (int)(0xffffffffu - (F64 ? ll : (uint32_t)(lh & 0xffffffffu)));
-      m.v = idx / nu;
-      m.u = idx - m.v * nu;
-      m.rho = F64 ? (float)double_unorder(lh) : float_unorder((uint32_t)(lh >> 32));
+    if (lane < k) {
+      sncc_match m;
+      m.u = m.v = -1;
+      m.rho = -__builtin_inff();
+      if (lh != 0 || ll != 0) {
+        const int idx = (int)(0xffffffffu - ll);
+        m.v = idx / nu;
+        m.u = idx - m.v * nu;
+        m.rho = (float)double_unorder(lh);
+      }
+      o[lane] = m;
     }
-    out[(long long)fp.pair * k + lane] = m;
+  } else if constexpr (!SPREAD) {
+    write_topk32(key_hi, n, k, nu, o, lane);
   }
   if (lane == 0) direct[fp.pair] = 0;
+}
+
+// The spread form of the FP32 candidates' scoring: accurate values, one wave
+// per candidate; the near ones in order, kSpreadNP at a time per workgroup; the
+// result, one wave per pair.
+constexpr int kSpreadWgs = 16, kSpreadNP = 3;
+
+__global__ __launch_bounds__(256) void filter_values(
+    const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride, int P,
+    const FilterPair *__restrict__ fps, const int4 *__restrict__ geom,
+    const double *__restrict__ c64, FilterSpread *__restrict__ spread) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int f = blockIdx.x / kSpreadWgs, part = blockIdx.x % kSpreadWgs;
+  const FilterPair &fp = fps[f];
+  FilterSpread &sp = spread[f];
+  const uint32_t *S = s + (long long)fp.frame * frame_stride;
+  const uint32_t *S2 = s2 + (long long)fp.frame * frame_stride;
+  for (int c = part * 4 + wave; c < sp.n; c += 4 * kSpreadWgs) {
+    const int idx = __builtin_amdgcn_readfirstlane(sp.cand[c]);
+    const int v = idx / fp.a.nu, u = idx - v * fp.a.nu;
+    const double r = wave_ref64(S, S2, P, u, v, fp, geom, c64, lane);
+    if (lane == 0) sp.val[c] = make_key((float)r, idx);
+  }
+}
+
+__global__ __launch_bounds__(64 * (kSpreadNP + 1)) void filter_order(
+    const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride, int P,
+    const FilterPair *__restrict__ fps, const SeqRec *__restrict__ seq, int k,
+    FilterSpread *__restrict__ spread) {
+  __shared__ OrderedLds<kSpreadNP> group;
+  __shared__ int near[kFilterCands];
+  __shared__ int n_near;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int f = blockIdx.x / kSpreadWgs, part = blockIdx.x % kSpreadWgs;
+  const FilterPair &fp = fps[f];
+  FilterSpread &sp = spread[f];
+  if (sp.n < 0) return;
+  if (wave == 0) {  // every workgroup of the pair lists the same ones
+    const int m = near_kth(sp.val, sp.n, k, near, lane);
+    if (lane == 0) {
+      n_near = m;
+      if (part == 0) sp.m = m;
+    }
+  }
+  __syncthreads();
+  const uint32_t *S = s + (long long)fp.frame * frame_stride;
+  const uint32_t *S2 = s2 + (long long)fp.frame * frame_stride;
+  const int n = n_near;
+  for (int c0 = part * kSpreadNP; c0 < n; c0 += kSpreadWgs * kSpreadNP)
+    ordered_group<kSpreadNP>(S, S2, P, fp, seq, near, c0, n, group, sp.key, wave, lane);
+}
+
+__global__ __launch_bounds__(64) void filter_result(const FilterPair *__restrict__ fps,
+                                                    const FilterSpread *__restrict__ spread, int k,
+                                                    sncc_match *__restrict__ out) {
+  const FilterPair &fp = fps[blockIdx.x];
+  const FilterSpread &sp = spread[blockIdx.x];
+  if (sp.n < 0) return;
+  write_topk32(sp.key, sp.m, k, fp.a.nu, out + (long long)fp.pair * k, (int)threadIdx.x);
 }
 
 int launch_filter_select(bool fp64, const uint32_t *s, const uint32_t *s2, long long frame_stride,
                          int P, const FilterPair *fps, int n_fps, const float *map,
                          const float2 *bmax, const SeqRec *seq, const int4 *geom,
                          const double *c64, int k, sncc_match *out, int *direct,
-                         hipStream_t st) {
-  if (fp64)
-    hipLaunchKernelGGL(filter_select<true>, dim3(n_fps), dim3(kSelThreads), 0, st, s, s2,
-                       frame_stride, P, fps, map, bmax, seq, geom, c64, k, out, direct);
-  else
-    hipLaunchKernelGGL(filter_select<false>, dim3(n_fps), dim3(kSelThreads), 0, st, s, s2,
-                       frame_stride, P, fps, map, bmax, seq, geom, c64, k, out, direct);
+                         FilterSpread *spread, hipStream_t st) {
+#define SNCC_SELECT(F64, SPREAD)                                                               \
+  hipLaunchKernelGGL((filter_select<F64, SPREAD>), dim3(n_fps), dim3(kSelThreads), 0, st, s, s2, \
+                     frame_stride, P, fps, map, bmax, seq, geom, c64, k, out, direct, spread)
+  if (fp64) {
+    SNCC_SELECT(true, false);
+  } else if (!spread) {
+    SNCC_SELECT(false, false);
+  } else {
+    SNCC_SELECT(false, true);
+    hipLaunchKernelGGL(filter_values, dim3(n_fps * kSpreadWgs), dim3(256), 0, st, s, s2,
+                       frame_stride, P, fps, geom, c64, spread);
+    hipLaunchKernelGGL(filter_order, dim3(n_fps * kSpreadWgs), dim3(64 * (kSpreadNP + 1)), 0, st, s,
+                       s2, frame_stride, P, fps, seq, k, spread);
+    hipLaunchKernelGGL(filter_result, dim3(n_fps), dim3(64), 0, st, fps, spread, k, out);
+  }
+#undef SNCC_SELECT
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -420,17 +531,19 @@ __device__ __forceinline__ float lane_ref32(const uint32_t *__restrict__ S,
   const Ref32 rf = ref32(S, S2, P, u, v, sp.W, sp.H, sp.n, sp.sq_rows, sp.q_k);
   const char *w = reinterpret_cast<const char *>(S + (long long)v * P + u);
   float acc = 0.f, cmp = 0.f, y = -cmp;
-  uint32_t prev = 0;
   const SeqRec *sr = seq + sp.seq0;
-#pragma unroll 4
-  for (int i = 0; i < sp.n_seq; ++i) {
-    const SeqRec e = sr[i];
-    const uint32_t D = *reinterpret_cast<const uint32_t *>(w + e.bot) -
-                       *reinterpret_cast<const uint32_t *>(w + e.top);
-    const int G = (int)(D - prev) + __mul24((int)(e.area_flags & kSeqArea), rf.nb);
-    if (!(e.area_flags & kSeqFirst)) y = __builtin_fmaf((float)G, e.c, y);
-    prev = D;
-    if (e.area_flags & kSeqEnd) ref_step(acc, cmp, y);
+  for (int i = 0; i < sp.n_seq; i += 8) {
+    uint32_t prev = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const SeqRec e = sr[i + j];
+      const uint32_t D = *reinterpret_cast<const uint32_t *>(w + e.bot) -
+                         *reinterpret_cast<const uint32_t *>(w + e.top);
+      const int G = (int)(D - prev) + __mul24((int)(e.area_flags & kSeqArea), rf.nb);
+      if (!(e.area_flags & (kSeqNoTerm | kSeqZero))) y = __builtin_fmaf((float)G, e.c, y);
+      prev = D;
+    }
+    ref_step(acc, cmp, y);
   }
   return (acc - cmp) * rf.scale;
 }
