@@ -196,7 +196,7 @@ __device__ __forceinline__ void dense_products(const uint32_t *__restrict__ S,
   for (int yp4 = 0; yp4 < n4all; yp4 += hb4) {
     const int n4 = min(hb4, n4all - yp4);
     if (yp4) __syncthreads();
-    dense_region<64 * NW, RV >= 8 ? 16 : 8>(S, a.P, a.N, u0, v0 + 4 * yp4, BV + 4 * n4 - 1, 28 + 4 * G, pitch, lds8,
+    dense_region<64 * NW, (RV >= 8 && D != 2) ? 16 : 8>(S, a.P, a.N, u0, v0 + 4 * yp4, BV + 4 * n4 - 1, 28 + 4 * G, pitch, lds8,
                           threadIdx.x);
     __syncthreads();
     // A of the pass's steps in order, the last one's again after it
@@ -251,14 +251,14 @@ __device__ __forceinline__ void dense_products(const uint32_t *__restrict__ S,
 // corner loads of a row are 16 bytes at any word address; with eight rows per
 // wave half (two waves a SIMD in any case) the next row's are requested before
 // this one's are used.
-template <int RV, class F>
+template <int RV, bool LOW, class F>
 __device__ __forceinline__ void dense_windows(const uint32_t *__restrict__ S,
                                               const uint32_t *__restrict__ S2, const DenseArgs &a,
                                               int u0, int u, int v0, F f) {
   const int uc = min(u, a.nu - 1);
   const double n = (double)a.n;
   if (u0 + kDenseBU + 3 + a.W <= a.P && a.sq_rows >= a.H) {
-    constexpr bool AHEAD = RV >= 8;
+    constexpr bool AHEAD = RV >= 8 && !LOW;
     v4u_a4 c[2][8];
     const long long down = (long long)a.H * a.P;
     auto load = [&](int r, v4u_a4(&q)[8]) {
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   dense_products<D, RV, NW>(S, (frag_ptr)a.frag, a, u0, v0, row0, lds8, lane, acc);
 
   const int u = u0 + 16 * (lane & 7) + 4 * (lane >> 4);
-  dense_windows<RV>(S, S2, a, u0, u, v0 + row0, [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
+  dense_windows<RV, false>(S, S2, a, u0, u, v0 + row0, [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
     const int v = v0 + row0 + r;
     const long long o = (long long)v * a.rho_pitch + u;
     if (v >= a.nv) return;
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int block = tile * NW + wave;
   float4 *o = reinterpret_cast<float4 *>(map + fp.map0 + (long long)block * (RV * 256)) + lane;
   float top = -__builtin_inff(), top_low = -__builtin_inff();
-  dense_windows<RV>(S, S2, a, u0, u, v0 + row0, [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
+  dense_windows<RV, D == 2>(S, S2, a, u0, u, v0 + row0, [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
     const bool row_ok = v0 + row0 + r < a.nv;
     float w[4];
 #pragma unroll
