@@ -1300,8 +1300,9 @@ void dense_constants(const sncc_tmpl *tm, int t, const DenseTmpl &dt, int N, int
 // workgroups in three launches instead of one per pair in the selection's.
 constexpr int kSpreadRecords = 2048;
 // Largest scratch map of a chunk of filtered pairs (floats; one pair may need
-// more).
-constexpr size_t kFilterMapFloats = (size_t)64 << 20;
+// more), and of a batch's, whose selections then run for hundreds of pairs at
+// a time.
+constexpr size_t kFilterMapFloats = (size_t)64 << 20, kFilterBatchFloats = (size_t)256 << 20;
 // Template t's sum in the FP32 segment form as plan `ph` orders it (see
 // SeqRec); returns its number of records.
 int seq_records(const PlanHost &ph, int t, int P, std::vector<SeqRec> &out) {
@@ -1375,16 +1376,19 @@ int seq_records(const PlanHost &ph, int t, int P, std::vector<SeqRec> &out) {
 
 // Which pairs the filter serves.  Estimates in ps per offset, fitted to calls of
 // six pairs on 1280 x 720 measured both ways (us, other form / filter).  FP64:
-// the direct form 17 + 0.6 K against 7 + 2.2e-3 matrix products per offset: 16 x
+// the direct form 17 + 0.6 K against 9 + 1.25e-3 matrix products per offset: 16 x
 // 16, K 11 118 / 41; 64 x 64, K 119 438 / 89; 128 x 128, K 135 435 / 194; 192 x
 // 192, K 58 225 / 318.  FP32: the segment form 0.24 K + 4e-4 staged entries
-// (and 13 for lists of more than one), with 20 us a call, against 3.5 + 2.25e-3
+// (and 13 for lists of more than one), with 20 us a call, against 3 + 1.25e-3
 // products, with 30 us and the ordered sum's 0.015 us per segment: 24 x 24,
 // K 11 122 / 52; 64 x 64, K 119 238 / 102; 128 x 128, K 135 318 / 206; 192 x
 // 192, K 58 215 / 325.  An FP32 call takes the cheapest of no filter, all
 // pairs, or those it gains on.
+// A batch's segment form starts its lists from other items' floors: 0.21 K +
+// 4e-4 staged entries - 1.5 (256 frames 1280 x 720 x 32 templates 12.5 at
+// K 37, 16 frames 1920 x 1080 x 64 templates 78 at K 314), no fixed costs.
 std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int n_pairs,
-                               const int32_t *pairs, int k, bool fp64) {
+                               const int32_t *pairs, int k, bool fp64, bool batch = false) {
   std::vector<char> use(n_pairs, 0), seen(tm->T, 0), can(tm->T, 0);
   std::vector<double> other(tm->T, 0.0), mine(tm->T, 0.0);
   const int forced = dense_forced();
@@ -1401,8 +1405,10 @@ std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N,
                dense_shape(tm, t, tm->digits_f[t], nu, nv, ctx->num_cu, a, 8);
       const double mac = 0.5 * a.digits * dense_macs(a);
       const double staged = (tm->W[t] + 128.0) * (tm->H[t] + 32.0);
-      other[t] = fp64 ? 17.0 + 0.6 * tm->K[t] : (k > 1 ? 13.0 : 0.0) + 0.24 * tm->K[t] + 4e-4 * staged;
-      mine[t] = fp64 ? 7.0 + 2.2e-3 * mac : 3.5 + 2.25e-3 * mac;
+      other[t] = fp64    ? 17.0 + 0.6 * tm->K[t]
+                 : batch ? 0.21 * tm->K[t] + 4e-4 * staged - 1.5
+                         : (k > 1 ? 13.0 : 0.0) + 0.24 * tm->K[t] + 4e-4 * staged;
+      mine[t] = (fp64 ? 9.0 : 3.0) + 1.25e-3 * mac;
     }
     const double offsets = (double)nu * nv * 1e-6;
     const bool gains = can[t] && mine[t] < other[t];
@@ -1415,7 +1421,8 @@ std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N,
     any |= gains;
   }
   k_all = std::max(k_all, k_some);
-  constexpr double kTileUs = 20.0, kFilterUs = 30.0, kOrderUs = 0.015;
+  const double kTileUs = batch ? 0.0 : 20.0, kFilterUs = batch ? 0.0 : 30.0;
+  constexpr double kOrderUs = 0.015;
   none += kTileUs;
   some += kFilterUs + kOrderUs * k_some + (rest_some ? kTileUs : 0.0);
   all += kFilterUs + kOrderUs * k_all + (rest_all ? kTileUs : 0.0);
@@ -1430,17 +1437,23 @@ std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N,
 
 // Plans the filter for the pairs marked in `use` (cleared where the operands
 // cannot be had) and the direct form for the others (FP64) or for those the
-// filter cannot decide (FP32, whose sums are ordered as plan `tile` has them).
+// filter cannot decide (FP32, whose sums are ordered as plan `tile` has them,
+// and in the last columns as a batch's `edge`).
 void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_pairs,
                  const int32_t *pairs, int k, bool fp64, const PlanHost *tile,
-                 std::vector<char> &use, FilterPlan &f) {
+                 std::vector<char> &use, FilterPlan &f, size_t map_floats = kFilterMapFloats,
+                 const PlanHost *edge = nullptr) {
   std::vector<std::pair<int, int>> want;
   for (int p = 0; p < n_pairs; ++p)
     if (use[p]) want.emplace_back(pairs[2 * p + 1], tm->digits_f[pairs[2 * p + 1]]);
   std::sort(want.begin(), want.end());
   want.erase(std::unique(want.begin(), want.end()), want.end());
   if (!want.empty()) dense_build(ctx, tm, want);
-  std::vector<int> seq0(tm->T, -1), n_seq(tm->T, 0);
+  std::vector<int> seq0[2], n_seq[2];
+  for (int i = 0; i < 2; ++i) {
+    seq0[i].assign(tm->T, -1);
+    n_seq[i].assign(tm->T, 0);
+  }
   f.pairs.resize(n_pairs);
   f.direct.assign(n_pairs, 0);
   std::vector<int> idx;
@@ -1453,9 +1466,10 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
     if (use[p]) {
       idx.push_back(p);
       cost[p] = (double)tm->H[t] * dense_groups(tm->W[t]) * tm->digits_f[t];
-      if (!fp64 && seq0[t] < 0) {
-        seq0[t] = (int)f.seq.size();
-        n_seq[t] = seq_records(*tile, t, P, f.seq);
+      for (int i = 0; !fp64 && i < (edge ? 2 : 1); ++i) {
+        if (seq0[i][t] >= 0) continue;
+        seq0[i][t] = (int)f.seq.size();
+        n_seq[i][t] = seq_records(i ? *edge : *tile, t, P, f.seq);
       }
     }
     f.direct[p] = fp64 && !use[p];
@@ -1468,8 +1482,11 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
     q.H = tm->H[t];
     q.n = q.W * q.H;
     q.sq_rows = tm->dev[t].sq_rows;
-    q.seq0 = std::max(0, seq0[t]);
-    q.n_seq = n_seq[t];
+    for (int i = 0; i < 2; ++i) {
+      q.seq0[i] = std::max(0, seq0[i][t]);
+      q.n_seq[i] = n_seq[i][t];
+    }
+    q.u_split = edge && edge->pairs[p].ntu > 0 ? edge->pairs[p].u_base : 1 << 30;
     q.seg_off = tm->seg_off[t];
     q.K = tm->K[t];
     q.q_k = tm->q_k[t];
@@ -1500,7 +1517,7 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
     for (size_t floats = 0; e < idx.size(); ++e) {
       const SeqPair &q = f.pairs[idx[e]];
       const size_t n = (size_t)((q.nu + 127) / 128 * 128) * ((q.nv + 63) / 64 * 64);
-      if (e > i && floats + n > kFilterMapFloats) break;
+      if (e > i && floats + n > map_floats) break;
       floats += n;
       tiles8 += (long long)((q.nu + 127) / 128) * ((q.nv + 63) / 64);
     }
@@ -1525,8 +1542,11 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
         fp.map0 = (long long)floats;
         fp.block0 = blocks;
         fp.n_blocks = tiles * kDenseNW;
-        fp.seq0 = f.pairs[p].seq0;
-        fp.n_seq = f.pairs[p].n_seq;
+        for (int x = 0; x < 2; ++x) {
+          fp.seq0[x] = f.pairs[p].seq0[x];
+          fp.n_seq[x] = f.pairs[p].n_seq[x];
+        }
+        fp.u_split = f.pairs[p].u_split;
         fp.seg_off = f.pairs[p].seg_off;
         fp.K = f.pairs[p].K;
         fp.r64 = f.pairs[p].r64;
@@ -1548,7 +1568,7 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
     }
     c.n_fps = (int)f.fps.size() - c.fp0;
     c.spread = false;
-    for (int j = c.fp0; j < c.fp0 + c.n_fps; ++j) c.spread |= f.fps[j].n_seq > kSpreadRecords;
+    for (int j = c.fp0; j < c.fp0 + c.n_fps; ++j) c.spread |= f.fps[j].n_seq[0] > kSpreadRecords;
     if (c.spread) f.spread_fps = std::max(f.spread_fps, (size_t)c.n_fps);
     f.map_floats = std::max(f.map_floats, floats);
     f.blocks = std::max(f.blocks, (size_t)blocks);
@@ -1570,11 +1590,11 @@ int upload_filter(FilterPlan &f, int k, bool fp64, hipStream_t st) {
   return SNCC_OK;
 }
 
-// Enqueues the filter, the selection and the direct form; mark(1) of the
-// context's stages falls before the last selection.
-int run_filter(sncc_ctx *ctx, const sncc_tmpl *tm, FilterPlan &f, const uint32_t *s,
-               const uint32_t *s2, long long fs, int P, int k, bool fp64, sncc_match *out) {
-  const hipStream_t st = ctx->stream;
+// Enqueues the filter (part 0: all but the last selection) and the last
+// selection and the direct form (part 1).
+int run_filter(hipStream_t st, const sncc_tmpl *tm, FilterPlan &f, const uint32_t *s,
+               const uint32_t *s2, long long fs, int P, int k, bool fp64, sncc_match *out,
+               int part) {
   const int4 *geom = tm->d_geom.as<int4>();
   const double *c64 = tm->d_c64.as<double>();
   bool ok = true;
@@ -1582,18 +1602,20 @@ int run_filter(sncc_ctx *ctx, const sncc_tmpl *tm, FilterPlan &f, const uint32_t
     const FilterChunk &c = f.chunks[i];
     const FilterPair *fps = f.d_fps.as<FilterPair>() + c.fp0;
     for (const FilterLaunch &l : c.launches)
-      ok = ok && launch_dense_filter(l.digits, l.rv, s, s2, fs, fps, f.d_items.as<int2>() + l.item0,
-                                     l.n_items, l.lds, f.d_map.as<float>(),
-                                     f.d_bmax.as<float2>(), st) == 0;
-    if (i + 1 == f.chunks.size() && !fp64) ctx->mark(1);
+      ok = ok && (part != 0 ||
+                  launch_dense_filter(l.digits, l.rv, s, s2, fs, fps,
+                                      f.d_items.as<int2>() + l.item0, l.n_items, l.lds,
+                                      f.d_map.as<float>(), f.d_bmax.as<float2>(), st) == 0);
+    if (part != (i + 1 == f.chunks.size())) continue;
     ok = ok && launch_filter_select(fp64, s, s2, fs, P, fps, c.n_fps, f.d_map.as<float>(),
                                     f.d_bmax.as<float2>(), f.d_seq.as<SeqRec>(), geom, c64, k, out,
                                     f.d_direct.as<int>(),
                                     c.spread ? f.d_spread.as<FilterSpread>() : nullptr, st) == 0;
   }
-  ok = ok && launch_seq_topk(fp64, s, s2, fs, P, f.d_pairs.as<SeqPair>(), (int)f.pairs.size(),
-                             f.d_direct.as<int>(), f.chunk, f.d_seq.as<SeqRec>(), geom, c64, k,
-                             f.d_partial.p, f.seq_grid, out, st) == 0;
+  if (part == 1)
+    ok = ok && launch_seq_topk(fp64, s, s2, fs, P, f.d_pairs.as<SeqPair>(), (int)f.pairs.size(),
+                               f.d_direct.as<int>(), f.chunk, f.d_seq.as<SeqRec>(), geom, c64, k,
+                               f.d_partial.p, f.seq_grid, out, st) == 0;
   if (!ok) SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
   return SNCC_OK;
 }
@@ -2100,7 +2122,8 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
       if (std::find(use.begin(), use.end(), 1) == use.end()) return SNCC_OK;
       plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, false, &d.h, use, d.f);
       if (d.f.chunks.empty() || upload_filter(d.f, k, false, ctx->stream) != SNCC_OK) {
-        d.f.pairs.clear();  // no operands, or no memory for it: the segment form for all pairs
+        d.f.~FilterPlan();  // no operands, or no memory for it: the segment form for all pairs
+        new (&d.f) FilterPlan();
         g_err.clear();
       } else {
         drop_items(d.h, use);
@@ -2117,13 +2140,14 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
     if (tiles &&
         launch_tile(pd->h.cfg, kSinkTopk, a, pd->h.grid, pd->h.lds_bytes, ctx->stream) != 0)
       SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
-    if (!filtered) ctx->mark(1);
-    // the merge writes every pair's slots (the filtered pairs' as empty), the
-    // filter's selection then its own
+    if (filtered)
+      CHK(run_filter(ctx->stream, tm, pd->f, d_s, d_s2, fs, sat_pitch, k, false, d_out, 0));
+    ctx->mark(1);
     if (tiles && launch_merge(pd->d_pairs.as<PairDesc>(), nullptr, n_pairs, a.partial, nullptr, k,
                               d_out, ctx->stream) != 0)
       SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
-    if (filtered) CHK(run_filter(ctx, tm, pd->f, d_s, d_s2, fs, sat_pitch, k, false, d_out));
+    if (filtered)
+      CHK(run_filter(ctx->stream, tm, pd->f, d_s, d_s2, fs, sat_pitch, k, false, d_out, 1));
     ctx->mark(2);
     if (ctx->timing) ctx->n_stages = 2;
     return SNCC_OK;
@@ -2149,7 +2173,9 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
     plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, true, nullptr, use, d.f);
     return upload_filter(d.f, k, true, ctx->stream);
   }, &pd, false));
-  return run_filter(ctx, tm, pd->f, d_s, d_s2, fs, sat_pitch, k, true, d_out);
+  for (int part = 0; part < 2; ++part)
+    CHK(run_filter(ctx->stream, tm, pd->f, d_s, d_s2, fs, sat_pitch, k, true, d_out, part));
+  return SNCC_OK;
 }
 
 int sncc_argmax(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uint32_t *d_s2,
@@ -2334,10 +2360,12 @@ int enqueue_stage(sncc_batch *b, int stage, hipStream_t st) {
         SNCC_FAIL(SNCC_EDEVICE, "sum-table launch");
       return SNCC_OK;
     case 1:
-      if (launch_zero(a.queue, a.n_zero, st) != 0 ||
-          launch_tile(pd.h.cfg, kSinkTopk, a, pd.h.grid, pd.h.lds_bytes, st) != 0)
+      // the segment form for the pairs the filter does not serve
+      if (!pd.h.order.empty() &&
+          (launch_zero(a.queue, a.n_zero, st) != 0 ||
+           launch_tile(pd.h.cfg, kSinkTopk, a, pd.h.grid, pd.h.lds_bytes, st) != 0))
         SNCC_FAIL(SNCC_EDEVICE, "scoring launch");
-      if (b->edge) {
+      if (b->edge && !b->edge->h.order.empty()) {
         // the last columns start from the floors the main launch published
         PlanDev &pe = *b->edge;
         TileArgs ae = pe.args(d.d_s, d.d_s2, fs, d.sat_pitch, d.M, d.N);
@@ -2346,9 +2374,14 @@ int enqueue_stage(sncc_batch *b, int stage, hipStream_t st) {
             launch_tile(pe.h.cfg, kSinkTopk, ae, pe.h.grid, pe.h.lds_bytes, st) != 0)
           SNCC_FAIL(SNCC_EDEVICE, "scoring launch (last columns)");
       }
+      if (pd.f.active())
+        CHK(run_filter(st, d.coarse, pd.f, d.d_s, d.d_s2, fs, d.sat_pitch, d.k, false, d.d_topk, 0));
       return SNCC_OK;
     case 2:
-      if (launch_merge(pd.d_pairs.as<PairDesc>(),
+      if (pd.f.active())
+        CHK(run_filter(st, d.coarse, pd.f, d.d_s, d.d_s2, fs, d.sat_pitch, d.k, false, d.d_topk, 1));
+      if ((!pd.h.order.empty() || (b->edge && !b->edge->h.order.empty())) &&
+          launch_merge(pd.d_pairs.as<PairDesc>(),
                        b->edge ? b->edge->d_pairs.as<PairDesc>() : nullptr, d.n_pairs, a.partial,
                        b->edge ? b->edge->d_partial.as<unsigned long long>() : nullptr, d.k,
                        d.d_topk, st) != 0)
@@ -2594,13 +2627,29 @@ int sncc_batch_create(sncc_ctx *ctx, const sncc_batch_desc *desc, sncc_batch **o
                kRefineSpanU, kRefineSpanV);
     plan_refine_order(b->plan->h, d.k, d.radius);
   }
-  CHK(b->plan->upload(ctx->stream));
   if (any_edge) {
     b->edge.reset(new PlanDev());
     CHK(build_plan(d.coarse, edge_cfg, d.M, d.N, d.sat_pitch, d.n_pairs, b->pairs.data(), d.k,
                    kSinkTopk, ctx->num_cu, b->edge->h, nullptr, kSplitEdge, main_tc.bu()));
-    CHK(b->edge->upload(ctx->stream));
   }
+  // the filter for the pairs it pays for (no memory for it: none)
+  FilterPlan &f = b->plan->f;
+  std::vector<char> use =
+      filter_pairs(ctx, d.coarse, d.M, d.N, d.n_pairs, b->pairs.data(), d.k, false, true);
+  if (std::find(use.begin(), use.end(), 1) != use.end()) {
+    plan_filter(ctx, d.coarse, d.M, d.N, d.sat_pitch, d.n_pairs, b->pairs.data(), d.k, false,
+                &b->plan->h, use, f, kFilterBatchFloats, any_edge ? &b->edge->h : nullptr);
+    if (f.chunks.empty() || upload_filter(f, d.k, false, ctx->stream) != SNCC_OK) {
+      f.~FilterPlan();
+      new (&f) FilterPlan();
+      g_err.clear();
+    } else {
+      drop_items(b->plan->h, use);
+      if (any_edge) drop_items(b->edge->h, use);
+    }
+  }
+  CHK(b->plan->upload(ctx->stream));
+  if (any_edge) CHK(b->edge->upload(ctx->stream));
   HIPCHK(hipStreamSynchronize(ctx->stream));
 
   HIPCHK(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));

@@ -611,6 +611,10 @@ __global__ __launch_bounds__(256) void merge_kernel(const PairDesc *__restrict__
   const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (p >= n_pairs) return;
   const PairDesc pd = pairs[p];
+  // a pair without work items has its list from elsewhere (the filter)
+  if (pd.item_begin == pd.item_end &&
+      (!pairs2 || pairs2[p].item_begin == pairs2[p].item_end))
+    return;
   u64 lkey = 0, thr = 0;
   // one load brings the partial lists of g = 64 / k items (lane l holds key
   // l mod k of item l / k), and the next load is issued before the current

@@ -319,7 +319,9 @@ struct FilterPair {
   int frame, pair;         // pair: index in the call's list
   long long map0;          // first value in the scratch map
   int block0, n_blocks;    // blocks (waves of tiles) of the pair
-  int seq0, n_seq;         // FP32: records of the segment form's sum (SeqRec)
+  // FP32: records of the segment form's sum (SeqRec), [0], and of the offsets
+  // from column u_split on, which a batch's second launch scores, [1]
+  int seq0[2], n_seq[2], u_split;
   int seg_off, K;          // FP64: the segments
   double r64;
   float error;             // bound on |filter - exact| from its rounded c
@@ -347,7 +349,7 @@ constexpr int kFilterCands = 512;
 // number (-1: left to the direct form), row-major indices, keys of the accurate
 // values, and of the reference's.
 struct FilterSpread {
-  int n, m;
+  int n, m;                // m: scored by the reference
   int cand[kFilterCands];
   unsigned long long val[kFilterCands], key[kFilterCands];
 };
@@ -355,7 +357,7 @@ struct FilterSpread {
 // One pair of the direct form: every offset by the reference arithmetic.
 struct SeqPair {
   int frame, nu, nv, W, H, n, sq_rows;
-  int seq0, n_seq, seg_off, K;
+  int seq0[2], n_seq[2], u_split, seg_off, K;
   int chunk0, n_chunks;    // partial lists
   double q_k, r64;
 };

@@ -103,8 +103,9 @@ struct OrderedLds {
   float scale[NP];
 };
 
-// FP32 reference values of the candidates c0 .. c0 + NP - 1 (those below n) by
-// a workgroup of NP + 1 waves, as keys.  The terms are added in the segment
+// FP32 reference values of the candidates c0 .. c0 + NP - 1 (those below n,
+// whose sums all have the pair's records of kind `side`) by a workgroup of
+// NP + 1 waves, as keys.  The terms are added in the segment
 // form's order, a chain of one addition after the other: waves 0 .. NP - 1 take
 // a candidate each and form its terms G_i = F_i - A_i b, a lane per record,
 // kRefChunk records ahead, and the last wave adds them, a lane per candidate,
@@ -115,10 +116,10 @@ __device__ __forceinline__ void ordered_group(const uint32_t *__restrict__ S,
                                               const uint32_t *__restrict__ S2, int P,
                                               const FilterPair &fp,
                                               const SeqRec *__restrict__ seq, const int *cand,
-                                              int c0, int n, OrderedLds<NP> &sh, u64 *key,
-                                              int wave, int lane) {
-  const SeqRec *sr = seq + fp.seq0;
-  const int n_seq = fp.n_seq, nu = fp.a.nu;
+                                              int c0, int n, int side, OrderedLds<NP> &sh,
+                                              u64 *key, int wave, int lane) {
+  const SeqRec *sr = seq + fp.seq0[side];
+  const int n_seq = fp.n_seq[side], nu = fp.a.nu;
   const bool mine = wave < NP && c0 + wave < n;  // wave 0's always is
   const uint32_t *w = S;
   int nb0 = 0;
@@ -186,8 +187,10 @@ __device__ __forceinline__ void ordered_group(const uint32_t *__restrict__ S,
 
 // From the keys of n candidates' accurate values, one wave: the candidates
 // within twice the FP32 reference's error of the k-th largest, listed in
-// `near`; returns their number.
-__device__ __forceinline__ int near_kth(const u64 *key, int n, int k, int *near, int lane) {
+// `near`, those left of column u_split (m_main of them) first; returns their
+// number.
+__device__ __forceinline__ int near_kth(const u64 *key, int n, int k, int nu, int u_split,
+                                        int *near, int *m_main, int lane) {
   u64 lk = 0;
   for (int c = 0; c < n; c += 64)
     topk_merge_sorted(lk, wave_sort_desc_u64(c + lane < n ? key[c + lane] : 0, lane), k, lane);
@@ -195,13 +198,16 @@ __device__ __forceinline__ int near_kth(const u64 *key, int n, int k, int *near,
   const float t = kth == 0 ? -__builtin_inff()
                            : float_unorder((uint32_t)(kth >> 32)) - 2.f * (3e-6f + 1e-7f);
   int m = 0;
-  for (int c = 0; c < n; c += 64) {
-    const u64 x = c + lane < n ? key[c + lane] : 0;
-    const u64 keep = __ballot(x != 0 && float_unorder((uint32_t)(x >> 32)) >= t);
-    if ((keep >> lane) & 1)
-      near[m + __popcll(keep & ((1ull << lane) - 1))] =
-          (int)(0xffffffffu - (uint32_t)(x & 0xffffffffu));
-    m += __popcll(keep);
+  for (int side = 0; side < 2; ++side) {
+    for (int c = 0; c < n; c += 64) {
+      const u64 x = c + lane < n ? key[c + lane] : 0;
+      const int idx = (int)(0xffffffffu - (uint32_t)(x & 0xffffffffu));
+      const u64 keep = __ballot(x != 0 && float_unorder((uint32_t)(x >> 32)) >= t &&
+                                (idx % nu >= u_split) == (side == 1));
+      if ((keep >> lane) & 1) near[m + __popcll(keep & ((1ull << lane) - 1))] = idx;
+      m += __popcll(keep);
+    }
+    if (side == 0) *m_main = m;
   }
   return m;
 }
@@ -393,13 +399,20 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
     }
     __syncthreads();
     if (wave == 0) {
-      const int m = near_kth(key_hi, n, k, cand, lane);
-      if (lane == 0) n_cand = m;
+      int m_main = 0;
+      const int m = near_kth(key_hi, n, k, nu, fp.u_split, cand, &m_main, lane);
+      if (lane == 0) {
+        n_cand = m;
+        n_list = m_main;
+      }
     }
     __syncthreads();
     n = n_cand;
-    for (int c0 = 0; c0 < n; c0 += kRefGroup)
-      ordered_group<kRefGroup>(S, S2, P, fp, seq, cand, c0, n, group, key_hi, wave, lane);
+    const int n_main = n_list;
+    for (int c0 = 0; c0 < n_main; c0 += kRefGroup)
+      ordered_group<kRefGroup>(S, S2, P, fp, seq, cand, c0, n_main, 0, group, key_hi, wave, lane);
+    for (int c0 = n_main; c0 < n; c0 += kRefGroup)
+      ordered_group<kRefGroup>(S, S2, P, fp, seq, cand, c0, n, 1, group, key_hi, wave, lane);
   }
   __syncthreads();
   if (wave != 0) return;
@@ -469,25 +482,29 @@ __global__ __launch_bounds__(64 * (kSpreadNP + 1)) void filter_order(
     FilterSpread *__restrict__ spread) {
   __shared__ OrderedLds<kSpreadNP> group;
   __shared__ int near[kFilterCands];
-  __shared__ int n_near;
+  __shared__ int n_near, n_near_main;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int f = blockIdx.x / kSpreadWgs, part = blockIdx.x % kSpreadWgs;
   const FilterPair &fp = fps[f];
   FilterSpread &sp = spread[f];
   if (sp.n < 0) return;
   if (wave == 0) {  // every workgroup of the pair lists the same ones
-    const int m = near_kth(sp.val, sp.n, k, near, lane);
+    int m_main = 0;
+    const int m = near_kth(sp.val, sp.n, k, fp.a.nu, fp.u_split, near, &m_main, lane);
     if (lane == 0) {
       n_near = m;
+      n_near_main = m_main;
       if (part == 0) sp.m = m;
     }
   }
   __syncthreads();
   const uint32_t *S = s + (long long)fp.frame * frame_stride;
   const uint32_t *S2 = s2 + (long long)fp.frame * frame_stride;
-  const int n = n_near;
-  for (int c0 = part * kSpreadNP; c0 < n; c0 += kSpreadWgs * kSpreadNP)
-    ordered_group<kSpreadNP>(S, S2, P, fp, seq, near, c0, n, group, sp.key, wave, lane);
+  const int n = n_near, n_main = n_near_main;
+  for (int c0 = part * kSpreadNP; c0 < n_main; c0 += kSpreadWgs * kSpreadNP)
+    ordered_group<kSpreadNP>(S, S2, P, fp, seq, near, c0, n_main, 0, group, sp.key, wave, lane);
+  for (int c0 = n_main + part * kSpreadNP; c0 < n; c0 += kSpreadWgs * kSpreadNP)
+    ordered_group<kSpreadNP>(S, S2, P, fp, seq, near, c0, n, 1, group, sp.key, wave, lane);
 }
 
 __global__ __launch_bounds__(64) void filter_result(const FilterPair *__restrict__ fps,
@@ -527,12 +544,13 @@ int launch_filter_select(bool fp64, const uint32_t *s, const uint32_t *s2, long 
 // rho of one offset per thread by the reference arithmetic.
 __device__ __forceinline__ float lane_ref32(const uint32_t *__restrict__ S,
                                             const uint32_t *__restrict__ S2, int P, int u, int v,
-                                            const SeqPair &sp, const SeqRec *__restrict__ seq) {
+                                            const SeqPair &sp, const SeqRec *__restrict__ seq,
+                                            int side) {
   const Ref32 rf = ref32(S, S2, P, u, v, sp.W, sp.H, sp.n, sp.sq_rows, sp.q_k);
   const char *w = reinterpret_cast<const char *>(S + (long long)v * P + u);
   float acc = 0.f, cmp = 0.f, y = -cmp;
-  const SeqRec *sr = seq + sp.seq0;
-  for (int i = 0; i < sp.n_seq; i += 8) {
+  const SeqRec *sr = seq + sp.seq0[side];
+  for (int i = 0; i < sp.n_seq[side]; i += 8) {
     uint32_t prev = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -618,7 +636,13 @@ __global__ __launch_bounds__(256) void seq_topk(
               if (ch == mh && cl == ml) ch = 0, cl = 0;
             }
           } else {
-            const float r = lane_ref32(S, S2, P, u, v, sp, seq);
+            float r = 0.f;  // either side of u_split only where the wave has offsets there
+            const bool right = u >= sp.u_split;
+            if (__ballot(!right)) r = lane_ref32(S, S2, P, u, v, sp, seq, 0);
+            if (__ballot(right)) {
+              const float r1 = lane_ref32(S, S2, P, u, v, sp, seq, 1);
+              r = right ? r1 : r;
+            }
             u64 cnd[1] = {ok ? make_key(r, (int)e) : 0};
             topk_offer<1>(lh, cnd, k, lane);
           }

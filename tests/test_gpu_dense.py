@@ -245,3 +245,51 @@ def test_fp32_lists_of_both_forms_in_one_call(S, ctx, monkeypatch):
         got = _lists(S, ctx, monkeypatch, "", [f], segs, W, H, pairs, k, S.SNCC_FP32_KAHAN)
         want = _lists(S, ctx, monkeypatch, "0", [f], segs, W, H, pairs, k, S.SNCC_FP32_KAHAN)
         assert (got == want).all()
+
+
+@pytest.mark.parametrize("M", [420, 640 + 33])
+def test_filtered_batch_is_the_direct_batch(S, ctx, monkeypatch, M):
+    """A batch with the filter for all its pairs, with none, and by rule gives
+    the same lists, refined matches and counts, also in the last tile columns
+    that a second launch scores."""
+    import torch
+    N, k = 300, 12
+    frames = [synth.scene(40 + i, M, N) for i in range(3)]
+    rng = np.random.default_rng(41)
+    coarse, fine, W, H = [], [], [], []
+    for w, h in ((21, 30), (33, 33), (64, 90), (150, 40), (40, 24)):
+        t, _, _ = synth.crop_template(rng, frames[len(W) % 3], w, h, sigma_max=9)
+        coarse.append(S.sncc_segment_template(t, 9)[0])
+        fine.append(S.sncc_segment_template(t, 3)[0])
+        W.append(w)
+        H.append(h)
+    pairs = [(f, t) for f in range(3) for t in range(5)]
+    got = []
+    for form in ("0", "1", ""):
+        print("case", M, "form", form, flush=True)
+        monkeypatch.setenv("SNCC_TEST_DENSE", form)
+        f = torch.from_numpy(np.stack(frames)).cuda()
+        s = torch.zeros((3, N + 1, S.sncc_sat_pitch(M)), dtype=torch.int32, device="cuda")
+        s2 = torch.zeros_like(s)
+        ct = S.sncc_upload_templates(ctx, coarse, W, H)
+        ft = S.sncc_upload_templates(ctx, fine, W, H)
+        top = torch.zeros((len(pairs), k, 3), dtype=torch.int32, device="cuda")
+        best = torch.zeros((len(pairs), 4), dtype=torch.int32, device="cuda")
+        count = torch.zeros(len(pairs), dtype=torch.int32, device="cuda")
+        b = S.sncc_batch_create(ctx, ct, s, s2, 3, M, N, pairs, k, top, fine=ft, radius=2,
+                                best_out=best, count_out=count, frames=f)
+        one = []
+        for _ in range(3):  # replays with the program's own work between them
+            for x in (top, best, count):
+                x.fill_(3)
+            b.run()
+            S.sncc_sync(ctx)
+            one.append([x.cpu().numpy() for x in (top, best, count)])
+        for x in one[1:]:
+            assert all((p == q).all() for p, q in zip(one[0], x))
+        got.append(one[0])
+        b.destroy()
+        S.sncc_tmpl_destroy(ct)
+        S.sncc_tmpl_destroy(ft)
+    for x in got[1:]:
+        assert all((p == q).all() for p, q in zip(got[0], x))
