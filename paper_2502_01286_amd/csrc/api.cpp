@@ -1221,11 +1221,12 @@ void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair
 // Launch shape of the matrix-core form for a map of nu x nv offsets: false
 // where it does not apply.  Rows per wave half: eight where the tiles then
 // still fill the CUs twice (FP32; 3840 x 2160, 128 x 128: 309 us against 343
-// with four and 493 with two when this was chosen), else four while they fill them once (1920 x
-// 1080, 64 x 64: 37.7 us, 45.6 with eight, 45.7 with two; FP64, at most four
-// for its 28 accumulators a row: while they fill 5/8), else two (640 x 480, 32
-// x 32: 10.6 us, 15.7 with four); for several pairs in one launch, as given (rv).
-// LDS for two workgroups per CU, three where one pass over the template fits.
+// with four and 493 with two, in the kernel as it was when this was chosen),
+// else four while they fill them once (1920 x 1080, 64 x 64: 37.7 us, 45.6 with
+// eight, 45.7 with two; FP64, at most four for its 28 accumulators a row: while
+// they fill 5/8), else two (640 x 480, 32 x 32: 10.6 us, 15.7 with four); for
+// several pairs in one launch, as given (rv).  LDS for two workgroups per CU,
+// three where one pass over the template fits.
 bool dense_shape(const sncc_tmpl *tm, int t, int digits, int nu, int nv, int num_cu,
                  DenseArgs &a, int rv = 0) {
   const int W = tm->W[t], H = tm->H[t], rows_all = 4 * dense_rows4(H);
@@ -1660,6 +1661,62 @@ int dense_map(sncc_ctx *ctx, const sncc_tmpl *tm, int t, const uint32_t *s, cons
   return 1;
 }
 
+// Whether a map straight from the frame is faster in the matrix-core form than
+// in the forms it competes with: `local` the tile-local one, else the frame's
+// tables and then the segment form or the matrix-core form from tables.
+// Estimates in us, fitted to 105 calls measured each way on one MI355X (this
+// form / the other): 640 x 480 with 32 x 32 at K 21 12.4 / 17.3 (tile-local),
+// 64 x 64 at K 983 19.2 / 29.2; 1920 x 1080 with 64 x 64 at K 24 38.9 / 45.2,
+// K 1005 38.8 / 58.2; 3840 x 2160 with 32 x 32 at K 5 66 / 80, 64 x 64 at K 6
+// 142 / 88, 24 x 96 at K 526 135 / 117.  A frame too small to fill the CUs
+// takes one workgroup's time, which grows with the template.
+bool dense_frame_wins(const sncc_tmpl *tm, int t, int M, int N, int num_cu, bool local,
+                      const DenseArgs &a) {
+  const double off = (double)a.nu * a.nv * 1e-6, mac = dense_macs(a);
+  const double one = 2e-3 * (double)a.H * a.G * 16, K = tm->K[t];
+  const double frame = std::max(10.0 + one, 8.0 + off * (4.5 + 2.4e-3 * mac));
+  if (local) return frame < 8.0 + 0.2 * K + 1.1e-3 * (a.W + 64.0) * (a.H + 16.0);
+  const double tables = 15.0 + 2.5e-6 * M * N;
+  DenseArgs d{};
+  if (dense_shape(tm, t, 3, a.nu, a.nv, num_cu, d) && dense_wins(tm, t, d))
+    return frame < tables + std::max(one, off * (d.rv == 8 ? 3.7 + 1.7e-3 * dense_macs(d)
+                                                           : 6.0 + 2.4e-3 * dense_macs(d)));
+  return frame <
+         tables + std::max(0.16 * K, off * (0.22 * K + 4e-4 * (a.W + 128.0) * (a.H + 32.0)));
+}
+
+// A map straight from the frame in the matrix-core form: 1 when it ran, 0 when
+// the call belongs to another form, or an error.
+int dense_frame_map(sncc_ctx *ctx, const sncc_tmpl *tm, int t, const uint8_t *f, int M, int N,
+                    int f_pitch, bool local, float *rho, int rho_pitch, uint8_t *degen,
+                    long long *energy) {
+  const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
+  const int forced = dense_forced();
+  DenseArgs a{};
+  int P = 0;
+  sncc_sat_pitch(M, &P);
+  if ((long long)(N + 1) * P * 4 > (long long)SNCC_MAX_TABLE_BYTES || tm->digits32[t] != 3 ||
+      tm->H[t] > 257 || (long long)tm->W[t] * tm->H[t] > kMaxSqBoxArea ||
+      !dense_shape(tm, t, 3, nu, nv, ctx->num_cu, a))
+    return 0;
+  if (a.rv > 4 && !dense_shape(tm, t, 3, nu, nv, ctx->num_cu, a, 4)) return 0;
+  a.hb = 4 * dense_rows4(a.H);
+  if (dense_frame_lds(a) > (size_t)kTileMaxLds / 2 - 256) return 0;
+  if (forced >= 0 ? forced == 0 : !dense_frame_wins(tm, t, M, N, ctx->num_cu, local, a)) return 0;
+  const DenseTmpl *dt = dense_built(tm, t, 3);
+  if (!dt) {
+    dense_build(ctx, tm, {{t, 3}});
+    if (!(dt = dense_built(tm, t, 3))) return 0;
+  }
+  dense_constants(tm, t, *dt, N, 0, a);
+  a.rho = rho;
+  a.rho_pitch = rho_pitch;
+  a.degen = degen;
+  if (launch_dense_frame(a, f, M, f_pitch, energy, ctx->stream) != 0)
+    SNCC_FAIL(SNCC_EDEVICE, "matrix-core launch: %s", hipGetErrorString(hipGetLastError()));
+  return 1;
+}
+
 }  // namespace
 
 // ================================================================ C-ABI
@@ -2051,6 +2108,17 @@ int sncc_score_frame(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint8_
       (form == SNCC_FORM_AUTO && local_ok && tm->K[index] <= kTileLocalMaxK &&
        (long long)nu * nv <= kTileLocalMaxOffsets);
   const int used = local ? SNCC_FORM_TILE_LOCAL : SNCC_FORM_GLOBAL;
+  // automatic and global form: the same values without tables where faster
+  const int dense = form == SNCC_FORM_TILE_LOCAL
+                        ? 0
+                        : dense_frame_map(ctx, tm, index, d_f, M, N, f_pitch, local, d_rho,
+                                          rho_pitch, d_degenerate,
+                                          reinterpret_cast<long long *>(d_energy));
+  if (dense < 0) return dense;
+  if (dense) {
+    if (form_used) *form_used = used;
+    return SNCC_OK;
+  }
   if (used == SNCC_FORM_TILE_LOCAL) {
     FusedArgs a;
     a.f = d_f;

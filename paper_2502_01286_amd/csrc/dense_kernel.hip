@@ -115,8 +115,9 @@ int launch_dense_pack(const int4 *geom, const double *c64, int K, double scale, 
 // pixel as f - 128 in a byte, `pitch` bytes per row.  Pixels come from the sum
 // table: f(x, y) is the one-pixel box sum of Eq. (11).  A thread walks down a
 // stripe of rows with four columns, RB rows of table entries requested at a
-// time (a stripe is 20 to 40 rows: the staging is a few memory latencies).  Table rows past N and entries past the pitch are clamped: only
-// offsets outside the valid range and zero rows of A use such pixels.
+// time (a stripe is 20 to 40 rows: the staging is a few memory latencies).
+// Table rows past N and entries past the pitch are clamped: only offsets
+// outside the valid range and zero rows of A use such pixels.
 template <int NT, int RB>
 __device__ __forceinline__ void dense_region(const uint32_t *__restrict__ S, int P, int N, int x0,
                                              int y0, int rows, int n4, int pitch,
@@ -173,12 +174,13 @@ __device__ __forceinline__ v4u_a4 dense_row4(const uint32_t *__restrict__ p, int
 // of a.hb, whose frame rows are staged in LDS.  Per step a wave loads D
 // operands A (from the caches: every wave of the launch reads the same ones)
 // and min(RV, 4) operands B (LDS) for D RV instructions.
-template <int D, int RV, int NW>
-__device__ __forceinline__ void dense_products(const uint32_t *__restrict__ S,
-                                               frag_ptr frag, const DenseArgs &a,
-                                               int u0, int v0, int row0, uint8_t *lds8, int lane,
+// `stage(first row, rows, column quads)` stages frame rows below v0.
+template <int D, int RV, int NW, class Stage>
+__device__ __forceinline__ void dense_products(Stage stage, const DenseArgs &a, int row0,
+                                               const uint8_t *lds8, int lane,
                                                v4i (&acc)[RV][D]) {
   constexpr int BV = 2 * NW * RV;
+  const frag_ptr frag = (frag_ptr)a.frag;
   const int j = lane & 7, g = lane >> 4;
 #pragma unroll
   for (int r = 0; r < RV; ++r)
@@ -196,8 +198,7 @@ __device__ __forceinline__ void dense_products(const uint32_t *__restrict__ S,
   for (int yp4 = 0; yp4 < n4all; yp4 += hb4) {
     const int n4 = min(hb4, n4all - yp4);
     if (yp4) __syncthreads();
-    dense_region<64 * NW, (RV >= 8 && D != 2) ? 16 : 8>(S, a.P, a.N, u0, v0 + 4 * yp4, BV + 4 * n4 - 1, 28 + 4 * G, pitch, lds8,
-                          threadIdx.x);
+    stage(4 * yp4, BV + 4 * n4 - 1, 28 + 4 * G);
     __syncthreads();
     // A of the pass's steps in order, the last one's again after it
     frag_ptr fa = frag + (long long)yp4 * (D * 64) + lane;
@@ -336,8 +337,7 @@ __device__ __forceinline__ double dense_num(const v4i (&acc)[D], int k, uint32_t
 
 template <int D, int RV, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dense_kernel(
-    const uint32_t *__restrict__ S, const uint32_t *__restrict__ S2,
-    DenseArgs a) {
+    const uint32_t *__restrict__ S, const uint32_t *__restrict__ S2, DenseArgs a) {
   extern __shared__ __align__(16) uint8_t lds8[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // tiles row by row, a contiguous range of them per XCD (workgroups go round
@@ -348,7 +348,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int tv = tile / a.ntu, u0 = (tile - tv * a.ntu) * kDenseBU, v0 = tv * 2 * NW * RV;
   const int row0 = RV * (2 * wave + ((lane >> 3) & 1));  // the lane's first offset row
   v4i acc[RV][D];
-  dense_products<D, RV, NW>(S, (frag_ptr)a.frag, a, u0, v0, row0, lds8, lane, acc);
+  auto stage = [&](int y, int rows, int n4) {
+    dense_region<64 * NW, (RV >= 8 && D != 2) ? 16 : 8>(S, a.P, a.N, u0, v0 + y, rows, n4, a.pitch,
+                                                        lds8, threadIdx.x);
+  };
+  dense_products<D, RV, NW>(stage, a, row0, lds8, lane, acc);
 
   const int u = u0 + 16 * (lane & 7) + 4 * (lane >> 4);
   dense_windows<RV, false>(S, S2, a, u0, u, v0 + row0, [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
@@ -404,7 +408,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int u0 = (tile - tv * a.ntu) * kDenseBU, v0 = tv * 2 * NW * RV;
   const int row0 = RV * (2 * wave + ((lane >> 3) & 1));
   v4i acc[RV][D];
-  dense_products<D, RV, NW>(S, (frag_ptr)a.frag, a, u0, v0, row0, lds8, lane, acc);
+  auto stage = [&](int y, int rows, int n4) {
+    dense_region<64 * NW, (RV >= 8 && D != 2) ? 16 : 8>(S, a.P, a.N, u0, v0 + y, rows, n4, a.pitch,
+                                                        lds8, threadIdx.x);
+  };
+  dense_products<D, RV, NW>(stage, a, row0, lds8, lane, acc);
 
   const int u = u0 + 16 * (lane & 7) + 4 * (lane >> 4);
   const double low = (double)a.n * (double)a.n * 0.01;
@@ -428,6 +436,181 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   });
   const uint32_t m = wave_incl_max(float_order(top)), ml = wave_incl_max(float_order(top_low));
   if (lane == 63) bmax[fp.block0 + block] = make_float2(float_unorder(m), float_unorder(ml));
+}
+
+// ------------------------------------------------------- straight from a frame
+// Rows [y0, y0 + rows) x columns [x0, x0 + 4 n4) of the frame to LDS as f - 128
+// (rows past the frame as its last, columns past it as 0).
+template <int NT>
+__device__ __forceinline__ void frame_region(const uint8_t *__restrict__ f, int M, int N,
+                                             int f_pitch, int x0, int y0, int rows, int n4,
+                                             int pitch, uint8_t *__restrict__ lds, int t) {
+  const int ns = max(1, NT / n4), per = (rows + ns - 1) / ns;
+  for (int unit = t; unit < n4 * ns; unit += NT) {
+    const int stripe = unit / n4, c4 = unit - stripe * n4, x = x0 + 4 * c4;
+    const int ra = stripe * per, rb = min(rows, ra + per);
+    typedef uint32_t u32_a1 __attribute__((aligned(1)));
+    auto px4 = [&](int r) {
+      const uint8_t *row = f + (size_t)min(r, N - 1) * f_pitch;
+      if (x + 3 < M) return (uint32_t)*reinterpret_cast<const u32_a1 *>(row + x);
+      uint32_t w = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (x + q < M) w |= (uint32_t)row[x + q] << (8 * q);
+      return w;
+    };
+    for (int r = ra; r < rb; r += 16) {
+      uint32_t w[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) w[k] = px4(y0 + min(r + k, rb - 1));
+#pragma unroll
+      for (int k = 0; k < 16; ++k)
+        if (r + k < rb)
+          *reinterpret_cast<uint32_t *>(lds + (r + k) * pitch + 4 * c4) = w[k] ^ 0x80808080u;
+    }
+  }
+}
+
+// A rho map from the frame itself, for templates whose region fits one pass and
+// whose windows are one exact box of squares: no tables are built, which for a
+// small frame are two launches more and most of the time.  The windows' sums
+// come from the staged region: each column's sums of f and f^2 over H rows for
+// every offset row (a thread takes four columns of some rows: the first H rows
+// added up, then one row added and one taken off per step), then running sums
+// along each row, in 32-bit modular arithmetic as in the tables.
+// What bounds it: one workgroup's chain of staging, sums, scans and matrix
+// steps where the frame is small (640 x 480, 32 x 32: 12.4 us a call, where the
+// tile-local form took 17.3 at K 21 and tables and a map 21.9; 64 x 64: 19.3
+// against 29.2), the matrix steps on larger ones (1920 x 1080, 64 x 64: 38.8
+// against 58.2).
+template <int RV, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dense_frame(
+    const uint8_t *__restrict__ f, int M, int f_pitch, DenseArgs a,
+    long long *__restrict__ energy) {
+  extern __shared__ __align__(16) uint8_t lds8[];
+  constexpr int D = 3, BV = 2 * NW * RV, NT = 64 * NW;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int tv = (int)blockIdx.x / a.ntu;
+  const int u0 = ((int)blockIdx.x - tv * a.ntu) * kDenseBU, v0 = tv * BV;
+  const int row0 = RV * (2 * wave + ((lane >> 3) & 1));
+  const int C = 112 + 16 * a.G, sp = C + 4;  // region columns; pitch of the sums (words)
+  uint32_t *const ps = reinterpret_cast<uint32_t *>(lds8 + (BV + a.hb - 1) * a.pitch);
+  uint32_t *const pq = ps + BV * sp;
+  v4i acc[RV][D];
+  auto stage = [&](int y, int rows, int n4) {
+    frame_region<NT>(f, M, a.N, f_pitch, u0, v0 + y, rows, n4, a.pitch, lds8, t);
+    __syncthreads();
+    // sums over H rows: column c of offset row v at [v][c + 1]
+    const int nq = C / 4, ns = max(1, NT / nq), per = (BV + ns - 1) / ns;
+    for (int unit = t; unit < nq * ns; unit += NT) {
+      const int stripe = unit / nq, q4 = unit - stripe * nq;
+      const int va = stripe * per, vb = min(BV, va + per);
+      const uint8_t *col = lds8 + 4 * q4;
+      uint32_t lo = 0, hi = 0, in[4] = {0, 0, 0, 0}, gone[4] = {0, 0, 0, 0};
+      auto px = [&](int r) {
+        return *reinterpret_cast<const uint32_t *>(col + r * a.pitch) ^ 0x80808080u;
+      };
+      auto squares = [&](uint32_t w, uint32_t(&s)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t m = w & (0xffu << (8 * q));
+          s[q] = __builtin_amdgcn_udot4(m, m, s[q], false);
+        }
+      };
+      auto add = [&](uint32_t w) {  // f as two 16-bit halves of a word: H <= 257 rows
+        lo += w & 0x00ff00ffu;
+        hi += (w >> 8) & 0x00ff00ffu;
+        squares(w, in);
+      };
+      if (va < vb) {
+#pragma unroll 8
+        for (int r = 0; r < a.H; ++r) add(px(va + r));
+        for (int v = va;; ++v) {
+          const uint32_t s[4] = {lo & 0xffffu, hi & 0xffffu, lo >> 16, hi >> 16};
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            ps[v * sp + 4 * q4 + 1 + q] = s[q];
+            pq[v * sp + 4 * q4 + 1 + q] = in[q] - gone[q];
+          }
+          if (v + 1 >= vb) break;
+          const uint32_t w = px(v);
+          lo -= w & 0x00ff00ffu;
+          hi -= (w >> 8) & 0x00ff00ffu;
+          squares(w, gone);
+          add(px(v + a.H));
+        }
+      }
+    }
+    __syncthreads();
+    // running sums along the rows, in place
+    for (int i = wave; i < 2 * BV; i += NW) {
+      uint32_t *row = ps + i * sp;  // the rows of pq follow those of ps
+      if (lane == 0) row[0] = 0;
+      uint32_t carry = 0;
+      for (int c0 = 0; c0 < C; c0 += 256) {
+        const int c = c0 + 4 * lane;
+        uint32_t p[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) p[q] = (q ? p[q - 1] : 0u) + (c < C ? row[1 + c + q] : 0u);
+        const uint32_t incl = wave_incl_scan(p[3]), base = carry + incl - p[3];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (c < C) row[1 + c + q] = base + p[q];
+        carry += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+      }
+    }
+  };
+  dense_products<D, RV, NW>(stage, a, row0, lds8, lane, acc);
+
+  const int ul = 16 * (lane & 7) + 4 * (lane >> 4), u = u0 + ul;
+  const double n = (double)a.n;
+#pragma unroll
+  for (int r = 0; r < RV; ++r) {
+    const int v = v0 + row0 + r;
+    const uint32_t *sr = ps + (row0 + r) * sp + ul, *qr = pq + (row0 + r) * sp + ul;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t sf = sr[a.W + k] - sr[k];   // Eq. (13)
+      const uint32_t sf2 = qr[a.W + k] - qr[k];  // Eq. (15)
+      const double fs = (double)sf, V = __builtin_fma(n, (double)sf2, -(fs * fs));
+      const double e = V * a.qnd, y = (double)__builtin_amdgcn_rsqf((float)e);
+      double rho = dense_num<D>(acc[r], k, sf, a) * (y * __builtin_fma(-0.5 * e * y, y, 1.5));
+      if (V == 0.0) rho = 0.0;
+      if (v < a.nv && u + k < a.nu) {
+        const long long o = (long long)v * a.rho_pitch + u + k;
+        static_cast<float *>(a.rho)[o] = (float)rho;
+        if (a.degen) a.degen[o] = V == 0.0 ? 1 : 0;
+        if (energy) energy[o] = (long long)V;
+      }
+    }
+  }
+}
+
+template <int RV, int NW>
+static int frame_go(const DenseArgs &a, const uint8_t *f, int M, int f_pitch, long long *energy,
+                    hipStream_t st) {
+  static bool attr = false;
+  const void *fn = (const void *)dense_frame<RV, NW>;
+  if (!attr) {
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kTileMaxLds) !=
+        hipSuccess)
+      return -1;
+    attr = true;
+  }
+  const size_t lds = dense_frame_lds(a);
+  hipLaunchKernelGGL((dense_frame<RV, NW>), dim3(a.ntu * a.ntv), dim3(64 * NW), lds, st, f, M,
+                     f_pitch, a, energy);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_dense_frame(const DenseArgs &a, const uint8_t *f, int M, int f_pitch,
+                       long long *energy, hipStream_t st) {
+  if (a.digits != 3) return -1;
+  switch (a.rv) {
+    case 2: return frame_go<2, kDenseNW>(a, f, M, f_pitch, energy, st);
+    case 4: return frame_go<4, kDenseNW>(a, f, M, f_pitch, energy, st);
+    default: return -1;
+  }
 }
 
 template <int D, int RV, int NW>

@@ -312,6 +312,13 @@ struct DenseArgs {
   int rho_pitch;
   uint8_t *degen;
 };
+// LDS of the form straight from a frame: the staged region, then the windows'
+// sums of f and f^2 (running along 112 + 16 G columns of each offset row).
+inline size_t dense_frame_lds(const DenseArgs &a) {
+  const size_t bv = (size_t)2 * kDenseNW * a.rv;
+  return (bv + a.hb - 1) * a.pitch + 2 * bv * (112 + 16 * a.G + 4) * 4;
+}
+
 // Top-k by filter and rescoring (dense_filter, topk_filter.hip).  One pair of
 // the filter; `a` as for a map, less the tables.
 struct FilterPair {
@@ -367,6 +374,8 @@ struct SeqPair {
 int launch_dense_pack(const int4 *geom, const double *c64, int K, double scale, int W, int H,
                       int digits, long long *img, void *frag, hipStream_t st) SNCC_WEAK;
 int launch_dense(const DenseArgs &a, hipStream_t st) SNCC_WEAK;
+int launch_dense_frame(const DenseArgs &a, const uint8_t *f, int M, int f_pitch,
+                       long long *energy, hipStream_t st) SNCC_WEAK;
 int launch_dense_filter(int digits, int rv, const uint32_t *s, const uint32_t *s2,
                         long long frame_stride, const FilterPair *fps, const int2 *items,
                         int n_items, int lds, float *map, float2 *bmax, hipStream_t st) SNCC_WEAK;

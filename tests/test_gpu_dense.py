@@ -113,6 +113,45 @@ def test_dense_map_launch_shapes(S, ctx, monkeypatch, rows):
     S.sncc_tmpl_destroy(tm)
 
 
+# one-pass templates and their neighbours: heights at the 16-bit sums' limit of
+# 257 rows and past it, regions near the LDS limit, odd frame pitches, one
+# offset row and column
+@pytest.mark.parametrize("size", SIZES[:9] + [(90, 400, 12, 257), (90, 400, 12, 258),
+                                              (700, 40, 500, 8), (641, 479, 31, 33),
+                                              (1921, 1081, 64, 64), (200, 180, 180, 170)])
+def test_dense_frame(S, ctx, monkeypatch, size):
+    """The map straight from the frame: rho against the oracle, flags and
+    energies exactly."""
+    import torch
+    M, N, W, H = size
+    f, t = _case(M * 3 + N, M, N, W, H, "crop")
+    if M * N < 1 << 20:
+        f[N // 2:] |= 0xF0  # bright rows: the largest sums
+    segs, _, _ = S.sncc_segment_template(t, 2.0)
+    ta = O.precompute_template_approximation(t, 2.0)
+    tm = S.sncc_upload_templates(ctx, [segs], [W], [H])
+    nu, nv = M - W + 1, N - H + 1
+    vv, uu = np.meshgrid(np.arange(nv), np.arange(nu), indexing="ij")
+    tables = O.sum_tables(f)
+    _, _, V = O.window_sums(*tables, W, H, uu, vv)
+    d = torch.from_numpy(np.ascontiguousarray(f)).cuda()
+    for form in "01":
+        print("case", size, "form", form, flush=True)
+        monkeypatch.setenv("SNCC_TEST_DENSE", form)
+        rho = torch.full((nv, nu + 3), 7.0, dtype=torch.float32, device="cuda")
+        deg = torch.full((nv, nu + 3), 9, dtype=torch.uint8, device="cuda")
+        en = torch.full((nv, nu + 3), -1, dtype=torch.int64, device="cuda")
+        S.sncc_score_frame(ctx, tm, 0, d, rho, form=S.SNCC_FORM_GLOBAL, degen=deg, energy=en)
+        S.sncc_sync(ctx)
+        r, g, e = rho.cpu().numpy(), deg.cpu().numpy(), en.cpu().numpy()
+        assert (r[:, nu:] == 7).all() and (g[:, nu:] == 9).all() and (e[:, nu:] == -1).all()
+        assert np.array_equal(e[:, :nu], V) and np.array_equal(g[:, :nu], V == 0)
+        us, vs = (uu, vv) if M * N < 1 << 20 else (uu[::37, ::5], vv[::37, ::5])
+        want = O.rho_at(*tables, ta, us.ravel(), vs.ravel()).reshape(us.shape)
+        assert np.abs(r[vs, us] - want).max() <= 1e-5
+    S.sncc_tmpl_destroy(tm)
+
+
 def test_fp64_map_under_capture(S, monkeypatch):
     """An FP64 map captured before its operands exist, and one after: both
     graphs replay to the oracle's map."""
