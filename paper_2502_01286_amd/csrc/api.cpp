@@ -192,11 +192,13 @@ struct sncc_tmpl {
   std::vector<std::vector<double>> c64;
   std::vector<double> q_k, r64;
   std::vector<DevTmpl> dev;  // generic (plain / refine) descriptors
-  DevBuf d_geom, d_c64, d_area, d_dev, d_c32;
+  DevBuf d_area, d_dev, d_c32;
+  // shared with the plans that read them: a plan may outlive the set
+  std::shared_ptr<DevBuf> d_geom = std::make_shared<DevBuf>(), d_c64 = std::make_shared<DevBuf>();
   // built on demand by calls that take the set as const, from any thread
   mutable std::mutex dense_mu;
   mutable std::unique_ptr<DenseTmpl[]> dense;  // kDenseForms per template (dense_form)
-  mutable std::vector<std::unique_ptr<DevBuf>> dense_bufs;
+  mutable std::vector<std::shared_ptr<DevBuf>> dense_bufs;
   mutable size_t dense_bytes = 0;
 };
 
@@ -844,6 +846,9 @@ struct FilterPlan {
   size_t map_floats = 0, blocks = 0;
   size_t spread_fps = 0;        // most pairs of a spread chunk
   DevBuf d_fps, d_items, d_seq, d_pairs, d_direct, d_map, d_bmax, d_partial, d_spread;
+  // the template set's memory that the launches read: a batch outlives the set
+  std::shared_ptr<DevBuf> d_geom, d_c64;
+  std::vector<std::shared_ptr<DevBuf>> operands;
   bool active() const { return !pairs.empty(); }
 };
 
@@ -1196,7 +1201,14 @@ void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
     return;
-  std::unique_ptr<DevBuf> buf(new (std::nothrow) DevBuf());
+  // (another stream of the caller's may be captured meanwhile: memory and the
+  // wait below stay allowed on this thread and out of that graph)
+  struct Relaxed {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  } relaxed;
+  std::shared_ptr<DevBuf> buf(new (std::nothrow) DevBuf());
   if (!buf || buf->reserve(bytes + image) != SNCC_OK) {
     g_err.clear();
     return;
@@ -1204,8 +1216,8 @@ void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair
   char *base = buf->as<char>();
   bool ok = true;
   for (const Job &j : jobs)
-    ok = ok && launch_dense_pack(tm->d_geom.as<int4>() + tm->seg_off[j.t],
-                                 tm->d_c64.as<double>() + tm->seg_off[j.t], tm->K[j.t],
+    ok = ok && launch_dense_pack(tm->d_geom->as<int4>() + tm->seg_off[j.t],
+                                 tm->d_c64->as<double>() + tm->seg_off[j.t], tm->K[j.t],
                                  j.made.scale, tm->W[j.t], tm->H[j.t], j.made.digits,
                                  reinterpret_cast<long long *>(base + bytes), base + j.at,
                                  ctx->stream) == 0;
@@ -1495,6 +1507,12 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
     offsets += (long long)nu * nv;
     most = std::max(most, (long long)nu * nv);
   }
+  f.d_geom = tm->d_geom;
+  f.d_c64 = tm->d_c64;
+  {
+    std::lock_guard<std::mutex> lk(tm->dense_mu);
+    f.operands = tm->dense_bufs;
+  }
   // lists of the direct form: short enough to spread a pair over the chip,
   // long enough that the lists of all pairs stay within 64 MB
   const size_t key = fp64 ? sizeof(Key96) : 8;
@@ -1593,11 +1611,10 @@ int upload_filter(FilterPlan &f, int k, bool fp64, hipStream_t st) {
 
 // Enqueues the filter (part 0: all but the last selection) and the last
 // selection and the direct form (part 1).
-int run_filter(hipStream_t st, const sncc_tmpl *tm, FilterPlan &f, const uint32_t *s,
-               const uint32_t *s2, long long fs, int P, int k, bool fp64, sncc_match *out,
-               int part) {
-  const int4 *geom = tm->d_geom.as<int4>();
-  const double *c64 = tm->d_c64.as<double>();
+int run_filter(hipStream_t st, FilterPlan &f, const uint32_t *s, const uint32_t *s2,
+               long long fs, int P, int k, bool fp64, sncc_match *out, int part) {
+  const int4 *geom = f.d_geom->as<int4>();
+  const double *c64 = f.d_c64->as<double>();
   bool ok = true;
   for (size_t i = 0; i < f.chunks.size(); ++i) {
     const FilterChunk &c = f.chunks[i];
@@ -1971,8 +1988,8 @@ int sncc_upload_templates(sncc_ctx *ctx, int T, const sncc_segment *const *segs,
     tm->error_f.push_back(error);
   }
   std::vector<float> c32all(c64all.begin(), c64all.end());
-  CHK(tm->d_geom.upload(geom, ctx->stream));
-  CHK(tm->d_c64.upload(c64all, ctx->stream));
+  CHK(tm->d_geom->upload(geom, ctx->stream));
+  CHK(tm->d_c64->upload(c64all, ctx->stream));
   CHK(tm->d_c32.upload(c32all, ctx->stream));
   CHK(tm->d_area.upload(areas, ctx->stream));
   CHK(tm->d_dev.upload(tm->dev, ctx->stream));
@@ -2038,8 +2055,8 @@ int sncc_score(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint32_t *d_
     a.sq_rows = tm->dev[index].sq_rows;
     a.q_k = tm->q_k[index];
     a.r64 = tm->r64[index];
-    a.geom = tm->d_geom.as<int4>() + tm->seg_off[index];
-    a.c64 = tm->d_c64.as<double>() + tm->seg_off[index];
+    a.geom = tm->d_geom->as<int4>() + tm->seg_off[index];
+    a.c64 = tm->d_c64->as<double>() + tm->seg_off[index];
     a.area = tm->d_area.as<int>() + tm->seg_off[index];
     a.rho = static_cast<double *>(d_rho);
     a.rho_pitch = rho_pitch;
@@ -2130,7 +2147,7 @@ int sncc_score_frame(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint8_
     a.K = tm->K[index];
     a.nu = nu;
     a.nv = nv;
-    a.geom = tm->d_geom.as<int4>() + tm->seg_off[index];
+    a.geom = tm->d_geom->as<int4>() + tm->seg_off[index];
     a.area = tm->d_area.as<int>() + tm->seg_off[index];
     a.c32 = tm->d_c32.as<float>() + tm->seg_off[index];
     a.q_k = tm->q_k[index];
@@ -2209,13 +2226,13 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
         launch_tile(pd->h.cfg, kSinkTopk, a, pd->h.grid, pd->h.lds_bytes, ctx->stream) != 0)
       SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
     if (filtered)
-      CHK(run_filter(ctx->stream, tm, pd->f, d_s, d_s2, fs, sat_pitch, k, false, d_out, 0));
+      CHK(run_filter(ctx->stream, pd->f, d_s, d_s2, fs, sat_pitch, k, false, d_out, 0));
     ctx->mark(1);
     if (tiles && launch_merge(pd->d_pairs.as<PairDesc>(), nullptr, n_pairs, a.partial, nullptr, k,
                               d_out, ctx->stream) != 0)
       SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
     if (filtered)
-      CHK(run_filter(ctx->stream, tm, pd->f, d_s, d_s2, fs, sat_pitch, k, false, d_out, 1));
+      CHK(run_filter(ctx->stream, pd->f, d_s, d_s2, fs, sat_pitch, k, false, d_out, 1));
     ctx->mark(2);
     if (ctx->timing) ctx->n_stages = 2;
     return SNCC_OK;
@@ -2242,7 +2259,7 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
     return upload_filter(d.f, k, true, ctx->stream);
   }, &pd, false));
   for (int part = 0; part < 2; ++part)
-    CHK(run_filter(ctx->stream, tm, pd->f, d_s, d_s2, fs, sat_pitch, k, true, d_out, part));
+    CHK(run_filter(ctx->stream, pd->f, d_s, d_s2, fs, sat_pitch, k, true, d_out, part));
   return SNCC_OK;
 }
 
@@ -2293,7 +2310,7 @@ int sncc_refine(sncc_ctx *ctx, const sncc_tmpl *fine, const uint32_t *d_s, const
   CHK(pd->d_slot_w.upload(h.slot_w, ctx->stream));
   CHK(pd->d_refine_order.upload(h.refine_order, ctx->stream));
   if (launch_refine(d_s, d_s2, (long long)(N + 1) * sat_pitch, sat_pitch,
-                    fine->d_dev.as<DevTmpl>(), fine->d_geom.as<int4>(), fine->d_c64.as<double>(),
+                    fine->d_dev.as<DevTmpl>(), fine->d_geom->as<int4>(), fine->d_c64->as<double>(),
                     pd->slots(), pd->d_pairs.as<PairDesc>(), n_pairs, d_cand, n_cand, radius,
                     d_out, d_count, ctx->stream) != 0)
     SNCC_FAIL(SNCC_EDEVICE, "refine launch: %s", hipGetErrorString(hipGetLastError()));
@@ -2361,8 +2378,8 @@ int sncc_threshold_match(sncc_ctx *ctx, const sncc_tmpl *fast, const sncc_tmpl *
   sa.P = sat_pitch;
   sa.N = N;
   sa.tmpls = slow->d_dev.as<DevTmpl>();
-  sa.geom = slow->d_geom.as<int4>();
-  sa.c64 = slow->d_c64.as<double>();
+  sa.geom = slow->d_geom->as<int4>();
+  sa.c64 = slow->d_c64->as<double>();
   sa.stmpl = pd->d_slow.as<SlowTmpl>();
   sa.slot_off = pd->d_slot_off.as<uint32_t>();
   sa.slot_w = pd->d_slot_w.as<double>();
@@ -2443,11 +2460,11 @@ int enqueue_stage(sncc_batch *b, int stage, hipStream_t st) {
           SNCC_FAIL(SNCC_EDEVICE, "scoring launch (last columns)");
       }
       if (pd.f.active())
-        CHK(run_filter(st, d.coarse, pd.f, d.d_s, d.d_s2, fs, d.sat_pitch, d.k, false, d.d_topk, 0));
+        CHK(run_filter(st, pd.f, d.d_s, d.d_s2, fs, d.sat_pitch, d.k, false, d.d_topk, 0));
       return SNCC_OK;
     case 2:
       if (pd.f.active())
-        CHK(run_filter(st, d.coarse, pd.f, d.d_s, d.d_s2, fs, d.sat_pitch, d.k, false, d.d_topk, 1));
+        CHK(run_filter(st, pd.f, d.d_s, d.d_s2, fs, d.sat_pitch, d.k, false, d.d_topk, 1));
       if ((!pd.h.order.empty() || (b->edge && !b->edge->h.order.empty())) &&
           launch_merge(pd.d_pairs.as<PairDesc>(),
                        b->edge ? b->edge->d_pairs.as<PairDesc>() : nullptr, d.n_pairs, a.partial,
@@ -2458,7 +2475,7 @@ int enqueue_stage(sncc_batch *b, int stage, hipStream_t st) {
     case 3:
       if (d.fine &&
           launch_refine(d.d_s, d.d_s2, fs, d.sat_pitch, d.fine->d_dev.as<DevTmpl>(),
-                        d.fine->d_geom.as<int4>(), d.fine->d_c64.as<double>(), pd.slots(),
+                        d.fine->d_geom->as<int4>(), d.fine->d_c64->as<double>(), pd.slots(),
                         pd.d_pairs.as<PairDesc>(), d.n_pairs, d.d_topk,
                         d.k, d.radius, d.d_best, d.d_count, st) != 0)
         SNCC_FAIL(SNCC_EDEVICE, "refine launch");

@@ -332,3 +332,34 @@ def test_filtered_batch_is_the_direct_batch(S, ctx, monkeypatch, M):
         S.sncc_tmpl_destroy(ft)
     for x in got[1:]:
         assert all((p == q).all() for p, q in zip(got[0], x))
+
+
+def test_batch_outlives_its_templates(S, ctx, monkeypatch):
+    """A batch owns what its launches read of the coarse set: runs after the
+    set is destroyed, and others have taken its memory, give the same lists."""
+    import torch
+    M, N, k = 400, 300, 6
+    f = synth.scene(70, M, N)
+    rng = np.random.default_rng(71)
+    temps = [synth.crop_template(rng, f, w, h, sigma_max=6)[0] for w, h in ((30, 40), (64, 50))]
+    segs = [S.sncc_segment_template(t, 6)[0] for t in temps]
+    W, H = [30, 64], [40, 50]
+    monkeypatch.setenv("SNCC_TEST_DENSE", "1")
+    _, s, s2 = build_sats(S, ctx, [f])
+    d = torch.from_numpy(f[None]).cuda()
+    ct = S.sncc_upload_templates(ctx, segs, W, H)
+    top = torch.zeros((2, k, 3), dtype=torch.int32, device="cuda")
+    b = S.sncc_batch_create(ctx, ct, s, s2, 1, M, N, [(0, 0), (0, 1)], k, top,
+                            frames=d)
+    b.run()
+    S.sncc_sync(ctx)
+    want = top.clone()
+    S.sncc_tmpl_destroy(ct)
+    others = [S.sncc_upload_templates(ctx, segs[::-1], W[::-1], H[::-1]) for _ in range(8)]
+    top.zero_()
+    b.run()
+    S.sncc_sync(ctx)
+    assert torch.equal(top, want) and int(want[0, 0, 0]) >= 0
+    b.destroy()
+    for o in others:
+        S.sncc_tmpl_destroy(o)
