@@ -852,10 +852,25 @@ struct FilterPlan {
   bool active() const { return !pairs.empty(); }
 };
 
+// The two-threshold search's filter: the slow approximations' rough maps as
+// bits, for the tiles with many survivors of the fast pass.
+struct AbovePlan {
+  std::vector<FilterPair> fps;
+  std::vector<int2> items;
+  std::vector<FilterLaunch> launches;
+  std::vector<int> fp_of_pair, tile0;  // -1: not filtered; first tile counter
+  int rv = 8, n_tiles = 0;
+  size_t words = 0;
+  DevBuf d_fps, d_items, d_fp_of_pair, d_tile0, d_bits, d_live;
+  std::vector<std::shared_ptr<DevBuf>> operands;
+  bool active() const { return !fps.empty(); }
+};
+
 // Device copy of a plan plus its completion event.
 struct PlanDev {
   PlanHost h;
   FilterPlan f;
+  AbovePlan above;
   DevBuf d_tmpls, d_passes, d_ivs, d_recs, d_pairs, d_items, d_order, d_qbeg, d_queue,
       d_partial, d_thr, d_slow, d_slot_off, d_slot_w, d_runs, d_refine_order;
   hipEvent_t done = nullptr;
@@ -895,10 +910,11 @@ struct PlanDev {
                       h.refine_lds_first};
   }
   // work counters, then one floor key per pair (top-k sink) or the run and
-  // slow-pass counters (compacting sink), zeroed per launch
+  // slow-pass counters and those of the tiles (compacting sink), zeroed per
+  // launch
   int zero_ints() const {
     return kQueueInts + (h.sink == kSinkTopk ? 2 * (int)h.pairs.size()
-                                             : h.sink == kSinkCompact ? 16 : 0);
+                                             : h.sink == kSinkCompact ? 16 + above.n_tiles : 0);
   }
   TileArgs args(const uint32_t *s, const uint32_t *s2, long long fs, int P, int M, int N) {
     TileArgs a;
@@ -925,11 +941,15 @@ struct PlanDev {
     a.pair_floor =
         h.sink == kSinkTopk ? reinterpret_cast<unsigned long long *>(a.queue + kQueueInts)
                             : nullptr;
-    a.co = CompactOut{nullptr, 0, nullptr, nullptr, 0, nullptr};
+    a.co = CompactOut{nullptr, 0, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
     if (h.sink == kSinkCompact) {
       a.co.runs = d_runs.as<RunDesc>();
       a.co.run_cap = h.run_cap;
       a.co.run_count = a.queue + kQueueInts;
+      if (above.active()) {
+        a.co.tile_count = a.queue + kQueueInts + 16;
+        a.co.tile0 = above.d_tile0.as<int>();
+      }
     }
     a.n_zero = zero_ints();
     a.rho = nullptr;
@@ -1607,6 +1627,104 @@ int upload_filter(FilterPlan &f, int k, bool fp64, hipStream_t st) {
   CHK(f.d_pairs.upload(f.pairs, st));
   CHK(f.d_direct.upload(f.direct, st));
   return SNCC_OK;
+}
+
+// Plans the two-threshold search's filter beside the fast pass's plan `h`
+// (nothing where it does not pay or cannot be had).  Estimates in ps: the filter
+// 4 + 1.25e-3 matrix products per offset of a tile, the slow pass 0.026 words of
+// a run's region and 0.19 K per survivor.  A tile is filtered when its survivors
+// cost twice the filter's time (some are left to the slow pass, and two launches
+// more).  Measured (us a call of 2 frames 1920 x 1080, without / with): 64 x 64,
+// K 1217 to 1863, 2.0 million survivors 1125 / 480; K 593 to 2041, 0.66 million
+// 571 / 415; 92 x 92, K 315 to 4794 919 / 490; 49 x 49, K 96 to 1242 578 / 430;
+// 35 x 35, K 56 to 742, many matches, with every tile filtered 461 / 482.  A
+// call whose slow pass would take less than the filter's shortest time, were 15
+// per cent of the offsets survivors, goes without (8 pairs of 324 x 200 with 96 x
+// 96 175 / 195).
+int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, int P, int n_pairs,
+               const int32_t *pairs, const double *thr, AbovePlan &f) {
+  const int forced = dense_forced();
+  if (forced == 0 || h.tc.bu() != kDenseBU || h.tc.bv() != kFastRows ||
+      kRunCols * h.tc.rv > kRunMax)
+    return SNCC_OK;
+  long long tiles8 = 0;
+  for (const PairDesc &q : h.pairs) tiles8 += (long long)q.ntu * ((q.nv + 63) / 64);
+  f.rv = tiles8 >= 2LL * ctx->num_cu ? 8 : 2 * tiles8 >= ctx->num_cu ? 4 : 2;
+  const int bv = 2 * kDenseNW * f.rv;
+  std::vector<std::pair<int, int>> want;
+  std::vector<int> limit(slow->T, -1);  // survivors a tile needs; -1: not filtered
+  double gain = 0, floor_us = 0;
+  for (int p = 0; p < n_pairs; ++p) {
+    const int t = pairs[2 * p + 1];
+    const double spared = 0.026 * (slow->H[t] + 4.0) * (slow->W[t] + kRunCols + 1.0) +
+                          0.19 * slow->K[t];
+    gain += 0.15e-6 * h.pairs[p].nu * h.pairs[p].nv * spared;
+    DenseArgs a{};
+    if (limit[t] >= 0 || !slow->digits_f[t] ||
+        !dense_shape(slow, t, slow->digits_f[t], h.pairs[p].nu, h.pairs[p].nv, ctx->num_cu, a,
+                     f.rv))
+      continue;
+    const double tile = (double)kDenseBU * bv, mac = 0.5 * a.digits * dense_macs(a);
+    floor_us = std::max(floor_us, 20.0 + 2e-3 * mac);
+    const double need = 2.0 * tile * (4.0 + 1.25e-3 * mac) / spared;
+    if (forced != 1 && need > 0.25 * tile) continue;
+    limit[t] = forced == 1 ? 1 : std::max(1, (int)need);
+    want.emplace_back(t, slow->digits_f[t]);
+  }
+  if (want.empty() || (forced != 1 && gain < floor_us)) return SNCC_OK;
+  dense_build(ctx, slow, want);
+  f.fp_of_pair.assign(n_pairs, -1);
+  f.tile0.assign(n_pairs, 0);
+  f.launches.clear();
+  for (int p = 0; p < n_pairs; ++p) {
+    f.tile0[p] = f.n_tiles;
+    f.n_tiles += h.pairs[p].ntu * h.pairs[p].ntv;
+  }
+  for (int digits = 2; digits <= 3; ++digits) {
+    FilterLaunch l{digits, f.rv, (int)f.items.size(), 0, 0};
+    for (int p = 0; p < n_pairs; ++p) {
+      const int t = pairs[2 * p + 1];
+      const DenseTmpl *dt = limit[t] >= 0 && slow->digits_f[t] == digits
+                                ? dense_built(slow, t, digits)
+                                : nullptr;
+      if (!dt) continue;
+      const PairDesc &q = h.pairs[p];
+      FilterPair fp{};
+      if (!dense_shape(slow, t, digits, q.nu, q.nv, ctx->num_cu, fp.a, f.rv)) continue;
+      dense_constants(slow, t, *dt, N, P, fp.a);
+      const int tiles = fp.a.ntu * fp.a.ntv;
+      fp.pair = p;
+      fp.frame = pairs[2 * p];
+      fp.map0 = (long long)f.words;
+      fp.block0 = f.tile0[p];
+      fp.n_blocks = q.ntv;
+      fp.min_count = limit[t];
+      // less the filter's error and its FP32 roundings, rounded down
+      fp.above = std::nextafter((float)(thr[t] - slow->error_f[t] - 2e-6), -2e30f);
+      f.words += (size_t)tiles * kDenseNW * 64;
+      l.lds = std::max(l.lds, (bv + fp.a.hb - 1) * fp.a.pitch);
+      const int per = (tiles + 7) / 8, local = (int)f.fps.size();
+      for (int x = 0; x < per * 8; ++x) {  // as in plan_filter
+        const int tile_i = x % 8 * per + x / 8;
+        f.items.push_back(make_int2(tile_i < tiles ? local : -1, tile_i));
+      }
+      f.fp_of_pair[p] = local;
+      f.fps.push_back(fp);
+    }
+    l.n_items = (int)f.items.size() - l.item0;
+    if (l.n_items > 0) f.launches.push_back(l);
+  }
+  if (f.fps.empty()) return SNCC_OK;
+  {
+    std::lock_guard<std::mutex> lk(slow->dense_mu);
+    f.operands = slow->dense_bufs;
+  }
+  CHK(f.d_bits.reserve(f.words * 4));
+  CHK(f.d_live.reserve(std::max<size_t>(16, (size_t)h.run_cap * sizeof(LiveRun))));
+  CHK(f.d_fps.upload(f.fps, ctx->stream));
+  CHK(f.d_items.upload(f.items, ctx->stream));
+  CHK(f.d_fp_of_pair.upload(f.fp_of_pair, ctx->stream));
+  return f.d_tile0.upload(f.tile0, ctx->stream);
 }
 
 // Enqueues the filter (part 0: all but the last selection) and the last
@@ -2356,6 +2474,12 @@ int sncc_threshold_match(sncc_ctx *ctx, const sncc_tmpl *fast, const sncc_tmpl *
     CHK(build_plan(fast, 0, M, N, sat_pitch, n_pairs, pairs, 1, kSinkCompact, ctx->num_cu, d.h,
                    thr_fast));
     plan_slow(slow, d.h.tc, d.h);
+    if (plan_above(ctx, slow, d.h, N, sat_pitch, n_pairs, pairs, thr_slow, d.above) != SNCC_OK ||
+        !d.above.active()) {
+      d.above.~AbovePlan();  // no operands, or no memory for it
+      new (&d.above) AbovePlan();
+      g_err.clear();
+    }
     std::vector<double> ts(thr_slow, thr_slow + slow->T);
     return d.d_thr.upload(ts, ctx->stream);
   }, &pd));
@@ -2395,6 +2519,24 @@ int sncc_threshold_match(sncc_ctx *ctx, const sncc_tmpl *fast, const sncc_tmpl *
   sa.out = d_out;
   sa.out_cap = out_cap;
   sa.out_count = d_counts + 1;
+  sa.live = nullptr;
+  sa.live_count = nullptr;
+  AbovePlan &f = pd->above;
+  if (f.active()) {
+    int *n_live = a.queue + kQueueInts + 12;
+    bool ok = true;
+    for (const FilterLaunch &l : f.launches)
+      ok = ok && launch_dense_above(l.digits, l.rv, d_s, d_s2, fs, f.d_fps.as<FilterPair>(),
+                                    f.d_items.as<int2>() + l.item0, l.n_items, l.lds,
+                                    a.co.tile_count, f.d_bits.as<uint32_t>(), ctx->stream) == 0;
+    const int grid = std::max(1, std::min((pd->h.run_cap + 15) / 16, 8 * ctx->num_cu));
+    if (!ok || launch_live_runs(sa, f.d_fps.as<FilterPair>(), f.d_fp_of_pair.as<int>(), f.rv,
+                                a.co.tile_count, f.d_bits.as<uint32_t>(), f.d_live.as<LiveRun>(),
+                                n_live, grid, ctx->stream) != 0)
+      SNCC_FAIL(SNCC_EDEVICE, "threshold search launch: %s", hipGetErrorString(hipGetLastError()));
+    sa.live = f.d_live.as<LiveRun>();
+    sa.live_count = n_live;
+  }
   const int slow_lds = pd->h.slow_lds;
   const int slow_grid = std::max(1, std::min(pd->h.run_cap, ctx->num_cu * slow_occupancy(slow_lds)));
   if (launch_slow(sa, slow_grid, slow_lds, ctx->stream) != 0)

@@ -438,6 +438,53 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   if (lane == 63) bmax[fp.block0 + block] = make_float2(float_unorder(m), float_unorder(ml));
 }
 
+// The two-threshold search's filter: which offsets of the tiles that hold many
+// survivors of the fast pass can reach the slow threshold, as one bit each, in
+// one word per lane (bit 4 r + k: row r, column k of the lane's offsets).  Two
+// digits of c and a margin of their error decide, so that the slow pass in FP64
+// sees a few per cent of the survivors (2 frames 1920 x 1080 x 4 templates 64 x
+// 64, 1.69 million survivors: 92 us here, the slow pass 810 -> 58 us).
+template <int D, int RV, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dense_above(
+    const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride,
+    const FilterPair *__restrict__ fps, const int2 *__restrict__ items,
+    const int *__restrict__ tile_count, uint32_t *__restrict__ bits) {
+  extern __shared__ __align__(16) uint8_t lds8[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int2 it = items[blockIdx.x];
+  if (it.x < 0) return;
+  const FilterPair &fp = fps[it.x];
+  const int tile = it.y, tv = tile / fp.a.ntu, tu = tile - tv * fp.a.ntu;
+  if (tile_survivors(fp, tile_count, tu, tv, 2 * NW * RV) < fp.min_count) return;
+  const DenseArgs a = fp.a;
+  const uint32_t *S = s + (long long)fp.frame * frame_stride;
+  const uint32_t *S2 = s2 + (long long)fp.frame * frame_stride;
+  const int u0 = tu * kDenseBU, v0 = tv * 2 * NW * RV;
+  const int row0 = RV * (2 * wave + ((lane >> 3) & 1));
+  v4i acc[RV][D];
+  auto stage = [&](int y, int rows, int n4) {
+    dense_region<64 * NW, (RV >= 8 && D != 2) ? 16 : 8>(S, a.P, a.N, u0, v0 + y, rows, n4, a.pitch,
+                                                        lds8, threadIdx.x);
+  };
+  dense_products<D, RV, NW>(stage, a, row0, lds8, lane, acc);
+
+  const int u = u0 + 16 * (lane & 7) + 4 * (lane >> 4);
+  const float above = fp.above;
+  uint32_t word = 0;
+  dense_windows<RV, D == 2>(S, S2, a, u0, u, v0 + row0,
+                            [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float num = (float)dense_num<D>(acc[r], k, sf[k], a);
+      const float y = __builtin_amdgcn_rsqf((float)(V[k] * a.qnd));
+      const float rho = V[k] == 0.0 ? 0.f : num * y;
+      word |= (rho >= above ? 1u : 0u) << (4 * r + k);
+    }
+    asm volatile("" : "+v"(word));  // row by row: all rows' loads at once would spill
+  });
+  bits[fp.map0 + (long long)(tile * NW + wave) * 64 + lane] = word;
+}
+
 // ------------------------------------------------------- straight from a frame
 // Rows [y0, y0 + rows) x columns [x0, x0 + 4 n4) of the frame to LDS as f - 128
 // (rows past the frame as its last, columns past it as 0).
@@ -673,6 +720,43 @@ int launch_dense_filter(int digits, int rv, const uint32_t *s, const uint32_t *s
     SNCC_FILTER(3, 4);
     SNCC_FILTER(3, 2);
 #undef SNCC_FILTER
+    default: return -1;
+  }
+}
+
+template <int D, int RV, int NW>
+static int above_go(const uint32_t *s, const uint32_t *s2, long long frame_stride,
+                    const FilterPair *fps, const int2 *items, int n_items, int lds,
+                    const int *tile_count, uint32_t *bits, hipStream_t st) {
+  static bool attr = false;
+  const void *fn = (const void *)dense_above<D, RV, NW>;
+  if (!attr) {
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kTileMaxLds) !=
+        hipSuccess)
+      return -1;
+    attr = true;
+  }
+  hipLaunchKernelGGL((dense_above<D, RV, NW>), dim3(n_items), dim3(64 * NW), lds, st, s, s2,
+                     frame_stride, fps, items, tile_count, bits);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_dense_above(int digits, int rv, const uint32_t *s, const uint32_t *s2,
+                       long long frame_stride, const FilterPair *fps, const int2 *items,
+                       int n_items, int lds, const int *tile_count, uint32_t *bits,
+                       hipStream_t st) {
+  switch (digits * 100 + rv) {
+#define SNCC_ABOVE(D, RV)                                                                       \
+  case D * 100 + RV:                                                                            \
+    return above_go<D, RV, kDenseNW>(s, s2, frame_stride, fps, items, n_items, lds, tile_count, \
+                                     bits, st)
+    SNCC_ABOVE(2, 8);
+    SNCC_ABOVE(2, 4);
+    SNCC_ABOVE(2, 2);
+    SNCC_ABOVE(3, 8);
+    SNCC_ABOVE(3, 4);
+    SNCC_ABOVE(3, 2);
+#undef SNCC_ABOVE
     default: return -1;
   }
 }

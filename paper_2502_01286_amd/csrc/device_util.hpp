@@ -301,4 +301,14 @@ __device__ __forceinline__ u64 window_sq(const uint32_t *__restrict__ a0, int W,
   return acc;
 }
 
+// Survivors of the two-threshold search's fast pass in a tile of its filter
+// (column tu of 128, rows tv bv .. over the fast pass's rows of kFastRows).
+__device__ __forceinline__ int tile_survivors(const FilterPair &fp, const int *tile_count, int tu,
+                                              int tv, int bv) {
+  int n = 0;
+  for (int y = tv * bv / kFastRows; y <= min((tv * bv + bv - 1) / kFastRows, fp.n_blocks - 1); ++y)
+    n += tile_count[fp.block0 + y * fp.a.ntu + tu];
+  return n;
+}
+
 }  // namespace sncc

@@ -981,13 +981,15 @@ __global__ __launch_bounds__(256) void slow_kernel(
     const PairDesc *__restrict__ pairs, const double *__restrict__ thrs,
     const sncc_hit *__restrict__ cand, const int *__restrict__ cand_count, int cand_cap,
     const RunDesc *__restrict__ runs, const int *__restrict__ run_count, int run_cap,
+    const LiveRun *__restrict__ live, const int *__restrict__ live_count,
     int *__restrict__ work, sncc_hit *__restrict__ out, int out_cap,
     int *__restrict__ out_count) {
   extern __shared__ uint32_t region[];
   __shared__ int run_sh;
+  __shared__ uint8_t pick[kRunMax];  // the run's survivors to score
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_cand = min(*cand_count, cand_cap);
-  const int n_runs = min(*run_count, run_cap);
+  const int n_runs = live ? *live_count : min(*run_count, run_cap);
   const int P4 = P * 4;
   const uint32_t bytes = (uint32_t)(frame_stride * 4);
   auto emit = [&](int pair, int u, int v, double rho) {
@@ -1002,20 +1004,33 @@ __global__ __launch_bounds__(256) void slow_kernel(
       out[pos] = o;
     }
   };
-  for (;;) {
-    if (threadIdx.x == 0) run_sh = atomicAdd(work, 1);
-    __syncthreads();
-    const int r = __builtin_amdgcn_readfirstlane(run_sh);
+  // all runs go by a shared counter (their sizes differ much), those the filter
+  // left, with few survivors each, in turn
+  for (int r = blockIdx.x;; r += gridDim.x) {
+    if (!live) {
+      if (threadIdx.x == 0) run_sh = atomicAdd(work, 1);
+      __syncthreads();
+      r = __builtin_amdgcn_readfirstlane(run_sh);
+    }
     if (r >= n_runs) break;
-    const RunDesc rd = runs[r];
-    const int start = rd.start, end = min(rd.start + rd.count, n_cand);
+    const RunDesc rd = live ? live[r].rd : runs[r];
+    const int start = rd.start;
+    int n = max(0, min(rd.count, n_cand - start)), to = threadIdx.x;
+    bool take = to < n;
+    if (live) {
+      const u64 m0 = live[r].m[0], m1 = live[r].m[1], below = (1ull << lane) - 1ull;
+      n = __popcll(m0) + __popcll(m1);
+      take = to < kRunMax && ((wave ? m1 : m0) >> lane & 1ull);
+      to = wave ? __popcll(m0) + __popcll(m1 & below) : __popcll(m0 & below);
+    }
+    if (take) pick[to] = (uint8_t)threadIdx.x;
     const PairDesc pd = pairs[rd.pair];
     const DevTmpl td = tmpls[pd.tmpl];
     const SlowTmpl st = stmpl[pd.tmpl];
     const double thr = thrs[pd.tmpl];
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(s + (long long)pd.frame * frame_stride, bytes);
     const __amdgpu_buffer_rsrc_t rs2 = make_rsrc(s2 + (long long)pd.frame * frame_stride, bytes);
-    if (start < end && st.tbl >= 0) {
+    if (n > 0 && st.tbl >= 0) {
       // region rows [v0, v0 + rows), columns [u0, u0 + pitch), clamped to
       // the table (clamped entries are never read by a window of the run)
       stage_region(rs, P, N, rd.v0, rd.u0, st.rows, st.pitch, st.pitch, region, wave, lane);
@@ -1023,11 +1038,11 @@ __global__ __launch_bounds__(256) void slow_kernel(
       __syncthreads();
       const __amdgpu_buffer_rsrc_t rso = make_rsrc(slot_off + st.tbl, (uint32_t)st.n_iter * 256u);
       const __amdgpu_buffer_rsrc_t rsw = make_rsrc(slot_w + st.tbl, (uint32_t)st.n_iter * 512u);
-      for (int b = start + wave * kSlowBatch; b < end; b += 4 * kSlowBatch) {
+      for (int b = wave * kSlowBatch; b < n; b += 4 * kSlowBatch) {
         int su[kSlowBatch], sv[kSlowBatch], base[kSlowBatch], gof[kSlowBatch];
 #pragma unroll
         for (int j = 0; j < kSlowBatch; ++j) {
-          const sncc_hit h = cand[min(b + j, end - 1)];
+          const sncc_hit h = cand[start + pick[min(b + j, n - 1)]];
           su[j] = h.u;
           sv[j] = h.v;
           base[j] = ((h.v - rd.v0) * st.pitch + (h.u - rd.u0)) * 4;
@@ -1043,21 +1058,22 @@ __global__ __launch_bounds__(256) void slow_kernel(
         const int jj = lane & 3;
         const int uu = jj == 0 ? su[0] : jj == 1 ? su[1] : jj == 2 ? su[2] : su[3];
         const int vv = jj == 0 ? sv[0] : jj == 1 ? sv[1] : jj == 2 ? sv[2] : sv[3];
-        if (lane < kSlowBatch && b + lane < end && rho >= thr) emit(rd.pair, uu, vv, rho);
+        if (lane < kSlowBatch && b + lane < n && rho >= thr) emit(rd.pair, uu, vv, rho);
       }
-    } else if (start < end) {
-      for (int b = start + wave * 64; b < end; b += 256) {
+    } else if (n > 0) {
+      __syncthreads();
+      for (int b = wave * 64; b < n; b += 256) {
         const int c = b + lane;
-        const sncc_hit h = cand[min(c, end - 1)];
+        const sncc_hit h = cand[start + pick[min(c, n - 1)]];
         const int voff = h.v * P4 + h.u * 4;
         const double acc = slow_sum(rs, voff, P4, geom + td.seg_off, c64 + td.seg_off, td.K);
         const uint32_t sf = window_box(rs, voff, 0, td.W * 4, td.H * P4);  // Eq. (13)
         const u64 sf2 = window_sq(rs2, voff, 0, td.W * 4, P4, td.H, td.sq_rows);
         const double rho = slow_rho(acc, sf, sf2, td);
-        if (c < end && rho >= thr) emit(rd.pair, h.u, h.v, rho);
+        if (c < n && rho >= thr) emit(rd.pair, h.u, h.v, rho);
       }
     }
-    __syncthreads();  // region and run_sh are rewritten for the next run
+    __syncthreads();  // region, pick and run_sh are rewritten for the next run
   }
 }
 
@@ -1073,7 +1089,7 @@ int launch_slow(const SlowArgs &a, int grid, int lds_bytes, hipStream_t st) {
   hipLaunchKernelGGL(slow_kernel, dim3(grid), dim3(256), lds_bytes, st, a.s, a.s2,
                      a.frame_stride, a.P, a.N, a.tmpls, a.geom, a.c64, a.stmpl, a.slot_off,
                      a.slot_w, a.pairs, a.thr, a.cand, a.cand_count, a.cand_cap, a.runs,
-                     a.run_count, a.run_cap, a.work, a.out, a.out_cap, a.out_count);
+                     a.run_count, a.run_cap, a.live, a.live_count, a.work, a.out, a.out_cap, a.out_count);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -134,6 +134,18 @@ struct CompactOut {
   RunDesc *runs;   // run_cap entries, one per (tile, wave) with survivors
   int run_cap;
   int *run_count;  // zero at launch
+  // survivors per tile (nullptr: not counted): tile i of pair p adds to
+  // tile_count[tile0[p] + i], zero at launch
+  int *tile_count;
+  const int *tile0;
+};
+
+// A run some of whose survivors the slow pass has to score: bit i of m[i / 64]
+// stands for hits[start + i] (a run holds at most kRunMax).
+constexpr int kRunMax = 128;
+struct LiveRun {
+  unsigned long long m[2];
+  RunDesc rd;
 };
 
 // Slow pass of the two-threshold search.  A template whose region (the
@@ -204,6 +216,8 @@ struct SlowArgs {
   const RunDesc *runs;
   const int *run_count;
   int run_cap;
+  const LiveRun *live;      // the runs to score (nullptr: all of them, entire)
+  const int *live_count;
   int *work;                // run counter, zero at launch
   sncc_hit *out;
   int out_cap;
@@ -332,7 +346,13 @@ struct FilterPair {
   int seg_off, K;          // FP64: the segments
   double r64;
   float error;             // bound on |filter - exact| from its rounded c
+  // two-threshold search (map0: first bit word; block0, n_blocks: first counter
+  // and rows of the fast pass's tiles): tiles with fewer survivors are left to
+  // the slow pass; offsets below `above` cannot reach the threshold
+  int min_count;
+  float above;
 };
+constexpr int kFastRows = 32;  // tile rows of the two-threshold search's fast pass
 
 // One boundary column of the FP32 segment form's chains in its order of
 // summation: byte offsets of the column's entries in the chain's top and bottom
@@ -379,6 +399,13 @@ int launch_dense_frame(const DenseArgs &a, const uint8_t *f, int M, int f_pitch,
 int launch_dense_filter(int digits, int rv, const uint32_t *s, const uint32_t *s2,
                         long long frame_stride, const FilterPair *fps, const int2 *items,
                         int n_items, int lds, float *map, float2 *bmax, hipStream_t st) SNCC_WEAK;
+int launch_dense_above(int digits, int rv, const uint32_t *s, const uint32_t *s2,
+                       long long frame_stride, const FilterPair *fps, const int2 *items,
+                       int n_items, int lds, const int *tile_count, uint32_t *bits,
+                       hipStream_t st) SNCC_WEAK;
+int launch_live_runs(const SlowArgs &a, const FilterPair *fps, const int *fp_of_pair, int rv,
+                     const int *tile_count, const uint32_t *bits, LiveRun *live, int *live_count,
+                     int grid, hipStream_t st) SNCC_WEAK;
 int launch_filter_select(bool fp64, const uint32_t *s, const uint32_t *s2, long long frame_stride,
                          int P, const FilterPair *fps, int n_fps, const float *map,
                          const float2 *bmax, const SeqRec *seq, const int4 *geom,

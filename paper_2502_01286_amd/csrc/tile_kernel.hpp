@@ -319,6 +319,7 @@ __device__ __forceinline__ void run_item(
         int base = 0;
         if (lane == 0) {
           base = atomicAdd(co.count, total);
+          if (co.tile_count) atomicAdd(co.tile_count + co.tile0[it.pair] + tile, total);
           int ri = atomicAdd(co.run_count, n_runs);
           int start = base;
 #pragma unroll

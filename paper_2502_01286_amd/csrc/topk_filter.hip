@@ -66,24 +66,25 @@ __device__ __forceinline__ void ref_step(float &acc, float &cmp, float &y) {
 // and then the wave, and the mean term of Eq. (12) for what b leaves.
 __device__ __forceinline__ double wave_ref64(const uint32_t *__restrict__ S,
                                              const uint32_t *__restrict__ S2, int P, int u, int v,
-                                             const FilterPair &fp, const int4 *__restrict__ geom,
+                                             int W, int H, int sq_rows, double q_k, int K,
+                                             double r64, const int4 *__restrict__ geom,
                                              const double *__restrict__ c64, int lane) {
   const long long o = (long long)v * P + u;
-  const int n = fp.a.n;
-  const uint32_t sf = ref_box(S + o, fp.a.W, fp.a.H, P);
-  const u64 sf2 = window_sq(S2 + o, fp.a.W, fp.a.H, P, fp.a.sq_rows);
+  const int n = W * H;
+  const uint32_t sf = ref_box(S + o, W, H, P);
+  const u64 sf2 = window_sq(S2 + o, W, H, P, sq_rows);
   const long long V = (long long)((u64)(uint32_t)n * sf2 - (u64)sf * sf);
   const double fbar = (double)sf / (double)n;
   const int b = (int)rint(fbar);
   double acc = 0.0;
-  for (int i = lane; i < fp.K; i += 64) {
-    const int4 g = geom[fp.seg_off + i];
+  for (int i = lane; i < K; i += 64) {
+    const int4 g = geom[i];
     const uint32_t F = ref_box(S + o + (long long)g.y * P + g.x, g.z, g.w, P);
-    acc = __builtin_fma((double)((int)F - g.z * g.w * b), c64[fp.seg_off + i], acc);
+    acc = __builtin_fma((double)((int)F - g.z * g.w * b), c64[i], acc);
   }
   for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
-  const double num = acc + ((double)b - fbar) * fp.r64;
-  return V == 0 ? 0.0 : num / sqrt((double)V / (double)n * fp.a.q_k);
+  const double num = acc + ((double)b - fbar) * r64;
+  return V == 0 ? 0.0 : num / sqrt((double)V / (double)n * q_k);
 }
 
 // ----------------------------------------------------------------- selection
@@ -383,7 +384,8 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
     for (int c = wave; c < n; c += kSelThreads / 64) {
       const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
       const int v = idx / nu, u = idx - v * nu;
-      const double r = wave_ref64(S, S2, P, u, v, fp, geom, c64, lane);
+      const double r = wave_ref64(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.sq_rows, fp.a.q_k, fp.K, fp.r64,
+                                  geom + fp.seg_off, c64 + fp.seg_off, lane);
       if (lane == 0) {
         key_hi[c] = double_order(r);
         key_lo[c] = 0xffffffffu - (uint32_t)idx;
@@ -394,7 +396,8 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
     for (int c = wave; c < n; c += kSelThreads / 64) {
       const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
       const int v = idx / nu, u = idx - v * nu;
-      const double r = wave_ref64(S, S2, P, u, v, fp, geom, c64, lane);
+      const double r = wave_ref64(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.sq_rows, fp.a.q_k, fp.K, fp.r64,
+                                  geom + fp.seg_off, c64 + fp.seg_off, lane);
       if (lane == 0) key_hi[c] = make_key((float)r, idx);
     }
     __syncthreads();
@@ -471,7 +474,8 @@ __global__ __launch_bounds__(256) void filter_values(
   for (int c = part * 4 + wave; c < sp.n; c += 4 * kSpreadWgs) {
     const int idx = __builtin_amdgcn_readfirstlane(sp.cand[c]);
     const int v = idx / fp.a.nu, u = idx - v * fp.a.nu;
-    const double r = wave_ref64(S, S2, P, u, v, fp, geom, c64, lane);
+    const double r = wave_ref64(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.sq_rows, fp.a.q_k, fp.K, fp.r64,
+                                  geom + fp.seg_off, c64 + fp.seg_off, lane);
     if (lane == 0) sp.val[c] = make_key((float)r, idx);
   }
 }
@@ -746,6 +750,92 @@ int launch_seq_topk(bool fp64, const uint32_t *s, const uint32_t *s2, long long 
     hipLaunchKernelGGL(seq_merge<false>, mg, dim3(256), 0, st, pairs, n_pairs, direct, partial, k,
                        out);
   }
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// ------------------------------------------------------ two-threshold search
+// Per run of the fast pass's survivors (a wave each), those that the filter
+// leaves or did not judge; runs without any are dropped.  (Scoring a few
+// survivors here, segments over lanes with corners from the tables, was slower
+// than the slow pass at any number of them: 490 against 502 to 760 us a call.)
+__global__ __launch_bounds__(256) void live_runs(
+    const FilterPair *__restrict__ fps, const int *__restrict__ fp_of_pair, int rv,
+    const int *__restrict__ tile_count, const uint32_t *__restrict__ bits,
+    const sncc_hit *__restrict__ cand, const int *__restrict__ cand_count, int cand_cap,
+    const RunDesc *__restrict__ runs, const int *__restrict__ run_count, int run_cap,
+    LiveRun *__restrict__ live, int *__restrict__ live_count) {
+  constexpr int NR = 4;  // runs per wave at a time
+  __shared__ int cnt[2][4], base[2];  // by turns, so that two barriers do
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_cand = min(*cand_count, cand_cap), n_runs = min(*run_count, run_cap);
+  const int bv = 2 * kDenseNW * rv;
+  for (int b = 4 * NR * blockIdx.x, turn = 0; b < n_runs; b += 4 * NR * gridDim.x, turn ^= 1) {
+    const int r0 = b + NR * wave;
+    LiveRun lr[NR];
+    int2 uv[NR][2];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      lr[q].rd = runs[min(r0 + q, n_runs - 1)];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const sncc_hit &c = cand[min(lr[q].rd.start + 64 * h + lane, n_cand - 1)];
+        uv[q][h] = make_int2(c.u, c.v);
+      }
+    }
+    int left = 0;
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const RunDesc &rd = lr[q].rd;
+      const int n = r0 + q < n_runs ? max(0, min(rd.count, n_cand - rd.start)) : 0;
+      lr[q].m[0] = n >= 64 ? ~0ull : (1ull << n) - 1ull;
+      lr[q].m[1] = n >= 128 ? ~0ull : n > 64 ? (1ull << (n - 64)) - 1ull : 0ull;
+      const int at = fp_of_pair[rd.pair];
+      if (at >= 0) {
+        const FilterPair &fp = fps[at];
+        // a run lies inside one tile
+        const int tu = rd.u0 / kDenseBU, tv = rd.v0 / bv;
+        if (tile_survivors(fp, tile_count, tu, tv, bv) >= fp.min_count) {
+          const uint32_t *w = bits + fp.map0 + (long long)(tv * fp.a.ntu + tu) * (kDenseNW * 64);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            bool keep = false;
+            if (64 * h + lane < n) {
+              const int x = uv[q][h].x - tu * kDenseBU, y = uv[q][h].y - tv * bv;
+              const int row = y / rv, l = (x >> 4) + 8 * (row & 1) + 16 * ((x >> 2) & 3);
+              keep = (w[(row >> 1) * 64 + l] >> (4 * (y - row * rv) + (x & 3))) & 1u;
+            }
+            lr[q].m[h] = __ballot(keep);
+          }
+        }
+      }
+      left += (lr[q].m[0] | lr[q].m[1]) != 0;
+    }
+    // one addition to the shared counter for the workgroup's runs: the
+    // additions of many workgroups go one by one (23 thousand runs, most of
+    // them left: 40 us with one per run, 24 with one per sixteen)
+    if (lane == 0) cnt[turn][wave] = left;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const int all = cnt[turn][0] + cnt[turn][1] + cnt[turn][2] + cnt[turn][3];
+      base[turn] = all ? atomicAdd(live_count, all) : 0;
+    }
+    __syncthreads();
+    if (lane == 0) {
+      LiveRun *to = live + base[turn];
+      for (int w = 0; w < wave; ++w) to += cnt[turn][w];
+#pragma unroll
+      for (int q = 0; q < NR; ++q)
+        if ((lr[q].m[0] | lr[q].m[1]) != 0) *to++ = lr[q];
+    }
+  }
+}
+
+int launch_live_runs(const SlowArgs &a, const FilterPair *fps, const int *fp_of_pair, int rv,
+                     const int *tile_count, const uint32_t *bits, LiveRun *live, int *live_count,
+                     int grid, hipStream_t st) {
+  hipLaunchKernelGGL(live_runs, dim3(grid), dim3(256), 0, st, fps, fp_of_pair, rv, tile_count,
+                     bits, a.cand, a.cand_count, a.cand_cap, a.runs, a.run_count, a.run_cap, live,
+                     live_count);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -363,3 +363,56 @@ def test_batch_outlives_its_templates(S, ctx, monkeypatch):
     b.destroy()
     for o in others:
         S.sncc_tmpl_destroy(o)
+
+
+@pytest.mark.parametrize("size", [(160, 120), (512, 333), (1920, 700)])
+@pytest.mark.parametrize("cand_cap", [1 << 20, 1000])
+def test_filtered_threshold_search_is_the_direct_one(S, ctx, monkeypatch, size, cand_cap):
+    """The two-threshold search with the slow pass behind the filter finds the
+    same survivors and matches as without, thresholds at and between the
+    offsets' own values, uniform windows among them, also where the survivor
+    list overflows; its replays too."""
+    import torch
+    M, N = size
+    frames = [synth.scene(80 + i, M, N) for i in range(2)]
+    frames[1][: N // 3, : M // 2] = 50  # uniform windows: rho is 0 there
+    rng = np.random.default_rng(M)
+    temps = [synth.crop_template(rng, frames[0], w, h, sigma_max=9)[0]
+             for w, h in ((33, 25), (64, 61), (90, 100), (17, 48))]
+    fast = [S.sncc_segment_template(t, 9)[0] for t in temps]
+    slow = [S.sncc_segment_template(t, 2)[0] for t in temps]
+    W, H = [t.shape[1] for t in temps], [t.shape[0] for t in temps]
+    _, s, s2 = build_sats(S, ctx, frames)
+    pairs = [(1, 3), (0, 0), (1, 1), (0, 2), (1, 0)]
+    for lo, hi in ((0.1, 0.3), (-2.0, 0.0), (0.2, -2.0)):
+        got = []
+        for form in "01":
+            print("case", size, cand_cap, lo, hi, "form", form, flush=True)
+            monkeypatch.setenv("SNCC_TEST_DENSE", form)
+            ft = S.sncc_upload_templates(ctx, fast, W, H)
+            st = S.sncc_upload_templates(ctx, slow, W, H)
+            cand = torch.zeros((cand_cap, 6), dtype=torch.int32, device="cuda")
+            out = torch.zeros((1 << 20, 6), dtype=torch.int32, device="cuda")
+            counts = torch.zeros(2, dtype=torch.int32, device="cuda")
+            for _ in range(2):
+                S.sncc_threshold_match(ctx, ft, st, np.full(4, lo), np.full(4, hi), s, s2, 2, M, N,
+                                       pairs, cand, out, counts)
+                S.sncc_sync(ctx)
+                nc, nm = (int(x) for x in counts.cpu())
+                c = S.decode_hits(cand, min(nc, cand_cap))
+                o = np.sort(S.decode_hits(out, min(nm, 1 << 20)), order=["pair", "v", "u"])
+                got.append((nc, nm, np.sort(c, order=["pair", "v", "u"]), o))
+            S.sncc_tmpl_destroy(ft)
+            S.sncc_tmpl_destroy(st)
+        for g in got[1:]:
+            assert g[0] == got[0][0] > 0
+            if g[0] > cand_cap:  # which survivors are listed depends on timing
+                assert len(g[2]) == cand_cap
+                continue
+            assert g[1] == got[0][1]
+            for f in ("pair", "u", "v"):
+                assert np.array_equal(g[2][f], got[0][2][f])
+            if g[1] <= 1 << 20:
+                for f in ("pair", "u", "v"):
+                    assert np.array_equal(g[3][f], got[0][3][f])
+                assert np.abs(g[3]["rho"] - got[0][3]["rho"]).max(initial=0) <= 1e-12
