@@ -268,7 +268,14 @@ int sncc_tmpl_count(const sncc_tmpl *tm, int *T);
  *              of its last such call and reuses it when the next has the
  *              same template set, index, sizes and pitch).  SNCC_FP64: d_rho
  *              is double; box sums are accumulated in FP64, one launch per
- *              call.
+ *              call.  Templates of at most 131071 pixels with many segments
+ *              for their size take the matrix-core form in either precision:
+ *              the numerator as an exact integer correlation of the frame
+ *              with the approximation in fixed point (errors no larger than
+ *              the segment sums').  Its operands, about 5 bytes per template
+ *              pixel and digit (3 or 7), are built at the first such call and
+ *              kept with the template set; a call captured into a HIP graph
+ *              before that uses the segment sums.
  *   d_rho      device, (N-H+1) rows x rho_pitch elements (>= M-W+1)
  *   d_degenerate  device, nullable, (N-H+1) x rho_pitch bytes: 1 where the
  *              window is uniform (rho written as 0), else 0
@@ -296,7 +303,9 @@ int sncc_score(sncc_ctx *ctx, const sncc_tmpl *tm, int index,
  * any table origin.  It applies when W * H <= SNCC_MAX_SQ_BOX_AREA, W <= 511
  * and (17 + H) x (pitch class >= 65 + W) words fit 160 KB of LDS (e.g. up to
  * 128 x 128 templates).  The global form builds the frame's tables (context
- * scratch) and runs sncc_score.
+ * scratch) and runs sncc_score.  SNCC_FORM_AUTO and SNCC_FORM_GLOBAL give the
+ * same values by sncc_score's matrix-core form straight from the frame where
+ * that is faster (form_used is then the form it stands in for).
  *
  *   d_f        device, N rows x f_pitch bytes
  *   form       SNCC_FORM_AUTO, SNCC_FORM_TILE_LOCAL (SNCC_ERANGE when the
@@ -319,11 +328,15 @@ int sncc_score_frame(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint8_
  * neighbours.  The order is that of the rho the precision computes: FP32
  * values for SNCC_FP32_KAHAN, the FP64 values themselves for SNCC_FP64 (two
  * offsets whose doubles differ are never tied, even where the reported
- * float rho is the same).  SNCC_FP32_KAHAN runs every pair in one persistent launch
- * over a cost-ordered work list; SNCC_FP64 runs one launch per pair.  The
- * context keeps the FP32 form's work list of its last call on the device and
- * reuses it when the next call has the same template set, sizes, pitch, k
- * and pairs (calls on one context are ordered by its stream).
+ * float rho is the same).  Pairs are scored in one persistent launch over a
+ * cost-ordered work list, or, where that is faster, by a matrix-core filter
+ * whose error bound leaves few candidates and the rho of those by the
+ * precision's own sums: the same lists, bit for bit, as without it.  The
+ * context keeps the work list of its last call of each precision on the
+ * device, with the filter's scratch (at most 256 MB, or one pair's map of 4
+ * bytes an offset if that is more), and reuses it when the next call has the
+ * same template set, sizes, pitch, k and pairs (calls on one context are
+ * ordered by its stream).
  *
  *   d_s, d_s2  sum tables of B frames (layout of sncc_build_sats)
  *   pairs      host, n_pairs x {frame, template}
@@ -368,9 +381,9 @@ int sncc_refine(sncc_ctx *ctx, const sncc_tmpl *fine, const uint32_t *d_s,
  * The matching algorithm of Section 5 as printed (steps 5 and 7a-j), over
  * pairs: rho with the fast approximation at every offset (FP32 compensated,
  * one persistent launch); offsets with rho >= thr_fast[template] survive and
- * are compacted into d_cand; each survivor is scored again with the slow
- * approximation in FP64 and appended to d_out when that rho is at least
- * thr_slow[template].  The paper sets the thresholds to precision (0.9)
+ * are compacted into d_cand; each survivor that a matrix-core filter with an
+ * error bound does not rule out is scored again with the slow approximation
+ * in FP64 and appended to d_out when that rho is at least thr_slow[template].  The paper sets the thresholds to precision (0.9)
  * times the NCC of each approximation with its template (rho_max of
  * sncc_segment_template) and builds the approximations with sigma_max of
  * 0.99 and 0.1 times the template's standard deviation.  The fast test is
@@ -443,8 +456,9 @@ typedef struct sncc_batch_stats {
  * items, chooses the tile shape (default, or timed candidates when
  * desc->tune is set), and captures sum-table construction, the persistent
  * scoring launches, top-k selection and (optionally) FP64 refinement into
- * one HIP graph on the context's stream.  The descriptor's buffers are
- * bound at this point.  Errors: as for the calls it combines.
+ * one HIP graph on the context's stream.  Pairs for which sncc_topk's filter
+ * is faster leave the persistent launches (scratch of at most 1 GB, or one
+ * pair's map).  The descriptor's buffers are bound at this point.  Errors: as for the calls it combines.
  */
 int sncc_batch_create(sncc_ctx *ctx, const sncc_batch_desc *desc,
                       sncc_batch **out);

@@ -989,8 +989,8 @@ int retire(sncc_ctx *ctx, std::unique_ptr<PlanDev> pd) {
 }
 
 // The context's plan for `key` (key.sink's slot), built and uploaded by
-// `make` on a miss (`tiles`: with a tile plan to upload); the plan it replaces is retired, since work queued with
-// it may still be running.  Calls on one context are ordered by its stream,
+// `make` on a miss (`tiles`: with a tile plan to upload); the plan it replaces
+// is retired, since work queued with it may still be running.  Calls on one context are ordered by its stream,
 // so reusing a plan while earlier work still reads it is safe.
 template <class Make>
 int cached_plan(sncc_ctx *ctx, PlanKey key, Make make, PlanDev **out, bool tiles = true) {
@@ -1330,7 +1330,9 @@ void dense_constants(const sncc_tmpl *tm, int t, const DenseTmpl &dt, int N, int
 }
 
 // Records of an FP32 sum above which a chunk's candidates are scored by many
-// workgroups in three launches instead of one per pair in the selection's.
+// workgroups in three launches instead of one per pair in the selection's: at
+// K up to 5000 (16 pairs of 1920 x 1080) 155 us in one launch against 41 + 27 +
+// 10 + 5 in four; at K 119 the one launch takes 10.
 constexpr int kSpreadRecords = 2048;
 // Largest scratch map of a chunk of filtered pairs (floats; one pair may need
 // more), and of a batch's, whose selections then run for hundreds of pairs at

@@ -22,12 +22,13 @@
 //
 // Contraction: one instruction multiplies A (16 x 64) by B (64 x 16).  Column
 // j of B is a block of 16 offset columns, u = u0 + 16 (j mod 8) + i, of one of
-// two offset rows (j / 8); row i of A is the offset within the block.  The 64 products are four template rows y .. y + 3
-// of 16 template columns 16 x - i .. + 15 (x = 0 .. G - 1, G = ceil((W + 15) /
-// 16)), so that B's entries are aligned 16-byte pieces of frame rows, the same
-// for every i, and A holds the template rows shifted by i (banded Toeplitz
-// blocks, zero outside the template), prepared once per template in the
-// instruction's register layout (dense_pack).  W / (16 G) of the products are
+// two offset rows (j / 8); row i of A is the offset within the block.  The 64
+// products are four template rows y .. y + 3 of 16 template columns 16 x - i
+// .. + 15 (x = 0 .. G - 1, G = ceil((W + 15) / 16)), so that B's entries are
+// aligned 16-byte pieces of frame rows, the same for every i, and A holds the
+// template rows shifted by i (banded Toeplitz blocks, zero outside the
+// template), prepared once per template in the instruction's register layout
+// (dense_pack).  W / (16 G) of the products are
 // not zero: 0.80 at W = 64, 0.89 at 128.  B of offset row v + 4 is B of offset
 // row v one step (four template rows) later, so a wave with eight offset rows
 // reads each B once for two uses.
@@ -355,7 +356,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   dense_products<D, RV, NW>(stage, a, row0, lds8, lane, acc);
 
   const int u = u0 + 16 * (lane & 7) + 4 * (lane >> 4);
-  dense_windows<RV, false>(S, S2, a, u0, u, v0 + row0, [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
+  dense_windows<RV, false>(S, S2, a, u0, u, v0 + row0,
+                           [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
     const int v = v0 + row0 + r;
     const long long o = (long long)v * a.rho_pitch + u;
     if (v >= a.nv) return;
@@ -419,7 +421,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int block = tile * NW + wave;
   float4 *o = reinterpret_cast<float4 *>(map + fp.map0 + (long long)block * (RV * 256)) + lane;
   float top = -__builtin_inff(), top_low = -__builtin_inff();
-  dense_windows<RV, D == 2>(S, S2, a, u0, u, v0 + row0, [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
+  dense_windows<RV, D == 2>(S, S2, a, u0, u, v0 + row0,
+                            [&](int r, const v4u_a4 &sf, const double(&V)[4]) {
     const bool row_ok = v0 + row0 + r < a.nv;
     float w[4];
 #pragma unroll
