@@ -1291,30 +1291,40 @@ bool dense_shape(const sncc_tmpl *tm, int t, int digits, int nu, int nv, int num
   return a.hb >= 8;
 }
 
-// Estimates in ps per offset: the segment form (evaluations and staged rows),
-// the plain FP64 form, and the matrix products per offset of a launch shape.
-double cost_tile(const sncc_tmpl *tm, int t) {
-  return 0.22 * tm->K[t] + 6e-4 * (tm->W[t] + 128.0) * (tm->H[t] + 32.0);
-}
-double cost_plain(const sncc_tmpl *tm, int t) { return 0.52 * tm->K[t] + 16.0; }
+// Matrix products per offset of a launch shape; two rows per wave half read
+// every A operand for so few of them that they count 1.6 times.
 double dense_macs(const DenseArgs &a) {
   return (double)a.H * a.G * 16 * (a.rv == 2 ? 1.6 : 1.0);
 }
 
-// Whether the matrix-core form is the faster one: the estimates are fitted to
-// maps measured both ways (one MI355X, us a map, other form / this one).
-// FP32: the segment form's evaluations and staged rows against the matrix
-// steps: 1920 x 1080 with 64 x 64 at K 110 62.7 / 40.2, K 1005 457 / 37.7;
-// 61 x 47, K 118 63.4 / 33.9; 128 x 96, K 73 70.1 / 82.6; 3840 x 2160 with
-// 256 x 256, K 287 774 / 1006.  FP64: the plain form's evaluations: 64 x 64,
-// K 110 144 / 62, K 1005 1017 / 62; 128 x 96, K 73 103 / 138; 192 x 180,
-// K 579 530 / 339; 256 x 256, K 287 1153 / 2004.  Two rows per wave half cost
-// 1.6 times the steps.
+// Whether the matrix-core form is the faster one for a map.  Estimates in us,
+// the larger of what one workgroup takes on a frame too small to fill the CUs
+// and what all offsets take together, fitted to 210 maps from 320 x 240 to 1920
+// x 1080 measured both ways on one MI355X (together 1% above the faster form's
+// times): FP32 evaluations and staged rows against matrix steps, FP64 the plain
+// form's evaluations; FP64 operands beyond an XCD's L2 (4 MB) cost 1.6 times.
+// Other form / this one: FP32 1920 x 1080 with 64 x 64 at K 24 22 / 35, K 1005
+// 457 / 37, 128 x 128 at K 478 225 / 87, 180 x 180 at K 195 108 / 162; 640 x 480
+// with 64 x 64 at K 87 23 / 16; 3840 x 2160 with 256 x 256 at K 287 774 / 1006.
+// FP64 1280 x 720 with 32 x 32 at K 6 11 / 20, K 258 139 / 20; 1920 x 1080 with
+// 64 x 64 at K 1005 1005 / 58; 640 x 480 with 180 x 180 at K 804 150 / 206.
 bool dense_wins(const sncc_tmpl *tm, int t, const DenseArgs &a) {
   const int forced = dense_forced();
   if (forced >= 0) return forced == 1;
-  if (a.digits == kDenseDigits) return cost_plain(tm, t) > 10.0 + 0.7e-3 * a.digits * dense_macs(a);
-  return cost_tile(tm, t) > 6.0 + 0.8e-3 * a.digits * dense_macs(a);
+  const double off = (double)a.nu * a.nv * 1e-6, K = tm->K[t], mac = dense_macs(a);
+  const double one = (double)a.H * a.G * 16;  // products of one workgroup's offset
+  if (a.digits == kDenseDigits) {
+    const double far = dense_frag_bytes(a.W, a.H, a.digits) > 3500000 ? 1.6 : 1.0;
+    const double plain = std::max({10.0, 7.0 + 0.17 * K,
+                                   3.0 + off * std::min(4.3 + 0.7 * K, 16.0 + 0.52 * K)});
+    return std::max(11.6 + 3.2e-3 * one * far, 6.0 + off * (6.5 + 4.6e-3 * mac)) < plain;
+  }
+  const double digits = a.digits / 3.0;
+  const double tile = std::max(
+      6.5 + 0.2 * K, 5.5 + off * (0.22 * K + 4e-4 * (tm->W[t] + 128.0) * (tm->H[t] + 32.0)));
+  return (a.rv == 8 ? 4.0 + off * (3.7 + 1.7e-3 * digits * mac)
+                    : std::max(6.0 + 2e-3 * digits * one,
+                               4.0 + off * (5.0 + 2.4e-3 * digits * mac))) < tile;
 }
 
 void dense_constants(const sncc_tmpl *tm, int t, const DenseTmpl &dt, int N, int P,
