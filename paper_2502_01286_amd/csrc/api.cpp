@@ -1658,11 +1658,14 @@ int upload_filter(FilterPlan &f, int k, bool fp64, hipStream_t st) {
 // cost twice the filter's time (some are left to the slow pass, and two launches
 // more).  Measured (us a call of 2 frames 1920 x 1080, without / with): 64 x 64,
 // K 1217 to 1863, 2.0 million survivors 1125 / 480; K 593 to 2041, 0.66 million
-// 571 / 415; 92 x 92, K 315 to 4794 919 / 490; 49 x 49, K 96 to 1242 578 / 430;
-// 35 x 35, K 56 to 742, many matches, with every tile filtered 461 / 482.  A
-// call whose slow pass would take less than the filter's shortest time, were 15
-// per cent of the offsets survivors, goes without (8 pairs of 324 x 200 with 96 x
-// 96 175 / 195).
+// 571 / 415; 92 x 92, K 315 to 4794 919 / 490; 49 x 49, K 96 to 1242 578 / 430.
+// Small templates match in so many places that most runs keep a survivor:
+// those whose survivor costs less than kAboveSpared go without (35 x 35, K 56 to
+// 742 461 / 482; 33 x 33, K 214 to 580 237 / 278; but 57 x 57, K 138 to 658 on
+// 873 x 474, at 268 ps, 230 / 216).  So does a call whose slow pass would take
+// less than the filter's shortest time, were 15 per cent of the offsets
+// survivors (8 pairs of 324 x 200 with 96 x 96 175 / 195).
+constexpr double kAboveSpared = 250.0;
 int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, int P, int n_pairs,
                const int32_t *pairs, const double *thr, AbovePlan &f) {
   const int forced = dense_forced();
@@ -1689,7 +1692,7 @@ int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, i
     const double tile = (double)kDenseBU * bv, mac = 0.5 * a.digits * dense_macs(a);
     floor_us = std::max(floor_us, 20.0 + 2e-3 * mac);
     const double need = 2.0 * tile * (4.0 + 1.25e-3 * mac) / spared;
-    if (forced != 1 && need > 0.25 * tile) continue;
+    if (forced != 1 && (need > 0.25 * tile || spared < kAboveSpared)) continue;
     limit[t] = forced == 1 ? 1 : std::max(1, (int)need);
     want.emplace_back(t, slow->digits_f[t]);
   }
