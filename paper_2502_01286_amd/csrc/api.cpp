@@ -2612,10 +2612,14 @@ int enqueue_stage(sncc_batch *b, int stage, hipStream_t st) {
         SNCC_FAIL(SNCC_EDEVICE, "sum-table launch");
       return SNCC_OK;
     case 1:
-      // the segment form for the pairs the filter does not serve
+      // the segment form for the pairs the filter does not serve.  The main
+      // plan's pair floors serve the last columns' launch too, also where no
+      // map is wide enough for a main tile
+      if ((!pd.h.order.empty() || (b->edge && !b->edge->h.order.empty())) &&
+          launch_zero(a.queue, a.n_zero, st) != 0)
+        SNCC_FAIL(SNCC_EDEVICE, "scoring launch");
       if (!pd.h.order.empty() &&
-          (launch_zero(a.queue, a.n_zero, st) != 0 ||
-           launch_tile(pd.h.cfg, kSinkTopk, a, pd.h.grid, pd.h.lds_bytes, st) != 0))
+          launch_tile(pd.h.cfg, kSinkTopk, a, pd.h.grid, pd.h.lds_bytes, st) != 0)
         SNCC_FAIL(SNCC_EDEVICE, "scoring launch");
       if (b->edge && !b->edge->h.order.empty()) {
         // the last columns start from the floors the main launch published
