@@ -301,6 +301,16 @@ __device__ __forceinline__ u64 window_sq(const uint32_t *__restrict__ a0, int W,
   return acc;
 }
 
+// rho of the plain FP64 form (Eq. (18)) from its sum over the segments, the
+// window's sum of f and its energy n sum f^2 - (sum f)^2; Eq. (12)'s mean term
+// is fbar * sum_i A_i c_i.
+__device__ __forceinline__ double plain_rho(double acc, uint32_t sf, long long V, int n, double q_k,
+                                            double r64) {
+  const double fbar = (double)sf / (double)n;
+  const double num = acc - fbar * r64;
+  return V == 0 ? 0.0 : num / sqrt((double)V / (double)n * q_k);
+}
+
 // Survivors of the two-threshold search's fast pass in a tile of its filter
 // (column tu of 128, rows tv bv .. over the fast pass's rows of kFastRows).
 __device__ __forceinline__ int tile_survivors(const FilterPair &fp, const int *tile_count, int tu,

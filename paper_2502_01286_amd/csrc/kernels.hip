@@ -511,7 +511,7 @@ int launch_tile(int cfg, int sink, const TileArgs &a, int grid, int lds_bytes,
 
 // --------------------------------------------------------------- plain FP64
 // rho at one offset, segments read from global memory, FP64 accumulation of
-// box_i * c_i; Eq. (12)'s mean term is fbar * sum_i A_i c_i.
+// box_i * c_i.
 __device__ __forceinline__ double rho_plain(const uint32_t *__restrict__ S,
                                             const uint32_t *__restrict__ S2, int P, int u,
                                             int v, int W, int H, int K, int sq_rows,
@@ -533,9 +533,7 @@ __device__ __forceinline__ double rho_plain(const uint32_t *__restrict__ S,
     acc = __builtin_fma((double)F, c64[i], acc);
   }
   flat = V == 0;
-  const double fbar = (double)sf / (double)n;
-  const double num = acc - fbar * r64;
-  return flat ? 0.0 : num / sqrt((double)V / (double)n * q_k);
+  return plain_rho(acc, sf, V, n, q_k, r64);
 }
 
 __global__ __launch_bounds__(256) void plain_kernel(

@@ -343,7 +343,7 @@ struct FilterPair {
   // FP32: records of the segment form's sum (SeqRec), [0], and of the offsets
   // from column u_split on, which a batch's second launch scores, [1]
   int seq0[2], n_seq[2], u_split;
-  int seg_off, K;          // FP64: the segments
+  int seg_off, K;          // the segments
   double r64;
   float error;             // bound on |filter - exact| from its rounded c
   // two-threshold search (map0: first bit word; block0, n_blocks: first counter

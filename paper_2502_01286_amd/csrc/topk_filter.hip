@@ -5,8 +5,9 @@
 // their order of summation; FP64: box sums in FP64) are then among the
 // candidates: the offsets whose filter value is not below the k-th largest by
 // more than twice the two errors.  filter_select finds them (one workgroup per
-// pair), scores them again by the reference arithmetic and orders them, so the
-// result is the reference's: for FP32 bit for bit.  A pair whose candidates do
+// pair), forms their accurate values, scores those near the k-th of them again
+// by the reference arithmetic and orders these, so the
+// result is the reference's, bit for bit.  A pair whose candidates do
 // not fit, or whose nearly uniform windows (where the FP32 bound is too wide)
 // come near the k-th value, is left to seq_topk, which scores every offset by
 // the reference arithmetic; it also takes the FP64 pairs that no filter serves.
@@ -61,10 +62,12 @@ __device__ __forceinline__ void ref_step(float &acc, float &cmp, float &y) {
   y = -cmp;
 }
 
-// rho of one offset by a whole wave, FP64: box sums less A_i b (b the window
-// mean rounded to an integer) in integers, c_i times them summed over the lanes
-// and then the wave, and the mean term of Eq. (12) for what b leaves.
-__device__ __forceinline__ double wave_ref64(const uint32_t *__restrict__ S,
+// Accurate rho of one offset by a whole wave, FP64: box sums less A_i b (b the
+// window mean rounded to an integer) in integers, c_i times them summed over the
+// lanes and then the wave, and the mean term of Eq. (12) for what b leaves.
+// (Neither reference's order of summation: it only tells which candidates the
+// reference is asked about.)
+__device__ __forceinline__ double wave_value(const uint32_t *__restrict__ S,
                                              const uint32_t *__restrict__ S2, int P, int u, int v,
                                              int W, int H, int sq_rows, double q_k, int K,
                                              double r64, const int4 *__restrict__ geom,
@@ -186,8 +189,88 @@ __device__ __forceinline__ void ordered_group(const uint32_t *__restrict__ S,
   __syncthreads();
 }
 
+// The same for FP64: box sums times c_i added in segment order (as lane_ref64
+// does), one fused multiply-add after the other.
+constexpr int kRefChunk64 = 128;  // segments per step
+template <int NP>
+struct OrderedLds64 {
+  alignas(16) uint32_t f[2][NP][kRefChunk64 + 4];
+  alignas(16) double c[2][kRefChunk64];
+  long long V[NP];
+  uint32_t sf[NP];
+};
+
+template <int NP>
+__device__ __forceinline__ void ordered_group64(const uint32_t *__restrict__ S,
+                                                const uint32_t *__restrict__ S2, int P,
+                                                const FilterPair &fp,
+                                                const int4 *__restrict__ geom,
+                                                const double *__restrict__ c64, const int *cand,
+                                                int c0, int n, OrderedLds64<NP> &sh, u64 *key_hi,
+                                                uint32_t *key_lo, int wave, int lane) {
+  const int4 *gp = geom + fp.seg_off;
+  const double *cp = c64 + fp.seg_off;
+  const int K = fp.K, nu = fp.a.nu, W = fp.a.W, H = fp.a.H;
+  const bool mine = wave < NP && c0 + wave < n;  // wave 0's always is
+  const uint32_t *w = S;
+  if (mine) {
+    const int idx = __builtin_amdgcn_readfirstlane(cand[c0 + wave]);
+    const int v = idx / nu, u = idx - v * nu;
+    const long long o = (long long)v * P + u;
+    w = S + o;
+    const uint32_t sf = ref_box(w, W, H, P);
+    const u64 sf2 = window_sq(S2 + o, W, H, P, fp.a.sq_rows);
+    if (lane == 0) {
+      sh.sf[wave] = sf;
+      sh.V[wave] = (long long)((u64)(uint32_t)fp.a.n * sf2 - (u64)sf * sf);
+    }
+  }
+  auto produce = [&](int base, int buf) {
+    constexpr int Q = kRefChunk64 / 64;
+    int4 g[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) g[q] = gp[min(base + 64 * q + lane, K - 1)];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      sh.f[buf][wave][64 * q + lane] =
+          ref_box(w + (long long)g[q].y * P + g[q].x, g[q].z, g[q].w, P);
+      if (wave == 0) sh.c[buf][64 * q + lane] = cp[min(base + 64 * q + lane, K - 1)];
+    }
+  };
+  if (mine) produce(0, 0);
+  double acc = 0.0;
+  __syncthreads();
+  for (int base = 0, buf = 0; base < K; base += kRefChunk64, buf ^= 1) {
+    if (wave == NP) {
+      const uint32_t *fl = sh.f[buf][min(lane, NP - 1)];
+      const double *cl = sh.c[buf];
+      const int m = min(kRefChunk64, K - base);
+      int l = 0;
+#pragma unroll 2
+      for (; l + 4 <= m; l += 4) {
+        const uint4 b = *reinterpret_cast<const uint4 *>(fl + l);
+        acc = __builtin_fma((double)b.x, cl[l], acc);
+        acc = __builtin_fma((double)b.y, cl[l + 1], acc);
+        acc = __builtin_fma((double)b.z, cl[l + 2], acc);
+        acc = __builtin_fma((double)b.w, cl[l + 3], acc);
+      }
+      for (; l < m; ++l) acc = __builtin_fma((double)fl[l], cl[l], acc);
+    } else if (mine && base + kRefChunk64 < K) {
+      produce(base + kRefChunk64, buf ^ 1);
+    }
+    __syncthreads();
+  }
+  if (wave == NP && lane < NP && c0 + lane < n) {
+    key_hi[c0 + lane] = double_order(
+        plain_rho(acc, sh.sf[lane], sh.V[lane], fp.a.n, fp.a.q_k, fp.r64));
+    key_lo[c0 + lane] = 0xffffffffu - (uint32_t)cand[c0 + lane];
+  }
+  __syncthreads();
+}
+
 // From the keys of n candidates' accurate values, one wave: the candidates
-// within twice the FP32 reference's error of the k-th largest, listed in
+// within twice the reference's error (FP32's, which is the larger) of the k-th
+// largest, listed in
 // `near`, those left of column u_split (m_main of them) first; returns their
 // number.
 __device__ __forceinline__ int near_kth(const u64 *key, int n, int k, int nu, int u_split,
@@ -275,6 +358,7 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   __shared__ u64 key_hi[SPREAD ? 1 : kFilterCands];
   __shared__ uint32_t key_lo[F64 ? kFilterCands : 1];
   __shared__ OrderedLds<F64 || SPREAD ? 1 : kRefGroup> group;
+  __shared__ OrderedLds64<F64 ? kRefGroup : 1> group64;
   __shared__ int n_list, n_cand, bin, bad;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -284,8 +368,9 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   const float *vals = map + fp.map0;
   // twice the errors of the filter (fp.error: its rounded c; the result's
   // roundings and 1 / sqrt, 3e-7; the thresholds' below, 1e-7) and of the reference (FP32: at
-  // most 3e-6 for windows of energy n / 100 and above, 1e-4 for any window)
-  const float margin = 2.f * (fp.error + 4e-7f + (F64 ? 0.f : 3e-6f));
+  // most 3e-6 for windows of energy n / 100 and above, 1e-4 for any window; FP64: K 2^-53
+  // sum |c_i| F_i, so K 2^-53 times 2550 and 255 sqrt(n), 4e-8 and 2e-6 at the largest K and n)
+  const float margin = 2.f * (fp.error + 4e-7f + (F64 ? 1e-7f : 3e-6f));
   const float low_margin = 2.f * (fp.error + 1e-4f);
 
   auto clear = [&]() {
@@ -377,26 +462,15 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
     }
     return;
   }
-  // the candidates by the reference arithmetic, one wave each
+  // the candidates' accurate values (FP64, a wave each, lanes over the
+  // segments), then those near the k-th by the reference arithmetic
   const uint32_t *S = s + (long long)fp.frame * frame_stride;
   const uint32_t *S2 = s2 + (long long)fp.frame * frame_stride;
-  if constexpr (F64) {
+  if constexpr (!SPREAD) {
     for (int c = wave; c < n; c += kSelThreads / 64) {
       const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
       const int v = idx / nu, u = idx - v * nu;
-      const double r = wave_ref64(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.sq_rows, fp.a.q_k, fp.K, fp.r64,
-                                  geom + fp.seg_off, c64 + fp.seg_off, lane);
-      if (lane == 0) {
-        key_hi[c] = double_order(r);
-        key_lo[c] = 0xffffffffu - (uint32_t)idx;
-      }
-    }
-  } else if constexpr (!SPREAD) {
-    // FP32: the accurate values first (FP64, lanes over the segments)
-    for (int c = wave; c < n; c += kSelThreads / 64) {
-      const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
-      const int v = idx / nu, u = idx - v * nu;
-      const double r = wave_ref64(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.sq_rows, fp.a.q_k, fp.K, fp.r64,
+      const double r = wave_value(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.sq_rows, fp.a.q_k, fp.K, fp.r64,
                                   geom + fp.seg_off, c64 + fp.seg_off, lane);
       if (lane == 0) key_hi[c] = make_key((float)r, idx);
     }
@@ -411,11 +485,17 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
     }
     __syncthreads();
     n = n_cand;
-    const int n_main = n_list;
-    for (int c0 = 0; c0 < n_main; c0 += kRefGroup)
-      ordered_group<kRefGroup>(S, S2, P, fp, seq, cand, c0, n_main, 0, group, key_hi, wave, lane);
-    for (int c0 = n_main; c0 < n; c0 += kRefGroup)
-      ordered_group<kRefGroup>(S, S2, P, fp, seq, cand, c0, n, 1, group, key_hi, wave, lane);
+    if constexpr (F64) {
+      for (int c0 = 0; c0 < n; c0 += kRefGroup)
+        ordered_group64<kRefGroup>(S, S2, P, fp, geom, c64, cand, c0, n, group64, key_hi, key_lo,
+                                   wave, lane);
+    } else {
+      const int n_main = n_list;
+      for (int c0 = 0; c0 < n_main; c0 += kRefGroup)
+        ordered_group<kRefGroup>(S, S2, P, fp, seq, cand, c0, n_main, 0, group, key_hi, wave, lane);
+      for (int c0 = n_main; c0 < n; c0 += kRefGroup)
+        ordered_group<kRefGroup>(S, S2, P, fp, seq, cand, c0, n, 1, group, key_hi, wave, lane);
+    }
   }
   __syncthreads();
   if (wave != 0) return;
@@ -474,7 +554,7 @@ __global__ __launch_bounds__(256) void filter_values(
   for (int c = part * 4 + wave; c < sp.n; c += 4 * kSpreadWgs) {
     const int idx = __builtin_amdgcn_readfirstlane(sp.cand[c]);
     const int v = idx / fp.a.nu, u = idx - v * fp.a.nu;
-    const double r = wave_ref64(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.sq_rows, fp.a.q_k, fp.K, fp.r64,
+    const double r = wave_value(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.sq_rows, fp.a.q_k, fp.K, fp.r64,
                                   geom + fp.seg_off, c64 + fp.seg_off, lane);
     if (lane == 0) sp.val[c] = make_key((float)r, idx);
   }
@@ -570,7 +650,7 @@ __device__ __forceinline__ float lane_ref32(const uint32_t *__restrict__ S,
   return (acc - cmp) * rf.scale;
 }
 
-// As plain_kernel's rho_plain: box_i c_i summed in segment order, FP64.
+// rho_plain's arithmetic: box_i c_i summed in segment order, FP64.
 __device__ __forceinline__ double lane_ref64(const uint32_t *__restrict__ S,
                                              const uint32_t *__restrict__ S2, int P, int u, int v,
                                              const SeqPair &sp, const int4 *__restrict__ geom,
@@ -587,8 +667,7 @@ __device__ __forceinline__ double lane_ref64(const uint32_t *__restrict__ S,
     const int4 g = gp[i];
     acc = __builtin_fma((double)ref_box(a0 + (long long)g.y * P + g.x, g.z, g.w, P), cp[i], acc);
   }
-  const double num = acc - (double)sf / (double)sp.n * sp.r64;
-  return V == 0 ? 0.0 : num / sqrt((double)V / (double)sp.n * sp.q_k);
+  return plain_rho(acc, sf, V, sp.n, sp.q_k, sp.r64);
 }
 
 // The k best offsets of each `chunk` offsets of the pairs that direct[] marks;
