@@ -467,24 +467,27 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   const uint32_t *S = s + (long long)fp.frame * frame_stride;
   const uint32_t *S2 = s2 + (long long)fp.frame * frame_stride;
   if constexpr (!SPREAD) {
-    for (int c = wave; c < n; c += kSelThreads / 64) {
-      const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
-      const int v = idx / nu, u = idx - v * nu;
-      const double r = wave_value(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.sq_rows, fp.a.q_k, fp.K, fp.r64,
-                                  geom + fp.seg_off, c64 + fp.seg_off, lane);
-      if (lane == 0) key_hi[c] = make_key((float)r, idx);
-    }
-    __syncthreads();
-    if (wave == 0) {
-      int m_main = 0;
-      const int m = near_kth(key_hi, n, k, nu, fp.u_split, cand, &m_main, lane);
-      if (lane == 0) {
-        n_cand = m;
-        n_list = m_main;
+    // (few FP64 candidates, all of one kind of records, at once)
+    if (!F64 || n > kRefGroup) {
+      for (int c = wave; c < n; c += kSelThreads / 64) {
+        const int idx = __builtin_amdgcn_readfirstlane(cand[c]);
+        const int v = idx / nu, u = idx - v * nu;
+        const double r = wave_value(S, S2, P, u, v, fp.a.W, fp.a.H, fp.a.sq_rows, fp.a.q_k, fp.K,
+                                    fp.r64, geom + fp.seg_off, c64 + fp.seg_off, lane);
+        if (lane == 0) key_hi[c] = make_key((float)r, idx);
       }
+      __syncthreads();
+      if (wave == 0) {
+        int m_main = 0;
+        const int m = near_kth(key_hi, n, k, nu, fp.u_split, cand, &m_main, lane);
+        if (lane == 0) {
+          n_cand = m;
+          n_list = m_main;
+        }
+      }
+      __syncthreads();
+      n = n_cand;
     }
-    __syncthreads();
-    n = n_cand;
     if constexpr (F64) {
       for (int c0 = 0; c0 < n; c0 += kRefGroup)
         ordered_group64<kRefGroup>(S, S2, P, fp, geom, c64, cand, c0, n, group64, key_hi, key_lo,
