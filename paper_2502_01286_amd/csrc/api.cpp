@@ -62,8 +62,9 @@ namespace {
 
 // Failure injection for tests of the allocation-failure paths: with
 // SNCC_TEST_FAIL_ALLOC set to a positive byte count in the environment, every
-// device allocation of at least that many bytes fails as if the device were
-// out of memory (read at each allocation, so a test can set and clear it).
+// device allocation of at least that many bytes asks for more than any device
+// has and fails as a real one does (read at each allocation, so a test can set
+// and clear it).
 // With SNCC_TEST_QUEUES=1 in the environment, scoring launches that would run
 // one workgroup per item use the work queues instead (read at each launch), so
 // that a test can compare the two forms on the same call.
@@ -96,12 +97,15 @@ struct DevBuf {
       p = nullptr;
       bytes = 0;
     }
-    if (alloc_fails_by_request(n))
-      SNCC_FAIL(SNCC_ENOMEM, "hipMalloc(%zu): refused (SNCC_TEST_FAIL_ALLOC)", n);
-    hipError_t e = hipMalloc(&p, n);
+    const bool refuse = alloc_fails_by_request(n);
+    hipError_t e = hipMalloc(&p, refuse ? (size_t)1 << 60 : n);
     if (e != hipSuccess) {
       p = nullptr;
-      SNCC_FAIL(SNCC_ENOMEM, "hipMalloc(%zu): %s", n, hipGetErrorString(e));
+      // the runtime keeps a failed call's error until it is read: launches
+      // check for one, and callers may go on without the buffer
+      (void)hipGetLastError();
+      SNCC_FAIL(SNCC_ENOMEM, "hipMalloc(%zu): %s%s", n, hipGetErrorString(e),
+                refuse ? " (SNCC_TEST_FAIL_ALLOC)" : "");
     }
     bytes = n;
     return SNCC_OK;
@@ -988,10 +992,27 @@ int retire(sncc_ctx *ctx, std::unique_ptr<PlanDev> pd) {
   return SNCC_OK;
 }
 
-// The context's plan for `key` (key.sink's slot), built and uploaded by
-// `make` on a miss (`tiles`: with a tile plan to upload); the plan it replaces
-// is retired, since work queued with it may still be running.  Calls on one context are ordered by its stream,
-// so reusing a plan while earlier work still reads it is safe.
+// Makes and uploads a plan: make(plan, true) with the filter's buffers, which
+// the call can do without, and where those or the plan's own do not fit the
+// device's memory again by make(plan, false).
+template <class Make>
+int make_plan(Make make, bool tiles, hipStream_t st, std::unique_ptr<PlanDev> *out) {
+  int rc = SNCC_OK;
+  for (bool filter : {true, false}) {
+    out->reset(new PlanDev());
+    rc = make(**out, filter);
+    if (rc == SNCC_OK && tiles) rc = (*out)->upload(st);
+    if (rc != SNCC_ENOMEM) break;
+  }
+  if (rc == SNCC_OK) g_err.clear();
+  return rc;
+}
+
+// The context's plan for `key` (key.sink's slot), made by `make` (make_plan) on
+// a miss (`tiles`: with a tile plan to upload); the plan it replaces is retired,
+// since work queued with it may still be running.  Calls on one context are
+// ordered by its stream, so reusing a plan while earlier work still reads it is
+// safe.
 template <class Make>
 int cached_plan(sncc_ctx *ctx, PlanKey key, Make make, PlanDev **out, bool tiles = true) {
   const int slot = key.sink;
@@ -1001,9 +1022,8 @@ int cached_plan(sncc_ctx *ctx, PlanKey key, Make make, PlanDev **out, bool tiles
   }
   if (ctx->cache[slot]) CHK(retire(ctx, std::move(ctx->cache[slot])));
   ctx->cache_key[slot] = PlanKey{};
-  std::unique_ptr<PlanDev> pd(new PlanDev());
-  CHK(make(*pd));
-  if (tiles) CHK(pd->upload(ctx->stream));
+  std::unique_ptr<PlanDev> pd;
+  CHK(make_plan(make, tiles, ctx->stream, &pd));
   ctx->cache[slot] = std::move(pd);
   ctx->cache_key[slot] = std::move(key);
   *out = ctx->cache[slot].get();
@@ -1739,7 +1759,10 @@ int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, i
     l.n_items = (int)f.items.size() - l.item0;
     if (l.n_items > 0) f.launches.push_back(l);
   }
-  if (f.fps.empty()) return SNCC_OK;
+  if (f.fps.empty()) {
+    f.n_tiles = 0;  // no counters
+    return SNCC_OK;
+  }
   {
     std::lock_guard<std::mutex> lk(slow->dense_mu);
     f.operands = slow->dense_bufs;
@@ -1794,6 +1817,25 @@ void drop_items(PlanHost &h, const std::vector<char> &use) {
   h.grid = std::max(1, std::min(h.grid, (int)h.order.size()));
   for (size_t p = 0; p < h.pairs.size(); ++p)
     if (use[p]) h.pairs[p].item_end = h.pairs[p].item_begin;
+}
+
+// Plans and uploads the filter for the pairs in `use` of an FP32 plan `d` (and a
+// batch's `edge`) and takes them out of its work; nothing where no operands can
+// be had.
+int add_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_pairs,
+               const int32_t *pairs, int k, std::vector<char> &use, PlanDev &d, PlanDev *edge,
+               size_t map_floats) {
+  if (std::find(use.begin(), use.end(), 1) == use.end()) return SNCC_OK;
+  plan_filter(ctx, tm, M, N, P, n_pairs, pairs, k, false, &d.h, use, d.f, map_floats,
+              edge ? &edge->h : nullptr);
+  if (d.f.chunks.empty()) {
+    d.f.pairs.clear();  // not active
+    return SNCC_OK;
+  }
+  CHK(upload_filter(d.f, k, false, ctx->stream));
+  drop_items(d.h, use);
+  if (edge) drop_items(edge->h, use);
+  return SNCC_OK;
 }
 
 // Scores a map with the matrix-core form; returns 1 when it ran, 0 when the
@@ -2219,7 +2261,7 @@ int sncc_score(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint32_t *d_
   key.P = sat_pitch;
   key.pairs.assign(pair, pair + 2);
   PlanDev *pd = nullptr;
-  CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d) {
+  CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d, bool) {
     return build_one_call_plan(tm, M, N, sat_pitch, 1, pair, 0, kSinkMap, ctx->num_cu, d.h);
   }, &pd));
   TileArgs a = pd->args(d_s, d_s2, (long long)(N + 1) * sat_pitch, sat_pitch, M, N);
@@ -2343,20 +2385,13 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
     key.k = k;
     key.pairs.assign(pairs, pairs + 2 * n_pairs);
     PlanDev *pd = nullptr;
-    CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d) {
+    CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d, bool filter) {
       CHK(build_one_call_plan(tm, M, N, sat_pitch, n_pairs, pairs, k, kSinkTopk, ctx->num_cu,
                               d.h));
+      if (!filter) return SNCC_OK;
       std::vector<char> use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, k, false);
-      if (std::find(use.begin(), use.end(), 1) == use.end()) return SNCC_OK;
-      plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, false, &d.h, use, d.f);
-      if (d.f.chunks.empty() || upload_filter(d.f, k, false, ctx->stream) != SNCC_OK) {
-        d.f.~FilterPlan();  // no operands, or no memory for it: the segment form for all pairs
-        new (&d.f) FilterPlan();
-        g_err.clear();
-      } else {
-        drop_items(d.h, use);
-      }
-      return SNCC_OK;
+      return add_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, use, d, nullptr,
+                        kFilterMapFloats);
     }, &pd));
     TileArgs a = pd->args(d_s, d_s2, fs, sat_pitch, M, N);
     ctx->n_stages = 0;
@@ -2390,14 +2425,9 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
   key.k = k;
   key.pairs.assign(pairs, pairs + 2 * n_pairs);
   PlanDev *pd = nullptr;
-  CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d) {
-    std::vector<char> use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, k, true);
-    plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, true, nullptr, use, d.f);
-    if (upload_filter(d.f, k, true, ctx->stream) == SNCC_OK) return SNCC_OK;
-    // no memory for the filter's maps: the direct form for all pairs
-    d.f.~FilterPlan();
-    new (&d.f) FilterPlan();
-    use.assign(n_pairs, 0);
+  CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d, bool filter) {
+    std::vector<char> use(n_pairs, 0);  // without the filter: the direct form for all pairs
+    if (filter) use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, k, true);
     plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, true, nullptr, use, d.f);
     return upload_filter(d.f, k, true, ctx->stream);
   }, &pd, false));
@@ -2495,16 +2525,12 @@ int sncc_threshold_match(sncc_ctx *ctx, const sncc_tmpl *fast, const sncc_tmpl *
   key.thr.assign(thr_fast, thr_fast + fast->T);
   key.thr.insert(key.thr.end(), thr_slow, thr_slow + slow->T);
   PlanDev *pd = nullptr;
-  CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d) {
+  CHK(cached_plan(ctx, std::move(key), [&](PlanDev &d, bool filter) {
     CHK(build_plan(fast, 0, M, N, sat_pitch, n_pairs, pairs, 1, kSinkCompact, ctx->num_cu, d.h,
                    thr_fast));
     plan_slow(slow, d.h.tc, d.h);
-    if (plan_above(ctx, slow, d.h, N, sat_pitch, n_pairs, pairs, thr_slow, d.above) != SNCC_OK ||
-        !d.above.active()) {
-      d.above.~AbovePlan();  // no operands, or no memory for it
-      new (&d.above) AbovePlan();
-      g_err.clear();
-    }
+    if (filter)
+      CHK(plan_above(ctx, slow, d.h, N, sat_pitch, n_pairs, pairs, thr_slow, d.above));
     std::vector<double> ts(thr_slow, thr_slow + slow->T);
     return d.d_thr.upload(ts, ctx->stream);
   }, &pd));
@@ -2875,37 +2901,27 @@ int sncc_batch_create(sncc_ctx *ctx, const sncc_batch_desc *desc, sncc_batch **o
   for (int p = 0; p < d.n_pairs && edge_cfg >= 0; ++p)
     any_edge |= has_edge(d.M - d.coarse->W[b->pairs[2 * p + 1]] + 1, main_tc.bu());
   const int split = any_edge ? kSplitMain : kSplitNone;
-  b->plan.reset(new PlanDev());
-  CHK(build_plan(d.coarse, cfg, d.M, d.N, d.sat_pitch, d.n_pairs, b->pairs.data(), d.k, kSinkTopk,
-                 ctx->num_cu, b->plan->h, nullptr, split));
-  if (d.fine) {
-    plan_slots(d.fine, kRefineWideSpanU, kRefineWideSpanV, kRefineRegionWords, b->plan->h,
-               kRefineSpanU, kRefineSpanV);
-    plan_refine_order(b->plan->h, d.k, d.radius);
-  }
-  if (any_edge) {
-    b->edge.reset(new PlanDev());
-    CHK(build_plan(d.coarse, edge_cfg, d.M, d.N, d.sat_pitch, d.n_pairs, b->pairs.data(), d.k,
-                   kSinkTopk, ctx->num_cu, b->edge->h, nullptr, kSplitEdge, main_tc.bu()));
-  }
-  // the filter for the pairs it pays for (no memory for it: none)
-  FilterPlan &f = b->plan->f;
-  std::vector<char> use =
-      filter_pairs(ctx, d.coarse, d.M, d.N, d.n_pairs, b->pairs.data(), d.k, false, true);
-  if (std::find(use.begin(), use.end(), 1) != use.end()) {
-    plan_filter(ctx, d.coarse, d.M, d.N, d.sat_pitch, d.n_pairs, b->pairs.data(), d.k, false,
-                &b->plan->h, use, f, kFilterBatchFloats, any_edge ? &b->edge->h : nullptr);
-    if (f.chunks.empty() || upload_filter(f, d.k, false, ctx->stream) != SNCC_OK) {
-      f.~FilterPlan();
-      new (&f) FilterPlan();
-      g_err.clear();
-    } else {
-      drop_items(b->plan->h, use);
-      if (any_edge) drop_items(b->edge->h, use);
+  CHK(make_plan([&](PlanDev &p, bool filter) {
+    CHK(build_plan(d.coarse, cfg, d.M, d.N, d.sat_pitch, d.n_pairs, b->pairs.data(), d.k,
+                   kSinkTopk, ctx->num_cu, p.h, nullptr, split));
+    if (d.fine) {
+      plan_slots(d.fine, kRefineWideSpanU, kRefineWideSpanV, kRefineRegionWords, p.h, kRefineSpanU,
+                 kRefineSpanV);
+      plan_refine_order(p.h, d.k, d.radius);
     }
-  }
-  CHK(b->plan->upload(ctx->stream));
-  if (any_edge) CHK(b->edge->upload(ctx->stream));
+    if (any_edge) {
+      b->edge.reset(new PlanDev());
+      CHK(build_plan(d.coarse, edge_cfg, d.M, d.N, d.sat_pitch, d.n_pairs, b->pairs.data(), d.k,
+                     kSinkTopk, ctx->num_cu, b->edge->h, nullptr, kSplitEdge, main_tc.bu()));
+    }
+    if (filter) {
+      std::vector<char> use =
+          filter_pairs(ctx, d.coarse, d.M, d.N, d.n_pairs, b->pairs.data(), d.k, false, true);
+      CHK(add_filter(ctx, d.coarse, d.M, d.N, d.sat_pitch, d.n_pairs, b->pairs.data(), d.k, use, p,
+                     b->edge.get(), kFilterBatchFloats));
+    }
+    return any_edge ? b->edge->upload(ctx->stream) : SNCC_OK;
+  }, true, ctx->stream, &b->plan));
   HIPCHK(hipStreamSynchronize(ctx->stream));
 
   HIPCHK(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
