@@ -844,16 +844,31 @@ struct FilterPlan {
   std::vector<FilterChunk> chunks;
   std::vector<SeqRec> seq;
   std::vector<SeqPair> pairs;   // every pair of the call
-  std::vector<int> direct;      // 1: always by the direct form
+  std::vector<int> direct;      // 1: every offset by the direct (FP64) or segment form
   int chunk = 0, n_lists = 0;   // offsets per partial list of the direct form
   int seq_grid = 1;
+  // the launches of the segment form for undecided FP32 pairs: grids, items that
+  // may be listed
+  int und_grid[2] = {0, 0}, und_items[2] = {0, 0};
   size_t map_floats = 0, blocks = 0;
   size_t spread_fps = 0;        // most pairs of a spread chunk
-  DevBuf d_fps, d_items, d_seq, d_pairs, d_direct, d_map, d_bmax, d_partial, d_spread;
+  DevBuf d_fps, d_items, d_seq, d_pairs, d_direct, d_map, d_bmax, d_partial, d_spread, d_und;
   // the template set's memory that the launches read: a batch outlives the set
   std::shared_ptr<DevBuf> d_geom, d_c64;
   std::vector<std::shared_ptr<DevBuf>> operands;
   bool active() const { return !pairs.empty(); }
+  // d_und: the counters and pair floors of the first launch and its queue's
+  // bounds, those of the second, which takes the same floors, then the items
+  int und_queue(int x) const { return x == 0 ? 0 : kQueueInts + 2 * (int)pairs.size() + 2; }
+  int und_bounds(int x) const {
+    return x == 0 ? kQueueInts + 2 * (int)pairs.size() : und_queue(1) + kQueueInts;
+  }
+  int und_zero() const { return und_bounds(1) + 2; }  // ints before the items
+  Undecided undecided() const {
+    int *p = d_und.as<int>();
+    return Undecided{{p + und_bounds(0) + 1, p + und_bounds(1) + 1},
+                     {p + und_zero(), p + und_zero() + und_items[0]}};
+  }
 };
 
 // The two-threshold search's filter: the slow approximations' rough maps as
@@ -1501,9 +1516,9 @@ std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N,
 }
 
 // Plans the filter for the pairs marked in `use` (cleared where the operands
-// cannot be had) and the direct form for the others (FP64) or for those the
-// filter cannot decide (FP32, whose sums are ordered as plan `tile` has them,
-// and in the last columns as a batch's `edge`).
+// cannot be had) and, in FP64, the direct form for the others and for those the
+// filter cannot decide; FP32 sums are ordered as plan `tile` has them, and in
+// the last columns as a batch's `edge`, whose items score the undecided pairs.
 void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_pairs,
                  const int32_t *pairs, int k, bool fp64, const PlanHost *tile,
                  std::vector<char> &use, FilterPlan &f, size_t map_floats = kFilterMapFloats,
@@ -1537,7 +1552,7 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
         n_seq[i][t] = seq_records(i ? *edge : *tile, t, P, f.seq);
       }
     }
-    f.direct[p] = fp64 && !use[p];
+    f.direct[p] = !use[p];
     SeqPair &q = f.pairs[p];
     q = SeqPair{};
     q.frame = pairs[2 * p];
@@ -1547,11 +1562,6 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
     q.H = tm->H[t];
     q.n = q.W * q.H;
     q.sq_rows = tm->dev[t].sq_rows;
-    for (int i = 0; i < 2; ++i) {
-      q.seq0[i] = std::max(0, seq0[i][t]);
-      q.n_seq[i] = n_seq[i][t];
-    }
-    q.u_split = edge && edge->pairs[p].ntu > 0 ? edge->pairs[p].u_base : 1 << 30;
     q.seg_off = tm->seg_off[t];
     q.K = tm->K[t];
     q.q_k = tm->q_k[t];
@@ -1615,7 +1625,7 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
         fp.frame = pairs[2 * p];
         if (!dense_shape(tm, t, digits, f.pairs[p].nu, f.pairs[p].nv, ctx->num_cu, fp.a, l.rv)) {
           use[p] = 0;
-          f.direct[p] = fp64;
+          f.direct[p] = 1;
           continue;
         }
         dense_constants(tm, t, *dense_built(tm, t, digits), N, P, fp.a);
@@ -1624,10 +1634,15 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
         fp.block0 = blocks;
         fp.n_blocks = tiles * kDenseNW;
         for (int x = 0; x < 2; ++x) {
-          fp.seq0[x] = f.pairs[p].seq0[x];
-          fp.n_seq[x] = f.pairs[p].n_seq[x];
+          fp.seq0[x] = std::max(0, seq0[x][t]);
+          fp.n_seq[x] = n_seq[x][t];
+          if (const PlanHost *h = x ? edge : tile) {
+            fp.item0[x] = h->pairs[p].item_begin;
+            fp.n_items[x] = h->pairs[p].item_end - h->pairs[p].item_begin;
+            f.und_items[x] += fp.n_items[x];
+          }
         }
-        fp.u_split = f.pairs[p].u_split;
+        fp.u_split = edge && edge->pairs[p].ntu > 0 ? edge->pairs[p].u_base : 1 << 30;
         fp.seg_off = f.pairs[p].seg_off;
         fp.K = f.pairs[p].K;
         fp.r64 = f.pairs[p].r64;
@@ -1661,12 +1676,16 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
 int upload_filter(FilterPlan &f, int k, bool fp64, hipStream_t st) {
   CHK(f.d_map.reserve(std::max<size_t>(16, f.map_floats * 4)));
   CHK(f.d_bmax.reserve(std::max<size_t>(16, f.blocks * sizeof(float2))));
-  CHK(f.d_partial.reserve((size_t)f.n_lists * k * (fp64 ? sizeof(Key96) : 8)));
+  if (fp64) {
+    CHK(f.d_partial.reserve((size_t)f.n_lists * k * sizeof(Key96)));
+    CHK(f.d_pairs.upload(f.pairs, st));
+  } else {
+    CHK(f.d_und.reserve(((size_t)f.und_zero() + f.und_items[0] + f.und_items[1]) * sizeof(int)));
+  }
   if (f.spread_fps) CHK(f.d_spread.reserve(f.spread_fps * sizeof(FilterSpread)));
   CHK(f.d_fps.upload(f.fps, st));
   CHK(f.d_items.upload(f.items, st));
   CHK(f.d_seq.upload(f.seq, st));
-  CHK(f.d_pairs.upload(f.pairs, st));
   CHK(f.d_direct.upload(f.direct, st));
   return SNCC_OK;
 }
@@ -1775,8 +1794,8 @@ int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, i
   return f.d_tile0.upload(f.tile0, ctx->stream);
 }
 
-// Enqueues the filter (part 0: all but the last selection) and the last
-// selection and the direct form (part 1).
+// Enqueues the filter (part 0: all but the last selection), and the last
+// selection and, in FP64, the direct form (part 1).
 int run_filter(hipStream_t st, FilterPlan &f, const uint32_t *s, const uint32_t *s2,
                long long fs, int P, int k, bool fp64, sncc_match *out, int part) {
   const int4 *geom = f.d_geom->as<int4>();
@@ -1785,26 +1804,46 @@ int run_filter(hipStream_t st, FilterPlan &f, const uint32_t *s, const uint32_t 
   for (size_t i = 0; i < f.chunks.size(); ++i) {
     const FilterChunk &c = f.chunks[i];
     const FilterPair *fps = f.d_fps.as<FilterPair>() + c.fp0;
-    for (const FilterLaunch &l : c.launches)
+    for (const FilterLaunch &l : c.launches) {
+      const bool first = !fp64 && i == 0 && &l == &c.launches[0];
       ok = ok && (part != 0 ||
                   launch_dense_filter(l.digits, l.rv, s, s2, fs, fps,
                                       f.d_items.as<int2>() + l.item0, l.n_items, l.lds,
-                                      f.d_map.as<float>(), f.d_bmax.as<float2>(), st) == 0);
+                                      f.d_map.as<float>(), f.d_bmax.as<float2>(),
+                                      f.d_und.as<int>(), first ? f.und_zero() : 0, st) == 0);
+    }
     if (part != (i + 1 == f.chunks.size())) continue;
     ok = ok && launch_filter_select(fp64, s, s2, fs, P, fps, c.n_fps, f.d_map.as<float>(),
                                     f.d_bmax.as<float2>(), f.d_seq.as<SeqRec>(), geom, c64, k, out,
-                                    f.d_direct.as<int>(),
+                                    f.d_direct.as<int>(), f.undecided(),
                                     c.spread ? f.d_spread.as<FilterSpread>() : nullptr, st) == 0;
   }
-  if (part == 1)
-    ok = ok && launch_seq_topk(fp64, s, s2, fs, P, f.d_pairs.as<SeqPair>(), (int)f.pairs.size(),
-                               f.d_direct.as<int>(), f.chunk, f.d_seq.as<SeqRec>(), geom, c64, k,
-                               f.d_partial.p, f.seq_grid, out, st) == 0;
+  if (part == 1 && fp64)
+    ok = ok && launch_seq_topk(s, s2, fs, P, f.d_pairs.as<SeqPair>(), (int)f.pairs.size(),
+                               f.d_direct.as<int>(), f.chunk, geom, c64, k,
+                               f.d_partial.as<Key96>(), f.seq_grid, out, st) == 0;
   if (!ok) SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
   return SNCC_OK;
 }
 
-// Takes the filtered pairs out of a tile plan's work (their records stay).
+// Enqueues the segment form for the FP32 pairs that the filter has left
+// undecided: launch x of plan `pd` (args `a`) over the items filter_select has
+// listed, with the first launch's floors.
+int run_undecided(hipStream_t st, const FilterPlan &f, int x, const PlanDev &pd, TileArgs a) {
+  if (f.und_items[x] == 0) return SNCC_OK;
+  int *p = f.d_und.as<int>();
+  a.order = f.undecided().order[x];
+  a.qbeg = p + f.und_bounds(x);
+  a.nq = 1;
+  a.queue = p + f.und_queue(x);
+  a.pair_floor = reinterpret_cast<unsigned long long *>(p + f.und_queue(0) + kQueueInts);
+  if (launch_tile(pd.h.cfg, kSinkTopk, a, f.und_grid[x], pd.h.lds_bytes, st) != 0)
+    SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
+  return SNCC_OK;
+}
+
+// Takes the filtered pairs' items out of a tile plan's order (the items and
+// their records stay: run_undecided may list them).
 void drop_items(PlanHost &h, const std::vector<char> &use) {
   std::vector<int> order, qbeg(1, 0);
   for (size_t q = 0; q + 1 < h.qbeg.size(); ++q) {
@@ -1815,8 +1854,6 @@ void drop_items(PlanHost &h, const std::vector<char> &use) {
   h.order = std::move(order);
   h.qbeg = std::move(qbeg);
   h.grid = std::max(1, std::min(h.grid, (int)h.order.size()));
-  for (size_t p = 0; p < h.pairs.size(); ++p)
-    if (use[p]) h.pairs[p].item_end = h.pairs[p].item_begin;
 }
 
 // Plans and uploads the filter for the pairs in `use` of an FP32 plan `d` (and a
@@ -1833,6 +1870,8 @@ int add_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_pa
     return SNCC_OK;
   }
   CHK(upload_filter(d.f, k, false, ctx->stream));
+  d.f.und_grid[0] = std::min(d.h.grid, d.f.und_items[0]);
+  if (edge) d.f.und_grid[1] = std::min(edge->h.grid, d.f.und_items[1]);
   drop_items(d.h, use);
   if (edge) drop_items(edge->h, use);
   return SNCC_OK;
@@ -2406,11 +2445,13 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
     if (filtered)
       CHK(run_filter(ctx->stream, pd->f, d_s, d_s2, fs, sat_pitch, k, false, d_out, 0));
     ctx->mark(1);
-    if (tiles && launch_merge(pd->d_pairs.as<PairDesc>(), nullptr, n_pairs, a.partial, nullptr, k,
-                              d_out, ctx->stream) != 0)
-      SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
-    if (filtered)
+    if (filtered) {
       CHK(run_filter(ctx->stream, pd->f, d_s, d_s2, fs, sat_pitch, k, false, d_out, 1));
+      CHK(run_undecided(ctx->stream, pd->f, 0, *pd, a));
+    }
+    if (launch_merge_lists(pd->d_pairs.as<PairDesc>(), nullptr, n_pairs, a.partial, nullptr,
+                           filtered ? pd->f.d_direct.as<int>() : nullptr, k, d_out, ctx->stream) != 0)
+      SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
     ctx->mark(2);
     if (ctx->timing) ctx->n_stages = 2;
     return SNCC_OK;
@@ -2660,13 +2701,18 @@ int enqueue_stage(sncc_batch *b, int stage, hipStream_t st) {
         CHK(run_filter(st, pd.f, d.d_s, d.d_s2, fs, d.sat_pitch, d.k, false, d.d_topk, 0));
       return SNCC_OK;
     case 2:
-      if (pd.f.active())
+      if (pd.f.active()) {
         CHK(run_filter(st, pd.f, d.d_s, d.d_s2, fs, d.sat_pitch, d.k, false, d.d_topk, 1));
-      if ((!pd.h.order.empty() || (b->edge && !b->edge->h.order.empty())) &&
-          launch_merge(pd.d_pairs.as<PairDesc>(),
-                       b->edge ? b->edge->d_pairs.as<PairDesc>() : nullptr, d.n_pairs, a.partial,
-                       b->edge ? b->edge->d_partial.as<unsigned long long>() : nullptr, d.k,
-                       d.d_topk, st) != 0)
+        CHK(run_undecided(st, pd.f, 0, pd, a));
+        if (b->edge)
+          CHK(run_undecided(st, pd.f, 1, *b->edge,
+                            b->edge->args(d.d_s, d.d_s2, fs, d.sat_pitch, d.M, d.N)));
+      }
+      if (launch_merge_lists(
+              pd.d_pairs.as<PairDesc>(), b->edge ? b->edge->d_pairs.as<PairDesc>() : nullptr,
+              d.n_pairs, a.partial,
+              b->edge ? b->edge->d_partial.as<unsigned long long>() : nullptr,
+              pd.f.active() ? pd.f.d_direct.as<int>() : nullptr, d.k, d.d_topk, st) != 0)
         SNCC_FAIL(SNCC_EDEVICE, "merge launch");
       return SNCC_OK;
     case 3:

@@ -397,8 +397,10 @@ template <int D, int RV, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void dense_filter(
     const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride,
     const FilterPair *__restrict__ fps, const int2 *__restrict__ items, float *__restrict__ map,
-    float2 *__restrict__ bmax) {
+    float2 *__restrict__ bmax, int *__restrict__ zero, int n_zero) {
   extern __shared__ __align__(16) uint8_t lds8[];
+  for (int i = blockIdx.x * (64 * NW) + threadIdx.x; i < n_zero; i += gridDim.x * (64 * NW))
+    zero[i] = 0;  // counters of the launches after this one
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int2 it = items[blockIdx.x];
   if (it.x < 0) return;
@@ -695,7 +697,7 @@ int launch_dense(const DenseArgs &a, hipStream_t st) {
 template <int D, int RV, int NW>
 static int filter_go(const uint32_t *s, const uint32_t *s2, long long frame_stride,
                      const FilterPair *fps, const int2 *items, int n_items, int lds, float *map,
-                     float2 *bmax, hipStream_t st) {
+                     float2 *bmax, int *zero, int n_zero, hipStream_t st) {
   static bool attr = false;
   const void *fn = (const void *)dense_filter<D, RV, NW>;
   if (!attr) {
@@ -705,17 +707,19 @@ static int filter_go(const uint32_t *s, const uint32_t *s2, long long frame_stri
     attr = true;
   }
   hipLaunchKernelGGL((dense_filter<D, RV, NW>), dim3(n_items), dim3(64 * NW), lds, st, s, s2,
-                     frame_stride, fps, items, map, bmax);
+                     frame_stride, fps, items, map, bmax, zero, n_zero);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int launch_dense_filter(int digits, int rv, const uint32_t *s, const uint32_t *s2,
                         long long frame_stride, const FilterPair *fps, const int2 *items,
-                        int n_items, int lds, float *map, float2 *bmax, hipStream_t st) {
+                        int n_items, int lds, float *map, float2 *bmax, int *zero, int n_zero,
+                        hipStream_t st) {
   switch (digits * 100 + rv) {
-#define SNCC_FILTER(D, RV) \
-  case D * 100 + RV:       \
-    return filter_go<D, RV, kDenseNW>(s, s2, frame_stride, fps, items, n_items, lds, map, bmax, st)
+#define SNCC_FILTER(D, RV)                                                                       \
+  case D * 100 + RV:                                                                             \
+    return filter_go<D, RV, kDenseNW>(s, s2, frame_stride, fps, items, n_items, lds, map, bmax, \
+                                      zero, n_zero, st)
     SNCC_FILTER(2, 8);
     SNCC_FILTER(2, 4);
     SNCC_FILTER(2, 2);

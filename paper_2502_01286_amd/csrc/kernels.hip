@@ -598,21 +598,20 @@ int launch_zero(int *p, int n, hipStream_t st) {
 // One wave per pair: merges the pair's item partials into the final top-k.
 // Per pair, the k best of its items' partial lists: the items of `pairs`
 // in `partial` and, when a second launch scored the pair's last tile
-// column, those of `pairs2` in `partial2`.
+// column, those of `pairs2` in `partial2`; pairs without their mark in `scored`
+// (unless it is NULL) have their list from the filter.
 __global__ __launch_bounds__(256) void merge_kernel(const PairDesc *__restrict__ pairs,
                                                     const PairDesc *__restrict__ pairs2,
                                                     int n_pairs,
                                                     const u64 *__restrict__ partial,
-                                                    const u64 *__restrict__ partial2, int k,
+                                                    const u64 *__restrict__ partial2,
+                                                    const int *__restrict__ scored, int k,
                                                     sncc_match *__restrict__ out) {
   const int lane = threadIdx.x & 63;
   const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (p >= n_pairs) return;
+  if (scored && scored[p] == 0) return;
   const PairDesc pd = pairs[p];
-  // a pair without work items has its list from elsewhere (the filter)
-  if (pd.item_begin == pd.item_end &&
-      (!pairs2 || pairs2[p].item_begin == pairs2[p].item_end))
-    return;
   u64 lkey = 0, thr = 0;
   // one load brings the partial lists of g = 64 / k items (lane l holds key
   // l mod k of item l / k), and the next load is issued before the current
@@ -668,10 +667,11 @@ __global__ __launch_bounds__(256) void merge_kernel(const PairDesc *__restrict__
   }
 }
 
-int launch_merge(const PairDesc *pairs, const PairDesc *pairs2, int n_pairs, const u64 *partial,
-                 const u64 *partial2, int k, sncc_match *out, hipStream_t st) {
+int launch_merge_lists(const PairDesc *pairs, const PairDesc *pairs2, int n_pairs,
+                       const u64 *partial, const u64 *partial2, const int *scored, int k,
+                       sncc_match *out, hipStream_t st) {
   hipLaunchKernelGGL(merge_kernel, dim3((n_pairs + 3) / 4), dim3(256), 0, st, pairs, pairs2,
-                     n_pairs, partial, partial2, k, out);
+                     n_pairs, partial, partial2, scored, k, out);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -343,6 +343,7 @@ struct FilterPair {
   // FP32: records of the segment form's sum (SeqRec), [0], and of the offsets
   // from column u_split on, which a batch's second launch scores, [1]
   int seq0[2], n_seq[2], u_split;
+  int item0[2], n_items[2];  // the pair's work items in those two launches
   int seg_off, K;          // the segments
   double r64;
   float error;             // bound on |filter - exact| from its rounded c
@@ -369,8 +370,16 @@ struct SeqRec {
 constexpr uint32_t kSeqNoTerm = 1u << 31, kSeqZero = 1u << 30, kSeqArea = (1u << 24) - 1;
 constexpr int kSeqSlot = 24;
 
-// Candidates a pair may hold; above it the pair takes the direct form.
+// Candidates a pair may hold; above it every offset is scored by the reference:
+// FP64 pairs in the direct form, FP32 pairs in the segment form.
 constexpr int kFilterCands = 512;
+
+// The work items of the FP32 pairs that the filter cannot decide, in the
+// launches [0] and [1] of FilterPair: their number (zero at the filter's first
+// launch; the second word of a queue's two bounds) and the items.
+struct Undecided {
+  int *n[2], *order[2];
+};
 
 // A pair's candidates where their scoring is spread over workgroups: their
 // number (-1: left to the direct form), row-major indices, keys of the accurate
@@ -381,10 +390,10 @@ struct FilterSpread {
   unsigned long long val[kFilterCands], key[kFilterCands];
 };
 
-// One pair of the direct form: every offset by the reference arithmetic.
+// One pair of the FP64 direct form: every offset by the reference arithmetic.
 struct SeqPair {
   int frame, nu, nv, W, H, n, sq_rows;
-  int seq0[2], n_seq[2], u_split, seg_off, K;
+  int seg_off, K;
   int chunk0, n_chunks;    // partial lists
   double q_k, r64;
 };
@@ -398,7 +407,8 @@ int launch_dense_frame(const DenseArgs &a, const uint8_t *f, int M, int f_pitch,
                        long long *energy, hipStream_t st) SNCC_WEAK;
 int launch_dense_filter(int digits, int rv, const uint32_t *s, const uint32_t *s2,
                         long long frame_stride, const FilterPair *fps, const int2 *items,
-                        int n_items, int lds, float *map, float2 *bmax, hipStream_t st) SNCC_WEAK;
+                        int n_items, int lds, float *map, float2 *bmax, int *zero, int n_zero,
+                        hipStream_t st) SNCC_WEAK;
 int launch_dense_above(int digits, int rv, const uint32_t *s, const uint32_t *s2,
                        long long frame_stride, const FilterPair *fps, const int2 *items,
                        int n_items, int lds, const int *tile_count, uint32_t *bits,
@@ -410,11 +420,12 @@ int launch_filter_select(bool fp64, const uint32_t *s, const uint32_t *s2, long 
                          int P, const FilterPair *fps, int n_fps, const float *map,
                          const float2 *bmax, const SeqRec *seq, const int4 *geom,
                          const double *c64, int k, sncc_match *out, int *direct,
-                         FilterSpread *spread, hipStream_t st) SNCC_WEAK;
-int launch_seq_topk(bool fp64, const uint32_t *s, const uint32_t *s2, long long frame_stride,
-                    int P, const SeqPair *pairs, int n_pairs, const int *direct, int chunk,
-                    const SeqRec *seq, const int4 *geom, const double *c64, int k, void *partial,
-                    int grid, sncc_match *out, hipStream_t st) SNCC_WEAK;
+                         const Undecided &und, FilterSpread *spread, hipStream_t st) SNCC_WEAK;
+struct Key96;
+int launch_seq_topk(const uint32_t *s, const uint32_t *s2, long long frame_stride, int P,
+                    const SeqPair *pairs, int n_pairs, const int *direct, int chunk,
+                    const int4 *geom, const double *c64, int k, Key96 *partial, int grid,
+                    sncc_match *out, hipStream_t st) SNCC_WEAK;
 
 // Tile kernel configuration: offsets per lane RU (u, stride 64) x RV (v),
 // NW waves per workgroup, each wave owning RV offset rows; `wgs` is the
@@ -511,9 +522,9 @@ int launch_fused(const FusedArgs &a, hipStream_t st);
 int launch_energy(const uint32_t *s, const uint32_t *s2, int P, int nu, int nv, int W, int H,
                   int sq_rows, long long *energy, int pitch, hipStream_t st);
 int launch_zero(int *p, int n, hipStream_t st);
-int launch_merge(const PairDesc *pairs, const PairDesc *pairs2, int n_pairs,
-                 const unsigned long long *partial, const unsigned long long *partial2,
-                 int k, sncc_match *out, hipStream_t st);
+int launch_merge_lists(const PairDesc *pairs, const PairDesc *pairs2, int n_pairs,
+                       const unsigned long long *partial, const unsigned long long *partial2,
+                       const int *scored, int k, sncc_match *out, hipStream_t st) SNCC_WEAK;
 // Exact selection key of an FP64 value: order code of the double, then the
 // complement of the index (ties to the smaller index).
 struct Key96 {

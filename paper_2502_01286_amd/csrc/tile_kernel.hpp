@@ -440,6 +440,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
   // workgroup b runs order[b] and leaves (no counters: a small launch would
   // otherwise end with each workgroup's round of atomics over every queue).
   const int home = (int)(__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15) % max(nq, 1);
+  // (a queue filled on the device may hold nothing: then no counter is touched)
+  if (SINK == kSinkTopk && nq == 1 && qbeg[1] == 0) return;
   int tried = 0;  // queues found empty (thread 0)
   for (;;) {
     if (threadIdx.x == 0) {

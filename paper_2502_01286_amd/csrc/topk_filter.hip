@@ -6,11 +6,15 @@
 // candidates: the offsets whose filter value is not below the k-th largest by
 // more than twice the two errors.  filter_select finds them (one workgroup per
 // pair), forms their accurate values, scores those near the k-th of them again
-// by the reference arithmetic and orders these, so the
-// result is the reference's, bit for bit.  A pair whose candidates do
-// not fit, or whose nearly uniform windows (where the FP32 bound is too wide)
-// come near the k-th value, is left to seq_topk, which scores every offset by
-// the reference arithmetic; it also takes the FP64 pairs that no filter serves.
+// by the reference arithmetic and orders these, so the result is the
+// reference's, bit for bit.  A pair whose candidates do not fit, or whose nearly
+// uniform windows (where the FP32 bound is too wide) come near the k-th value,
+// is scored at every offset: FP32 pairs by the segment form itself, whose work
+// items filter_select lists for a launch that finds none on most frames, FP64
+// pairs by seq_topk, which also takes those that no filter serves.  Such a call
+// costs that form and the filter: 8 FP32 pairs of 1280 x 720 in us, segment form
+// alone / with the filter, K 2 to 1444: uniform 790 / 980, nearly uniform 795 /
+// 1080, rows of glyphs 1210 / 1050, K 571 to 4957 periodic 4080 / 4070.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -350,7 +354,7 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
     const FilterPair *__restrict__ fps, const float *__restrict__ map,
     const float2 *__restrict__ bmax, const SeqRec *__restrict__ seq,
     const int4 *__restrict__ geom, const double *__restrict__ c64, int k,
-    sncc_match *__restrict__ out, int *__restrict__ direct,
+    sncc_match *__restrict__ out, int *__restrict__ direct, Undecided und,
     FilterSpread *__restrict__ spread) {
   __shared__ int hist[kSelBins];
   __shared__ int list[kSelBlocks];
@@ -387,10 +391,14 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
       }
     __syncthreads();
   };
-  // calls f(value, row-major index) for the values of the listed blocks
+  // calls f(value, row-major index) for the values of the listed blocks (until
+  // there are more candidates than the pair may hold)
   auto scan = [&](auto f) {
     const int units = min(n_list, kSelBlocks) * rv;
     for (int un = wave * 4; un < units; un += kSelThreads / 64 * 4) {
+      if (__hip_atomic_load(&n_cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >
+          kFilterCands)
+        break;
       float4 w[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -431,7 +439,16 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   const float lo = b0 == 0 ? -1.001f : T0;
   const float scale = (float)(kSelBins - 1) / (1.001f - lo);
   scan([&](float x, int) {
-    if (x >= T0) atomicAdd(&hist[min(kSelBins - 1, max(0, (int)((x - lo) * scale)))], 1);
+    if (x >= T0) {
+      // lanes that all meet one bin (uniform frames) add once (8 pairs of a
+      // uniform 1280 x 720: 1870 -> 980 us a call, with the candidates' end above)
+      const int b = min(kSelBins - 1, max(0, (int)((x - lo) * scale)));
+      const int b_first = __builtin_amdgcn_readfirstlane(b);
+      const u64 active = __ballot(1);
+      const bool one = __ballot(b == b_first) == active;
+      if (!one || lane == __ffsll((long long)active) - 1)
+        atomicAdd(&hist[b], one ? __popcll(active) : 1);
+    }
   });
   const int b1 = kth_bin(hist, k, &bin);
   const float T1 = b1 == 0 ? T0 : lo + ((float)b1 - 0.01f) / scale;
@@ -451,6 +468,18 @@ __global__ __launch_bounds__(kSelThreads) void filter_select(
   if (bad || n > kFilterCands) {
     if (tid == 0) direct[fp.pair] = 1;
     if (SPREAD && tid == 0) spread[blockIdx.x].n = -1;
+    if constexpr (!F64) {
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const int m = fp.n_items[x];
+        if (m == 0) continue;
+        __syncthreads();
+        if (tid == 0) n_list = atomicAdd(und.n[x], m);
+        __syncthreads();
+        int *to = und.order[x] + n_list;
+        for (int i = tid; i < m; i += kSelThreads) to[i] = fp.item0[x] + i;
+      }
+    }
     return;
   }
   if constexpr (SPREAD) {
@@ -607,10 +636,11 @@ int launch_filter_select(bool fp64, const uint32_t *s, const uint32_t *s2, long 
                          int P, const FilterPair *fps, int n_fps, const float *map,
                          const float2 *bmax, const SeqRec *seq, const int4 *geom,
                          const double *c64, int k, sncc_match *out, int *direct,
-                         FilterSpread *spread, hipStream_t st) {
+                         const Undecided &und, FilterSpread *spread, hipStream_t st) {
 #define SNCC_SELECT(F64, SPREAD)                                                               \
   hipLaunchKernelGGL((filter_select<F64, SPREAD>), dim3(n_fps), dim3(kSelThreads), 0, st, s, s2, \
-                     frame_stride, P, fps, map, bmax, seq, geom, c64, k, out, direct, spread)
+                     frame_stride, P, fps, map, bmax, seq, geom, c64, k, out, direct, und, \
+                     spread)
   if (fp64) {
     SNCC_SELECT(true, false);
   } else if (!spread) {
@@ -628,31 +658,6 @@ int launch_filter_select(bool fp64, const uint32_t *s, const uint32_t *s2, long 
 }
 
 // --------------------------------------------------------------- direct form
-// rho of one offset per thread by the reference arithmetic.
-__device__ __forceinline__ float lane_ref32(const uint32_t *__restrict__ S,
-                                            const uint32_t *__restrict__ S2, int P, int u, int v,
-                                            const SeqPair &sp, const SeqRec *__restrict__ seq,
-                                            int side) {
-  const Ref32 rf = ref32(S, S2, P, u, v, sp.W, sp.H, sp.n, sp.sq_rows, sp.q_k);
-  const char *w = reinterpret_cast<const char *>(S + (long long)v * P + u);
-  float acc = 0.f, cmp = 0.f, y = -cmp;
-  const SeqRec *sr = seq + sp.seq0[side];
-  for (int i = 0; i < sp.n_seq[side]; i += 8) {
-    uint32_t prev = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const SeqRec e = sr[i + j];
-      const uint32_t D = *reinterpret_cast<const uint32_t *>(w + e.bot) -
-                         *reinterpret_cast<const uint32_t *>(w + e.top);
-      const int G = (int)(D - prev) + __mul24((int)(e.area_flags & kSeqArea), rf.nb);
-      if (!(e.area_flags & (kSeqNoTerm | kSeqZero))) y = __builtin_fmaf((float)G, e.c, y);
-      prev = D;
-    }
-    ref_step(acc, cmp, y);
-  }
-  return (acc - cmp) * rf.scale;
-}
-
 // rho_plain's arithmetic: box_i c_i summed in segment order, FP64.
 __device__ __forceinline__ double lane_ref64(const uint32_t *__restrict__ S,
                                              const uint32_t *__restrict__ S2, int P, int u, int v,
@@ -676,12 +681,11 @@ __device__ __forceinline__ double lane_ref64(const uint32_t *__restrict__ S,
 // The k best offsets of each `chunk` offsets of the pairs that direct[] marks;
 // the chunks of all of them go round the workgroups.  A launch without such
 // pairs only reads the marks.
-template <bool F64>
 __global__ __launch_bounds__(256) void seq_topk(
     const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride, int P,
     const SeqPair *__restrict__ pairs, int n_pairs, const int *__restrict__ direct, int chunk,
-    const SeqRec *__restrict__ seq, const int4 *__restrict__ geom,
-    const double *__restrict__ c64, int k, void *__restrict__ partial) {
+    const int4 *__restrict__ geom, const double *__restrict__ c64, int k,
+    Key96 *__restrict__ partial) {
   __shared__ u64 bh[4 * 64];
   __shared__ uint32_t bl[4 * 64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -706,31 +710,19 @@ __global__ __launch_bounds__(256) void seq_topk(
           const long long e = min(e0 + lane, c1 - 1);
           const int v = (int)(e / sp.nu), u = (int)(e - (long long)v * sp.nu);
           const bool ok = e0 + lane < c1;
-          if constexpr (F64) {
-            const double r = lane_ref64(S, S2, P, u, v, sp, geom, c64);
-            u64 ch = ok ? double_order(r) : 0;
-            uint32_t cl = ok ? 0xffffffffu - (uint32_t)e : 0;
-            for (;;) {  // best first, while they beat the k-th
-              if (!key96_gt(ch, cl, lane_u64(lh, k - 1),
-                            (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)))
-                ch = 0, cl = 0;
-              if (__ballot(ch != 0 || cl != 0) == 0) break;
-              u64 mh;
-              uint32_t ml;
-              wave_max96(ch, cl, mh, ml);
-              topk96_insert(lh, ll, mh, ml, k, lane);
-              if (ch == mh && cl == ml) ch = 0, cl = 0;
-            }
-          } else {
-            float r = 0.f;  // either side of u_split only where the wave has offsets there
-            const bool right = u >= sp.u_split;
-            if (__ballot(!right)) r = lane_ref32(S, S2, P, u, v, sp, seq, 0);
-            if (__ballot(right)) {
-              const float r1 = lane_ref32(S, S2, P, u, v, sp, seq, 1);
-              r = right ? r1 : r;
-            }
-            u64 cnd[1] = {ok ? make_key(r, (int)e) : 0};
-            topk_offer<1>(lh, cnd, k, lane);
+          const double r = lane_ref64(S, S2, P, u, v, sp, geom, c64);
+          u64 ch = ok ? double_order(r) : 0;
+          uint32_t cl = ok ? 0xffffffffu - (uint32_t)e : 0;
+          for (;;) {  // best first, while they beat the k-th
+            if (!key96_gt(ch, cl, lane_u64(lh, k - 1),
+                          (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)))
+              ch = 0, cl = 0;
+            if (__ballot(ch != 0 || cl != 0) == 0) break;
+            u64 mh;
+            uint32_t ml;
+            wave_max96(ch, cl, mh, ml);
+            topk96_insert(lh, ll, mh, ml, k, lane);
+            if (ch == mh && cl == ml) ch = 0, cl = 0;
           }
         }
         if (lane < k) {
@@ -748,13 +740,7 @@ __global__ __launch_bounds__(256) void seq_topk(
                 break;
               topk96_insert(lh, ll, kh, kl, k, lane);
             }
-          if (lane < k) {
-            const long long o = (long long)(sp.chunk0 + c) * k + lane;
-            if constexpr (F64)
-              static_cast<Key96 *>(partial)[o] = Key96{lh, ll, 0};
-            else
-              static_cast<u64 *>(partial)[o] = lh;
-          }
+          if (lane < k) partial[(long long)(sp.chunk0 + c) * k + lane] = Key96{lh, ll, 0};
         }
         __syncthreads();
       }
@@ -765,10 +751,9 @@ __global__ __launch_bounds__(256) void seq_topk(
 
 // One wave per marked pair: the k best of its chunks' lists; one load brings
 // 64 / k of them.
-template <bool F64>
 __global__ __launch_bounds__(256) void seq_merge(const SeqPair *__restrict__ pairs, int n_pairs,
                                                  const int *__restrict__ direct,
-                                                 const void *__restrict__ partial, int k,
+                                                 const Key96 *__restrict__ partial, int k,
                                                  sncc_match *__restrict__ out) {
   const int lane = threadIdx.x & 63;
   const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -781,14 +766,9 @@ __global__ __launch_bounds__(256) void seq_merge(const SeqPair *__restrict__ pai
     u64 h = 0;
     uint32_t l = 0;
     if (lane < g * k && c + lane / k < end) {
-      const long long o = (long long)c * k + lane;
-      if constexpr (F64) {
-        const Key96 e = static_cast<const Key96 *>(partial)[o];
-        h = e.hi;
-        l = e.lo;
-      } else {
-        h = static_cast<const u64 *>(partial)[o];
-      }
+      const Key96 e = partial[(long long)c * k + lane];
+      h = e.hi;
+      l = e.lo;
     }
     u64 todo = __ballot(key96_gt(h, l, lane_u64(lh, k - 1),
                                  (uint32_t)__builtin_amdgcn_readlane((int)ll, k - 1)));
@@ -807,31 +787,23 @@ __global__ __launch_bounds__(256) void seq_merge(const SeqPair *__restrict__ pai
     m.u = m.v = -1;
     m.rho = -__builtin_inff();
     if (lh != 0 || ll != 0) {
-      const int idx = (int)(0xffffffffu - (F64 ? ll : (uint32_t)(lh & 0xffffffffu)));
+      const int idx = (int)(0xffffffffu - ll);
       m.v = idx / sp.nu;
       m.u = idx - m.v * sp.nu;
-      m.rho = F64 ? (float)double_unorder(lh) : float_unorder((uint32_t)(lh >> 32));
+      m.rho = (float)double_unorder(lh);
     }
     out[(long long)p * k + lane] = m;
   }
 }
 
-int launch_seq_topk(bool fp64, const uint32_t *s, const uint32_t *s2, long long frame_stride,
-                    int P, const SeqPair *pairs, int n_pairs, const int *direct, int chunk,
-                    const SeqRec *seq, const int4 *geom, const double *c64, int k, void *partial,
-                    int grid, sncc_match *out, hipStream_t st) {
-  const dim3 mg((n_pairs + 3) / 4);
-  if (fp64) {
-    hipLaunchKernelGGL(seq_topk<true>, dim3(grid), dim3(256), 0, st, s, s2, frame_stride, P, pairs,
-                       n_pairs, direct, chunk, seq, geom, c64, k, partial);
-    hipLaunchKernelGGL(seq_merge<true>, mg, dim3(256), 0, st, pairs, n_pairs, direct, partial, k,
-                       out);
-  } else {
-    hipLaunchKernelGGL(seq_topk<false>, dim3(grid), dim3(256), 0, st, s, s2, frame_stride, P,
-                       pairs, n_pairs, direct, chunk, seq, geom, c64, k, partial);
-    hipLaunchKernelGGL(seq_merge<false>, mg, dim3(256), 0, st, pairs, n_pairs, direct, partial, k,
-                       out);
-  }
+int launch_seq_topk(const uint32_t *s, const uint32_t *s2, long long frame_stride, int P,
+                    const SeqPair *pairs, int n_pairs, const int *direct, int chunk,
+                    const int4 *geom, const double *c64, int k, Key96 *partial, int grid,
+                    sncc_match *out, hipStream_t st) {
+  hipLaunchKernelGGL(seq_topk, dim3(grid), dim3(256), 0, st, s, s2, frame_stride, P, pairs,
+                     n_pairs, direct, chunk, geom, c64, k, partial);
+  hipLaunchKernelGGL(seq_merge, dim3((n_pairs + 3) / 4), dim3(256), 0, st, pairs, n_pairs, direct,
+                     partial, k, out);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

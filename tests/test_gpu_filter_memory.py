@@ -72,7 +72,7 @@ def test_no_memory_for_the_matrix_core_forms(monkeypatch, refuse):
     temps = [synth.crop_template(rng, frames[0], w, h, sigma_max=12)[0] for w, h in zip(W, H)]
     coarse = [S.sncc_segment_template(t, 12)[0] for t in temps]
     detail = [S.sncc_segment_template(t, 8)[0] for t in temps]
-    ctx = S.sncc_ctx_create(0)
+    ctx, other = S.sncc_ctx_create(0), None
     try:
         f, s, s2 = build_sats(S, ctx, frames)
         want = {}
@@ -86,13 +86,11 @@ def test_no_memory_for_the_matrix_core_forms(monkeypatch, refuse):
         fine2 = S.sncc_upload_templates(ctx, detail, W, H)
         calls = _calls(S, ctx, s, s2, f, new, fine2)
         if refuse == "scratch":
-            for call in calls.values():  # operands exist; a map plan takes the place of the rest
+            for call in calls.values():
                 call()
-            S.sncc_tmpl_destroy(tm)
-            S.sncc_tmpl_destroy(fine)
-            S.sncc_ctx_destroy(ctx)
-            ctx = S.sncc_ctx_create(0)  # the operands stay with the templates
-            calls = _calls(S, ctx, s, s2, f, new, fine2)
+            S.sncc_sync(ctx)
+            other = S.sncc_ctx_create(0)  # without plans; the operands are the templates'
+            calls = _calls(S, other, s, s2, f, new, fine2)
         monkeypatch.setenv("SNCC_TEST_FAIL_ALLOC", "300000")
         for name in calls:
             for turn in range(2):
@@ -105,11 +103,10 @@ def test_no_memory_for_the_matrix_core_forms(monkeypatch, refuse):
                 else:
                     assert torch.equal(got, want[name]), name
         monkeypatch.delenv("SNCC_TEST_FAIL_ALLOC")
-        if refuse == "operands":
-            S.sncc_tmpl_destroy(tm)
-            S.sncc_tmpl_destroy(fine)
-        S.sncc_tmpl_destroy(new)
-        S.sncc_tmpl_destroy(fine2)
+        for x in (tm, fine, new, fine2):
+            S.sncc_tmpl_destroy(x)
     finally:
         monkeypatch.delenv("SNCC_TEST_FAIL_ALLOC", raising=False)
+        if other:
+            S.sncc_ctx_destroy(other)
         S.sncc_ctx_destroy(ctx)
