@@ -845,7 +845,7 @@ struct FilterPlan {
   std::vector<SeqRec> seq;
   std::vector<SeqPair> pairs;   // every pair of the call
   std::vector<int> direct;      // 1: every offset by the direct (FP64) or segment form
-  int chunk = 0, n_lists = 0;   // offsets per partial list of the direct form
+  int n_lists = 0;              // partial lists of the direct form
   int seq_grid = 1;
   // the launches of the segment form for undecided FP32 pairs: grids, items that
   // may be listed
@@ -1515,6 +1515,13 @@ std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N,
   return use;
 }
 
+// Offsets per partial list of the direct form; a quarter of it for pairs of more
+// than kSeqLongK segments, whose lists would otherwise be the launch's tail (one
+// pair of 1320 x 720 with 64 x 64 at K 2620: 3.75 -> 1.56 ms, its map in the
+// plain form 1.25; 8 pairs of 1280 x 720 at K 2 to 1444 on a uniform frame 2.71
+// -> 1.64, with one plain map and list after the other 2.40).
+constexpr int kSeqChunk = 4096, kSeqLongK = 64;
+
 // Plans the filter for the pairs marked in `use` (cleared where the operands
 // cannot be had) and, in FP64, the direct form for the others and for those the
 // filter cannot decide; FP32 sums are ordered as plan `tile` has them, and in
@@ -1538,7 +1545,6 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
   f.direct.assign(n_pairs, 0);
   std::vector<int> idx;
   std::vector<double> cost(n_pairs, 0.0);
-  long long offsets = 0, most = 0;
   for (int p = 0; p < n_pairs; ++p) {
     const int t = pairs[2 * p + 1];
     const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
@@ -1566,8 +1572,6 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
     q.K = tm->K[t];
     q.q_k = tm->q_k[t];
     q.r64 = tm->r64[t];
-    offsets += (long long)nu * nv;
-    most = std::max(most, (long long)nu * nv);
   }
   f.d_geom = tm->d_geom;
   f.d_c64 = tm->d_c64;
@@ -1575,15 +1579,23 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
     std::lock_guard<std::mutex> lk(tm->dense_mu);
     f.operands = tm->dense_bufs;
   }
-  // lists of the direct form: short enough to spread a pair over the chip,
-  // long enough that the lists of all pairs stay within 64 MB
-  const size_t key = fp64 ? sizeof(Key96) : 8;
-  f.chunk = 4096;
-  while (f.chunk < (64 << 10) && (size_t)(offsets / f.chunk + n_pairs) * k * key > ((size_t)64 << 20))
-    f.chunk *= 2;
+  // lists of the direct form: short enough to spread a pair over the chip, also
+  // where few pairs of many segments make up the work, long enough that the
+  // lists of all pairs stay within 64 MB
+  int chunk = kSeqChunk;
+  auto pair_chunk = [&](const SeqPair &q) { return q.K > kSeqLongK ? chunk / 4 : chunk; };
+  auto lists = [&]() {
+    long long n = 0;
+    for (const SeqPair &q : f.pairs)
+      n += ((long long)q.nu * q.nv + pair_chunk(q) - 1) / pair_chunk(q);
+    return n;
+  };
+  while (fp64 && chunk < (1 << 24) && (size_t)lists() * k * sizeof(Key96) > ((size_t)64 << 20))
+    chunk *= 2;
   for (SeqPair &q : f.pairs) {
+    q.chunk = pair_chunk(q);
     q.chunk0 = f.n_lists;
-    q.n_chunks = (int)(((long long)q.nu * q.nv + f.chunk - 1) / f.chunk);
+    q.n_chunks = (int)(((long long)q.nu * q.nv + q.chunk - 1) / q.chunk);
     f.n_lists += q.n_chunks;
   }
   f.seq_grid = (int)std::min<long long>(f.n_lists, 8LL * std::max(1, ctx->num_cu));
@@ -1820,7 +1832,7 @@ int run_filter(hipStream_t st, FilterPlan &f, const uint32_t *s, const uint32_t 
   }
   if (part == 1 && fp64)
     ok = ok && launch_seq_topk(s, s2, fs, P, f.d_pairs.as<SeqPair>(), (int)f.pairs.size(),
-                               f.d_direct.as<int>(), f.chunk, geom, c64, k,
+                               f.d_direct.as<int>(), geom, c64, k,
                                f.d_partial.as<Key96>(), f.seq_grid, out, st) == 0;
   if (!ok) SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
   return SNCC_OK;

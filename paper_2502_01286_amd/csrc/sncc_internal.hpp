@@ -394,7 +394,7 @@ struct FilterSpread {
 struct SeqPair {
   int frame, nu, nv, W, H, n, sq_rows;
   int seg_off, K;
-  int chunk0, n_chunks;    // partial lists
+  int chunk, chunk0, n_chunks;  // offsets per partial list; first list, lists
   double q_k, r64;
 };
 
@@ -423,7 +423,7 @@ int launch_filter_select(bool fp64, const uint32_t *s, const uint32_t *s2, long 
                          const Undecided &und, FilterSpread *spread, hipStream_t st) SNCC_WEAK;
 struct Key96;
 int launch_seq_topk(const uint32_t *s, const uint32_t *s2, long long frame_stride, int P,
-                    const SeqPair *pairs, int n_pairs, const int *direct, int chunk,
+                    const SeqPair *pairs, int n_pairs, const int *direct,
                     const int4 *geom, const double *c64, int k, Key96 *partial, int grid,
                     sncc_match *out, hipStream_t st) SNCC_WEAK;
 

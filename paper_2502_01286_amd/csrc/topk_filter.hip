@@ -678,12 +678,12 @@ __device__ __forceinline__ double lane_ref64(const uint32_t *__restrict__ S,
   return plain_rho(acc, sf, V, sp.n, sp.q_k, sp.r64);
 }
 
-// The k best offsets of each `chunk` offsets of the pairs that direct[] marks;
+// The k best offsets of each sp.chunk offsets of the pairs that direct[] marks;
 // the chunks of all of them go round the workgroups.  A launch without such
 // pairs only reads the marks.
 __global__ __launch_bounds__(256) void seq_topk(
     const uint32_t *__restrict__ s, const uint32_t *__restrict__ s2, long long frame_stride, int P,
-    const SeqPair *__restrict__ pairs, int n_pairs, const int *__restrict__ direct, int chunk,
+    const SeqPair *__restrict__ pairs, int n_pairs, const int *__restrict__ direct,
     const int4 *__restrict__ geom, const double *__restrict__ c64, int k,
     Key96 *__restrict__ partial) {
   __shared__ u64 bh[4 * 64];
@@ -703,7 +703,7 @@ __global__ __launch_bounds__(256) void seq_topk(
       if (c < 0) c += grid;
       for (; c < sp.n_chunks; c += grid) {
         const long long total = (long long)sp.nu * sp.nv;
-        const long long c0 = (long long)c * chunk, c1 = min(total, c0 + chunk);
+        const long long c0 = (long long)c * sp.chunk, c1 = min(total, c0 + sp.chunk);
         u64 lh = 0;
         uint32_t ll = 0;
         for (long long e0 = c0 + wave * 64; e0 < c1; e0 += 4 * 64) {
@@ -797,11 +797,11 @@ __global__ __launch_bounds__(256) void seq_merge(const SeqPair *__restrict__ pai
 }
 
 int launch_seq_topk(const uint32_t *s, const uint32_t *s2, long long frame_stride, int P,
-                    const SeqPair *pairs, int n_pairs, const int *direct, int chunk,
+                    const SeqPair *pairs, int n_pairs, const int *direct,
                     const int4 *geom, const double *c64, int k, Key96 *partial, int grid,
                     sncc_match *out, hipStream_t st) {
   hipLaunchKernelGGL(seq_topk, dim3(grid), dim3(256), 0, st, s, s2, frame_stride, P, pairs,
-                     n_pairs, direct, chunk, geom, c64, k, partial);
+                     n_pairs, direct, geom, c64, k, partial);
   hipLaunchKernelGGL(seq_merge, dim3((n_pairs + 3) / 4), dim3(256), 0, st, pairs, n_pairs, direct,
                      partial, k, out);
   return hipGetLastError() == hipSuccess ? 0 : -1;

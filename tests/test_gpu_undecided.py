@@ -73,3 +73,42 @@ def test_undecided_pairs_cost_the_segment_form(monkeypatch, kind, batch):
         assert ms[1] < 2.0 * ms[0]
     finally:
         S.sncc_ctx_destroy(ctx)
+
+
+def test_undecided_fp64_pair_costs_the_plain_form(monkeypatch):
+    """One FP64 pair of many segments whose every offset is scored: about the
+    time of the plain form's map (which has no list to keep), so its lists fill
+    the chip."""
+    import torch
+    import paper_2502_01286_amd as S
+    torch.cuda.init()
+    ctx = S.sncc_ctx_create(0)
+    w = h = 64
+    t, _, _ = synth.crop_template(np.random.default_rng(8), synth.scene(3, M, N), w, h, sigma_max=2)
+    segs = S.sncc_segment_template(t, 2)[0]
+    assert len(segs) > 500
+    _, s, s2 = build_sats(S, ctx, [_frame("uniform")])
+    rho = torch.zeros((N - h + 1, M - w + 1), dtype=torch.float64, device="cuda")
+    top = torch.zeros((1, K, 3), dtype=torch.int32, device="cuda")
+    ms = []
+    try:
+        monkeypatch.setenv("SNCC_TEST_DENSE", "0")
+        tm = S.sncc_upload_templates(ctx, [segs], [w], [h])
+        for call in (lambda: S.sncc_score(ctx, tm, 0, s[0], s2[0], M, N, S.SNCC_FP64, rho),
+                     lambda: S.sncc_topk(ctx, tm, s, s2, 1, M, N, [(0, 0)], K, S.SNCC_FP64, top)):
+            best = 1e9
+            for _ in range(8):
+                e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                e[0].record()
+                call()
+                e[1].record()
+                S.sncc_sync(ctx)
+                best = min(best, e[0].elapsed_time(e[1]))
+            ms.append(best)
+        print("case K", len(segs), "plain map", round(ms[0], 3), "top-k", round(ms[1], 3), flush=True)
+        got = S.decode_matches(top)[0]
+        assert [(int(m["u"]), int(m["v"])) for m in got] == [(i, 0) for i in range(K)]
+        assert ms[1] < 1.5 * ms[0]
+        S.sncc_tmpl_destroy(tm)
+    finally:
+        S.sncc_ctx_destroy(ctx)
