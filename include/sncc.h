@@ -333,10 +333,14 @@ int sncc_score_frame(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint8_
  * whose error bound leaves few candidates and the rho of those by the
  * precision's own sums: the same lists, bit for bit, as without it.  The
  * context keeps the work list of its last call of each precision on the
- * device, with the filter's scratch (at most 256 MB, or one pair's map of 4
- * bytes an offset if that is more), and reuses it when the next call has the
- * same template set, sizes, pitch, k and pairs (calls on one context are
- * ordered by its stream).
+ * device and reuses it when the next call has the same template set, sizes,
+ * pitch, k and pairs (calls on one context are ordered by its stream).  For
+ * each precision it also keeps the filter's scratch, as large as its largest
+ * call's: maps of at most 256 MB (or one pair's map of 4 bytes an offset, if
+ * that is more), FP64 partial lists of about 64 MB (at least k of 16 bytes per
+ * pair) and at most 11 kB per pair of a map chunk; sncc_ctx_destroy frees it.
+ * A work list keeps the matrix-core operands that it uses after their template
+ * set is destroyed.
  *
  *   d_s, d_s2  sum tables of B frames (layout of sncc_build_sats)
  *   pairs      host, n_pairs x {frame, template}
@@ -457,8 +461,10 @@ typedef struct sncc_batch_stats {
  * desc->tune is set), and captures sum-table construction, the persistent
  * scoring launches, top-k selection and (optionally) FP64 refinement into
  * one HIP graph on the context's stream.  Pairs for which sncc_topk's filter
- * is faster leave the persistent launches (scratch of at most 1 GB, or one
- * pair's map).  The descriptor's buffers are bound at this point.  Errors: as for the calls it combines.
+ * is faster leave the persistent launches (the batch keeps their maps of at
+ * most 1 GB, or one pair's map, up to 11 kB per pair of a map chunk and the
+ * operands that it uses).  The descriptor's buffers are bound at this point.
+ * Errors: as for the calls it combines.
  */
 int sncc_batch_create(sncc_ctx *ctx, const sncc_batch_desc *desc,
                       sncc_batch **out);

@@ -148,11 +148,21 @@ struct PlanKey {
 
 constexpr int kSlotTopk64 = kSinkCompact + 1;
 
+// What the filter's launches of one call write and read again: the rough maps,
+// their blocks' largest values, the direct form's lists and the spread
+// candidates.  Kept by the context for the top-k of each precision (calls on it
+// are ordered by its stream) and grown on demand, so that a new pair list brings
+// only its tables, and by each batch for itself.
+struct FilterScratch {
+  DevBuf map, bmax, partial, spread;
+};
+
 struct sncc_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
   int num_cu = 0;
   DevBuf sat_scratch;
+  FilterScratch filter32, filter64;
   DevBuf frame_s, frame_s2;  // one frame's tables (global form of sncc_score_frame)
   std::vector<std::unique_ptr<PlanDev>> retired;  // awaiting completion
   bool timing = false;                             // record stage events
@@ -852,7 +862,8 @@ struct FilterPlan {
   int und_grid[2] = {0, 0}, und_items[2] = {0, 0};
   size_t map_floats = 0, blocks = 0;
   size_t spread_fps = 0;        // most pairs of a spread chunk
-  DevBuf d_fps, d_items, d_seq, d_pairs, d_direct, d_map, d_bmax, d_partial, d_spread, d_und;
+  DevBuf d_fps, d_items, d_seq, d_pairs, d_direct, d_und;
+  FilterScratch *scratch = nullptr, own;  // the context's, or a batch's own
   // the template set's memory that the launches read: a batch outlives the set
   std::shared_ptr<DevBuf> d_geom, d_c64;
   std::vector<std::shared_ptr<DevBuf>> operands;
@@ -1685,16 +1696,16 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
   }
 }
 
-int upload_filter(FilterPlan &f, int k, bool fp64, hipStream_t st) {
-  CHK(f.d_map.reserve(std::max<size_t>(16, f.map_floats * 4)));
-  CHK(f.d_bmax.reserve(std::max<size_t>(16, f.blocks * sizeof(float2))));
-  if (fp64) {
-    CHK(f.d_partial.reserve((size_t)f.n_lists * k * sizeof(Key96)));
+int upload_filter(FilterPlan &f, FilterScratch *scratch, int k, bool fp64, hipStream_t st) {
+  f.scratch = scratch;
+  CHK(scratch->map.reserve(std::max<size_t>(16, f.map_floats * 4)));
+  CHK(scratch->bmax.reserve(std::max<size_t>(16, f.blocks * sizeof(float2))));
+  if (fp64) CHK(scratch->partial.reserve((size_t)f.n_lists * k * sizeof(Key96)));
+  if (f.spread_fps) CHK(scratch->spread.reserve(f.spread_fps * sizeof(FilterSpread)));
+  if (fp64)
     CHK(f.d_pairs.upload(f.pairs, st));
-  } else {
+  else
     CHK(f.d_und.reserve(((size_t)f.und_zero() + f.und_items[0] + f.und_items[1]) * sizeof(int)));
-  }
-  if (f.spread_fps) CHK(f.d_spread.reserve(f.spread_fps * sizeof(FilterSpread)));
   CHK(f.d_fps.upload(f.fps, st));
   CHK(f.d_items.upload(f.items, st));
   CHK(f.d_seq.upload(f.seq, st));
@@ -1812,6 +1823,7 @@ int run_filter(hipStream_t st, FilterPlan &f, const uint32_t *s, const uint32_t 
                long long fs, int P, int k, bool fp64, sncc_match *out, int part) {
   const int4 *geom = f.d_geom->as<int4>();
   const double *c64 = f.d_c64->as<double>();
+  FilterScratch &sc = *f.scratch;
   bool ok = true;
   for (size_t i = 0; i < f.chunks.size(); ++i) {
     const FilterChunk &c = f.chunks[i];
@@ -1821,19 +1833,19 @@ int run_filter(hipStream_t st, FilterPlan &f, const uint32_t *s, const uint32_t 
       ok = ok && (part != 0 ||
                   launch_dense_filter(l.digits, l.rv, s, s2, fs, fps,
                                       f.d_items.as<int2>() + l.item0, l.n_items, l.lds,
-                                      f.d_map.as<float>(), f.d_bmax.as<float2>(),
+                                      sc.map.as<float>(), sc.bmax.as<float2>(),
                                       f.d_und.as<int>(), first ? f.und_zero() : 0, st) == 0);
     }
     if (part != (i + 1 == f.chunks.size())) continue;
-    ok = ok && launch_filter_select(fp64, s, s2, fs, P, fps, c.n_fps, f.d_map.as<float>(),
-                                    f.d_bmax.as<float2>(), f.d_seq.as<SeqRec>(), geom, c64, k, out,
+    ok = ok && launch_filter_select(fp64, s, s2, fs, P, fps, c.n_fps, sc.map.as<float>(),
+                                    sc.bmax.as<float2>(), f.d_seq.as<SeqRec>(), geom, c64, k, out,
                                     f.d_direct.as<int>(), f.undecided(),
-                                    c.spread ? f.d_spread.as<FilterSpread>() : nullptr, st) == 0;
+                                    c.spread ? sc.spread.as<FilterSpread>() : nullptr, st) == 0;
   }
   if (part == 1 && fp64)
     ok = ok && launch_seq_topk(s, s2, fs, P, f.d_pairs.as<SeqPair>(), (int)f.pairs.size(),
                                f.d_direct.as<int>(), geom, c64, k,
-                               f.d_partial.as<Key96>(), f.seq_grid, out, st) == 0;
+                               sc.partial.as<Key96>(), f.seq_grid, out, st) == 0;
   if (!ok) SNCC_FAIL(SNCC_EDEVICE, "top-k launch: %s", hipGetErrorString(hipGetLastError()));
   return SNCC_OK;
 }
@@ -1873,7 +1885,7 @@ void drop_items(PlanHost &h, const std::vector<char> &use) {
 // be had.
 int add_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_pairs,
                const int32_t *pairs, int k, std::vector<char> &use, PlanDev &d, PlanDev *edge,
-               size_t map_floats) {
+               size_t map_floats, FilterScratch *scratch) {
   if (std::find(use.begin(), use.end(), 1) == use.end()) return SNCC_OK;
   plan_filter(ctx, tm, M, N, P, n_pairs, pairs, k, false, &d.h, use, d.f, map_floats,
               edge ? &edge->h : nullptr);
@@ -1881,7 +1893,7 @@ int add_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_pa
     d.f.pairs.clear();  // not active
     return SNCC_OK;
   }
-  CHK(upload_filter(d.f, k, false, ctx->stream));
+  CHK(upload_filter(d.f, scratch, k, false, ctx->stream));
   d.f.und_grid[0] = std::min(d.h.grid, d.f.und_items[0]);
   if (edge) d.f.und_grid[1] = std::min(edge->h.grid, d.f.und_items[1]);
   drop_items(d.h, use);
@@ -2442,7 +2454,7 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
       if (!filter) return SNCC_OK;
       std::vector<char> use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, k, false);
       return add_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, use, d, nullptr,
-                        kFilterMapFloats);
+                        kFilterMapFloats, &ctx->filter32);
     }, &pd));
     TileArgs a = pd->args(d_s, d_s2, fs, sat_pitch, M, N);
     ctx->n_stages = 0;
@@ -2482,7 +2494,7 @@ int sncc_topk(sncc_ctx *ctx, const sncc_tmpl *tm, const uint32_t *d_s, const uin
     std::vector<char> use(n_pairs, 0);  // without the filter: the direct form for all pairs
     if (filter) use = filter_pairs(ctx, tm, M, N, n_pairs, pairs, k, true);
     plan_filter(ctx, tm, M, N, sat_pitch, n_pairs, pairs, k, true, nullptr, use, d.f);
-    return upload_filter(d.f, k, true, ctx->stream);
+    return upload_filter(d.f, &ctx->filter64, k, true, ctx->stream);
   }, &pd, false));
   for (int part = 0; part < 2; ++part)
     CHK(run_filter(ctx->stream, pd->f, d_s, d_s2, fs, sat_pitch, k, true, d_out, part));
@@ -2976,7 +2988,7 @@ int sncc_batch_create(sncc_ctx *ctx, const sncc_batch_desc *desc, sncc_batch **o
       std::vector<char> use =
           filter_pairs(ctx, d.coarse, d.M, d.N, d.n_pairs, b->pairs.data(), d.k, false, true);
       CHK(add_filter(ctx, d.coarse, d.M, d.N, d.sat_pitch, d.n_pairs, b->pairs.data(), d.k, use, p,
-                     b->edge.get(), kFilterBatchFloats));
+                     b->edge.get(), kFilterBatchFloats, &p.f.own));
     }
     return any_edge ? b->edge->upload(ctx->stream) : SNCC_OK;
   }, true, ctx->stream, &b->plan));
