@@ -148,6 +148,38 @@ struct PlanKey {
 
 constexpr int kSlotTopk64 = kSinkCompact + 1;
 
+// Another stream of the caller's may be under capture while operands are built
+// or waited for: memory, events and waits stay allowed on this thread and out
+// of that graph.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// The stream on which a device's operands are built.  It belongs to the contexts
+// and operands that use it and is never captured, so that its events may be
+// asked for while the callers' streams are.
+struct BuildStream {
+  hipStream_t st = nullptr;
+  ~BuildStream() {
+    if (st) (void)hipStreamDestroy(st);
+  }
+};
+
+// Operands built together; `built` is recorded behind them, `done` is set once
+// it was seen to be complete.
+struct DenseBuf {
+  std::shared_ptr<BuildStream> stream;
+  DevBuf mem;
+  hipEvent_t built = nullptr;
+  std::atomic<bool> done{false};
+  ~DenseBuf() {
+    RelaxedCapture relaxed;
+    if (built && !done.load()) (void)hipEventSynchronize(built);
+    if (built) (void)hipEventDestroy(built);
+  }
+};
 // What the filter's launches of one call write and read again: the rough maps,
 // their blocks' largest values, the direct form's lists and the spread
 // candidates.  Kept by the context for the top-k of each precision (calls on it
@@ -163,6 +195,7 @@ struct sncc_ctx {
   int num_cu = 0;
   DevBuf sat_scratch;
   FilterScratch filter32, filter64;
+  std::shared_ptr<BuildStream> build;  // made at the first build of operands
   DevBuf frame_s, frame_s2;  // one frame's tables (global form of sncc_score_frame)
   std::vector<std::unique_ptr<PlanDev>> retired;  // awaiting completion
   bool timing = false;                             // record stage events
@@ -188,6 +221,7 @@ constexpr int kDenseForms = 4;
 int dense_form(int digits) { return digits == 7 ? 3 : digits - 2; }
 struct DenseTmpl {
   const void *frag = nullptr;  // nullptr: not built
+  std::shared_ptr<DenseBuf> buf;
   int digits = 0;
   double scale = 0;            // 2^e: c in units of the last digit
   double csum = 0;             // sum of the fixed-point image
@@ -212,7 +246,6 @@ struct sncc_tmpl {
   // built on demand by calls that take the set as const, from any thread
   mutable std::mutex dense_mu;
   mutable std::unique_ptr<DenseTmpl[]> dense;  // kDenseForms per template (dense_form)
-  mutable std::vector<std::shared_ptr<DevBuf>> dense_bufs;
   mutable size_t dense_bytes = 0;
 };
 
@@ -866,7 +899,7 @@ struct FilterPlan {
   FilterScratch *scratch = nullptr, own;  // the context's, or a batch's own
   // the template set's memory that the launches read: a batch outlives the set
   std::shared_ptr<DevBuf> d_geom, d_c64;
-  std::vector<std::shared_ptr<DevBuf>> operands;
+  std::vector<std::shared_ptr<DenseBuf>> operands;
   bool active() const { return !pairs.empty(); }
   // d_und: the counters and pair floors of the first launch and its queue's
   // bounds, those of the second, which takes the same floors, then the items
@@ -892,7 +925,7 @@ struct AbovePlan {
   int rv = 8, n_tiles = 0;
   size_t words = 0;
   DevBuf d_fps, d_items, d_fp_of_pair, d_tile0, d_bits, d_live;
-  std::vector<std::shared_ptr<DevBuf>> operands;
+  std::vector<std::shared_ptr<DenseBuf>> operands;
   bool active() const { return !fps.empty(); }
 };
 
@@ -1233,10 +1266,59 @@ const DenseTmpl *dense_built(const sncc_tmpl *tm, int t, int digits) {
   return dt.frag ? &dt : nullptr;
 }
 
+bool stream_captured(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// Makes the context's stream wait for operands that may still be on their way
+// (the host only where the stream is under capture: a graph cannot wait for work
+// outside it); false where that fails.
+bool dense_wait(sncc_ctx *ctx, const DenseTmpl &dt) {
+  DenseBuf &b = *dt.buf;
+  if (b.done.load(std::memory_order_acquire)) return true;
+  RelaxedCapture relaxed;
+  hipError_t e = hipEventQuery(b.built);
+  if (e == hipErrorNotReady) {
+    (void)hipGetLastError();
+    const bool captured = stream_captured(ctx->stream);
+    e = captured ? hipEventSynchronize(b.built) : hipStreamWaitEvent(ctx->stream, b.built, 0);
+    if (!captured && e == hipSuccess) return true;
+  }
+  if (e == hipSuccess)
+    b.done.store(true, std::memory_order_release);
+  else
+    (void)hipGetLastError();
+  return e == hipSuccess;
+}
+
+// The device's build stream, made where neither the context nor another one
+// holds it (nullptr: cannot be had).
+std::shared_ptr<BuildStream> build_stream(sncc_ctx *ctx) {
+  if (ctx->build) return ctx->build;
+  static std::mutex mu;
+  static std::map<int, std::weak_ptr<BuildStream>> shared;
+  std::lock_guard<std::mutex> lk(mu);
+  std::shared_ptr<BuildStream> b = shared[ctx->device].lock();
+  if (!b) {
+    b = std::make_shared<BuildStream>();
+    if (hipStreamCreateWithFlags(&b->st, hipStreamNonBlocking) != hipSuccess) {
+      b->st = nullptr;
+      return nullptr;
+    }
+    shared[ctx->device] = b;
+  }
+  return ctx->build = b;
+}
+
 // Builds the operands of the templates in `want` ({template, digits}) that are
-// not built yet (small launches, then one wait, so that any stream may read
-// them afterwards).  Where they cannot be had (no memory, or the stream is
-// being captured) they stay unbuilt, and callers take another form.
+// not built yet: small launches on the build stream, without a wait (the
+// segments they read were complete when the set was uploaded; dense_wait orders
+// the callers' streams behind them).  Where they cannot be had (no memory, or
+// the context's stream is being captured) they stay unbuilt, and callers take
+// another form.
 void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair<int, int>> &want) {
   std::lock_guard<std::mutex> lk(tm->dense_mu);
   if (!tm->dense) tm->dense.reset(new (std::nothrow) DenseTmpl[kDenseForms * (size_t)tm->T]);
@@ -1264,36 +1346,50 @@ void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair
     image = std::max(image, (size_t)W * H * 8);
   }
   if (jobs.empty()) return;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
-    return;
-  // (another stream of the caller's may be captured meanwhile: memory and the
-  // wait below stay allowed on this thread and out of that graph)
-  struct Relaxed {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-    ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-  } relaxed;
-  std::shared_ptr<DevBuf> buf(new (std::nothrow) DevBuf());
-  if (!buf || buf->reserve(bytes + image) != SNCC_OK) {
+  if (stream_captured(ctx->stream)) return;
+  RelaxedCapture relaxed;
+  std::shared_ptr<DenseBuf> buf(new (std::nothrow) DenseBuf());
+  if (!buf || !(buf->stream = build_stream(ctx)) || buf->mem.reserve(bytes + image) != SNCC_OK ||
+      hipEventCreateWithFlags(&buf->built, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
     g_err.clear();
     return;
   }
-  char *base = buf->as<char>();
+  char *base = buf->mem.as<char>();
   bool ok = true;
   for (const Job &j : jobs)
     ok = ok && launch_dense_pack(tm->d_geom->as<int4>() + tm->seg_off[j.t],
                                  tm->d_c64->as<double>() + tm->seg_off[j.t], tm->K[j.t],
                                  j.made.scale, tm->W[j.t], tm->H[j.t], j.made.digits,
                                  reinterpret_cast<long long *>(base + bytes), base + j.at,
-                                 ctx->stream) == 0;
-  if (hipStreamSynchronize(ctx->stream) != hipSuccess || !ok) return;
+                                 buf->stream->st) == 0;
+  if (!ok || hipEventRecord(buf->built, buf->stream->st) != hipSuccess) {
+    (void)hipStreamSynchronize(buf->stream->st);  // the buffer goes
+    (void)hipGetLastError();
+    return;
+  }
   for (Job &j : jobs) {
     j.made.frag = base + j.at;
+    j.made.buf = buf;
     *j.dt = j.made;
   }
   tm->dense_bytes += bytes + image;
-  tm->dense_bufs.push_back(std::move(buf));
+}
+
+// Template t's operands of `digits` digits, built if they are not and in order
+// before what follows on the context's stream, or nullptr.
+const DenseTmpl *dense_operands(sncc_ctx *ctx, const sncc_tmpl *tm, int t, int digits) {
+  const DenseTmpl *dt = dense_built(tm, t, digits);
+  if (!dt) {
+    dense_build(ctx, tm, {{t, digits}});
+    dt = dense_built(tm, t, digits);
+  }
+  return dt && dense_wait(ctx, *dt) ? dt : nullptr;
+}
+
+// Adds the operands a plan uses to those it keeps alive.
+void keep_operands(const DenseTmpl &dt, std::vector<std::shared_ptr<DenseBuf>> &kept) {
+  if (std::find(kept.begin(), kept.end(), dt.buf) == kept.end()) kept.push_back(dt.buf);
 }
 
 // Launch shape of the matrix-core form for a map of nu x nv offsets: false
@@ -1559,7 +1655,7 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
   for (int p = 0; p < n_pairs; ++p) {
     const int t = pairs[2 * p + 1];
     const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
-    if (use[p] && !dense_built(tm, t, tm->digits_f[t])) use[p] = 0;
+    if (use[p] && !dense_operands(ctx, tm, t, tm->digits_f[t])) use[p] = 0;
     if (use[p]) {
       idx.push_back(p);
       cost[p] = (double)tm->H[t] * dense_groups(tm->W[t]) * tm->digits_f[t];
@@ -1586,10 +1682,6 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
   }
   f.d_geom = tm->d_geom;
   f.d_c64 = tm->d_c64;
-  {
-    std::lock_guard<std::mutex> lk(tm->dense_mu);
-    f.operands = tm->dense_bufs;
-  }
   // lists of the direct form: short enough to spread a pair over the chip, also
   // where few pairs of many segments make up the work, long enough that the
   // lists of all pairs stay within 64 MB
@@ -1651,7 +1743,9 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
           f.direct[p] = 1;
           continue;
         }
-        dense_constants(tm, t, *dense_built(tm, t, digits), N, P, fp.a);
+        const DenseTmpl &dt = *dense_built(tm, t, digits);
+        dense_constants(tm, t, dt, N, P, fp.a);
+        keep_operands(dt, f.operands);
         const int tiles = fp.a.ntu * fp.a.ntv;
         fp.map0 = (long long)floats;
         fp.block0 = blocks;
@@ -1772,13 +1866,14 @@ int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, i
     for (int p = 0; p < n_pairs; ++p) {
       const int t = pairs[2 * p + 1];
       const DenseTmpl *dt = limit[t] >= 0 && slow->digits_f[t] == digits
-                                ? dense_built(slow, t, digits)
+                                ? dense_operands(ctx, slow, t, digits)
                                 : nullptr;
       if (!dt) continue;
       const PairDesc &q = h.pairs[p];
       FilterPair fp{};
       if (!dense_shape(slow, t, digits, q.nu, q.nv, ctx->num_cu, fp.a, f.rv)) continue;
       dense_constants(slow, t, *dt, N, P, fp.a);
+      keep_operands(*dt, f.operands);
       const int tiles = fp.a.ntu * fp.a.ntv;
       fp.pair = p;
       fp.frame = pairs[2 * p];
@@ -1804,10 +1899,6 @@ int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, i
   if (f.fps.empty()) {
     f.n_tiles = 0;  // no counters
     return SNCC_OK;
-  }
-  {
-    std::lock_guard<std::mutex> lk(slow->dense_mu);
-    f.operands = slow->dense_bufs;
   }
   CHK(f.d_bits.reserve(f.words * 4));
   CHK(f.d_live.reserve(std::max<size_t>(16, (size_t)h.run_cap * sizeof(LiveRun))));
@@ -1910,11 +2001,8 @@ int dense_map(sncc_ctx *ctx, const sncc_tmpl *tm, int t, const uint32_t *s, cons
   if ((long long)tm->W[t] * tm->H[t] > kDenseMaxArea) return 0;
   const int digits = fp64 ? kDenseDigits : tm->digits32[t];
   if (!dense_shape(tm, t, digits, nu, nv, ctx->num_cu, a) || !dense_wins(tm, t, a)) return 0;
-  const DenseTmpl *dt = dense_built(tm, t, digits);
-  if (!dt) {
-    dense_build(ctx, tm, {{t, digits}});
-    if (!(dt = dense_built(tm, t, digits))) return 0;
-  }
+  const DenseTmpl *dt = dense_operands(ctx, tm, t, digits);
+  if (!dt) return 0;
   a.s = s;
   a.s2 = s2;
   dense_constants(tm, t, *dt, N, P, a);
@@ -1968,11 +2056,8 @@ int dense_frame_map(sncc_ctx *ctx, const sncc_tmpl *tm, int t, const uint8_t *f,
   a.hb = 4 * dense_rows4(a.H);
   if (dense_frame_lds(a) > (size_t)kTileMaxLds / 2 - 256) return 0;
   if (forced >= 0 ? forced == 0 : !dense_frame_wins(tm, t, M, N, ctx->num_cu, local, a)) return 0;
-  const DenseTmpl *dt = dense_built(tm, t, 3);
-  if (!dt) {
-    dense_build(ctx, tm, {{t, 3}});
-    if (!(dt = dense_built(tm, t, 3))) return 0;
-  }
+  const DenseTmpl *dt = dense_operands(ctx, tm, t, 3);
+  if (!dt) return 0;
   dense_constants(tm, t, *dt, N, 0, a);
   a.rho = rho;
   a.rho_pitch = rho_pitch;
