@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -157,29 +158,27 @@ struct RelaxedCapture {
   ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
-// The stream on which a device's operands are built.  It belongs to the contexts
-// and operands that use it and is never captured, so that its events may be
-// asked for while the callers' streams are.
-struct BuildStream {
-  hipStream_t st = nullptr;
-  ~BuildStream() {
-    if (st) (void)hipStreamDestroy(st);
+// Counts a context's finished builds of operands in host memory, where the
+// device writes it: unlike an event's state it may be read while any stream is
+// under capture (HIP ends the capture of a stream whose events are asked for).
+struct BuildCount {
+  unsigned long long *host = nullptr, *dev = nullptr;
+  unsigned long long next = 0;
+  ~BuildCount() {
+    if (host) (void)hipHostFree(host);
   }
 };
 
-// Operands built together; `built` is recorded behind them, `done` is set once
-// it was seen to be complete.
+// Operands built together by the context `ctx` (its serial), on its stream;
+// complete when its count reaches `ticket`.
 struct DenseBuf {
-  std::shared_ptr<BuildStream> stream;
-  DevBuf mem;
-  hipEvent_t built = nullptr;
-  std::atomic<bool> done{false};
-  ~DenseBuf() {
-    RelaxedCapture relaxed;
-    if (built && !done.load()) (void)hipEventSynchronize(built);
-    if (built) (void)hipEventDestroy(built);
-  }
+  std::shared_ptr<BuildCount> count;
+  DevBuf mem;  // freed first, which waits for the build
+  unsigned long long ticket = 0;
+  uint64_t ctx = 0;
+  bool complete() const { return __atomic_load_n(count->host, __ATOMIC_ACQUIRE) >= ticket; }
 };
+
 // What the filter's launches of one call write and read again: the rough maps,
 // their blocks' largest values, the direct form's lists and the spread
 // candidates.  Kept by the context for the top-k of each precision (calls on it
@@ -195,7 +194,8 @@ struct sncc_ctx {
   int num_cu = 0;
   DevBuf sat_scratch;
   FilterScratch filter32, filter64;
-  std::shared_ptr<BuildStream> build;  // made at the first build of operands
+  uint64_t serial = 0;                 // unique per context
+  std::shared_ptr<BuildCount> builds;  // made at the first build of operands
   DevBuf frame_s, frame_s2;  // one frame's tables (global form of sncc_score_frame)
   std::vector<std::unique_ptr<PlanDev>> retired;  // awaiting completion
   bool timing = false;                             // record stage events
@@ -216,11 +216,12 @@ struct sncc_ctx {
 
 // A template's operands of one matrix-core form (FP32 or FP64;
 // dense_kernel.hip), built at the first call that uses them and kept with the
-// template set.
+// template set: those of one build, or several while contexts on different
+// streams need them before the first build is complete.
 constexpr int kDenseForms = 4;
 int dense_form(int digits) { return digits == 7 ? 3 : digits - 2; }
 struct DenseTmpl {
-  const void *frag = nullptr;  // nullptr: not built
+  const void *frag = nullptr;  // nullptr: none
   std::shared_ptr<DenseBuf> buf;
   int digits = 0;
   double scale = 0;            // 2^e: c in units of the last digit
@@ -240,12 +241,17 @@ struct sncc_tmpl {
   std::vector<std::vector<double>> c64;
   std::vector<double> q_k, r64;
   std::vector<DevTmpl> dev;  // generic (plain / refine) descriptors
-  DevBuf d_area, d_dev, d_c32;
-  // shared with the plans that read them: a plan may outlive the set
-  std::shared_ptr<DevBuf> d_geom = std::make_shared<DevBuf>(), d_c64 = std::make_shared<DevBuf>();
+  // one device buffer (shared with the plans that read it: a plan may outlive
+  // the set) and its parts: segments, c_i in FP64 and FP32, areas, constants
+  std::shared_ptr<DevBuf> d_all = std::make_shared<DevBuf>();
+  const int4 *geom = nullptr;
+  const double *c64_dev = nullptr;
+  const float *c32_dev = nullptr;
+  const int *area_dev = nullptr;
+  const DevTmpl *dev_dev = nullptr;
   // built on demand by calls that take the set as const, from any thread
   mutable std::mutex dense_mu;
-  mutable std::unique_ptr<DenseTmpl[]> dense;  // kDenseForms per template (dense_form)
+  mutable std::vector<std::vector<DenseTmpl>> dense;  // kDenseForms per template (dense_form)
   mutable size_t dense_bytes = 0;
 };
 
@@ -898,7 +904,9 @@ struct FilterPlan {
   DevBuf d_fps, d_items, d_seq, d_pairs, d_direct, d_und;
   FilterScratch *scratch = nullptr, own;  // the context's, or a batch's own
   // the template set's memory that the launches read: a batch outlives the set
-  std::shared_ptr<DevBuf> d_geom, d_c64;
+  std::shared_ptr<DevBuf> segs;
+  const int4 *geom = nullptr;
+  const double *c64 = nullptr;
   std::vector<std::shared_ptr<DenseBuf>> operands;
   bool active() const { return !pairs.empty(); }
   // d_und: the counters and pair floors of the first launch and its queue's
@@ -1258,14 +1266,6 @@ int dense_digits_filter(const sncc_tmpl *tm, int t, float *error) {
   return 0;
 }
 
-// Template t's operands of `digits` digits, or nullptr where not built.
-const DenseTmpl *dense_built(const sncc_tmpl *tm, int t, int digits) {
-  std::lock_guard<std::mutex> lk(tm->dense_mu);
-  if (!tm->dense) return nullptr;
-  const DenseTmpl &dt = tm->dense[kDenseForms * (size_t)t + dense_form(digits)];
-  return dt.frag ? &dt : nullptr;
-}
-
 bool stream_captured(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
@@ -1273,58 +1273,47 @@ bool stream_captured(hipStream_t st) {
   return true;
 }
 
-// Makes the context's stream wait for operands that may still be on their way
-// (the host only where the stream is under capture: a graph cannot wait for work
-// outside it); false where that fails.
-bool dense_wait(sncc_ctx *ctx, const DenseTmpl &dt) {
-  DenseBuf &b = *dt.buf;
-  if (b.done.load(std::memory_order_acquire)) return true;
-  RelaxedCapture relaxed;
-  hipError_t e = hipEventQuery(b.built);
-  if (e == hipErrorNotReady) {
-    (void)hipGetLastError();
-    const bool captured = stream_captured(ctx->stream);
-    e = captured ? hipEventSynchronize(b.built) : hipStreamWaitEvent(ctx->stream, b.built, 0);
-    if (!captured && e == hipSuccess) return true;
+// Template t's operands of `digits` digits that the context may read: complete
+// ones, else those it enqueued itself (with tm->dense_mu held).
+DenseTmpl dense_usable(const sncc_ctx *ctx, const sncc_tmpl *tm, int t, int digits) {
+  DenseTmpl mine;
+  if (tm->dense.empty()) return mine;
+  for (const DenseTmpl &dt : tm->dense[kDenseForms * (size_t)t + dense_form(digits)]) {
+    if (dt.buf->complete()) return dt;
+    if (dt.buf->ctx == ctx->serial) mine = dt;
   }
-  if (e == hipSuccess)
-    b.done.store(true, std::memory_order_release);
-  else
-    (void)hipGetLastError();
-  return e == hipSuccess;
+  return mine;
 }
 
-// The device's build stream, made where neither the context nor another one
-// holds it (nullptr: cannot be had).
-std::shared_ptr<BuildStream> build_stream(sncc_ctx *ctx) {
-  if (ctx->build) return ctx->build;
-  static std::mutex mu;
-  static std::map<int, std::weak_ptr<BuildStream>> shared;
-  std::lock_guard<std::mutex> lk(mu);
-  std::shared_ptr<BuildStream> b = shared[ctx->device].lock();
-  if (!b) {
-    b = std::make_shared<BuildStream>();
-    if (hipStreamCreateWithFlags(&b->st, hipStreamNonBlocking) != hipSuccess) {
-      b->st = nullptr;
-      return nullptr;
-    }
-    shared[ctx->device] = b;
+bool build_count(sncc_ctx *ctx) {
+  if (ctx->builds) return true;
+  auto b = std::make_shared<BuildCount>();
+  if (hipHostMalloc(reinterpret_cast<void **>(&b->host), sizeof *b->host,
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+    b->host = nullptr;
+    return false;
   }
-  return ctx->build = b;
+  *b->host = 0;
+  if (hipHostGetDevicePointer(reinterpret_cast<void **>(&b->dev), b->host, 0) != hipSuccess)
+    return false;
+  ctx->builds = std::move(b);
+  return true;
 }
 
-// Builds the operands of the templates in `want` ({template, digits}) that are
-// not built yet: small launches on the build stream, without a wait (the
-// segments they read were complete when the set was uploaded; dense_wait orders
-// the callers' streams behind them).  Where they cannot be had (no memory, or
-// the context's stream is being captured) they stay unbuilt, and callers take
-// another form.
+// Builds the operands of the templates in `want` ({template, digits}) that the
+// context cannot read yet: small launches on its stream, without a wait, so that
+// a template's first call costs little more than the next (640 x 480 with 32 x
+// 32, us for the upload and the first map from the frame: 23 + 40, later maps
+// 29; with a wait and an upload in five copies 37 + 48, on a stream of their own
+// behind an event 23 + 58, in the tile-local form without operands 39 + 36 and
+// 34).  Where
+// they cannot be had (no memory, or the stream is being captured) they stay
+// unbuilt, and callers take another form.
 void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair<int, int>> &want) {
   std::lock_guard<std::mutex> lk(tm->dense_mu);
-  if (!tm->dense) tm->dense.reset(new (std::nothrow) DenseTmpl[kDenseForms * (size_t)tm->T]);
-  if (!tm->dense) return;
+  if (tm->dense.empty()) tm->dense.resize(kDenseForms * (size_t)tm->T);
   struct Job {
-    DenseTmpl *dt;
+    size_t slot;
     DenseTmpl made;
     int t;
     size_t at;
@@ -1332,59 +1321,71 @@ void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair
   std::vector<Job> jobs;
   size_t bytes = 0, image = 0;  // the fixed-point image is reused, in stream order
   for (const auto &w : want) {
-    DenseTmpl *dt = &tm->dense[kDenseForms * (size_t)w.first + dense_form(w.second)];
-    bool listed = dt->frag != nullptr;
-    for (const Job &j : jobs) listed |= j.dt == dt;
+    const size_t slot = kDenseForms * (size_t)w.first + dense_form(w.second);
+    bool listed = dense_usable(ctx, tm, w.first, w.second).frag != nullptr;
+    for (const Job &j : jobs) listed |= j.slot == slot;
     if (listed) continue;
     const int W = tm->W[w.first], H = tm->H[w.first];
     const size_t fb = dense_frag_bytes(W, H, w.second);
     if (tm->dense_bytes + bytes + fb > kDenseSetBytes) continue;
-    Job j{dt, DenseTmpl{}, w.first, bytes};
+    Job j{slot, DenseTmpl{}, w.first, bytes};
     (void)dense_fixed_point(tm, w.first, w.second, j.made);
     jobs.push_back(j);
     bytes += fb;
     image = std::max(image, (size_t)W * H * 8);
   }
-  if (jobs.empty()) return;
-  if (stream_captured(ctx->stream)) return;
+  if (jobs.empty() || stream_captured(ctx->stream)) return;
   RelaxedCapture relaxed;
   std::shared_ptr<DenseBuf> buf(new (std::nothrow) DenseBuf());
-  if (!buf || !(buf->stream = build_stream(ctx)) || buf->mem.reserve(bytes + image) != SNCC_OK ||
-      hipEventCreateWithFlags(&buf->built, hipEventDisableTiming) != hipSuccess) {
+  if (!buf || !build_count(ctx) || buf->mem.reserve(bytes + image) != SNCC_OK) {
     (void)hipGetLastError();
     g_err.clear();
     return;
   }
+  buf->count = ctx->builds;
+  buf->ticket = ++ctx->builds->next;
+  buf->ctx = ctx->serial;
   char *base = buf->mem.as<char>();
   bool ok = true;
   for (const Job &j : jobs)
-    ok = ok && launch_dense_pack(tm->d_geom->as<int4>() + tm->seg_off[j.t],
-                                 tm->d_c64->as<double>() + tm->seg_off[j.t], tm->K[j.t],
-                                 j.made.scale, tm->W[j.t], tm->H[j.t], j.made.digits,
+    ok = ok && launch_dense_pack(tm->geom + tm->seg_off[j.t], tm->c64_dev + tm->seg_off[j.t],
+                                 tm->K[j.t], j.made.scale, tm->W[j.t], tm->H[j.t], j.made.digits,
                                  reinterpret_cast<long long *>(base + bytes), base + j.at,
-                                 buf->stream->st) == 0;
-  if (!ok || hipEventRecord(buf->built, buf->stream->st) != hipSuccess) {
-    (void)hipStreamSynchronize(buf->stream->st);  // the buffer goes
+                                 ctx->stream) == 0;
+  if (!ok || launch_count(buf->count->dev, buf->ticket, ctx->stream) != 0) {
+    (void)hipStreamSynchronize(ctx->stream);  // the buffer goes
     (void)hipGetLastError();
     return;
   }
   for (Job &j : jobs) {
     j.made.frag = base + j.at;
     j.made.buf = buf;
-    *j.dt = j.made;
+    tm->dense[j.slot].push_back(j.made);
   }
   tm->dense_bytes += bytes + image;
 }
 
-// Template t's operands of `digits` digits, built if they are not and in order
-// before what follows on the context's stream, or nullptr.
-const DenseTmpl *dense_operands(sncc_ctx *ctx, const sncc_tmpl *tm, int t, int digits) {
-  const DenseTmpl *dt = dense_built(tm, t, digits);
-  if (!dt) {
+// Template t's operands of `digits` digits, built if the context has none to
+// read; frag is nullptr where they cannot be had.  Under capture the context's
+// own are waited for on the host (at most 10 s), since a graph may be launched
+// on another stream than theirs.
+DenseTmpl dense_operands(sncc_ctx *ctx, const sncc_tmpl *tm, int t, int digits) {
+  auto usable = [&]() {
+    std::lock_guard<std::mutex> lk(tm->dense_mu);
+    return dense_usable(ctx, tm, t, digits);
+  };
+  DenseTmpl dt = usable();
+  if (!dt.frag) {
     dense_build(ctx, tm, {{t, digits}});
-    dt = dense_built(tm, t, digits);
+    dt = usable();
   }
-  return dt && dense_wait(ctx, *dt) ? dt : nullptr;
+  if (!dt.frag || dt.buf->complete() || !stream_captured(ctx->stream)) return dt;
+  const auto give_up = std::chrono::steady_clock::now() + std::chrono::seconds(10);
+  while (!dt.buf->complete()) {
+    if (std::chrono::steady_clock::now() > give_up) return DenseTmpl{};
+    std::this_thread::yield();
+  }
+  return dt;
 }
 
 // Adds the operands a plan uses to those it keeps alive.
@@ -1643,6 +1644,7 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
   std::sort(want.begin(), want.end());
   want.erase(std::unique(want.begin(), want.end()), want.end());
   if (!want.empty()) dense_build(ctx, tm, want);
+  std::vector<DenseTmpl> ops(tm->T);
   std::vector<int> seq0[2], n_seq[2];
   for (int i = 0; i < 2; ++i) {
     seq0[i].assign(tm->T, -1);
@@ -1655,7 +1657,8 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
   for (int p = 0; p < n_pairs; ++p) {
     const int t = pairs[2 * p + 1];
     const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
-    if (use[p] && !dense_operands(ctx, tm, t, tm->digits_f[t])) use[p] = 0;
+    if (use[p] && !ops[t].frag) ops[t] = dense_operands(ctx, tm, t, tm->digits_f[t]);
+    if (use[p] && !ops[t].frag) use[p] = 0;
     if (use[p]) {
       idx.push_back(p);
       cost[p] = (double)tm->H[t] * dense_groups(tm->W[t]) * tm->digits_f[t];
@@ -1680,8 +1683,9 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
     q.q_k = tm->q_k[t];
     q.r64 = tm->r64[t];
   }
-  f.d_geom = tm->d_geom;
-  f.d_c64 = tm->d_c64;
+  f.segs = tm->d_all;
+  f.geom = tm->geom;
+  f.c64 = tm->c64_dev;
   // lists of the direct form: short enough to spread a pair over the chip, also
   // where few pairs of many segments make up the work, long enough that the
   // lists of all pairs stay within 64 MB
@@ -1743,9 +1747,8 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
           f.direct[p] = 1;
           continue;
         }
-        const DenseTmpl &dt = *dense_built(tm, t, digits);
-        dense_constants(tm, t, dt, N, P, fp.a);
-        keep_operands(dt, f.operands);
+        dense_constants(tm, t, ops[t], N, P, fp.a);
+        keep_operands(ops[t], f.operands);
         const int tiles = fp.a.ntu * fp.a.ntv;
         fp.map0 = (long long)floats;
         fp.block0 = blocks;
@@ -1865,15 +1868,14 @@ int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, i
     FilterLaunch l{digits, f.rv, (int)f.items.size(), 0, 0};
     for (int p = 0; p < n_pairs; ++p) {
       const int t = pairs[2 * p + 1];
-      const DenseTmpl *dt = limit[t] >= 0 && slow->digits_f[t] == digits
-                                ? dense_operands(ctx, slow, t, digits)
-                                : nullptr;
-      if (!dt) continue;
+      DenseTmpl dt;
+      if (limit[t] >= 0 && slow->digits_f[t] == digits) dt = dense_operands(ctx, slow, t, digits);
+      if (!dt.frag) continue;
       const PairDesc &q = h.pairs[p];
       FilterPair fp{};
       if (!dense_shape(slow, t, digits, q.nu, q.nv, ctx->num_cu, fp.a, f.rv)) continue;
-      dense_constants(slow, t, *dt, N, P, fp.a);
-      keep_operands(*dt, f.operands);
+      dense_constants(slow, t, dt, N, P, fp.a);
+      keep_operands(dt, f.operands);
       const int tiles = fp.a.ntu * fp.a.ntv;
       fp.pair = p;
       fp.frame = pairs[2 * p];
@@ -1912,8 +1914,8 @@ int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, i
 // selection and, in FP64, the direct form (part 1).
 int run_filter(hipStream_t st, FilterPlan &f, const uint32_t *s, const uint32_t *s2,
                long long fs, int P, int k, bool fp64, sncc_match *out, int part) {
-  const int4 *geom = f.d_geom->as<int4>();
-  const double *c64 = f.d_c64->as<double>();
+  const int4 *geom = f.geom;
+  const double *c64 = f.c64;
   FilterScratch &sc = *f.scratch;
   bool ok = true;
   for (size_t i = 0; i < f.chunks.size(); ++i) {
@@ -2001,11 +2003,11 @@ int dense_map(sncc_ctx *ctx, const sncc_tmpl *tm, int t, const uint32_t *s, cons
   if ((long long)tm->W[t] * tm->H[t] > kDenseMaxArea) return 0;
   const int digits = fp64 ? kDenseDigits : tm->digits32[t];
   if (!dense_shape(tm, t, digits, nu, nv, ctx->num_cu, a) || !dense_wins(tm, t, a)) return 0;
-  const DenseTmpl *dt = dense_operands(ctx, tm, t, digits);
-  if (!dt) return 0;
+  const DenseTmpl dt = dense_operands(ctx, tm, t, digits);
+  if (!dt.frag) return 0;
   a.s = s;
   a.s2 = s2;
-  dense_constants(tm, t, *dt, N, P, a);
+  dense_constants(tm, t, dt, N, P, a);
   a.rho = rho;
   a.rho_pitch = rho_pitch;
   a.degen = degen;
@@ -2056,9 +2058,9 @@ int dense_frame_map(sncc_ctx *ctx, const sncc_tmpl *tm, int t, const uint8_t *f,
   a.hb = 4 * dense_rows4(a.H);
   if (dense_frame_lds(a) > (size_t)kTileMaxLds / 2 - 256) return 0;
   if (forced >= 0 ? forced == 0 : !dense_frame_wins(tm, t, M, N, ctx->num_cu, local, a)) return 0;
-  const DenseTmpl *dt = dense_operands(ctx, tm, t, 3);
-  if (!dt) return 0;
-  dense_constants(tm, t, *dt, N, 0, a);
+  const DenseTmpl dt = dense_operands(ctx, tm, t, 3);
+  if (!dt.frag) return 0;
+  dense_constants(tm, t, dt, N, 0, a);
   a.rho = rho;
   a.rho_pitch = rho_pitch;
   a.degen = degen;
@@ -2207,6 +2209,8 @@ int sncc_ctx_create(int device, uintptr_t hip_stream, sncc_ctx **out) {
               hipGetErrorString(hipGetLastError()));
   sncc_ctx *c = new (std::nothrow) sncc_ctx();
   if (!c) SNCC_FAIL(SNCC_ENOMEM, "context allocation");
+  static std::atomic<uint64_t> serials{0};
+  c->serial = ++serials;
   c->device = device;
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   c->num_cu = prop.multiProcessorCount;
@@ -2320,12 +2324,27 @@ int sncc_upload_templates(sncc_ctx *ctx, int T, const sncc_segment *const *segs,
     tm->digits_f.push_back(dense_digits_filter(tm.get(), t, &error));
     tm->error_f.push_back(error);
   }
+  // one copy of all parts, each at a multiple of 16 bytes
   std::vector<float> c32all(c64all.begin(), c64all.end());
-  CHK(tm->d_geom->upload(geom, ctx->stream));
-  CHK(tm->d_c64->upload(c64all, ctx->stream));
-  CHK(tm->d_c32.upload(c32all, ctx->stream));
-  CHK(tm->d_area.upload(areas, ctx->stream));
-  CHK(tm->d_dev.upload(tm->dev, ctx->stream));
+  std::vector<char> all;
+  auto put = [&](const void *p, size_t bytes) {
+    const size_t at = all.size();
+    all.resize(at + (bytes + 15) / 16 * 16);
+    memcpy(all.data() + at, p, bytes);
+    return at;
+  };
+  const size_t geom_at = put(geom.data(), geom.size() * sizeof(int4));
+  const size_t c64_at = put(c64all.data(), c64all.size() * sizeof(double));
+  const size_t c32_at = put(c32all.data(), c32all.size() * sizeof(float));
+  const size_t area_at = put(areas.data(), areas.size() * sizeof(int));
+  const size_t dev_at = put(tm->dev.data(), tm->dev.size() * sizeof(DevTmpl));
+  CHK(tm->d_all->upload(all, ctx->stream));
+  const char *base = tm->d_all->as<char>();
+  tm->geom = reinterpret_cast<const int4 *>(base + geom_at);
+  tm->c64_dev = reinterpret_cast<const double *>(base + c64_at);
+  tm->c32_dev = reinterpret_cast<const float *>(base + c32_at);
+  tm->area_dev = reinterpret_cast<const int *>(base + area_at);
+  tm->dev_dev = reinterpret_cast<const DevTmpl *>(base + dev_at);
   HIPCHK(hipStreamSynchronize(ctx->stream));
   *out = tm.release();
   return SNCC_OK;
@@ -2388,9 +2407,9 @@ int sncc_score(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint32_t *d_
     a.sq_rows = tm->dev[index].sq_rows;
     a.q_k = tm->q_k[index];
     a.r64 = tm->r64[index];
-    a.geom = tm->d_geom->as<int4>() + tm->seg_off[index];
-    a.c64 = tm->d_c64->as<double>() + tm->seg_off[index];
-    a.area = tm->d_area.as<int>() + tm->seg_off[index];
+    a.geom = tm->geom + tm->seg_off[index];
+    a.c64 = tm->c64_dev + tm->seg_off[index];
+    a.area = tm->area_dev + tm->seg_off[index];
     a.rho = static_cast<double *>(d_rho);
     a.rho_pitch = rho_pitch;
     a.degen = d_degenerate;
@@ -2480,9 +2499,9 @@ int sncc_score_frame(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint8_
     a.K = tm->K[index];
     a.nu = nu;
     a.nv = nv;
-    a.geom = tm->d_geom->as<int4>() + tm->seg_off[index];
-    a.area = tm->d_area.as<int>() + tm->seg_off[index];
-    a.c32 = tm->d_c32.as<float>() + tm->seg_off[index];
+    a.geom = tm->geom + tm->seg_off[index];
+    a.area = tm->area_dev + tm->seg_off[index];
+    a.c32 = tm->c32_dev + tm->seg_off[index];
     a.q_k = tm->q_k[index];
     a.rho = d_rho;
     a.rho_pitch = rho_pitch;
@@ -2633,7 +2652,7 @@ int sncc_refine(sncc_ctx *ctx, const sncc_tmpl *fine, const uint32_t *d_s, const
   CHK(pd->d_slot_w.upload(h.slot_w, ctx->stream));
   CHK(pd->d_refine_order.upload(h.refine_order, ctx->stream));
   if (launch_refine(d_s, d_s2, (long long)(N + 1) * sat_pitch, sat_pitch,
-                    fine->d_dev.as<DevTmpl>(), fine->d_geom->as<int4>(), fine->d_c64->as<double>(),
+                    fine->dev_dev, fine->geom, fine->c64_dev,
                     pd->slots(), pd->d_pairs.as<PairDesc>(), n_pairs, d_cand, n_cand, radius,
                     d_out, d_count, ctx->stream) != 0)
     SNCC_FAIL(SNCC_EDEVICE, "refine launch: %s", hipGetErrorString(hipGetLastError()));
@@ -2702,9 +2721,9 @@ int sncc_threshold_match(sncc_ctx *ctx, const sncc_tmpl *fast, const sncc_tmpl *
   sa.frame_stride = fs;
   sa.P = sat_pitch;
   sa.N = N;
-  sa.tmpls = slow->d_dev.as<DevTmpl>();
-  sa.geom = slow->d_geom->as<int4>();
-  sa.c64 = slow->d_c64->as<double>();
+  sa.tmpls = slow->dev_dev;
+  sa.geom = slow->geom;
+  sa.c64 = slow->c64_dev;
   sa.stmpl = pd->d_slow.as<SlowTmpl>();
   sa.slot_off = pd->d_slot_off.as<uint32_t>();
   sa.slot_w = pd->d_slot_w.as<double>();
@@ -2826,8 +2845,8 @@ int enqueue_stage(sncc_batch *b, int stage, hipStream_t st) {
       return SNCC_OK;
     case 3:
       if (d.fine &&
-          launch_refine(d.d_s, d.d_s2, fs, d.sat_pitch, d.fine->d_dev.as<DevTmpl>(),
-                        d.fine->d_geom->as<int4>(), d.fine->d_c64->as<double>(), pd.slots(),
+          launch_refine(d.d_s, d.d_s2, fs, d.sat_pitch, d.fine->dev_dev,
+                        d.fine->geom, d.fine->c64_dev, pd.slots(),
                         pd.d_pairs.as<PairDesc>(), d.n_pairs, d.d_topk,
                         d.k, d.radius, d.d_best, d.d_count, st) != 0)
         SNCC_FAIL(SNCC_EDEVICE, "refine launch");

@@ -111,6 +111,16 @@ int launch_dense_pack(const int4 *geom, const double *c64, int K, double scale, 
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// Notes in host memory that the work before it on the stream is complete.
+__global__ void count_kernel(unsigned long long *p, unsigned long long n) {
+  __hip_atomic_store(p, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+int launch_count(unsigned long long *p, unsigned long long n, hipStream_t st) {
+  hipLaunchKernelGGL(count_kernel, dim3(1), dim3(1), 0, st, p, n);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 // ------------------------------------------------------------------ scoring
 // Rows [y0, y0 + rows) x columns [x0, x0 + 4 n4) of the frame to LDS, each
 // pixel as f - 128 in a byte, `pitch` bytes per row.  Pixels come from the sum

@@ -402,6 +402,7 @@ struct SeqPair {
 #define SNCC_WEAK __attribute__((weak))
 int launch_dense_pack(const int4 *geom, const double *c64, int K, double scale, int W, int H,
                       int digits, long long *img, void *frag, hipStream_t st) SNCC_WEAK;
+int launch_count(unsigned long long *p, unsigned long long n, hipStream_t st) SNCC_WEAK;
 int launch_dense(const DenseArgs &a, hipStream_t st) SNCC_WEAK;
 int launch_dense_frame(const DenseArgs &a, const uint8_t *f, int M, int f_pitch,
                        long long *energy, hipStream_t st) SNCC_WEAK;
