@@ -198,6 +198,7 @@ struct sncc_ctx {
   std::shared_ptr<BuildCount> builds;  // made at the first build of operands
   DevBuf frame_s, frame_s2;  // one frame's tables (global form of sncc_score_frame)
   std::vector<std::unique_ptr<PlanDev>> retired;  // awaiting completion
+  std::vector<std::unique_ptr<PlanDev>> in_graphs;  // made or replaced under capture
   bool timing = false;                             // record stage events
   hipEvent_t tev[4] = {};
   int n_stages = 0;                                // stages of the last timed call
@@ -905,6 +906,7 @@ struct FilterPlan {
   FilterScratch *scratch = nullptr, own;  // the context's, or a batch's own
   // the template set's memory that the launches read: a batch outlives the set
   std::shared_ptr<DevBuf> segs;
+  bool missing = false;         // pairs it would serve lack their operands
   const int4 *geom = nullptr;
   const double *c64 = nullptr;
   std::vector<std::shared_ptr<DenseBuf>> operands;
@@ -930,6 +932,7 @@ struct AbovePlan {
   std::vector<int2> items;
   std::vector<FilterLaunch> launches;
   std::vector<int> fp_of_pair, tile0;  // -1: not filtered; first tile counter
+  bool missing = false;                // as in FilterPlan
   int rv = 8, n_tiles = 0;
   size_t words = 0;
   DevBuf d_fps, d_items, d_fp_of_pair, d_tile0, d_bits, d_live;
@@ -942,6 +945,11 @@ struct PlanDev {
   PlanHost h;
   FilterPlan f;
   AbovePlan above;
+  std::vector<double> thr;  // slow thresholds (host copy of d_thr)
+  bool captured = false;    // its uploads are part of a graph
+  // made without the filter, or parts of it, that the call should have: calls
+  // until it is tried again (0: complete)
+  int retry_in = 0, retry_next = 64;
   DevBuf d_tmpls, d_passes, d_ivs, d_recs, d_pairs, d_items, d_order, d_qbeg, d_queue,
       d_partial, d_thr, d_slow, d_slot_off, d_slot_w, d_runs, d_refine_order;
   hipEvent_t done = nullptr;
@@ -1032,6 +1040,13 @@ struct PlanDev {
 
 namespace {
 
+bool stream_captured(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Frees retired plans whose work has completed (all of them when `wait`).
 void reap(sncc_ctx *ctx, bool wait) {
   auto &v = ctx->retired;
@@ -1069,7 +1084,11 @@ int make_plan(Make make, bool tiles, hipStream_t st, std::unique_ptr<PlanDev> *o
     out->reset(new PlanDev());
     rc = make(**out, filter);
     if (rc == SNCC_OK && tiles) rc = (*out)->upload(st);
-    if (rc != SNCC_ENOMEM) break;
+    if (rc != SNCC_ENOMEM) {
+      if (!filter || (*out)->f.missing || (*out)->above.missing)
+        (*out)->retry_in = (*out)->retry_next;
+      break;
+    }
   }
   if (rc == SNCC_OK) g_err.clear();
   return rc;
@@ -1079,18 +1098,36 @@ int make_plan(Make make, bool tiles, hipStream_t st, std::unique_ptr<PlanDev> *o
 // a miss (`tiles`: with a tile plan to upload); the plan it replaces is retired,
 // since work queued with it may still be running.  Calls on one context are
 // ordered by its stream, so reusing a plan while earlier work still reads it is
-// safe.
+// safe.  A plan made under capture serves that call alone, since its uploads
+// run with the graph, and stays until the context is destroyed; so does one
+// that is replaced under capture, where no event can tell when it is free.  A
+// plan that lacks the filter for want of memory is made again after 64 calls,
+// then 128, and so on.
 template <class Make>
 int cached_plan(sncc_ctx *ctx, PlanKey key, Make make, PlanDev **out, bool tiles = true) {
   const int slot = key.sink;
-  if (ctx->cache[slot] && ctx->cache_key[slot] == key) {
-    *out = ctx->cache[slot].get();
-    return SNCC_OK;
+  int retry_next = 0;
+  if (ctx->cache[slot] && !ctx->cache[slot]->captured && ctx->cache_key[slot] == key) {
+    PlanDev &pd = *ctx->cache[slot];
+    if (pd.retry_in == 0 || --pd.retry_in > 0 || stream_captured(ctx->stream)) {
+      pd.retry_in = pd.retry_in == 0 ? 0 : std::max(pd.retry_in, 1);
+      *out = &pd;
+      return SNCC_OK;
+    }
+    retry_next = std::min(2 * pd.retry_next, 1 << 20);
   }
-  if (ctx->cache[slot]) CHK(retire(ctx, std::move(ctx->cache[slot])));
+  const bool captured = stream_captured(ctx->stream);
+  if (ctx->cache[slot]) {
+    if (captured || ctx->cache[slot]->captured)
+      ctx->in_graphs.push_back(std::move(ctx->cache[slot]));
+    else
+      CHK(retire(ctx, std::move(ctx->cache[slot])));
+  }
   ctx->cache_key[slot] = PlanKey{};
   std::unique_ptr<PlanDev> pd;
   CHK(make_plan(make, tiles, ctx->stream, &pd));
+  pd->captured = captured;
+  if (pd->retry_in > 0 && retry_next > 0) pd->retry_in = pd->retry_next = retry_next;
   ctx->cache[slot] = std::move(pd);
   ctx->cache_key[slot] = std::move(key);
   *out = ctx->cache[slot].get();
@@ -1264,13 +1301,6 @@ int dense_digits_filter(const sncc_tmpl *tm, int t, float *error) {
     if (e <= std::ldexp(1.0, -12)) return digits;
   }
   return 0;
-}
-
-bool stream_captured(hipStream_t st) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();
-  return true;
 }
 
 // Template t's operands of `digits` digits that the context may read: complete
@@ -1658,7 +1688,10 @@ void plan_filter(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int P, int n_
     const int t = pairs[2 * p + 1];
     const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
     if (use[p] && !ops[t].frag) ops[t] = dense_operands(ctx, tm, t, tm->digits_f[t]);
-    if (use[p] && !ops[t].frag) use[p] = 0;
+    if (use[p] && !ops[t].frag) {
+      use[p] = 0;
+      f.missing = true;
+    }
     if (use[p]) {
       idx.push_back(p);
       cost[p] = (double)tm->H[t] * dense_groups(tm->W[t]) * tm->digits_f[t];
@@ -1868,9 +1901,12 @@ int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, i
     FilterLaunch l{digits, f.rv, (int)f.items.size(), 0, 0};
     for (int p = 0; p < n_pairs; ++p) {
       const int t = pairs[2 * p + 1];
-      DenseTmpl dt;
-      if (limit[t] >= 0 && slow->digits_f[t] == digits) dt = dense_operands(ctx, slow, t, digits);
-      if (!dt.frag) continue;
+      if (limit[t] < 0 || slow->digits_f[t] != digits) continue;
+      const DenseTmpl dt = dense_operands(ctx, slow, t, digits);
+      if (!dt.frag) {
+        f.missing = true;
+        continue;
+      }
       const PairDesc &q = h.pairs[p];
       FilterPair fp{};
       if (!dense_shape(slow, t, digits, q.nu, q.nv, ctx->num_cu, fp.a, f.rv)) continue;
@@ -2700,8 +2736,8 @@ int sncc_threshold_match(sncc_ctx *ctx, const sncc_tmpl *fast, const sncc_tmpl *
     plan_slow(slow, d.h.tc, d.h);
     if (filter)
       CHK(plan_above(ctx, slow, d.h, N, sat_pitch, n_pairs, pairs, thr_slow, d.above));
-    std::vector<double> ts(thr_slow, thr_slow + slow->T);
-    return d.d_thr.upload(ts, ctx->stream);
+    d.thr.assign(thr_slow, thr_slow + slow->T);
+    return d.d_thr.upload(d.thr, ctx->stream);
   }, &pd));
   TileArgs a = pd->args(d_s, d_s2, fs, sat_pitch, M, N);
   a.co.hits = d_cand;
