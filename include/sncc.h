@@ -303,9 +303,9 @@ int sncc_score(sncc_ctx *ctx, const sncc_tmpl *tm, int index,
  * any table origin.  It applies when W * H <= SNCC_MAX_SQ_BOX_AREA, W <= 511
  * and (17 + H) x (pitch class >= 65 + W) words fit 160 KB of LDS (e.g. up to
  * 128 x 128 templates).  The global form builds the frame's tables (context
- * scratch) and runs sncc_score.  SNCC_FORM_AUTO and SNCC_FORM_GLOBAL give the
- * same values by sncc_score's matrix-core form straight from the frame where
- * that is faster (form_used is then the form it stands in for).
+ * scratch) and runs sncc_score.  SNCC_FORM_AUTO takes sncc_score's matrix-core
+ * form straight from the frame where that is faster, in the place of one of the
+ * two.
  *
  *   d_f        device, N rows x f_pitch bytes
  *   form       SNCC_FORM_AUTO, SNCC_FORM_TILE_LOCAL (SNCC_ERANGE when the
@@ -314,7 +314,9 @@ int sncc_score(sncc_ctx *ctx, const sncc_tmpl *tm, int index,
  *   d_degenerate  nullable, as in sncc_score
  *   d_energy   device, nullable, int64 at the same positions as d_rho: the
  *              exact window energy n * sum f^2 - (sum f)^2 (n times Eq. (16))
- *   form_used  host, nullable: the form that ran
+ *   form_used  host, nullable: the form that ran; with SNCC_FORM_AUTO the one
+ *              chosen by the rule above, whose place the matrix-core form may
+ *              have taken
  * Errors: SNCC_EINVAL, SNCC_ERANGE, SNCC_ENOMEM, SNCC_EDEVICE.
  */
 int sncc_score_frame(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint8_t *d_f,

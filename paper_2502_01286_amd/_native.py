@@ -395,7 +395,8 @@ def sncc_score_frame(ctx, tm, index, f, rho, form=SNCC_FORM_AUTO, degen=None, en
     """FP32-compensated rho map of one frame (uint8 (N, M) device tensor)
     for template `index`, without sum tables passed in; rho: float32
     (N-H+1, pitch >= M-W+1); degen: nullable uint8 and energy: nullable int64
-    tensors of rho's shape.  Returns the form that ran."""
+    tensors of rho's shape.  Returns the form that ran (of the automatic form:
+    the one whose place the matrix-core form may have taken)."""
     import torch
     if not isinstance(f, torch.Tensor) or f.dim() != 2:
         raise ValueError("f must be a 2-D uint8 tensor")

@@ -2513,8 +2513,10 @@ int sncc_score_frame(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint8_
       (form == SNCC_FORM_AUTO && local_ok && tm->K[index] <= kTileLocalMaxK &&
        (long long)nu * nv <= kTileLocalMaxOffsets);
   const int used = local ? SNCC_FORM_TILE_LOCAL : SNCC_FORM_GLOBAL;
-  // automatic and global form: the same values without tables where faster
-  const int dense = form == SNCC_FORM_TILE_LOCAL
+  // automatic form: the same values without tables where faster (a form that is
+  // asked for runs, unless a test forces this one)
+  const int dense = form == SNCC_FORM_TILE_LOCAL ||
+                            (form == SNCC_FORM_GLOBAL && dense_forced() != 1)
                         ? 0
                         : dense_frame_map(ctx, tm, index, d_f, M, N, f_pitch, local, d_rho,
                                           rho_pitch, d_degenerate,

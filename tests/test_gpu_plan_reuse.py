@@ -20,7 +20,7 @@ def _setup(S, ctx):
     segs = [S.sncc_segment_template(synth.crop_template(rng, frames[0], 48, 48, sigma_max=4)[0], 4)[0]
             for _ in range(T)]
     _, s, s2 = build_sats(S, ctx, frames)
-    pairs = [(b, t) for b in range(B) for t in range(T)]
+    pairs = [(b, t) for b in range(B) for t in range(T)] * 3
     return s, s2, segs, pairs
 
 
@@ -68,7 +68,7 @@ def test_filter_returns_when_memory_does(monkeypatch, prec):
     top = torch.zeros((len(pairs), K, 3), dtype=torch.int32, device="cuda")
     want = None
     try:
-        monkeypatch.setenv("SNCC_TEST_FAIL_ALLOC", str(4 << 20))  # the maps: 9 MB
+        monkeypatch.setenv("SNCC_TEST_FAIL_ALLOC", str(8 << 20))  # the maps: 31 MB
         S.sncc_topk(ctx, tm, s, s2, B, M, N, pairs, K, prec, top)
         torch.cuda.synchronize()
         want = top.clone()
@@ -81,7 +81,7 @@ def test_filter_returns_when_memory_does(monkeypatch, prec):
         assert torch.equal(top, want)
         taken = before - torch.cuda.mem_get_info()[0]
         print("case", prec, "taken", taken >> 20, "MB", flush=True)
-        assert taken >= 8 << 20
+        assert taken >= 24 << 20
     finally:
         S.sncc_tmpl_destroy(tm)
         S.sncc_ctx_destroy(ctx)
