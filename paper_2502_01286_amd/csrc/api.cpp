@@ -1854,12 +1854,26 @@ int upload_filter(FilterPlan &f, FilterScratch *scratch, int k, bool fp64, hipSt
 // Small templates match in so many places that most runs keep a survivor:
 // those whose survivor costs less than kAboveSpared go without (35 x 35, K 56 to
 // 742 461 / 482; 33 x 33, K 214 to 580 237 / 278; but 57 x 57, K 138 to 658 on
-// 873 x 474, at 268 ps, 230 / 216).  So does a call whose slow pass would take
-// less than the filter's shortest time, were 15 per cent of the offsets
-// survivors (8 pairs of 324 x 200 with 96 x 96 175 / 195).
+// 873 x 474, at 268 ps, 230 / 216).
+//
+// How many survive is only known on the device, but the thresholds tell: of the
+// offsets of scenes a share of about match_share(threshold) reach a fast
+// threshold (measured at 0.4 to 0.8), and about match_share(slow threshold) a
+// slow one.  A template is filtered when that rules out three quarters of its
+// survivors and spares more than the filter's time, a call when what its
+// templates spare is 1.3 times that time and two launches.  So calls go without
+// whose thresholds lie close together (64 x 64 at 0.8 and 0.8, without / with:
+// 433 / 476; at 0.5 and 0.7 950 / 981; 96 x 96 at 0.5 and 0.6 1402 / 1481),
+// whose fast test is sharp (40 x 40 at 0.73 and 0.9 267 / 301) and of small
+// frames (640 x 480, 8 pairs of 96 x 96 at 0.57 and 0.9 139 / 157).
 constexpr double kAboveSpared = 250.0;
+double match_share(double threshold, int W, int H) {
+  const double miss = 1.0 - std::min(1.0, std::max(0.0, threshold));
+  return std::min(0.5, 0.5 * std::pow(miss, 2.3) * std::pow(64.0 / std::sqrt((double)W * H), 0.7));
+}
+
 int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, int P, int n_pairs,
-               const int32_t *pairs, const double *thr, AbovePlan &f) {
+               const int32_t *pairs, const double *thr_fast, const double *thr, AbovePlan &f) {
   const int forced = dense_forced();
   if (forced == 0 || h.tc.bu() != kDenseBU || h.tc.bv() != kFastRows ||
       kRunCols * h.tc.rv > kRunMax)
@@ -1870,25 +1884,35 @@ int plan_above(sncc_ctx *ctx, const sncc_tmpl *slow, const PlanHost &h, int N, i
   const int bv = 2 * kDenseNW * f.rv;
   std::vector<std::pair<int, int>> want;
   std::vector<int> limit(slow->T, -1);  // survivors a tile needs; -1: not filtered
-  double gain = 0, floor_us = 0;
+  std::vector<double> offsets(slow->T, 0.0);
+  for (int p = 0; p < n_pairs; ++p)
+    offsets[pairs[2 * p + 1]] += 1e-6 * h.pairs[p].nu * h.pairs[p].nv;
+  double gain = 0, cost = 0, floor_us = 0;
   for (int p = 0; p < n_pairs; ++p) {
-    const int t = pairs[2 * p + 1];
-    const double spared = 0.026 * (slow->H[t] + 4.0) * (slow->W[t] + kRunCols + 1.0) +
-                          0.19 * slow->K[t];
-    gain += 0.15e-6 * h.pairs[p].nu * h.pairs[p].nv * spared;
+    const int t = pairs[2 * p + 1], W = slow->W[t], H = slow->H[t];
     DenseArgs a{};
     if (limit[t] >= 0 || !slow->digits_f[t] ||
         !dense_shape(slow, t, slow->digits_f[t], h.pairs[p].nu, h.pairs[p].nv, ctx->num_cu, a,
                      f.rv))
       continue;
+    const double spared = 0.026 * (H + 4.0) * (W + kRunCols + 1.0) + 0.19 * slow->K[t];
     const double tile = (double)kDenseBU * bv, mac = 0.5 * a.digits * dense_macs(a);
+    const double filter = 4.0 + 1.25e-3 * mac, need = 2.0 * tile * filter / spared;
+    if (forced != 1) {
+      const double in = match_share(thr_fast[t], W, H), out = match_share(thr[t], W, H);
+      const double spares = 0.75 * offsets[t] * (in - out) * spared;
+      const double takes = 0.55 * offsets[t] * filter;  // tiles without survivors are skipped
+      if (need > 0.25 * tile || spared < kAboveSpared || out > 0.25 * in || spares < takes)
+        continue;
+      gain += spares;
+      cost += takes;
+    }
     floor_us = std::max(floor_us, 20.0 + 2e-3 * mac);
-    const double need = 2.0 * tile * (4.0 + 1.25e-3 * mac) / spared;
-    if (forced != 1 && (need > 0.25 * tile || spared < kAboveSpared)) continue;
     limit[t] = forced == 1 ? 1 : std::max(1, (int)need);
     want.emplace_back(t, slow->digits_f[t]);
   }
-  if (want.empty() || (forced != 1 && gain < floor_us)) return SNCC_OK;
+  if (want.empty() || (forced != 1 && gain < 1.3 * (std::max(cost, floor_us) + 25.0)))
+    return SNCC_OK;
   dense_build(ctx, slow, want);
   f.fp_of_pair.assign(n_pairs, -1);
   f.tile0.assign(n_pairs, 0);
@@ -2737,7 +2761,8 @@ int sncc_threshold_match(sncc_ctx *ctx, const sncc_tmpl *fast, const sncc_tmpl *
                    thr_fast));
     plan_slow(slow, d.h.tc, d.h);
     if (filter)
-      CHK(plan_above(ctx, slow, d.h, N, sat_pitch, n_pairs, pairs, thr_slow, d.above));
+      CHK(plan_above(ctx, slow, d.h, N, sat_pitch, n_pairs, pairs, thr_fast, thr_slow,
+                     d.above));
     d.thr.assign(thr_slow, thr_slow + slow->T);
     return d.d_thr.upload(d.thr, ctx->stream);
   }, &pd));
