@@ -195,7 +195,7 @@ struct sncc_ctx {
   DevBuf sat_scratch;
   FilterScratch filter32, filter64;
   uint64_t serial = 0;                 // unique per context
-  std::shared_ptr<BuildCount> builds;  // made at the first build of operands
+  std::shared_ptr<BuildCount> builds;  // nullptr: no memory for it, no operands
   DevBuf frame_s, frame_s2;  // one frame's tables (global form of sncc_score_frame)
   std::vector<std::unique_ptr<PlanDev>> retired;  // awaiting completion
   std::vector<std::unique_ptr<PlanDev>> in_graphs;  // made or replaced under capture
@@ -1315,21 +1315,6 @@ DenseTmpl dense_usable(const sncc_ctx *ctx, const sncc_tmpl *tm, int t, int digi
   return mine;
 }
 
-bool build_count(sncc_ctx *ctx) {
-  if (ctx->builds) return true;
-  auto b = std::make_shared<BuildCount>();
-  if (hipHostMalloc(reinterpret_cast<void **>(&b->host), sizeof *b->host,
-                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-    b->host = nullptr;
-    return false;
-  }
-  *b->host = 0;
-  if (hipHostGetDevicePointer(reinterpret_cast<void **>(&b->dev), b->host, 0) != hipSuccess)
-    return false;
-  ctx->builds = std::move(b);
-  return true;
-}
-
 // Builds the operands of the templates in `want` ({template, digits}) that the
 // context cannot read yet: small launches on its stream, without a wait, so that
 // a template's first call costs little more than the next (640 x 480 with 32 x
@@ -1367,7 +1352,7 @@ void dense_build(sncc_ctx *ctx, const sncc_tmpl *tm, const std::vector<std::pair
   if (jobs.empty() || stream_captured(ctx->stream)) return;
   RelaxedCapture relaxed;
   std::shared_ptr<DenseBuf> buf(new (std::nothrow) DenseBuf());
-  if (!buf || !build_count(ctx) || buf->mem.reserve(bytes + image) != SNCC_OK) {
+  if (!buf || !ctx->builds || buf->mem.reserve(bytes + image) != SNCC_OK) {
     (void)hipGetLastError();
     g_err.clear();
     return;
@@ -2252,6 +2237,23 @@ int sncc_segment_templates(int T, const uint8_t *const *t, const int *W, const i
   return SNCC_OK;
 }
 
+// (40 us of host time, so with the context and not at its first build)
+static std::shared_ptr<BuildCount> make_build_count() {
+  auto b = std::make_shared<BuildCount>();
+  if (hipHostMalloc(reinterpret_cast<void **>(&b->host), sizeof *b->host,
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+    b->host = nullptr;
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  *b->host = 0;
+  if (hipHostGetDevicePointer(reinterpret_cast<void **>(&b->dev), b->host, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return b;
+}
+
 int sncc_ctx_create(int device, uintptr_t hip_stream, sncc_ctx **out) {
   g_err.clear();
   if (!out) SNCC_FAIL(SNCC_EINVAL, "NULL output");
@@ -2274,6 +2276,7 @@ int sncc_ctx_create(int device, uintptr_t hip_stream, sncc_ctx **out) {
   c->device = device;
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   c->num_cu = prop.multiProcessorCount;
+  c->builds = make_build_count();
   *out = c;
   return SNCC_OK;
 }
