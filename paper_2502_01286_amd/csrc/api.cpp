@@ -1475,7 +1475,9 @@ bool dense_wins(const sncc_tmpl *tm, int t, const DenseArgs &a) {
     const double far = dense_frag_bytes(a.W, a.H, a.digits) > 3500000 ? 1.6 : 1.0;
     const double plain = std::max({10.0, 7.0 + 0.17 * K,
                                    3.0 + off * std::min(4.3 + 0.7 * K, 16.0 + 0.52 * K)});
-    return std::max(11.6 + 3.2e-3 * one * far, 6.0 + off * (6.5 + 4.6e-3 * mac)) < plain;
+    // (3 us apart, or the plain form, which needs no operands: 1280 x 720 with 32 x
+    // 32 at K 23 19.4 / 21.4 where the estimates say 20.5 / 17.7)
+    return std::max(11.6 + 3.2e-3 * one * far, 6.0 + off * (6.5 + 4.6e-3 * mac)) + 3.0 < plain;
   }
   const double digits = a.digits / 3.0;
   const double tile = std::max(
@@ -1583,21 +1585,51 @@ int seq_records(const PlanHost &ph, int t, int P, std::vector<SeqRec> &out) {
 // 16, K 11 118 / 41; 64 x 64, K 119 438 / 89; 128 x 128, K 135 435 / 194; 192 x
 // 192, K 58 225 / 318.  FP32: the segment form 0.24 K + 4e-4 staged entries
 // (and 13 for lists of more than one), with 20 us a call, against 3 + 1.25e-3
-// products, with 30 us and the ordered sum's 0.015 us per segment: 24 x 24,
+// products, with 33 us and the ordered sum's 0.015 us per segment: 24 x 24,
 // K 11 122 / 52; 64 x 64, K 119 238 / 102; 128 x 128, K 135 318 / 206; 192 x
 // 192, K 58 215 / 325.  An FP32 call takes the cheapest of no filter, all
 // pairs, or those it gains on.
 // A batch's segment form starts its lists from other items' floors: 0.21 K +
 // 4e-4 staged entries - 1.5 (256 frames 1280 x 720 x 32 templates 12.5 at
-// K 37, 16 frames 1920 x 1080 x 64 templates 78 at K 314), no fixed costs.
+// K 37, 16 frames 1920 x 1080 x 64 templates 78 at K 314); its launches, two
+// with their counters cleared and the filter's three, cost 30 and 20 us.
+// Few tiles fill the chip badly: the filter's fewer rows per wave half take 1.3
+// (four) and 1.7 times the products' time (two), and the last round of
+// workgroups, two a CU, as long as a full one; the segment form's last round of
+// tiles likewise, and no less than 6.5 us and 0.2 per segment in all (FP32 calls
+// on 1280 x 720, other form / filter: one pair of 192 x 192, K 139 96 / 117, K
+// 585 188 / 122, four of K 102 to 298 201 / 284; 128 x 128, K 53 64 / 70, four of
+// K 53 to 228 209 / 131; 640 x 480, 128 x 128, K 595 140 / 66).
+struct FilterEstimate {
+  double tile = 0, products = 0, rest = 0;  // us on a full chip: segment form; filter
+  long long tiles[3] = {0, 0, 0};           // filter tiles of two, four and eight rows
+  long long wide = 0, narrow = 0;           // segment form's tiles (one_call_cfg)
+  int k_tile = 0, k_filter = 0;             // largest K
+  double us(int num_cu, bool batch) const {
+    auto uneven = [](double rounds) { return std::ceil(rounds) / rounds; };
+    double t = 0;
+    if (k_tile > 0) {
+      const double n = (double)(batch || 2 * wide >= num_cu ? wide : narrow);
+      t += std::max(tile * uneven(n / num_cu), 6.5 + 0.2 * k_tile) + (batch ? 30.0 : 20.0);
+    }
+    if (k_filter > 0) {
+      const int shape = tiles[2] >= 2LL * num_cu ? 2 : 2 * tiles[2] >= num_cu ? 1 : 0;
+      const double slow = shape == 2 ? 1.0 : shape == 1 ? 1.3 : 1.7;
+      t += rest + products * slow * uneven(tiles[shape] / (2.0 * num_cu)) +
+           (batch ? 20.0 : 33.0) + (batch ? 0.0 : 0.015) * k_filter;
+    }
+    return t;
+  }
+};
+
 std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N, int n_pairs,
                                const int32_t *pairs, int k, bool fp64, bool batch = false) {
   std::vector<char> use(n_pairs, 0), seen(tm->T, 0), can(tm->T, 0);
   std::vector<double> other(tm->T, 0.0), mine(tm->T, 0.0);
-  const int forced = dense_forced();
-  double none = 0, some = 0, all = 0;  // us
-  int k_some = 0, k_all = 0;
-  bool rest_some = false, rest_all = false, any = false;
+  const int forced = dense_forced(), num_cu = std::max(1, ctx->num_cu);
+  FilterEstimate none, some, all;
+  const double base = fp64 ? 9.0 : 3.0;
+  bool any = false;
   for (int p = 0; p < n_pairs; ++p) {
     const int t = pairs[2 * p + 1];
     const int nu = M - tm->W[t] + 1, nv = N - tm->H[t] + 1;
@@ -1611,26 +1643,36 @@ std::vector<char> filter_pairs(sncc_ctx *ctx, const sncc_tmpl *tm, int M, int N,
       other[t] = fp64    ? 17.0 + 0.6 * tm->K[t]
                  : batch ? 0.21 * tm->K[t] + 4e-4 * staged - 1.5
                          : (k > 1 ? 13.0 : 0.0) + 0.24 * tm->K[t] + 4e-4 * staged;
-      mine[t] = (fp64 ? 9.0 : 3.0) + 1.25e-3 * mac;
+      mine[t] = base + 1.25e-3 * mac;
     }
     const double offsets = (double)nu * nv * 1e-6;
     const bool gains = can[t] && mine[t] < other[t];
-    none += offsets * other[t];
-    some += offsets * (gains ? mine[t] : other[t]);
-    all += offsets * (can[t] ? mine[t] : other[t]);
-    (gains ? k_some : k_all) = std::max(gains ? k_some : k_all, can[t] ? tm->K[t] : 0);
-    rest_some |= !gains;
-    rest_all |= !can[t];
     any |= gains;
+    auto add = [&](FilterEstimate &e, bool filter) {
+      if (!filter) {
+        e.tile += offsets * other[t];
+        e.k_tile = std::max(e.k_tile, tm->K[t]);
+        e.wide += (long long)((nu + 127) / 128) * ((nv + 31) / 32);
+        e.narrow += (long long)((nu + 63) / 64) * ((nv + 15) / 16);
+        return;
+      }
+      e.rest += offsets * base;
+      e.products += offsets * (mine[t] - base);
+      e.k_filter = std::max(e.k_filter, tm->K[t]);
+      for (int i = 0; i < 3; ++i) {
+        const int bv = 2 * kDenseNW * (2 << i);
+        e.tiles[i] += (long long)((nu + kDenseBU - 1) / kDenseBU) * ((nv + bv - 1) / bv);
+      }
+    };
+    add(none, false);
+    add(some, gains);
+    add(all, can[t]);
   }
-  k_all = std::max(k_all, k_some);
-  const double kTileUs = batch ? 0.0 : 20.0, kFilterUs = batch ? 0.0 : 30.0;
-  constexpr double kOrderUs = 0.015;
-  none += kTileUs;
-  some += kFilterUs + kOrderUs * k_some + (rest_some ? kTileUs : 0.0);
-  all += kFilterUs + kOrderUs * k_all + (rest_all ? kTileUs : 0.0);
-  const bool take_all = forced == 1 || (!fp64 && all < none && (!any || all < some));
-  const bool take_some = fp64 || (any && some < none);
+  const double t_none = none.us(num_cu, batch), t_some = some.us(num_cu, batch),
+               t_all = all.us(num_cu, batch);
+  const bool take_all =
+      forced == 1 || (!fp64 && all.k_filter > 0 && t_all < t_none && (!any || t_all < t_some));
+  const bool take_some = fp64 || (any && t_some < t_none);
   for (int p = 0; p < n_pairs; ++p) {
     const int t = pairs[2 * p + 1];
     use[p] = can[t] && (take_all || (take_some && mine[t] < other[t]));
