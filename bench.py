@@ -25,6 +25,7 @@ second of the whole step.
 from __future__ import annotations
 
 import argparse
+import contextlib
 import hashlib
 import json
 import os
@@ -540,9 +541,25 @@ def _events_ms(torch, fn, reps):
     return e0.elapsed_time(e1) / reps
 
 
+@contextlib.contextmanager
+def _segment_sums():
+    """Calls inside take the forms without matrix cores (the library reads the
+    variable when it chooses): the plain FP64 form, for comparison."""
+    old = os.environ.get("SNCC_TEST_DENSE")
+    os.environ["SNCC_TEST_DENSE"] = "0"
+    try:
+        yield
+    finally:
+        if old is None:
+            del os.environ["SNCC_TEST_DENSE"]
+        else:
+            os.environ["SNCC_TEST_DENSE"] = old
+
+
 def _single_config(S, torch, ctx, ex, n_proc, wl, sigma, k_max, full_oracle, reps=5):
     """One frame, one template: device times of the sum tables, the FP32
-    map, the FP32 top-1 and the FP64 map, each in the form the library takes;
+    map, the FP32 top-1 and the FP64 map, each in the form the library takes,
+    and the FP64 map in the plain form;
     FP32 and FP64 against the oracle (whole map, or a seeded sample of
     offsets plus the neighbourhoods of both sides' best offsets)."""
     import numpy as np
@@ -568,12 +585,17 @@ def _single_config(S, torch, ctx, ex, n_proc, wl, sigma, k_max, full_oracle, rep
                                                       S.SNCC_FP32_KAHAN, top1), reps)
     ms64 = _events_ms(torch, lambda: S.sncc_score(ctx, tm, 0, s, s2, M, N, S.SNCC_FP64, r64),
                       max(2, reps // 2))
-    # from the frame: tile-local sum tables (when the template allows) and the
-    # global form (tables of the frame, then the map)
+    with _segment_sums():
+        ms_plain = _events_ms(torch, lambda: S.sncc_score(ctx, tm, 0, s, s2, M, N, S.SNCC_FP64,
+                                                          r64), max(2, reps // 2))
+    S.sncc_score(ctx, tm, 0, s, s2, M, N, S.SNCC_FP64, r64)
+    # from the frame: tile-local sum tables (when the template allows), the
+    # global form (tables of the frame, then the map) and the library's choice
     rf = torch.empty((nv, nu), dtype=torch.float32, device="cuda")
     fr = d[0]
     forms = {}
-    for name, form in (("tile_local", S.SNCC_FORM_TILE_LOCAL), ("global", S.SNCC_FORM_GLOBAL)):
+    for name, form in (("tile_local", S.SNCC_FORM_TILE_LOCAL), ("global", S.SNCC_FORM_GLOBAL),
+                       ("auto", S.SNCC_FORM_AUTO)):
         try:
             forms[name] = round(_events_ms(torch, lambda: S.sncc_score_frame(
                 ctx, tm, 0, fr, rf, form=form), reps), 4)
@@ -596,8 +618,9 @@ def _single_config(S, torch, ctx, ex, n_proc, wl, sigma, k_max, full_oracle, rep
            "ms_fp32_top1": round(ms_top1, 4), "ms_fp64_map": round(ms64, 4),
            "fp32_map_evals_per_s": evals / (ms32 / 1e3),
            "fp32_top1_evals_per_s": evals / (ms_top1 / 1e3),
-           "plain_fp64_evals_per_s": evals / (ms64 / 1e3),
-           "speedup_fp32_top1_vs_plain_fp64": round(ms64 / ms_top1, 2),
+           "ms_plain_fp64_map": round(ms_plain, 4),
+           "plain_fp64_evals_per_s": evals / (ms_plain / 1e3),
+           "speedup_fp32_top1_vs_plain_fp64": round(ms_plain / ms_top1, 2),
            "ms_map_from_frame": forms,
            "fp32_vs_gpu_fp64_max_abs_drho": float(np.abs(g32 - g64).max())}
     if full_oracle:
@@ -638,7 +661,7 @@ def run_configs(S, torch, ctx, args):
     sigma 8; 1920x1080 with a 64x64 template at sigma 4, 8, 16; 3840x2160
     textures with 128x128 and 256x256 templates at sigma 4, K_max 5000, and
     the 128x128 one uncapped) and the 16 x 64 batch (top-5), each with its
-    FP32 throughput, the FP64 call's, and its error against the oracle."""
+    FP32 throughput, the plain FP64 form's, and its error against the oracle."""
     from concurrent.futures import ProcessPoolExecutor
     from workloads import synth
     n_proc = max(1, min(16, len(os.sched_getaffinity(0))))
@@ -654,7 +677,7 @@ def run_configs(S, torch, ctx, args):
             t0 = time.perf_counter()
             res[name] = _single_config(S, torch, ctx, ex, n_proc, wl, sg, km, full)
             log(f"[bench] {name}: {res[name]} ({time.perf_counter() - t0:.1f} s)")
-    # the 16 x 64 batch: one tuned graph launch per step, against the FP64 call
+    # the 16 x 64 batch: one tuned graph launch per step, against the plain FP64 form
     wl = synth.batch_16x64()
     B, N, M = len(wl.frames), wl.N, wl.M
     segs = [S.sncc_segment_template(t, sg, wl.k_max)[0] for t, sg in zip(wl.templates, wl.sigmas)]
@@ -673,8 +696,9 @@ def run_configs(S, torch, ctx, args):
     st = batch.stats()
     evals = st["coarse_evals"]
     out64 = torch.zeros_like(topk)
-    ms64 = _events_ms(torch, lambda: S.sncc_topk(ctx, tm, s, s2, B, M, N, wl.pairs, wl.k,
-                                                 S.SNCC_FP64, out64), 1)
+    with _segment_sums():
+        ms64 = _events_ms(torch, lambda: S.sncc_topk(ctx, tm, s, s2, B, M, N, wl.pairs, wl.k,
+                                                     S.SNCC_FP64, out64), 1)
     batch.run()
     torch.cuda.synchronize()
     g_top = [[(int(m["u"]), int(m["v"]), float(m["rho"])) for m in row]
@@ -852,23 +876,24 @@ def main():
 
     plain = None
     if not args.no_plain:
-        log("[bench] FP64 comparator (one sncc_topk call)")
+        log("[bench] plain FP64 comparator (one sncc_topk call)")
         out64 = torch.zeros_like(topk)
-        S.sncc_topk(ctx, coarse, s, s2, B, M, N, wl.pairs, wl.k, S.SNCC_FP64, out64)
-        torch.cuda.synchronize()
-        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         reps = 2
-        e0.record()
-        for _ in range(reps):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        with _segment_sums():
             S.sncc_topk(ctx, coarse, s, s2, B, M, N, wl.pairs, wl.k, S.SNCC_FP64, out64)
-        e1.record()
-        torch.cuda.synchronize()
+            torch.cuda.synchronize()
+            e0.record()
+            for _ in range(reps):
+                S.sncc_topk(ctx, coarse, s, s2, B, M, N, wl.pairs, wl.k, S.SNCC_FP64, out64)
+            e1.record()
+            torch.cuda.synchronize()
         pms = e0.elapsed_time(e1) / reps
         plain = {"value": evals / (pms / 1e3), "unit": UNIT, "ms": round(pms, 3),
                  "speedup_batched_fp32": round((evals / (avg["ms_score"] / 1e3)) / (evals / (pms / 1e3)), 3)
                  if avg["ms_score"] else None,
-                 "form": "one FP64 sncc_topk call over all pairs (matrix-core filter where it "
-                         "pays, candidates in FP64 segment sums; else FP64 segment sums), no graph"}
+                 "form": "FP64 segment sums at every offset, one sncc_topk call over all pairs, "
+                         "no matrix cores, no graph"}
         log(f"[bench] FP64 {pms:.2f} ms")
 
     cpu = parity = None
@@ -905,7 +930,9 @@ def main():
                    "K_coarse": [min(Kc), max(Kc)], "coarse_evals": evals,
                    "fine_offsets_scored": fine_offsets,
                    "arith": "u32 box sums, i64 window energy, f32 compensated accumulation "
-                            "and f32 rho (coarse), f64 refine"},
+                            "and f32 rho (coarse; pairs of detailed templates at the offsets "
+                            "that exact i8 matrix products with an error bound leave), "
+                            "f64 refine"},
         "frames_per_s": B / (ms_per_step / 1e3),
         "stage_ms": avg, "prep_ms_host": prep_ms,
         "roofline": roof, "plain_fp64": plain, "cpu_baseline": cpu, "parity": parity,
