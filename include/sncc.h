@@ -272,10 +272,12 @@ int sncc_tmpl_count(const sncc_tmpl *tm, int *T);
  *              for their size take the matrix-core form in either precision:
  *              the numerator as an exact integer correlation of the frame
  *              with the approximation in fixed point (errors no larger than
- *              the segment sums').  Its operands, about 5 bytes per template
- *              pixel and digit (3 or 7), are built at the first such call and
- *              kept with the template set; a call captured into a HIP graph
- *              before that uses the segment sums.
+ *              the segment sums').  Its operands, 16 (1 + 30 / W) bytes or a
+ *              little more per template pixel and digit (3, 4 or 7; 20 at 64
+ *              x 64), are built at the first such call, enqueued like all
+ *              device work, and kept with the template set (at most 2 GiB);
+ *              a call captured into a HIP graph before that uses the segment
+ *              sums, as do calls for which there is no memory.
  *   d_rho      device, (N-H+1) rows x rho_pitch elements (>= M-W+1)
  *   d_degenerate  device, nullable, (N-H+1) x rho_pitch bytes: 1 where the
  *              window is uniform (rho written as 0), else 0
@@ -342,7 +344,9 @@ int sncc_score_frame(sncc_ctx *ctx, const sncc_tmpl *tm, int index, const uint8_
  * that is more), FP64 partial lists of about 64 MB (at least k of 16 bytes per
  * pair) and at most 11 kB per pair of a map chunk; sncc_ctx_destroy frees it.
  * A work list keeps the matrix-core operands that it uses after their template
- * set is destroyed.
+ * set is destroyed.  A HIP graph that captured such a call reads the work list
+ * and the scratch: it may be launched until the next sncc_topk of that
+ * precision on the context with other arguments.
  *
  *   d_s, d_s2  sum tables of B frames (layout of sncc_build_sats)
  *   pairs      host, n_pairs x {frame, template}

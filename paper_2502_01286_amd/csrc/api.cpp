@@ -878,8 +878,8 @@ void plan_slow(const sncc_tmpl *slow, const TileCfg &tc, PlanHost &ph) {
 }  // namespace
 
 // Top-k by filter and rescoring (topk_filter.hip): the pairs it serves, in
-// chunks whose maps share one scratch buffer, and what the direct form needs
-// for the pairs left to it.
+// chunks whose maps share one scratch buffer, and what the direct form (FP64)
+// or the segment form's launches (FP32) need for the pairs left to them.
 struct FilterLaunch {
   int digits, rv, item0, n_items, lds;
 };

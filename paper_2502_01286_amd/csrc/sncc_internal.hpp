@@ -382,7 +382,7 @@ struct Undecided {
 };
 
 // A pair's candidates where their scoring is spread over workgroups: their
-// number (-1: left to the direct form), row-major indices, keys of the accurate
+// number (-1: left to the segment form), row-major indices, keys of the accurate
 // values, and of the reference's.
 struct FilterSpread {
   int n, m;                // m: scored by the reference
